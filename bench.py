@@ -6,7 +6,7 @@ HBM: transactions -> tidlists, size order and layout, 2-of-3 construction,
 encoding, failure corrections, tiled compare of all pairs, corrections added,
 support >= sigma compaction.  The value is item-pair supports produced per
 second of step time.  Besides the step, the line reports the compare kernel
-against the VALU roofline (HIP events on the launch stream), the dense int8
+against the VALU roofline (HIP events on the launch stream), the dense
 MFMA comparator on the same instance, exactness checks against the oracle,
 and the oracle itself timed on the host cores on a bounded sample.
 """
@@ -22,7 +22,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_VALU_TOPS = 256 * 64 * 2.4e9 / 1e12      # int32 VALU lane-ops/s: 256 CUs x 64 lanes x 2.4 GHz
-PEAK_I8_MFMA_TOPS = 5.0e3                     # dense int8 MFMA, TOP/s
+PEAK_F4_MFMA_TOPS = 10.07e3                   # dense 4-bit float MFMA, TOP/s
 PEAK_HBM_GBS = 8.0e3
 OPS_PER_GROUP_PAIR = 9                        # bit-sliced compare of 32 slot pairs (8-bit slots; w-bit: w + 1)
 SLOTS_PER_GROUP = 32
@@ -80,7 +80,7 @@ def main():
     ap.add_argument("--mode", default="step",
                     choices=["step", "serving", "dense-sweep", "batch", "bipartite", "triples"],
                     help="step: the path on one instance (default); serving: subset-query stream against the "
-                         "resident serving instance; dense-sweep: BatMap (slot width by density) vs int8-MFMA "
+                         "resident serving instance; dense-sweep: BatMap (slot width by density) vs MFMA "
                          "bitmap across densities; batch: 64 uneven instances in one graph-captured launch vs one "
                          "call per instance; bipartite: |A_i cap B_j| of two families (boolean matrix product); "
                          "triples: supports of item triples on order-3 maps")
@@ -214,7 +214,7 @@ def step_mode(args):
     if not args.no_dense:
         ctx.set_profiling(True)
         out2 = torch.empty_like(out)
-        idx.all_pair_supports_dense(out2)       # builds the 0/1 bitmap once
+        idx.all_pair_supports_dense(out2)       # builds the bit rows once
         dt0 = ctx.timings()
         dms = []
         for _ in range(3):
@@ -223,16 +223,15 @@ def step_mode(args):
         torch.cuda.synchronize()
         dense_ok = bool(torch.equal(out, out2))
         dense_ms = float(np.mean(dms))
-        m_pad = (w.m + 127) // 128 * 128
         useful_ops = 2.0 * w.m * n_pairs_total
         dense = {
-            "path": "0/1 int8 bitmap, A A^T on v_mfma_i32_16x16x64_i8, int32 accumulate",
+            "path": "bit rows, A A^T on v_mfma_scale_f32_32x32x64_f8f6f4 (0/1 as E2M1), exact counts",
             "bitmap_build_ms": round(dt0["encode_ms"], 3),
             "gemm_ms": round(dense_ms, 3),
             "pairs_per_s": n_pairs_total / (dense_ms * 1e-3),
             "useful_tops": useful_ops / (dense_ms * 1e-3) / 1e12,
-            "frac_of_int8_peak": useful_ops / (dense_ms * 1e-3) / 1e12 / PEAK_I8_MFMA_TOPS,
-            "bitmap_bytes": m_pad * ((w.n + 127) // 128 * 128),
+            "frac_of_f4_peak": useful_ops / (dense_ms * 1e-3) / 1e12 / PEAK_F4_MFMA_TOPS,
+            "bitmap_bytes": (w.m + 511) // 512 * 64 * (w.n + 1),
             "equal_to_batmap": dense_ok,
             "batmap_over_dense_speed": dense_ms / compare_ms,
         }
@@ -324,7 +323,7 @@ def step_mode(args):
 
 def extras(args):
     """Short runs of the other benchmark workloads, summarised inside the default line: the
-    m=2^20 x 8192 Bernoulli instance at 5% (BatMap against the int8-MFMA bitmap), the batch of 64
+    m=2^20 x 8192 Bernoulli instance at 5% (BatMap against the MFMA bitmap), the batch of 64
     uneven instances, and the resident serving instance (a shorter query stream than its own mode)."""
     out = {}
 
@@ -343,7 +342,7 @@ def extras(args):
         keys = ("density", "slot_bits", "build_ms", "batmap_compare_ms", "dense_bitmap_build_ms", "dense_gemm_ms",
                 "dense_tops", "faster", "equal", "closed_form_sum")
         return {"workload": "Bernoulli m=2^20, n=8192, p=5%", **{k: row[k] for k in keys},
-                "frac_of_int8_peak": row["dense_tops"] / PEAK_I8_MFMA_TOPS}
+                "frac_of_f4_peak": row["dense_tops"] / PEAK_F4_MFMA_TOPS}
 
     def batch_keep(r):
         keys = ("batch_ms", "alone_sum_ms", "persistent_launch_ms", "speedup_vs_alone", "graph", "frac_of_valu_peak",
@@ -505,7 +504,7 @@ def serving_mode(args):
 
 
 def dense_sweep_mode(args):
-    """BatMap all pairs vs the int8-MFMA bitmap product on m=2^20, n=8192 Bernoulli instances of rising
+    """BatMap all pairs vs the MFMA bitmap product on m=2^20, n=8192 Bernoulli instances of rising
     density (inputs drawn on the GPU); both exact, compared element by element."""
     import torch
 
@@ -578,7 +577,7 @@ def dense_sweep_mode(args):
         del d_off, d_tids, tl
         torch.cuda.empty_cache()
     cross = [r["density"] for r in rows if r["faster"] == "dense_mfma"]
-    return {"metric": "BatMap vs int8-MFMA bitmap all-pairs time across density (exact both)",
+    return {"metric": "BatMap vs MFMA bitmap all-pairs time across density (exact both)",
             "config": {"workload": f"Bernoulli m={m}, n={n}", "densities": [r["density"] for r in rows]},
             "rows": rows, "dense_wins_from_density": min(cross) if cross else None}
 

@@ -351,8 +351,9 @@ bm_status bm_server_stats_get(bm_server *srv, bm_server_stats *out);
 void bm_server_destroy(bm_server *srv);
 
 /* Same result as bm_all_pair_supports by the plain bitmap route (Sec. I-A,
- * bitmaps: AND and count): a 0/1 int8 item x transaction matrix A and the
- * product A A^T on the int8 matrix cores with int32 accumulation. */
+ * bitmaps: AND and count): a bit row per item (one bit per transaction, kept
+ * in the index from the first such call) and the product A A^T on the matrix
+ * cores, 0 and 1 as 4-bit floats, counts exact. */
 bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_len);
 
 /* Inspection (tests, tools).  Copies to host buffers:

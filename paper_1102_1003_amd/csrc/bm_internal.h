@@ -467,15 +467,24 @@ uint32_t threshold_blocks(uint64_t n_pairs);
 hipError_t launch_subset_prepare(const uint32_t *items, uint32_t k, uint32_t n, const int32_t *sorted_pos,
                                  uint32_t *pos_of_item, uint32_t *flag, hipStream_t s);
 
-// Dense comparator.
-// Scratch words launch_bitmap_build needs for the bitmap of n rows of ld bytes.
-uint64_t bitmap_bounds_words(uint32_t n, uint64_t ld);
-hipError_t launch_bitmap_build(const uint64_t *off, const uint32_t *tids, uint32_t n, uint64_t ld, int8_t *A,
-                               uint64_t *bnd, hipStream_t s);
-// Rows of the dense bitmap are padded to a multiple of this.
-uint32_t dense_row_pad();
-hipError_t launch_dense_gram(const int8_t *A, uint32_t n, uint64_t ld, uint64_t k_len, uint32_t *out,
-                             uint32_t k_split, hipStream_t s);
+// The bitmap route (plan.h: kGramStage, bit_row_words, GramPlan): an all-zero
+// row stands behind the last row.
+// Writes the rows of `items` (item ids, device; null: items 0 .. n_rows - 1)
+// and the zero row behind them: (n_rows + 1) bit_row_words(m) words.
+hipError_t launch_bit_rows(const uint64_t *off, const uint32_t *tids, const uint32_t *items, uint32_t n_rows,
+                           uint32_t m, uint32_t *bits, hipStream_t s);
+// n rows of a bit matrix: position p is row rows[p] (device; null: row p).
+struct BitMat {
+    const uint32_t *bits = nullptr;
+    uint64_t ld = 0;  // words of a row
+    const uint32_t *rows = nullptr;
+    uint32_t n = 0;
+    uint32_t zero = 0;  // the all-zero row
+};
+// Counts |a_i cap b_j|: tri (a == b): the packed upper triangle over n_out
+// positions; else rows of n_out.  Every count is written (none is read).
+hipError_t launch_gram(const GramPlan &p, const BitMat &a, const BitMat &b, uint32_t *out, uint64_t n_out, float *ws,
+                       hipStream_t s);
 
 }  // namespace bm
 

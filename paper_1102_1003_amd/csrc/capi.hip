@@ -403,9 +403,9 @@ struct bm_index {
     DevBuf<uint32_t> x_outpos, x_out;
     DevBuf<WorkItem> x_work;
     DevBuf<InstDesc> x_descs;
-    // dense comparator
-    DevBuf<int8_t> dense_A;
-    uint64_t dense_ld = 0;
+    // bitmap route: a bit row per item and the zero row, made at first use
+    DevBuf<uint32_t> bits;
+    DevBuf<float> gram_ws;
 };
 
 struct bm_batch {
@@ -488,6 +488,14 @@ int forced_variant()
 }
 
 
+
+// BM_GRAM_TILE=<64 | 128 | 256> pins the tile of the bitmap route's Gram kernel.
+int pinned_gram_tile()
+{
+    const char *e = getenv("BM_GRAM_TILE");
+    const int t = e ? atoi(e) : 0;
+    return t == 64 || t == 128 || t == 256 ? t : 0;
+}
 
 // Whether whole-index plans may pack rows of several width classes into one
 // tile (the maps of an index lie in sorted order in its arena); on unless
@@ -1533,6 +1541,35 @@ InstDesc whole_desc(const bm_index *idx, uint32_t *out)
     d.mode = OUT_PACKED;
     d.carena = d.arena;
     return d;
+}
+
+// The index's bit rows (every item's), made at the first call that needs them.
+bm_status ensure_bits(bm_index *idx)
+{
+    bm_context *ctx = idx->ctx;
+    if (idx->bits.p)
+        return BM_OK;
+    Span sp(ctx, PH_ENCODE);
+    DevBuf<uint32_t> bits;
+    HIPC(ctx, bits.alloc(((uint64_t)idx->n + 1) * bit_row_words(idx->m)));
+    HIPC(ctx, launch_bit_rows(idx->off.p, idx->tids.p, nullptr, idx->n, idx->m, bits.p, ctx->stream));
+    idx->bits.swap(bits);
+    return BM_OK;
+}
+
+// All pair counts from the bit rows into the packed buffer `out` (device; every entry written).
+bm_status gram_all(bm_index *idx, uint32_t *out)
+{
+    bm_context *ctx = idx->ctx;
+    BitMat a;
+    a.bits = idx->bits.p;
+    a.ld = bit_row_words(idx->m);
+    a.n = a.zero = idx->n;
+    const GramPlan p = plan_gram(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+    HIPC(ctx, idx->gram_ws.ensure(p.ws_floats));
+    Span sp(ctx, PH_COMPARE);
+    HIPC(ctx, launch_gram(p, a, a, out, idx->n, idx->gram_ws.p, ctx->stream));
+    return BM_OK;
 }
 
 // Counts of all pairs among sorted indices >= first into the packed buffer `out` (device, zeroed here).
@@ -2811,42 +2848,17 @@ bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_
         return fail(ctx, BM_ECAPACITY, "out holds %llu entries, %llu needed", (unsigned long long)out_len,
                     (unsigned long long)np);
     HIPC(ctx, hipSetDevice(ctx->device));
-    hipStream_t s = ctx->stream;
-    if (!idx->dense_A.p) {
-        Span sp(ctx, PH_ENCODE);
-        uint64_t ld = ((uint64_t)idx->m + 127) / 128 * 128;
-        const uint64_t pad = dense_row_pad();
-        uint64_t rows = ((uint64_t)idx->n + pad - 1) / pad * pad;
-        HIPC(ctx, idx->dense_A.alloc(rows * ld));
-        DevBuf<uint64_t> bnd;
-        HIPC(ctx, bnd.alloc(bitmap_bounds_words(idx->n, ld)));
-        HIPC(ctx, launch_bitmap_build(idx->off.p, idx->tids.p, idx->n, ld, idx->dense_A.p, bnd.p, s));
-        idx->dense_ld = ld;
-    }
+    BMC(ensure_bits(idx));
     bool host = ptr_kind(out) == PTR_HOST;
     uint32_t *dst = out;
     if (host) {
         HIPC(ctx, idx->pairbuf.ensure(np));
         dst = idx->pairbuf.p;
     }
-    {
-        Span sp(ctx, PH_FILL);
-        HIPC(ctx, fill_u32(dst, np, 0, s));
-    }
-    // one workgroup per CU at a time: about four rounds of them (a short
-    // tail), the contraction split as far as that needs
-    uint64_t T = ((uint64_t)idx->n + dense_row_pad() - 1) / dense_row_pad();
-    uint64_t tiles = T * (T + 1) / 2;
-    uint64_t want = (uint64_t)ctx->n_cu * 4;
-    uint32_t ksplit = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want / std::max<uint64_t>(tiles, 1),
-                                                                          idx->dense_ld / 1024));
-    {
-        Span sp(ctx, PH_COMPARE);
-        HIPC(ctx, launch_dense_gram(idx->dense_A.p, idx->n, idx->dense_ld, idx->dense_ld, dst, ksplit, s));
-    }
+    BMC(gram_all(idx, dst));
     if (host) {
         BMC(download(ctx, out, dst, np * 4));
-        HIPC(ctx, hipStreamSynchronize(s));
+        HIPC(ctx, hipStreamSynchronize(ctx->stream));
     }
     return BM_OK;
 }

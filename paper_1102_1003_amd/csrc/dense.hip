@@ -1,10 +1,15 @@
-// Dense comparator: the plain bitmap route (Sec. I-A, "bitmaps ... AND ... count
-// the number of 1s"; the PBI-GPU layout of Sec. I-B).  Every tidlist becomes a
-// row of a 0/1 int8 matrix A (n x m, zero padded), and all supports are the
-// Gram matrix A A^T, taken on the int8 matrix cores (v_mfma_i32_16x16x64_i8,
-// int32 accumulation, exact while m < 2^31).  Only tiles on or above the
-// diagonal are computed; the contraction dimension may be split across
-// workgroups, partial sums being added atomically.
+// The bitmap route (Sec. I-A, "bitmaps ... AND ... count the number of 1s"; the
+// PBI-GPU layout of Sec. I-B): every tidlist becomes a row of a bit matrix, one
+// bit per transaction, and all supports are the Gram matrix A A^T, taken on
+// the matrix cores.
+//
+// The bits become 4-bit floats (E2M1) in registers: bit 0, 1 or 2 of a nibble
+// alone is 0.5, 1 or 2, so one AND with 0x11111111, 0x22222222 or 0x44444444
+// turns a word of 32 bits into eight operands, and the instruction's block
+// scale (an exact power of two) brings every product of two set bits to 1.
+// v_mfma_scale_f32_32x32x64_f8f6f4 adds them in fp32: counts are whole numbers,
+// exact up to 2^24, and no segment sums more than 2^24 transactions before its
+// counts become u32 (kGramMaxStages).
 #include <algorithm>
 
 #include "bm_internal.h"
@@ -13,297 +18,391 @@ namespace bm {
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-constexpr int DT = 256;   // output tile (rows and columns)
-constexpr int DK = 128;   // contraction bytes staged per step
-constexpr int DPAD = 16;  // LDS row padding against bank conflicts
+// ---------------------------------------------------------------- bit rows
 
-// One workgroup per (row, segment of kBitmapSeg bytes) of A: the segment is
-// assembled in LDS (zeros, then a 1 at every tid of the row's set that falls
-// in it, found by binary search in the sorted tidlist) and written out with
-// 16-byte stores, so every byte of A is written once, in order, and rows past
-// n (the padding) come out zero.
-constexpr uint32_t kBitmapSeg = 16384;
-
-__device__ inline uint64_t lower_bound_u32(const uint32_t *a, uint64_t n, uint64_t x)
+// First position in [lo, hi) of the sorted `a` with a[pos] >= x, by a whole
+// wavefront: 64 probes a round narrow the range 64-fold (three dependent loads
+// for a set of 10^5 where a binary search takes seventeen).
+__device__ inline uint64_t wave_lower_bound(const uint32_t *a, uint64_t lo, uint64_t hi, uint64_t x)
 {
-    uint64_t lo = 0, hi = n;
-    while (lo < hi) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (a[mid] < x)
-            lo = mid + 1;
-        else
-            hi = mid;
+    const uint32_t lane = threadIdx.x & 63;
+    while (hi - lo > 64) {
+        const uint64_t step = (hi - lo + 63) / 64;
+        const uint64_t at = lo + lane * step;
+        const uint64_t below = __ballot(at < hi && a[at] < x);  // a prefix of the lanes
+        const uint32_t c = (uint32_t)__popcll(below);
+        if (c == 0)
+            return lo;
+        hi = std::min(hi, lo + c * step);
+        lo = lo + (uint64_t)(c - 1) * step + 1;
     }
-    return lo;
+    const uint64_t at = lo + lane;
+    return lo + (uint64_t)__popcll(__ballot(at < hi && a[at] < x));
 }
 
-// bnd[i (n_seg + 1) + c] = first position of row i's tids at or past column c
-// kBitmapSeg (a thread per entry: the searches run side by side instead of
-// one after another inside each segment's workgroup).
-__global__ void bitmap_bounds_kernel(const uint64_t *off, const uint32_t *tids, uint32_t n, uint64_t rows,
-                                     uint32_t n_seg, uint64_t *bnd)
-{
-    const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rows * (n_seg + 1))
-        return;
-    const uint64_t i = e / (n_seg + 1), c = e % (n_seg + 1);
-    uint64_t at = 0;
-    if (i < n) {
-        const uint64_t base = off[i], size = off[i + 1] - base;
-        at = base + lower_bound_u32(tids + base, size, c * kBitmapSeg);
-    }
-    bnd[e] = at;
-}
+// One workgroup per (row, segment of kBitSeg transactions): the segment is
+// put together in LDS (zeros, then the bits of the row's tids that fall in it)
+// and leaves in 16-byte stores, so every word of the matrix is written once.
+// Four consecutive tids a thread: the bits of one word are merged before the
+// LDS atomic (in a dense row all four share a word).  Row n_rows is all zero:
+// the rows that pad a tile read it.
+constexpr uint32_t kBitSeg = 1u << 17;  // transactions: 16 KB of LDS, eight workgroups a CU
 
-__global__ void __launch_bounds__(256) bitmap_rows_kernel(const uint32_t *tids, const uint64_t *bnd, uint64_t ld,
-                                                          uint32_t n_seg, int8_t *A)
+__global__ void __launch_bounds__(256) bit_rows_kernel(const uint64_t *__restrict__ off,
+                                                       const uint32_t *__restrict__ tids,
+                                                       const uint32_t *__restrict__ items, uint32_t n_rows,
+                                                       uint64_t ld, uint32_t n_seg, uint32_t *__restrict__ bits)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t seg[kBitmapSeg];
-    const uint64_t i = blockIdx.x / n_seg;
-    const uint32_t c = blockIdx.x % n_seg;
-    const uint64_t c0 = (uint64_t)c * kBitmapSeg;
-    const uint32_t len = (uint32_t)(ld - c0 < kBitmapSeg ? ld - c0 : kBitmapSeg);  // a multiple of 128
-    const uint64_t k0 = bnd[i * (n_seg + 1) + c], k1 = bnd[i * (n_seg + 1) + c + 1];
-    for (uint32_t b = threadIdx.x * 16; b < len; b += blockDim.x * 16)
+    __shared__ __attribute__((aligned(16))) uint32_t seg[kBitSeg / 32];
+    __shared__ uint64_t range[2];
+    const uint32_t row = blockIdx.x / n_seg, c = blockIdx.x % n_seg;
+    const uint64_t w0 = (uint64_t)c * (kBitSeg / 32);
+    const uint32_t len = (uint32_t)std::min<uint64_t>(ld - w0, kBitSeg / 32);  // words, a multiple of 16
+    uint64_t e0 = 0, e1 = 0;
+    if (row < n_rows) {
+        const uint32_t item = items ? items[row] : row;
+        e0 = off[item];
+        e1 = off[item + 1];
+    }
+    for (uint32_t b = threadIdx.x * 4; b < len; b += blockDim.x * 4)
         *reinterpret_cast<uint4 *>(seg + b) = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    for (uint64_t k = k0 + threadIdx.x; k < k1; k += blockDim.x)
-        seg[tids[k] - c0] = 1;
-    __syncthreads();
-    int8_t *row = A + i * ld + c0;
-    for (uint32_t b = threadIdx.x * 16; b < len; b += blockDim.x * 16)
-        *reinterpret_cast<uint4 *>(row + b) = *reinterpret_cast<const uint4 *>(seg + b);
-}
-
-__device__ inline uint64_t packed_index(uint64_t n, uint64_t i, uint64_t j)
-{
-    return i * n - i * (i + 1) / 2 + (j - i - 1);
-}
-
-// 512 threads = 2 x 4 wavefronts, each owning a 128 x 64 part of a 256 x 256
-// tile as 8 x 4 MFMA blocks of 16 x 16 (the int32 x 4 accumulators live in
-// the accumulation registers).  For the MFMA operands, lane l supplies row
-// (l mod 16) of its 16-row block and the 16 contraction bytes
-// [16 (l / 16), 16 (l / 16) + 16) of the current 64; the result lane l,
-// element e holds row 4 (l / 16) + e, column l mod 16 of the block.  Each
-// step stages DK (128) contraction bytes of the 256 row maps and 256 column
-// maps in LDS: 64 KB (whole 128-byte lines of every row) for 256 x 256 x 128
-// MACs.  Per 64 contraction bytes a wavefront reads 12 operand fragments
-// (12 KB) from LDS for 32 MFMAs; at 128 LDS bytes per clock that is about 1.5
-// times the MFMA time of the CU's eight wavefronts, which is what bounds the
-// kernel.  128 x 128 wavefront tiles read 16 KB per 64 MFMAs, but with their
-// 256 accumulation registers only one wavefront fits a SIMD, and its own LDS
-// waits then show (51.7 against 37.3 ms for n = 8192, m = 2^20).
-constexpr int DWR = 2, DWC = 4;                 // wavefronts along rows, columns
-constexpr int DTHREADS = 64 * DWR * DWC;
-constexpr int DMA = DT / DWR / 16, DMB = DT / DWC / 16;  // 16 x 16 blocks of a wavefront
-constexpr int DQ = DT * DK / 16 / DTHREADS;     // 16-byte chunks of each operand a thread stages
-
-// Workgroup b runs on XCD b mod kXcds.  The contraction chunks are dealt to
-// the XCDs (chunk c to XCD c mod kXcds) and, within an XCD, the workgroups of
-// one chunk take every tile on or above the diagonal, in super-tiles of
-// kSuper x kSuper tiles (row-major inside): the workgroups an XCD runs at one
-// time (one per CU) cover a few rows and kSuper columns of one super-tile and
-// walk the contraction at about the same pace, so each row or column panel's
-// lines come from HBM once for all of those tiles and the rest from its L2.
-constexpr uint32_t kSuper = 8;
-template <bool kOff32>
-__global__ __launch_bounds__(DTHREADS, 1) void dense_gram_kernel(const int8_t *__restrict__ A, uint32_t n,
-                                                                 uint64_t ld, uint64_t k_len, uint32_t T,
-                                                                 uint64_t k_chunk, uint32_t n_chunks, uint32_t *out)
-{
-    const uint32_t nS = (T + kSuper - 1) / kSuper;
-    const uint32_t per_chunk = nS * (nS + 1) / 2 * kSuper * kSuper;
-    const uint32_t x = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const uint32_t kc = x + kXcds * (slot / per_chunk);
-    if (kc >= n_chunks)
-        return;
-    const uint32_t u = slot % per_chunk, v = u % (kSuper * kSuper);
-    uint32_t sup = u / (kSuper * kSuper), I = 0;
-    while (sup >= nS - I) {  // super-row I holds super-tiles (I, I) .. (I, nS - 1)
-        sup -= nS - I;
-        I++;
+    if (threadIdx.x < 128) {  // wavefront 0 finds the segment's first tid, wavefront 1 its end
+        const uint32_t w = threadIdx.x >> 6;
+        uint64_t at = w ? e1 : e0;
+        if (n_seg > 1 && e1 > e0 && (w ? c + 1 < n_seg : c > 0))
+            at = wave_lower_bound(tids, e0, e1, (uint64_t)(c + w) * kBitSeg);
+        if ((threadIdx.x & 63) == 0)
+            range[w] = at;
     }
-    const uint32_t ti = I * kSuper + v / kSuper, tj = (I + sup) * kSuper + v % kSuper;
-    if (ti > tj || tj >= T)
-        return;  // below the diagonal, or past the last tile: no work
-    const uint64_t k0 = (uint64_t)kc * k_chunk;
-    const uint64_t k1 = k0 + k_chunk < k_len ? k0 + k_chunk : k_len;
-    // two LDS stages: the MFMAs of step k read one while the waves that are
-    // done with step k - 1 fill the other with step k + 1 (held in registers
-    // since it was fetched during step k - 1), then fetch step k + 2
-    __shared__ __attribute__((aligned(16))) int8_t sA[2][DT][DK + DPAD];
-    __shared__ __attribute__((aligned(16))) int8_t sB[2][DT][DK + DPAD];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wr = wv / DWC, wc = wv % DWC;
-    v4i acc[DMA][DMB];
-#pragma unroll
-    for (int a = 0; a < DMA; a++)
-#pragma unroll
-        for (int b = 0; b < DMB; b++)
-            acc[a][b] = v4i{0, 0, 0, 0};
-    const int8_t *Ar = A + (uint64_t)ti * DT * ld;
-    const int8_t *Br = A + (uint64_t)tj * DT * ld;
-    // thread tid stages chunks tid + DTHREADS q (q < DQ) of each operand: chunk
-    // u is row u / (DK / 16), bytes 16 (u mod (DK / 16)) .. + 16 of the step
-    const int ch = tid % (DK / 16), rq = DTHREADS / (DK / 16), row0 = tid / (DK / 16);
-    const uint64_t rstep = (uint64_t)rq * ld;  // bytes between the rows of chunks q and q + 1
-    // the staging addresses are a uniform base (panel, chunk q, step) plus
-    // this thread's offset; kOff32: the offset fits 32 bits, so every load
-    // takes the base in scalar registers and one shared offset register
-    const uint64_t loff = (uint64_t)row0 * ld + ch * 16;
-    const uint32_t loff32 = (uint32_t)loff;
-    auto ld16 = [&](const int8_t *panel, uint64_t uoff) -> uint4 {
-        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-        typedef __attribute__((address_space(1))) const int8_t GlobalI8;
-        typedef __attribute__((address_space(1))) const u32x4 GlobalV4;
-        GlobalI8 *base = (GlobalI8 *)uniform_u64((uint64_t)panel + uoff);
-        u32x4 v;
-        if constexpr (kOff32)
-            v = *(GlobalV4 *)(base + loff32);
-        else
-            v = *(GlobalV4 *)(base + loff);
-        return uint4{v.x, v.y, v.z, v.w};
-    };
-    static_assert(DQ == 4, "four 16-byte chunks of each operand per thread and step");
-    uint4 ra0{}, ra1{}, ra2{}, ra3{}, rb0{}, rb1{}, rb2{}, rb3{};
-#define BM_DENSE_FETCH(K)                                                   \
-    do {                                                                    \
-        ra0 = ld16(Ar, (K));                  \
-        ra1 = ld16(Ar, 1 * rstep + (K));          \
-        ra2 = ld16(Ar, 2 * rstep + (K));      \
-        ra3 = ld16(Ar, 3 * rstep + (K));      \
-        rb0 = ld16(Br, (K));                  \
-        rb1 = ld16(Br, 1 * rstep + (K));          \
-        rb2 = ld16(Br, 2 * rstep + (K));      \
-        rb3 = ld16(Br, 3 * rstep + (K));      \
-    } while (0)
-#define BM_DENSE_STORE(S)                                                   \
-    do {                                                                    \
-        *reinterpret_cast<uint4 *>(&sA[S][row0][ch * 16]) = ra0;           \
-        *reinterpret_cast<uint4 *>(&sA[S][row0 + rq][ch * 16]) = ra1;      \
-        *reinterpret_cast<uint4 *>(&sA[S][row0 + 2 * rq][ch * 16]) = ra2;  \
-        *reinterpret_cast<uint4 *>(&sA[S][row0 + 3 * rq][ch * 16]) = ra3;  \
-        *reinterpret_cast<uint4 *>(&sB[S][row0][ch * 16]) = rb0;           \
-        *reinterpret_cast<uint4 *>(&sB[S][row0 + rq][ch * 16]) = rb1;      \
-        *reinterpret_cast<uint4 *>(&sB[S][row0 + 2 * rq][ch * 16]) = rb2;  \
-        *reinterpret_cast<uint4 *>(&sB[S][row0 + 3 * rq][ch * 16]) = rb3;  \
-    } while (0)
-    const uint64_t steps = (k1 - k0) / DK;  // k_chunk and k_len are multiples of DK
-    if (steps > 0) {
-        BM_DENSE_FETCH(k0);
-        BM_DENSE_STORE(0);
-    }
-    if (steps > 1)
-        BM_DENSE_FETCH(k0 + DK);
     __syncthreads();
-    for (uint64_t st = 0; st < steps; st++) {
-        const int cur = (int)(st & 1);
+    const uint64_t k1 = range[1];
+    const uint32_t base = c * kBitSeg;
+    for (uint64_t k = range[0] + 4 * threadIdx.x; k < k1; k += 4 * blockDim.x) {
+        uint32_t t[4];
+        const uint32_t cnt = (uint32_t)std::min<uint64_t>(4, k1 - k);
 #pragma unroll
-        for (int ks = 0; ks < DK / 64; ks++) {
-            // every fragment of the sub-step in its own registers, all reads
-            // issued before the first MFMA: the reads arrive while the MFMAs
-            // of the fragments before them run (one register set reused for
-            // the row fragments would put a read's whole latency between
-            // every four MFMAs)
-            v4i fa[DMA], fb[DMB];
-            fa[0] = *reinterpret_cast<const v4i *>(
-                &sA[cur][wr * (DT / DWR) + (lane & 15)][ks * 64 + (lane >> 4) * 16]);
+        for (uint32_t q = 0; q < 4; q++)
+            t[q] = tids[k + (q < cnt ? q : 0)] - base;  // a short tail repeats its first tid
+        uint32_t w = t[0] >> 5, acc = 1u << (t[0] & 31);
 #pragma unroll
-            for (int b = 0; b < DMB; b++)
-                fb[b] = *reinterpret_cast<const v4i *>(
-                    &sB[cur][wc * (DT / DWC) + b * 16 + (lane & 15)][ks * 64 + (lane >> 4) * 16]);
-#pragma unroll
-            for (int a = 1; a < DMA; a++)
-                fa[a] = *reinterpret_cast<const v4i *>(
-                    &sA[cur][wr * (DT / DWR) + a * 16 + (lane & 15)][ks * 64 + (lane >> 4) * 16]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int a = 0; a < DMA; a++)
-#pragma unroll
-                for (int b = 0; b < DMB; b++)
-                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[a], fb[b], acc[a][b], 0, 0, 0);
-        }
-        // the other stage was last read during step st - 1, which every wave
-        // finished before the barrier that closed it
-        if (st + 1 < steps)
-            BM_DENSE_STORE(cur ^ 1);
-        if (st + 2 < steps)
-            BM_DENSE_FETCH(k0 + (st + 2) * DK);
-        __syncthreads();
-    }
-#undef BM_DENSE_STORE
-#undef BM_DENSE_FETCH
-#pragma unroll
-    for (int a = 0; a < DMA; a++) {
-#pragma unroll
-        for (int b = 0; b < DMB; b++) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const uint64_t i = (uint64_t)ti * DT + wr * (DT / DWR) + a * 16 + (lane >> 4) * 4 + e;
-                const uint64_t j = (uint64_t)tj * DT + wc * (DT / DWC) + b * 16 + (lane & 15);
-                const int v = acc[a][b][e];
-                if (i < j && j < n && v != 0)
-                    atomicAdd(&out[packed_index(n, i, j)], (uint32_t)v);
+        for (uint32_t q = 1; q < 4; q++) {
+            const uint32_t bit = 1u << (t[q] & 31);
+            if ((t[q] >> 5) != w) {
+                atomicOr(&seg[w], acc);
+                w = t[q] >> 5;
+                acc = 0;
             }
+            acc |= bit;
+        }
+        atomicOr(&seg[w], acc);
+    }
+    __syncthreads();
+    uint32_t *dst = bits + (uint64_t)row * ld + w0;
+    for (uint32_t b = threadIdx.x * 4; b < len; b += blockDim.x * 4)
+        *reinterpret_cast<uint4 *>(dst + b) = *reinterpret_cast<const uint4 *>(seg + b);
+}
+
+// ---------------------------------------------------------------- Gram matrix
+
+constexpr uint32_t kStageBytes = kGramStage / 8;       // of a row, per stage: 64
+constexpr uint32_t kLdsRow = kStageBytes + 16;         // LDS row stride: 16-byte reads of 32 rows spread over all banks
+
+struct GramArgs {
+    BitMat a, b;
+    uint32_t TR, TC, S, W;  // tile rows and columns, stages per tile, workgroups
+    uint64_t U;             // stages in all: tiles * S
+    uint32_t tri;
+    uint32_t *out;
+    uint64_t n_out;
+    float *ws;
+};
+
+// Tile t of the grid: row-major over the rectangle, or over the tiles on and
+// above the diagonal.
+__device__ inline void tile_at(const GramArgs &g, uint32_t t, uint32_t &ti, uint32_t &tj)
+{
+    if (!g.tri) {
+        ti = t / g.TC;
+        tj = t % g.TC;
+        return;
+    }
+    ti = 0;
+    while (t >= g.TR - ti) {
+        t -= g.TR - ti;
+        ti++;
+    }
+    tj = ti + t;
+}
+
+__device__ inline void put_count(const GramArgs &g, uint32_t i, uint32_t j, uint32_t v)
+{
+    if (g.tri) {
+        if (i < j && j < g.b.n)
+            g.out[(uint64_t)i * g.n_out - (uint64_t)i * (i + 1) / 2 + (j - i - 1)] = v;
+    } else if (i < g.a.n && j < g.b.n) {
+        g.out[(uint64_t)i * g.n_out + j] = v;
+    }
+}
+
+// A workgroup is WR x WC wavefronts, each owning BR x BC blocks of 32 x 32
+// counts.  Lane l holds row (or column) l mod 32 of a block and the 16 bytes
+// l / 32 of the current 32: rows and columns read their bits in the same order,
+// so which bit meets which operand slot does not matter.  Result register e of
+// lane l is row 8 (e / 4) + 4 (l / 32) + e mod 4, column l mod 32.
+//
+// The work is the list of all (tile, stage) in tile order, cut into W equal
+// runs, one per workgroup: whatever the tile count, no workgroup idles.  A run
+// that covers a whole tile writes its counts; a part of a tile goes to the
+// workgroup's own place in ws (its first run part in place 2 w, its last in
+// 2 w + 1), and gram_reduce_kernel adds the parts.  (Device atomics run at about
+// 27 * 10^9 a second here: 0.6 ms for 256 parts of 256 x 256, against 0.03 ms
+// for writing them out and reading them back.)
+//
+// Bound by the matrix cores: 32 MFMAs of 32 cycles a wavefront against 6 LDS
+// reads and 120 VALU operations per 256 transactions (128 x 64 counts).  Bits
+// rather than bytes or nibbles in memory and LDS make the panels 8 and 4 times
+// smaller: a workgroup reads 32 KB per 512 transactions of 256 x 256 counts,
+// about 3 TB/s over the chip at full rate, so that no tile order for the L2s is
+// needed.  m = 2^20, n = 4096: 2.5 ms, 7.0 * 10^15 operations (2 m per pair) a
+// second; the int8 kernel before it (0/1 bytes, v_mfma_i32_16x16x64_i8, bound by
+// its LDS reads) took 9.8 ms.
+template <int BR, int BC, int WR, int WC>
+__global__ void __launch_bounds__(64 * WR * WC, BR * BC >= 8 ? 2 : BR * BC >= 4 ? 3 : 4) bit_gram_kernel(const GramArgs g)
+{
+    constexpr int R = 32 * BR * WR, C = 32 * BC * WC, NT = 64 * WR * WC;
+    constexpr int Q = (R + C) * 4 / NT;  // 16-byte pieces a thread stages
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][R + C][kLdsRow];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, wr = wv / WC, wc = wv % WC;
+    const uint32_t wg = blockIdx.x;
+    const uint64_t u0 = g.U * wg / g.W, u1 = g.U * (wg + 1) / g.W;
+    for (uint64_t u = u0; u < u1;) {
+        const uint32_t t = (uint32_t)(u / g.S), s0 = (uint32_t)(u % g.S);
+        const uint32_t steps = (uint32_t)std::min<uint64_t>(g.S - s0, u1 - u);
+        uint32_t ti, tj;
+        tile_at(g, t, ti, tj);
+        const v4u *src[Q];
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const uint32_t id = tid + NT * q, r = id / 4;
+            const BitMat &m = r < (uint32_t)R ? g.a : g.b;
+            const uint32_t p = r < (uint32_t)R ? ti * R + r : tj * C + (r - R);
+            const uint32_t row = p < m.n ? (m.rows ? m.rows[p] : p) : m.zero;
+            src[q] = reinterpret_cast<const v4u *>(m.bits + (uint64_t)row * m.ld) + (uint64_t)s0 * 4 + id % 4;
+        }
+        v16f acc[BR][BC];
+#pragma unroll
+        for (int a = 0; a < BR; a++)
+#pragma unroll
+            for (int b = 0; b < BC; b++)
+#pragma unroll
+                for (int e = 0; e < 16; e++)
+                    acc[a][b][e] = 0.f;
+        v4u held[Q];
+#define BM_GRAM_FETCH(ST)                                      \
+    _Pragma("unroll") for (int q = 0; q < Q; q++) held[q] = src[q][(uint64_t)(ST) * 4]
+#define BM_GRAM_STORE(TO)                                      \
+    _Pragma("unroll") for (int q = 0; q < Q; q++)              \
+        *reinterpret_cast<v4u *>(&lds[TO][(tid + NT * q) / 4][(tid + NT * q) % 4 * 16]) = held[q]
+        BM_GRAM_FETCH(0);
+        BM_GRAM_STORE(0);
+        if (steps > 1)
+            BM_GRAM_FETCH(1);
+        __syncthreads();
+        for (uint32_t st = 0; st < steps; st++) {
+            const int cur = (int)(st & 1);
+#pragma unroll
+            for (int sub = 0; sub < (int)kStageBytes / 32; sub++) {
+                v4u wa[BR], wb[BC];
+#pragma unroll
+                for (int a = 0; a < BR; a++)
+                    wa[a] = *reinterpret_cast<const v4u *>(
+                        &lds[cur][(wr * BR + a) * 32 + (lane & 31)][sub * 32 + (lane >> 5) * 16]);
+#pragma unroll
+                for (int b = 0; b < BC; b++)
+                    wb[b] = *reinterpret_cast<const v4u *>(
+                        &lds[cur][R + (wc * BC + b) * 32 + (lane & 31)][sub * 32 + (lane >> 5) * 16]);
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    // bit j of every nibble: values 0.5, 1, 2 and (moved down one) 2; the scale of the
+                    // row operand, 2^(s - 127), makes each product 1
+                    constexpr uint32_t kMask[4] = {0x11111111u, 0x22222222u, 0x44444444u, 0x44444444u};
+                    constexpr int kScale[4] = {129, 127, 125, 125};
+                    auto nib = [&](v4u w) {
+                        const int s = j == 3 ? 1 : 0;
+                        return v8i{(int)((w.x >> s) & kMask[j]), (int)((w.y >> s) & kMask[j]),
+                                   (int)((w.z >> s) & kMask[j]), (int)((w.w >> s) & kMask[j]), 0, 0, 0, 0};
+                    };
+                    v8i fa[BR], fb[BC];
+#pragma unroll
+                    for (int a = 0; a < BR; a++)
+                        fa[a] = nib(wa[a]);
+#pragma unroll
+                    for (int b = 0; b < BC; b++)
+                        fb[b] = nib(wb[b]);
+#pragma unroll
+                    for (int a = 0; a < BR; a++)
+#pragma unroll
+                        for (int b = 0; b < BC; b++)
+                            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                                fa[a], fb[b], acc[a][b], 4, 4, 0, kScale[j], 0, 127);
+                }
+            }
+            // the other stage was last read during step st - 1, which every wavefront ended
+            // before the barrier that closed it
+            if (st + 1 < steps)
+                BM_GRAM_STORE(cur ^ 1);
+            if (st + 2 < steps)
+                BM_GRAM_FETCH(st + 2);
+            __syncthreads();
+        }
+#undef BM_GRAM_STORE
+#undef BM_GRAM_FETCH
+        if (steps == g.S) {
+#pragma unroll
+            for (int a = 0; a < BR; a++)
+#pragma unroll
+                for (int b = 0; b < BC; b++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++)
+                        put_count(g, ti * R + (wr * BR + a) * 32 + 8 * (e / 4) + 4 * (lane >> 5) + e % 4,
+                                  tj * C + (wc * BC + b) * 32 + (lane & 31), (uint32_t)acc[a][b][e]);
+        } else {
+            float *part = g.ws + (uint64_t)(2 * wg + (u != u0)) * ((uint64_t)R * C) + wv * (BR * BC * 1024) + lane;
+#pragma unroll
+            for (int a = 0; a < BR; a++)
+#pragma unroll
+                for (int b = 0; b < BC; b++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++)
+                        part[((a * BC + b) * 16 + e) * 64] = acc[a][b][e];
+        }
+        u += steps;
+    }
+}
+
+// Adds the parts of the tiles that several workgroups shared, in the order in
+// which bit_gram_kernel left them, and writes the counts.  Four counts a
+// thread; Y threads share the parts of the same counts (a tile of a small query
+// has hundreds of parts).
+template <int BR, int BC, int WR, int WC, int Y>
+__global__ void __launch_bounds__(256) gram_reduce_kernel(const GramArgs g)
+{
+    constexpr uint32_t R = 32 * BR * WR, C = 32 * BC * WC, X = 256 / Y, kParts = R * C / (4 * X);
+    const uint32_t t = blockIdx.x / kParts, p = blockIdx.x % kParts;
+    const uint64_t t0 = (uint64_t)t * g.S, t1 = t0 + g.S;  // the tile's stages
+    auto at = [&](uint64_t u) {                            // the workgroup that ran stage u
+        uint64_t w = u * g.W / g.U;
+        while (g.U * (w + 1) / g.W <= u)
+            w++;
+        while (g.U * w / g.W > u)
+            w--;
+        return (uint32_t)w;
+    };
+    const uint32_t wa = at(t0), wb = at(t1 - 1);
+    if (wa == wb)
+        return;  // one workgroup covered the tile and wrote its counts
+    const uint32_t x = threadIdx.x % X, y = threadIdx.x / X;
+    const uint32_t e4 = (p * X + x) * 4;
+    const uint32_t late = g.U * wa / g.W != t0;  // the first group came to the tile from another one
+    uint4 sum = make_uint4(0, 0, 0, 0);
+#pragma unroll 4
+    for (uint32_t w = wa + y; w <= wb; w += Y) {
+        const uint32_t place = 2 * w + (w == wa ? late : 0);
+        const float4 v = *reinterpret_cast<const float4 *>(g.ws + (uint64_t)place * (R * C) + e4);
+        sum.x += (uint32_t)v.x;
+        sum.y += (uint32_t)v.y;
+        sum.z += (uint32_t)v.z;
+        sum.w += (uint32_t)v.w;
+    }
+    if constexpr (Y > 1) {
+        __shared__ uint4 part[Y][X];
+        part[y][x] = sum;
+        __syncthreads();
+        if (y != 0)
+            return;
+        for (int k = 1; k < Y; k++) {
+            const uint4 v = part[k][x];
+            sum.x += v.x;
+            sum.y += v.y;
+            sum.z += v.z;
+            sum.w += v.w;
         }
     }
+    uint32_t ti, tj;
+    tile_at(g, t, ti, tj);
+    const uint32_t lane = e4 & 63, e = (e4 >> 6) & 15, blk = e4 >> 10;
+    const uint32_t b = blk % BC, a = blk / BC % BR, wv = blk / (BC * BR), wr = wv / WC, wc = wv % WC;
+    const uint32_t i = ti * R + (wr * BR + a) * 32 + 8 * (e / 4) + 4 * (lane >> 5) + e % 4;
+    const uint32_t j = tj * C + (wc * BC + b) * 32 + (lane & 31);
+    put_count(g, i, j, sum.x);
+    put_count(g, i, j + 1, sum.y);
+    put_count(g, i, j + 2, sum.z);
+    put_count(g, i, j + 3, sum.w);
+}
+
+template <int BR, int BC, int WR, int WC>
+hipError_t run_gram(const GramArgs &g, uint32_t tiles, bool split, hipStream_t s)
+{
+    constexpr uint32_t R = 32 * BR * WR, C = 32 * BC * WC;
+    bit_gram_kernel<BR, BC, WR, WC><<<g.W, 64 * WR * WC, 0, s>>>(g);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !split)
+        return e;
+    const uint32_t per_tile = g.W / tiles;  // parts of a tile, about
+    if (per_tile >= 128)
+        gram_reduce_kernel<BR, BC, WR, WC, 64><<<tiles * (R * C / 16), 256, 0, s>>>(g);
+    else if (per_tile >= 32)
+        gram_reduce_kernel<BR, BC, WR, WC, 16><<<tiles * (R * C / 64), 256, 0, s>>>(g);
+    else if (per_tile >= 8)
+        gram_reduce_kernel<BR, BC, WR, WC, 4><<<tiles * (R * C / 256), 256, 0, s>>>(g);
+    else
+        gram_reduce_kernel<BR, BC, WR, WC, 1><<<tiles * (R * C / 1024), 256, 0, s>>>(g);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-// A: rows x ld (rows = n rounded up to dense_row_pad(), ld a multiple of 128),
-// every byte written; bnd: rows (ceil(ld / kBitmapSeg) + 1) words of scratch.
-uint64_t bitmap_bounds_words(uint32_t n, uint64_t ld)
+hipError_t launch_bit_rows(const uint64_t *off, const uint32_t *tids, const uint32_t *items, uint32_t n_rows,
+                           uint32_t m, uint32_t *bits, hipStream_t s)
 {
-    const uint64_t rows = ((uint64_t)n + DT - 1) / DT * DT;
-    return rows * ((ld + kBitmapSeg - 1) / kBitmapSeg + 1);
-}
-
-hipError_t launch_bitmap_build(const uint64_t *off, const uint32_t *tids, uint32_t n, uint64_t ld, int8_t *A,
-                               uint64_t *bnd, hipStream_t s)
-{
-    const uint64_t rows = ((uint64_t)n + DT - 1) / DT * DT;
-    const uint64_t n_seg = (ld + kBitmapSeg - 1) / kBitmapSeg;
-    if (rows == 0 || ld == 0)
-        return hipSuccess;
-    if (ld % 128 || rows * (n_seg + 1) > 0x7FFFFFFFull)
+    const uint64_t ld = bit_row_words(m);
+    const uint64_t n_seg = (ld + kBitSeg / 32 - 1) / (kBitSeg / 32);
+    if (((uint64_t)n_rows + 1) * n_seg > 0x7FFFFFFFull)
         return hipErrorInvalidValue;
-    const uint64_t entries = rows * (n_seg + 1);
-    bitmap_bounds_kernel<<<(uint32_t)((entries + 255) / 256), 256, 0, s>>>(off, tids, n, rows, (uint32_t)n_seg, bnd);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    bitmap_rows_kernel<<<(uint32_t)(rows * n_seg), 256, 0, s>>>(tids, bnd, ld, (uint32_t)n_seg, A);
+    bit_rows_kernel<<<(uint32_t)((n_rows + 1) * n_seg), 256, 0, s>>>(off, tids, items, n_rows, ld, (uint32_t)n_seg,
+                                                                     bits);
     return hipGetLastError();
 }
 
-// A: n_pad x ld int8 with n_pad a multiple of dense_row_pad() and ld (= k_len) a multiple of 128.
-uint32_t dense_row_pad() { return DT; }
-
-hipError_t launch_dense_gram(const int8_t *A, uint32_t n, uint64_t ld, uint64_t k_len, uint32_t *out,
-                             uint32_t k_split, hipStream_t s)
+hipError_t launch_gram(const GramPlan &p, const BitMat &a, const BitMat &b, uint32_t *out, uint64_t n_out, float *ws,
+                       hipStream_t s)
 {
-    uint32_t T = (n + DT - 1) / DT;
-    if (T == 0 || k_len == 0)
+    if (p.tiles == 0)
         return hipSuccess;
-    // a multiple of kXcds contraction chunks, so every XCD gets as many
-    const uint64_t want = ((uint64_t)std::max<uint32_t>(k_split, 1) + kXcds - 1) / kXcds * kXcds;
-    uint64_t chunk = (k_len + want - 1) / want;
-    chunk = (chunk + DK - 1) / DK * DK;
-    const uint32_t ks = (uint32_t)((k_len + chunk - 1) / chunk);
-    const uint64_t nS = (T + kSuper - 1) / kSuper;
-    const uint64_t per_chunk = nS * (nS + 1) / 2 * kSuper * kSuper;
-    const uint64_t grid = per_chunk * ((ks + kXcds - 1) / kXcds * kXcds);
-    if (grid > 0x7FFFFFFFull)
+    if (a.ld != b.ld || a.ld != (uint64_t)p.stages * (kGramStage / 32) || (p.ws_floats && !ws))
         return hipErrorInvalidValue;
-    // a thread's staging offset is at most (rows per chunk - 1) ld + DK
-    if ((uint64_t)(DTHREADS / (DK / 16) - 1) * ld + DK < (1ull << 32))
-        dense_gram_kernel<true><<<(uint32_t)grid, DTHREADS, 0, s>>>(A, n, ld, k_len, T, chunk, ks, out);
-    else
-        dense_gram_kernel<false><<<(uint32_t)grid, DTHREADS, 0, s>>>(A, n, ld, k_len, T, chunk, ks, out);
-    return hipGetLastError();
+    GramArgs g;
+    g.a = a;
+    g.b = b;
+    g.TR = p.tile_rows;
+    g.TC = p.tile_cols;
+    g.S = p.stages;
+    g.W = p.groups;
+    g.U = (uint64_t)p.tiles * p.stages;
+    g.tri = p.tri;
+    g.out = out;
+    g.n_out = n_out;
+    g.ws = ws;
+    const bool split = p.ws_floats != 0;
+    switch (p.tile) {
+    case 256: return run_gram<4, 2, 2, 4>(g, p.tiles, split, s);
+    case 128: return run_gram<2, 2, 2, 2>(g, p.tiles, split, s);
+    default: return run_gram<1, 1, 2, 2>(g, p.tiles, split, s);
+    }
 }
 
 }  // namespace bm

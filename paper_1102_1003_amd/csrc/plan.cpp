@@ -834,5 +834,50 @@ std::vector<Cls> classes_from(const std::vector<Cls> &cls, uint32_t first)
     return out;
 }
 
+// Time of a plan = launches (10 us for the pair) + stages over the chip + parts
+// written and read back (4 TB/s).  A stage of a 256-, 128- or 64-wide tile takes
+// a CU 2.3, 0.62 or 0.27 us (MI355X, m = 2^20, n = 4096); one, three and up to
+// three workgroups a CU hold it there (their registers).  Small tiles waste
+// less on ragged edges and write smaller parts, large ones read each bit row
+// fewer times.  Measured against this (us): 10^6 x 48: 14 (64) / 34 (128) / 84
+// (256); 50,000 x 1000: 26 / 34 / 41; 50,000 x 4000: 214 / 162 / 167; 10^6 x
+// 2000: 930 / 668 / 671; 2^20 x 4096: 4655 / 2771 / 2618; 500,000 x 8192: 8754
+// / 5435 / 4573.  A group of 64-wide tiles takes at least 8 stages, one of
+// 128-wide ones 4: fewer only add parts (10^6 x 48 with 768 groups of 64-wide
+// tiles 21 us).
+GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned)
+{
+    GramPlan best;
+    for (int tile : {256, 128, 64}) {
+        if (pinned && tile != pinned)
+            continue;
+        GramPlan p;
+        p.tile = tile;
+        p.tri = tri;
+        p.stages = (uint32_t)(row_words / (kGramStage / 32));
+        p.tile_rows = (na + tile - 1) / tile;
+        p.tile_cols = (nb + tile - 1) / tile;
+        const uint64_t tiles =
+            tri ? (uint64_t)p.tile_rows * (p.tile_rows + 1) / 2 : (uint64_t)p.tile_rows * p.tile_cols;
+        p.tiles = (uint32_t)tiles;
+        const uint64_t U = tiles * p.stages;
+        const double stage_us = tile == 256 ? 2.3 : (tile == 128 ? 0.62 : 0.27);
+        uint64_t per_cu = 1;
+        if (tile != 256)
+            per_cu = std::min<uint64_t>(std::max<uint64_t>(U / ((uint64_t)n_cu * (tile == 64 ? 8 : 4)), 1), 3);
+        // enough groups that none adds more than kGramMaxStages stages
+        const uint64_t least = std::max<uint64_t>((U + kGramMaxStages - 1) / kGramMaxStages, 1);
+        p.groups = (uint32_t)std::max<uint64_t>(std::min<uint64_t>(U, n_cu * per_cu), least);
+        const double part = 4.0 * tile * tile;
+        p.us = 10 + (double)U * stage_us / n_cu;
+        if (p.groups && (U % p.groups != 0 || (U / p.groups) % p.stages != 0)) {
+            p.ws_floats = (uint64_t)p.groups * 2 * tile * tile;
+            p.us += (double)std::min<uint64_t>(2ull * p.groups, p.groups + tiles) * part * 2 / 4e6;
+        }
+        if (!best.groups || p.us < best.us)
+            best = p;
+    }
+    return best;
+}
 
 }  // namespace bm

@@ -171,5 +171,34 @@ constexpr uint32_t kXcds = 8;
 // reordered list.
 void xcd_queues(std::vector<WorkItem> &flat, uint32_t off[kXcds + 1]);
 
+// ------------------------------------------------------------- bitmap route
+// Bit rows hold one bit per transaction, padded to whole stages: a stage is
+// what the Gram kernel stages at a time.
+constexpr uint32_t kGramStage = 512;
+inline uint64_t bit_row_words(uint32_t m)
+{
+    return ((uint64_t)m + kGramStage - 1) / kGramStage * (kGramStage / 32);
+}
+// A workgroup adds at most this many stages of a tile in fp32 (2^24
+// transactions: counts stay exact whole numbers).
+constexpr uint64_t kGramMaxStages = (1u << 24) / kGramStage;
+
+// How a Gram matrix is cut: tiles of tile x tile counts (tri: those on and
+// above the diagonal), each over `stages` stages.  The (tile, stage) list in
+// tile order is cut into `groups` equal runs, run w = [U w / W, U (w + 1) / W)
+// of the U = tiles * stages; ws_floats of scratch hold the parts of tiles that
+// several runs share (0: none is shared).
+struct GramPlan {
+    int tile = 256;
+    uint32_t tile_rows = 0, tile_cols = 0, tiles = 0, stages = 0, groups = 0;
+    bool tri = true;
+    uint64_t ws_floats = 0;
+    double us = 0;  // expected time
+};
+
+// The tile size with the least expected time for na x nb counts (tri: the
+// pairs i < j of one family, na == nb) over rows of row_words words.  pinned:
+// 64, 128 or 256 takes that tile.
+GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0);
 
 }  // namespace bm

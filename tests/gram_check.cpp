@@ -1,0 +1,49 @@
+// Host checks of plan_gram, built with plan.cpp (no GPU).
+#include <cstdint>
+#include <cstdio>
+#include <set>
+
+#include "../paper_1102_1003_amd/csrc/plan.h"
+
+// Walks every group's run as the Gram kernel does: 0, or a message.  Each
+// (tile, stage) is visited once, no run part passes the fp32 bound, each shared
+// part has a place of its own inside ws, and gram_reduce_kernel's rule finds it.
+extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned, char *msg,
+                          uint32_t len)
+{
+    const bm::GramPlan p = bm::plan_gram(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned);
+    const uint64_t U = (uint64_t)p.tiles * p.stages, W = p.groups;
+    auto bad = [&](const char *what) {
+        snprintf(msg, len, "%s: tile %d tiles %u stages %u groups %u", what, p.tile, p.tiles, p.stages, p.groups);
+        return 1;
+    };
+    if ((uint64_t)p.tile_rows * p.tile < na || (uint64_t)p.tile_cols * p.tile < nb)
+        return bad("counts left out");
+    if ((uint64_t)p.stages * bm::kGramStage < m || W == 0 || W > U)
+        return bad("bad cut");
+    uint64_t seen = 0;
+    std::set<uint64_t> places;
+    for (uint64_t w = 0; w < W; w++) {
+        const uint64_t u0 = U * w / W, u1 = U * (w + 1) / W;
+        if (u0 != seen || u1 <= u0)
+            return bad("runs do not follow one another");
+        for (uint64_t u = u0; u < u1;) {
+            const uint64_t t = u / p.stages, s0 = u % p.stages;
+            const uint64_t steps = p.stages - s0 < u1 - u ? p.stages - s0 : u1 - u;
+            if (steps > bm::kGramMaxStages)
+                return bad("a part passes the fp32 bound");
+            if (steps != p.stages) {
+                const uint64_t place = 2 * w + (u != u0);
+                if ((place + 1) * p.tile * p.tile > p.ws_floats || !places.insert(place).second)
+                    return bad("a part without a place of its own");
+                // the reduction's rule: the first group's place is its second when it came from another tile
+                const bool first = u == t * p.stages;
+                if (place != 2 * w + (first && u0 != t * p.stages))
+                    return bad("the reduction would look elsewhere");
+            }
+            u += steps;
+        }
+        seen = u1;
+    }
+    return seen == U ? 0 : bad("stages left out");
+}

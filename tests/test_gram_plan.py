@@ -1,0 +1,33 @@
+"""The bitmap route's cut (plan_gram), checked on the CPU: every (tile, stage) is counted once, fp32
+parts stay within 2^24 transactions, and the reduction finds every part."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("gram") / "libgramcheck.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC",
+                    os.path.join(ROOT, "paper_1102_1003_amd", "csrc", "plan.cpp"),
+                    os.path.join(ROOT, "tests", "gram_check.cpp"), "-o", out], check=True)
+    lib = ctypes.CDLL(out)
+
+    def run(na, nb, tri, m, n_cu=256, pinned=0):
+        msg = ctypes.create_string_buffer(256)
+        assert lib.gram_check(na, nb, int(tri), ctypes.c_uint32(m), n_cu, pinned, msg, 256) == 0, msg.value.decode()
+    return run
+
+
+@pytest.mark.parametrize("pinned", [0, 64, 128, 256])
+@pytest.mark.parametrize("m", [1, 511, 512, 513, 10_000, 1_000_003, 2**24 + 1, 2**32 - 1])
+def test_cut(check, m, pinned):
+    for n in (2, 63, 64, 65, 129, 257, 2000):
+        if n < 300 or m < 2**24:
+            check(n, n, True, m, pinned=pinned)
+            check(n, 31, False, m, pinned=pinned)
+    check(300, 1, False, m, n_cu=8, pinned=pinned)
