@@ -117,7 +117,8 @@ typedef struct {
 /* Per-phase device times of the last build and the last query on a context,
  * taken with HIP events on the context's stream while profiling is on.
  * compare_slot_pairs is the algorithmic work of the last query's compare:
- * the sum over its pairs of 3 max(r_i, r_j) slot comparisons. */
+ * the sum over its pairs of 3 max(r_i, r_j) slot comparisons; 0 when the
+ * query took the bitmap route (see bm_all_pair_supports). */
 typedef struct {
     double ingest_ms;     /* validation / transactions -> tidlists */
     double layout_ms;     /* permutations, size order, r_i and offsets */
@@ -205,7 +206,12 @@ void bm_index_destroy(bm_index *idx);
 
 /* Exact |S_i cap S_j| for all i < j (Sec. II; the output of Sec. IV-A is "the
  * support of every pair"), packed upper triangle.  out: host or device,
- * out_len >= n(n-1)/2.  BM_EINVAL if the index was built with min_support > 0. */
+ * out_len >= n(n-1)/2.  BM_EINVAL if the index was built with min_support > 0.
+ * The pairs are counted by comparing BatMaps or, where that is expected to be
+ * faster (sets of more than about half a percent of the transactions), from
+ * bit rows on the matrix cores as bm_all_pair_supports_dense does; the counts
+ * are exact either way.  Bit rows take n m / 8 bytes, at most a sixteenth of
+ * the device's memory, and the index keeps them until it is destroyed. */
 bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len);
 
 /* Frequent pair mining (Sec. I: pairs with support at least sigma): every

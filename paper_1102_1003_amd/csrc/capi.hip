@@ -243,6 +243,7 @@ struct bm_context {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int n_cu = 256;
+    uint64_t mem_bytes = 0;  // of the device
     std::string err;
     DevBuf<uint32_t> counter;  // persistent-kernel work counters
     DevBuf<InstDesc> desc1;    // the instance of a single-call persistent compare
@@ -405,7 +406,7 @@ struct bm_index {
     DevBuf<InstDesc> x_descs;
     // bitmap route: a bit row per item and the zero row, made at first use
     DevBuf<uint32_t> bits;
-    DevBuf<float> gram_ws;
+    DevBuf<float> gram_ws;  // bm_all_pair_supports_dense
 };
 
 struct bm_batch {
@@ -1543,6 +1544,60 @@ InstDesc whole_desc(const bm_index *idx, uint32_t *out)
     return d;
 }
 
+// ------------------------------------------------------------ bitmap route
+// Which way a call's pairs are counted is a matter of time alone: the counts
+// are exact either way.  A pair of maps costs 3 max(r_i, r_j) slot compares,
+// so the slot compare is the faster one where sets are sparse; a pair of bit
+// rows costs m bits on the matrix cores whatever the sets.
+
+// BM_BITMAP_ROUTE=0 keeps every call on the slot compare, 1 takes the bitmap
+// route wherever it can be taken, whatever the expected times.
+int bitmap_route_env()
+{
+    const char *e = getenv("BM_BITMAP_ROUTE");
+    return !e || !*e ? -1 : (e[0] != '0');
+}
+
+// Whether calls may take the bitmap route: not when the environment or the
+// context pins how slots are compared (those calls are there to run that
+// compare).
+bool bitmap_route_on(const bm_context *ctx)
+{
+    return bitmap_route_env() != 0 && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
+}
+
+// Expected time of a slot compare (us): W + 1 VALU operations per 32 slot
+// pairs, 30 * 10^12 a second with 8-bit slots and 20 with wider ones; fixed_us
+// for its launches, zero fill and corrections.  Both sides measured (MI355X,
+// us, rows built in the call included): 10^4 x 200 at 2 %: 85 slots, 25 bits;
+// 50,000 x 4000 at 5 %: 1818 and 175; 10^6 x 2000 Zipf at 2 %: 4700 and 760;
+// 2^20 x 8192 at 0.05 % (16-bit slots): 4806 and 9900, which stays with slots.
+double compare_us(double slot_pairs, uint32_t planes, double fixed_us)
+{
+    return fixed_us + slot_pairs / 32 * (planes + 1) / (planes == 8 ? 30e6 : 20e6);
+}
+
+// Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
+double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (rows * row_words + tids) * 4 / 2.5e6; }
+
+// Whether `rows` bit rows may be made: at most a sixteenth of the device's memory.
+bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
+{
+    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16;
+}
+
+// A stream being captured takes the slot compare, as ever: the bitmap
+// route's rows and scratch would become part of the graph.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 // The index's bit rows (every item's), made at the first call that needs them.
 bm_status ensure_bits(bm_index *idx)
 {
@@ -1557,18 +1612,64 @@ bm_status ensure_bits(bm_index *idx)
     return BM_OK;
 }
 
-// All pair counts from the bit rows into the packed buffer `out` (device; every entry written).
-bm_status gram_all(bm_index *idx, uint32_t *out)
+BitMat whole_bits(const bm_index *idx)
 {
-    bm_context *ctx = idx->ctx;
     BitMat a;
     a.bits = idx->bits.p;
     a.ld = bit_row_words(idx->m);
     a.n = a.zero = idx->n;
-    const GramPlan p = plan_gram(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
-    HIPC(ctx, idx->gram_ws.ensure(p.ws_floats));
-    Span sp(ctx, PH_COMPARE);
-    HIPC(ctx, launch_gram(p, a, a, out, idx->n, idx->gram_ws.p, ctx->stream));
+    return a;
+}
+
+// All pair counts of `list` (k item ids in host memory; null: all items, k =
+// n) into the packed triangle `out` (device, every entry written), when the
+// bitmap route is expected to beat a slot compare of other_us; `taken` says
+// whether it was.  It is not where its memory cannot be had.  A list of most
+// items (or all) makes every item's row, which the index keeps; a shorter one
+// makes its own rows unless the index already holds them.  ids: receives the
+// list on the device.
+bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double other_us, uint32_t *out,
+                     DevBuf<uint32_t> &ids, bool &taken)
+{
+    taken = false;
+    bm_context *ctx = idx->ctx;
+    hipStream_t s = ctx->stream;
+    if (!bitmap_route_on(ctx))
+        return BM_OK;
+    const uint64_t ld = bit_row_words(idx->m);
+    const GramPlan p = plan_gram(k, k, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+    const bool have = idx->bits.p != nullptr;
+    const bool whole = have || !list || (uint64_t)k * 4 >= (uint64_t)idx->n * 3;
+    const uint32_t rows = whole ? idx->n : k;
+    double us = p.us;
+    if (!have)
+        us += bit_rows_us(rows, ld, (double)idx->nnz * rows / idx->n);
+    if ((us >= other_us && bitmap_route_env() != 1) || (!have && !bit_rows_fit(ctx, rows, ld)) || capturing(s))
+        return BM_OK;
+    DevBuf<float> ws;
+    DevBuf<uint32_t> own;
+    if (ws.alloc(p.ws_floats) != hipSuccess || (list && ids.alloc(k) != hipSuccess))
+        return BM_OK;
+    if (!whole && own.alloc(((uint64_t)k + 1) * ld) != hipSuccess)
+        return BM_OK;
+    if (whole && ensure_bits(idx) != BM_OK) {
+        ctx->err.clear();
+        return BM_OK;
+    }
+    if (list)
+        BMC(upload(ctx, ids.p, list, 4ull * k));
+    BitMat a = whole_bits(idx);
+    Span sp(ctx, PH_COMPARE);  // rows made for this call alone included
+    if (whole) {
+        a.rows = list ? ids.p : nullptr;
+        a.n = k;
+    } else {
+        HIPC(ctx, launch_bit_rows(idx->off.p, idx->tids.p, ids.p, k, idx->m, own.p, s));
+        a.bits = own.p;
+        a.n = a.zero = k;
+    }
+    HIPC(ctx, launch_gram(p, a, a, out, k, ws.p, s));
+    taken = true;
     return BM_OK;
 }
 
@@ -1754,8 +1855,10 @@ bm_status bm_context_create(int device, void *hip_stream, bm_context **out)
         ctx->own_stream = true;
     }
     hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, device) == hipSuccess)
+    if (hipGetDeviceProperties(&prop, device) == hipSuccess) {
         ctx->n_cu = prop.multiProcessorCount;
+        ctx->mem_bytes = prop.totalGlobalMem;
+    }
     // BM_COMPARE_PERSISTENT=1 runs single-call compares as one multi-shape
     // persistent launch (tuning aid).  The default, one launch per tile shape,
     // is faster there on the same items: its waves retire after one item, so
@@ -2231,9 +2334,11 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
         HIPC(ctx, idx->pairbuf.ensure(np));
         dst = idx->pairbuf.p;
     }
-    bm_status st = count_pairs(idx, 0, dst);
-    if (st != BM_OK)
-        return st;
+    bool taken = false;
+    DevBuf<uint32_t> ids;
+    BMC(gram_pairs(idx, nullptr, idx->n, compare_us(class_work(idx->classes), idx->planes, 40), dst, ids, taken));
+    if (!taken)
+        BMC(count_pairs(idx, 0, dst));
     if (host) {
         BMC(download(ctx, out, dst, np * 4));
         HIPC(ctx, hipStreamSynchronize(ctx->stream));
@@ -2265,10 +2370,30 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
     uint32_t first = (uint32_t)(std::lower_bound(idx->h_sizes_sorted.begin(), idx->h_sizes_sorted.end(), min_support) -
                                 idx->h_sizes_sorted.begin());
     first = std::max(first, idx->first_built);
+    // the items that can be in one, by id: the bitmap route counts the pairs
+    // among them alone, packed over this list
+    const uint32_t live = idx->n - first;
+    if (live < 2)
+        return BM_OK;
+    std::vector<uint32_t> ids;
+    if (first > 0) {
+        ids.assign(idx->h_sorted_items.begin() + first, idx->h_sorted_items.end());
+        std::sort(ids.begin(), ids.end());
+    }
+    const double slots = class_work(first ? classes_from(idx->classes, first) : idx->classes);
+    DevBuf<uint32_t> d_ids;
+    bool taken = false;
     HIPC(ctx, idx->pairbuf.ensure(np));
-    bm_status st = count_pairs(idx, first, idx->pairbuf.p);
-    if (st != BM_OK)
-        return st;
+    BMC(gram_pairs(idx, first ? ids.data() : nullptr, live, compare_us(slots, idx->planes, 40), idx->pairbuf.p, d_ids,
+                   taken));
+    uint32_t n_eff = idx->n;
+    if (!taken) {
+        BMC(count_pairs(idx, first, idx->pairbuf.p));
+    } else if (first) {
+        n_eff = live;
+        np = n_pairs(live);
+    }
+    const uint32_t *thr_ids = n_eff < idx->n ? d_ids.p : nullptr;
     uint32_t nb = threshold_blocks(np);
     HIPC(ctx, idx->thr_counts.ensure((uint64_t)nb + 1));
     HIPC(ctx, idx->thr_off.ensure((uint64_t)nb + 1));
@@ -2281,13 +2406,11 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
     // writes nothing when the total exceeds capacity)
     const bool host = out && ptr_kind(out) == PTR_HOST;
     if (out && !host)
-        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, idx->n, min_support, idx->thr_off.p, nb, capacity, out,
+        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, n_eff, thr_ids, min_support, idx->thr_off.p, nb, capacity, out,
                                          s));
     uint64_t total = 0;
     span_thr.end();
-    st = read_back(ctx, &total, idx->thr_off.p + nb, 8);
-    if (st != BM_OK)
-        return st;
+    BMC(read_back(ctx, &total, idx->thr_off.p + nb, 8));
     *n_out = total;
     if (total == 0)
         return BM_OK;
@@ -2301,7 +2424,7 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
         HIPC(ctx, idx->pair_out.ensure(total));
         dst = idx->pair_out.p;
         Span sp(ctx, PH_THRESHOLD);
-        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, idx->n, min_support, idx->thr_off.p, nb, total, dst, s));
+        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, n_eff, thr_ids, min_support, idx->thr_off.p, nb, total, dst, s));
     }
     if (host) {
         BMC(download(ctx, out, dst, total * sizeof(bm_pair)));
@@ -2381,7 +2504,7 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     HIPC(ctx, launch_threshold_count(counts, np, min_support, thr_counts, nb, s));
     HIPC(ctx, exclusive_scan_u32_to_u64(thr_counts, thr_off, (uint64_t)nb + 1, sc + o_tmp, s));
     if (out)
-        HIPC(ctx, launch_threshold_write(counts, np, idx->n, min_support, thr_off, nb, capacity, out, s));
+        HIPC(ctx, launch_threshold_write(counts, np, idx->n, nullptr, min_support, thr_off, nb, capacity, out, s));
     uint64_t total = 0;
     BMC(read_back(ctx, &total, thr_off + nb, 8));
     *n_out = total;
@@ -2855,7 +2978,13 @@ bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_
         HIPC(ctx, idx->pairbuf.ensure(np));
         dst = idx->pairbuf.p;
     }
-    BMC(gram_all(idx, dst));
+    const BitMat a = whole_bits(idx);
+    const GramPlan p = plan_gram(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+    HIPC(ctx, idx->gram_ws.ensure(p.ws_floats));
+    {
+        Span sp(ctx, PH_COMPARE);
+        HIPC(ctx, launch_gram(p, a, a, dst, idx->n, idx->gram_ws.p, ctx->stream));
+    }
     if (host) {
         BMC(download(ctx, out, dst, np * 4));
         HIPC(ctx, hipStreamSynchronize(ctx->stream));

@@ -180,7 +180,9 @@ __device__ inline uint64_t row_of_packed(uint64_t k, uint64_t n)
 
 // Writes nothing when the total (block_off[n_blocks]) exceeds capacity, so the
 // write can be queued before the host has read the total.
-__global__ void threshold_write_kernel(const uint32_t *sup, uint64_t n_pairs, uint64_t n, uint32_t sigma,
+// ids: the item of each of the n positions (null: position p is item p).
+__global__ void threshold_write_kernel(const uint32_t *sup, uint64_t n_pairs, uint64_t n, const uint32_t *ids,
+                                       uint32_t sigma,
                                        const uint64_t *block_off, uint32_t n_blocks, uint64_t capacity,
                                        bm_pair *out)
 {
@@ -214,6 +216,10 @@ __global__ void threshold_write_kernel(const uint32_t *sup, uint64_t n_pairs, ui
             bm_pair pr;
             pr.i = (uint32_t)row;
             pr.j = (uint32_t)(row + 1 + (k - row_start));
+            if (ids) {
+                pr.i = ids[pr.i];
+                pr.j = ids[pr.j];
+            }
             pr.support = v[i];
             out[pos++] = pr;
         }
@@ -354,13 +360,13 @@ hipError_t launch_threshold_count(const uint32_t *sup, uint64_t n_pairs, uint32_
     return hipGetLastError();
 }
 
-hipError_t launch_threshold_write(const uint32_t *sup, uint64_t n_pairs, uint64_t n, uint32_t sigma,
-                                  const uint64_t *block_off, uint32_t n_blocks, uint64_t capacity, bm_pair *out,
-                                  hipStream_t s)
+hipError_t launch_threshold_write(const uint32_t *sup, uint64_t n_pairs, uint64_t n, const uint32_t *ids,
+                                  uint32_t sigma, const uint64_t *block_off, uint32_t n_blocks, uint64_t capacity,
+                                  bm_pair *out, hipStream_t s)
 {
     if (n_blocks == 0)
         return hipSuccess;
-    threshold_write_kernel<<<n_blocks, kBlock, 0, s>>>(sup, n_pairs, n, sigma, block_off, n_blocks, capacity, out);
+    threshold_write_kernel<<<n_blocks, kBlock, 0, s>>>(sup, n_pairs, n, ids, sigma, block_off, n_blocks, capacity, out);
     return hipGetLastError();
 }
 

@@ -44,3 +44,64 @@ def test_counts_past_fp32(ctx):
     tids = np.tile(np.arange(m, dtype=np.uint32), n)
     idx = bm.Index.from_sets(ctx, m, off, tids)
     assert np.array_equal(idx.all_pair_supports_dense(), np.full(3, m, np.uint32))
+
+
+@pytest.mark.parametrize("route", ["0", "1", None])
+@pytest.mark.parametrize("m,n,p,opts", [
+    (10_000, 200, 0.02, {}),
+    (20_000, 90, 0.3, dict(max_loop=0)),             # every insertion fails: slot counts are all corrections
+    (60_000, 150, 0.002, dict(slot_bits=16)),
+    (5_000, 2, 0.5, {}),
+])
+def test_pairs_either_route(ctx, monkeypatch, route, m, n, p, opts):
+    """All pairs and frequent pairs give the same counts by slots and by bits."""
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    rng = np.random.default_rng(m)
+    off, tids = datagen.sets_from_probs(m, p * rng.uniform(0, 2, n), seed=m + n)
+    want = oracle.all_pairs(off, tids)
+    sizes = np.sort(np.diff(off))
+    idx = bm.Index.from_sets(ctx, m, off, tids, **opts)
+    for rep in range(2):                               # rows made, rows kept
+        assert np.array_equal(idx.all_pair_supports(np.full(want.size, 9, np.uint32)), want)
+        ctx.set_profiling(True)
+        idx.all_pair_supports()
+        assert (ctx.timings()["compare_slot_pairs"] == 0) == (route == "1") or route is None
+        ctx.set_profiling(False)
+    for sigma in (0, 1, int(np.median(want)) + 1, int(sizes[n // 2]), int(sizes[-1]), int(sizes[-1]) + 1):
+        fresh = bm.Index.from_sets(ctx, m, off, tids, **opts)          # rows of the live items alone
+        pruned = bm.Index.from_sets(ctx, m, off, tids, min_support=sigma, **opts)
+        ref = oracle.frequent_pairs(off, tids, sigma)
+        for ix in (idx, fresh, pruned):
+            assert np.array_equal(ix.frequent_pairs(sigma), ref), sigma
+
+
+def test_capture_takes_the_slot_compare(monkeypatch):
+    """A captured call replays right after eager calls have made (and used) the bit rows."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    stream = torch.cuda.Stream()
+    c = bm.Context(0, stream)
+    m, n = 40_000, 300
+    off, tids = datagen.bernoulli_sets(m, n, 0.05, seed=3)
+    want = oracle.all_pairs(off, tids)
+    idx = bm.Index.from_sets(c, m, off, tids)
+    out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
+    monkeypatch.setenv("BM_BITMAP_ROUTE", "0")
+    torch.cuda.synchronize()
+    idx.all_pair_supports(out)                         # the slot compare's streams and events exist
+    monkeypatch.setenv("BM_BITMAP_ROUTE", "1")
+    idx.all_pair_supports(out)
+    c.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        idx.all_pair_supports(out)
+    for rep in range(3):
+        out.fill_(-1)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+        assert np.array_equal(idx.all_pair_supports(), want)
+    del g
+    c.close()
