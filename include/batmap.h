@@ -271,7 +271,8 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
 /* Pair supports among a subset of items (k distinct ids, host or device):
  * out (host or device) gets k(k-1)/2 entries, packed upper triangle in the
  * order given.  BM_EINVAL on a repeated id or an item without a BatMap,
- * BM_ERANGE on an id >= n. */
+ * BM_ERANGE on an id >= n.  Counted by slots or by bits as for
+ * bm_all_pair_supports. */
 bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t k, uint32_t *out);
 
 /* Many instances at once.  A batch plans all pairs of `count` indexes

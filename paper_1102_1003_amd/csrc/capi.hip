@@ -406,7 +406,8 @@ struct bm_index {
     DevBuf<InstDesc> x_descs;
     // bitmap route: a bit row per item and the zero row, made at first use
     DevBuf<uint32_t> bits;
-    DevBuf<float> gram_ws;  // bm_all_pair_supports_dense
+    uint64_t bit_rows_made = 0;  // by calls that made the rows of their list alone
+    DevBuf<float> gram_ws;       // bm_all_pair_supports_dense
 };
 
 struct bm_batch {
@@ -1626,8 +1627,9 @@ BitMat whole_bits(const bm_index *idx)
 // bitmap route is expected to beat a slot compare of other_us; `taken` says
 // whether it was.  It is not where its memory cannot be had.  A list of most
 // items (or all) makes every item's row, which the index keeps; a shorter one
-// makes its own rows unless the index already holds them.  ids: receives the
-// list on the device.
+// makes its own rows, until such lists have made as many rows as the index has
+// items: then the index's are made (their cost is what was spent already).
+// ids: receives the list on the device.
 bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double other_us, uint32_t *out,
                      DevBuf<uint32_t> &ids, bool &taken)
 {
@@ -1639,12 +1641,15 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
     const uint64_t ld = bit_row_words(idx->m);
     const GramPlan p = plan_gram(k, k, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
     const bool have = idx->bits.p != nullptr;
-    const bool whole = have || !list || (uint64_t)k * 4 >= (uint64_t)idx->n * 3;
-    const uint32_t rows = whole ? idx->n : k;
+    const bool most = !list || (uint64_t)k * 4 >= (uint64_t)idx->n * 3;
+    const bool whole = have || ((most || idx->bit_rows_made + k > idx->n) && bit_rows_fit(ctx, idx->n, ld));
+    if (!whole && (!list || !bit_rows_fit(ctx, k, ld)))
+        return BM_OK;
+    const uint32_t paid = most ? idx->n : k;  // rows this call accounts for
     double us = p.us;
     if (!have)
-        us += bit_rows_us(rows, ld, (double)idx->nnz * rows / idx->n);
-    if ((us >= other_us && bitmap_route_env() != 1) || (!have && !bit_rows_fit(ctx, rows, ld)) || capturing(s))
+        us += bit_rows_us(paid, ld, (double)idx->nnz * paid / idx->n);
+    if ((us >= other_us && bitmap_route_env() != 1) || capturing(s))
         return BM_OK;
     DevBuf<float> ws;
     DevBuf<uint32_t> own;
@@ -1667,6 +1672,7 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
         HIPC(ctx, launch_bit_rows(idx->off.p, idx->tids.p, ids.p, k, idx->m, own.p, s));
         a.bits = own.p;
         a.n = a.zero = k;
+        idx->bit_rows_made += k;
     }
     HIPC(ctx, launch_gram(p, a, a, out, k, ws.p, s));
     taken = true;
@@ -2617,6 +2623,42 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
     for (uint32_t p = 0; p < k; p++)
         if (q[p] >= idx->n)
             return fail(ctx, BM_ERANGE, "item %u >= n", q[p]);
+    const bool host = ptr_kind(out) == PTR_HOST;
+    uint32_t *dst = out;
+    if (host && np) {
+        HIPC(ctx, idx->sub_out.ensure(np));
+        dst = idx->sub_out.p;
+    }
+    if (np && bitmap_route_on(ctx)) {
+        // a query that would be refused goes on to the checks below
+        bool good = true;
+        std::vector<bool> seen(idx->n);
+        uint32_t of_width[33] = {};  // maps by log2 r_i
+        for (uint32_t p = 0; p < k && good; p++) {
+            const uint64_t sz = idx->h_off[q[p] + 1] - idx->h_off[q[p]];
+            good = !seen[q[p]] && sz >= idx->min_support;
+            seen[q[p]] = true;
+            uint32_t l = 0;
+            while ((1ull << l) < std::max<uint64_t>(idx->r0, 2 * sz))
+                l++;
+            of_width[l]++;
+        }
+        std::vector<Cls> cls;
+        for (uint32_t l = 0, at = 0; l < 33; at += of_width[l++])
+            if (of_width[l])
+                cls.push_back({(uint32_t)std::min<uint64_t>(1ull << l, UINT32_MAX), at, of_width[l]});
+        bool taken = false;
+        DevBuf<uint32_t> ids;
+        // the slot compare plans its tiles on the host and uploads five lists: about 80 us
+        if (good)
+            BMC(gram_pairs(idx, q.data(), k, compare_us(class_work(cls), idx->planes, 80), dst, ids, taken));
+        if (taken) {
+            if (host)
+                BMC(download(ctx, out, dst, np * 4));
+            HIPC(ctx, hipStreamSynchronize(s));
+            return BM_OK;
+        }
+    }
     HIPC(ctx, idx->pos_of_item.ensure(idx->n));
     HIPC(ctx, idx->sub_items.ensure(k));
     HIPC(ctx, idx->sub_flag.ensure(1));
@@ -2671,12 +2713,6 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
     BMC(upload(ctx, idx->sub_goff.p, h_goff.data(), (uint64_t)k * 8));
     BMC(upload(ctx, idx->sub_outpos.p, h_outpos.data(), (uint64_t)k * 4));
     BMC(upload(ctx, idx->sub_gcnt.p, h_gcnt.data(), (uint64_t)k * 4));
-    bool host = ptr_kind(out) == PTR_HOST;
-    uint32_t *dst = out;
-    if (host) {
-        HIPC(ctx, idx->sub_out.ensure(np));
-        dst = idx->sub_out.p;
-    }
     InstDesc d;
     d.arena = reinterpret_cast<const uint4 *>(idx->arena.p);
     d.goff = idx->sub_goff.p;

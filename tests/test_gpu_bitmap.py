@@ -105,3 +105,28 @@ def test_capture_takes_the_slot_compare(monkeypatch):
         assert np.array_equal(idx.all_pair_supports(), want)
     del g
     c.close()
+
+
+@pytest.mark.parametrize("route", ["0", "1", None])
+def test_subsets_either_route(ctx, monkeypatch, route):
+    """Subset queries in any order, on host and device buffers, while the index makes rows per query and
+    then keeps them all; refused queries stay refused."""
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    m, n = 20_000, 150
+    rng = np.random.default_rng(7)
+    off, tids = datagen.sets_from_probs(m, 0.1 * rng.uniform(0, 2, n), seed=8)
+    idx = bm.Index.from_sets(ctx, m, off, tids)
+    for k in (2, 3, 64, 65, 33, 100, 150, 40, 1):
+        q = rng.choice(n, size=k, replace=False).astype(np.uint32)
+        want = oracle.subset_pairs(off, tids, q)
+        assert np.array_equal(idx.subset_pair_supports(q)[:want.size], want), k
+        out = torch.full((max(want.size, 1),), -1, dtype=torch.int32, device="cuda:0")
+        torch.cuda.synchronize()
+        idx.subset_pair_supports(torch.from_numpy(q.view(np.int32)).to("cuda:0"), out)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32)[:want.size], want), k
+    pruned = bm.Index.from_sets(ctx, m, off, tids, min_support=int(np.diff(off)[5]) + 1)
+    for ix, q, code in ((idx, [1, 2, 1], bm.BM_EINVAL), (idx, [1, n], bm.BM_ERANGE), (pruned, [5, 6], bm.BM_EINVAL)):
+        with pytest.raises(bm.BatmapError) as e:
+            ix.subset_pair_supports(q)
+        assert e.value.status == code
