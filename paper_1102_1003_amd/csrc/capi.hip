@@ -3086,6 +3086,42 @@ bm_status check_cross(bm_index *a, bm_index *b)
     return BM_OK;
 }
 
+// cross_counts by the bitmap route, when it is expected to beat the slot
+// compare (as gram_pairs).
+bm_status cross_gram(bm_index *a, bm_index *b, uint32_t *out, bool &taken)
+{
+    taken = false;
+    bm_context *ctx = a->ctx;
+    if (!bitmap_route_on(ctx))
+        return BM_OK;
+    const uint64_t ld = bit_row_words(a->m);
+    const GramPlan p = plan_gram(a->n, b->n, false, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+    double us = p.us, slots = 0;
+    for (const bm_index *x : {a, b})
+        if (!x->bits.p) {
+            us += bit_rows_us(x->n, ld, (double)x->nnz);
+            if (!bit_rows_fit(ctx, x->n, ld))
+                return BM_OK;
+        }
+    for (const Cls &x : a->classes)
+        for (const Cls &y : b->classes)
+            slots += 3.0 * std::max(x.r, y.r) * x.count * y.count;
+    // planning, the uploads and the launches of the slot compare: about 150 us
+    if ((us >= compare_us(slots, a->planes, 150) && bitmap_route_env() != 1) || capturing(ctx->stream))
+        return BM_OK;
+    DevBuf<float> ws;
+    if (ws.alloc(p.ws_floats) != hipSuccess)
+        return BM_OK;
+    if (ensure_bits(a) != BM_OK || ensure_bits(b) != BM_OK) {
+        ctx->err.clear();
+        return BM_OK;
+    }
+    Span sp(ctx, PH_COMPARE);
+    HIPC(ctx, launch_gram(p, whole_bits(a), whole_bits(b), out, b->n, ws.p, ctx->stream));
+    taken = true;
+    return BM_OK;
+}
+
 // Counts |A_i cap B_j| into out (device, na * nb, row-major), zeroed here.
 bm_status cross_counts(bm_index *a, bm_index *b, uint32_t *out)
 {
@@ -3093,6 +3129,10 @@ bm_status cross_counts(bm_index *a, bm_index *b, uint32_t *out)
     hipStream_t s = ctx->stream;
     const uint32_t na = a->n, nb = b->n;
     const uint64_t cells = (uint64_t)na * nb;
+    bool taken = false;
+    BMC(cross_gram(a, b, out, taken));
+    if (taken)
+        return BM_OK;
     {
         Span sp(ctx, PH_FILL);
         HIPC(ctx, fill_u32(out, cells, 0, s));

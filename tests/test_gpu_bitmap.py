@@ -130,3 +130,19 @@ def test_subsets_either_route(ctx, monkeypatch, route):
         with pytest.raises(bm.BatmapError) as e:
             ix.subset_pair_supports(q)
         assert e.value.status == code
+
+
+@pytest.mark.parametrize("route", ["0", "1", None])
+@pytest.mark.parametrize("m,na,nb", [(5_000, 1, 1), (20_000, 65, 130), (3_000, 300, 3), (40_000, 64, 128)])
+def test_cross_either_route(ctx, monkeypatch, route, m, na, nb):
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    oa, ta = datagen.bernoulli_sets(m, na, 0.1, seed=m)
+    ob, tb = datagen.bernoulli_sets(m, nb, 0.03, seed=m + 1)
+    A, B = (bm.Index.from_sets(ctx, m, o, t, max_loop=2) for o, t in ((oa, ta), (ob, tb)))
+    want = oracle.cross(oa, ta, ob, tb).reshape(na, nb)
+    assert np.array_equal(bm.cross_pair_supports(A, B, np.full((na, nb), 5, np.uint32)), want)
+    assert np.array_equal(bm.cross_pair_supports(B, A), want.T)
+    sigma = max(1, int(np.median(want)))
+    i, j = np.nonzero(want >= sigma)
+    assert np.array_equal(bm.cross_pairs(A, B, sigma), np.stack([i, j, want[i, j]], 1))
