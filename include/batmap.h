@@ -284,7 +284,9 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
  * stream.  When the context holds autotuned tile
  * speeds, creation runs the batch twice (plans from built-in and from
  * measured speeds) and keeps the faster plan; outs then already hold the
- * result.  outs[q]: device, n_q(n_q-1)/2 uint32, bound to the batch until
+ * result.  Instances that the bitmap route is expected to count faster (see
+ * bm_all_pair_supports) leave the work list: their indexes get their bit rows
+ * at creation, and the graph multiplies them, several side by side.  outs[q]: device, n_q(n_q-1)/2 uint32, bound to the batch until
  * bm_batch_destroy; the indexes must outlive it.  bm_batch_run replays the
  * graph (asynchronously); when the stream cannot be captured the same
  * kernels are enqueued eagerly. */

@@ -422,6 +422,16 @@ struct bm_batch {
     XcdQueues queues{};       // persistent: per-XCD queues of `items`
     std::vector<std::pair<int, uint32_t>> ranges;  // per shape: (shape, items) runs of `items`
     InstDesc d0{};            // the first instance's descriptor (its layout selects the kernels)
+    // instances counted from their bit rows: the first lane runs on the stream,
+    // the others on the context's side streams, each with scratch of its own
+    struct Gram {
+        uint32_t q;
+        GramPlan plan;
+    };
+    static constexpr int kLanes = bm_context::kSide + 1;
+    std::vector<Gram> lane[kLanes];
+    DevBuf<float> lane_ws[kLanes];
+    std::vector<char> by_bits;  // per instance
     double slot_pairs = 0;
     float tuned_ms[2] = {0, 0};  // batch time with catalogue / measured tile speeds (0: not tried)
     hipGraph_t graph = nullptr;
@@ -1710,14 +1720,29 @@ hipError_t bm_batch::enqueue(hipStream_t s)
 {
     hipError_t e = fill_u32(counter.p, kQueueCounterWords, 0, s);
     for (size_t q = 0; q < idx.size() && e == hipSuccess; q++)
-        if (n_pairs(idx[q]->n))
+        if (n_pairs(idx[q]->n) && !by_bits[q])
             e = fill_u32(outs[q], n_pairs(idx[q]->n), 0, s);
     if (e == hipSuccess && persistent)
         e = launch_compare_multi_persistent(items.p, queues, descs.p, counter.p, grid, s);
     if (e == hipSuccess && !persistent && run_compare(ctx, items.p, ranges, d0, descs.p) != BM_OK)
         e = hipErrorLaunchFailure;  // the context's message names the call that failed
     for (size_t q = 0; q < idx.size() && e == hipSuccess; q++)
-        e = launch_apply_corrections(idx[q]->corr.p, idx[q]->n_corr, outs[q], idx[q]->n, s);
+        if (!by_bits[q])
+            e = launch_apply_corrections(idx[q]->corr.p, idx[q]->n_corr, outs[q], idx[q]->n, s);
+    int n_side = 0;
+    for (int l = 1; l < kLanes; l++)
+        n_side = lane[l].empty() ? n_side : l;
+    if (e == hipSuccess && fork_side(ctx, n_side) != BM_OK)
+        e = hipErrorLaunchFailure;
+    for (int l = 0; l < kLanes; l++)
+        for (const Gram &g : lane[l]) {
+            if (e != hipSuccess)
+                break;
+            const BitMat a = whole_bits(idx[g.q]);
+            e = launch_gram(g.plan, a, a, outs[g.q], a.n, lane_ws[l].p, l ? ctx->side[l - 1] : s);
+        }
+    if (e == hipSuccess && join_side(ctx, n_side) != BM_OK)
+        e = hipErrorLaunchFailure;
     return e;
 }
 
@@ -2757,6 +2782,55 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
 
 namespace {
 
+// Moves the instances of a batch that the bitmap route is expected to count
+// faster to its lanes (the least loaded one, longest instance first), with
+// their rows made and the lanes' scratch in place; an instance whose memory
+// cannot be had stays in the work list.  All of a batch's new rows take at most
+// an eighth of the device's memory.
+void batch_by_bits(bm_batch *b, const std::vector<double> &inst_work)
+{
+    bm_context *ctx = b->ctx;
+    if (!bitmap_route_on(ctx))
+        return;
+    std::vector<bm_batch::Gram> g;
+    for (uint32_t q = 0; q < b->idx.size(); q++) {
+        const bm_index *ix = b->idx[q];
+        if (n_pairs(ix->n) == 0)
+            continue;
+        const uint64_t ld = bit_row_words(ix->m);
+        const GramPlan p = plan_gram(ix->n, ix->n, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+        double us = p.us;
+        if (!ix->bits.p)
+            us += bit_rows_us(ix->n, ld, (double)ix->nnz);
+        if ((us < compare_us(inst_work[q], ix->planes, 20) || bitmap_route_env() == 1) &&
+            (ix->bits.p || bit_rows_fit(ctx, ix->n, ld)))
+            g.push_back({q, p});
+    }
+    std::sort(g.begin(), g.end(), [](const bm_batch::Gram &x, const bm_batch::Gram &y) {
+        return x.plan.us != y.plan.us ? x.plan.us > y.plan.us : x.q < y.q;
+    });
+    double load[bm_batch::kLanes] = {};
+    uint64_t rows = 0;
+    AllocScope scope(ctx->as);
+    for (const bm_batch::Gram &x : g) {
+        bm_index *ix = b->idx[x.q];
+        const uint64_t bytes = ix->bits.p ? 0 : ((uint64_t)ix->n + 1) * bit_row_words(ix->m) * 4;
+        if (rows + bytes > ctx->mem_bytes / 8 || ensure_bits(ix) != BM_OK) {
+            ctx->err.clear();
+            continue;
+        }
+        rows += bytes;
+        int l = 0;
+        for (int c = 1; c < bm_batch::kLanes; c++)
+            l = load[c] < load[l] ? c : l;
+        if (b->lane_ws[l].ensure(x.plan.ws_floats) != hipSuccess)
+            continue;
+        load[l] += x.plan.us;
+        b->lane[l].push_back(x);
+        b->by_bits[x.q] = 1;
+    }
+}
+
 bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, uint32_t *const *outs,
                        bm_batch **out, bool trial)
 {
@@ -2799,10 +2873,11 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
     // item, as in single calls); BM_COMPARE_PERSISTENT=1: one persistent
     // launch over per-XCD queues.
     b->persistent = use_persistent(ctx);
+    b->by_bits.assign(count, 0);
     std::vector<double> inst_work(count);
     for (uint32_t q = 0; q < count; q++)
         inst_work[q] = class_work(idxs[q]->classes);
-    const std::vector<uint64_t> inst_target = shared_targets(inst_work, target_items(ctx), 8);
+    std::vector<uint64_t> inst_target = shared_targets(inst_work, target_items(ctx), 8);
     typedef std::vector<std::pair<int, uint32_t>> Ranges;
     auto make_list = [&](const std::vector<float> *speeds, std::vector<WorkItem> &flat, Ranges &ranges,
                          XcdQueues &queues, double &slot_pairs) {
@@ -2811,6 +2886,8 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
         slot_pairs = 0;
         std::vector<std::vector<WorkItem>> by_variant(kVariantCount);
         for (uint32_t q = 0; q < count; q++) {
+            if (b->by_bits[q])
+                continue;
             Plan one;
             if (b->persistent)
                 plan_classes(idxs[q]->classes, q, inst_target[q], one, speeds, 1, -1);
@@ -2840,16 +2917,17 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
     Ranges r_flat, r_cand;
     double sp = 0, sp2 = 0;
     XcdQueues q_flat{}, q_cand{};
-    make_list(nullptr, flat, r_flat, q_flat, sp);
     const bool tuned = trial && (int)ctx->speeds.size() == kVariantCount * kWrapBuckets;
-    if (tuned)
+    if (tuned) {
+        make_list(nullptr, flat, r_flat, q_flat, sp);
         make_list(&ctx->speeds, cand, r_cand, q_cand, sp2);
+    }
     b->d0 = descs[0];
     if (!b->persistent)
         BMC(create_side(ctx));  // the side streams exist before any capture
     b->grid = multi_persistent_grid((uint32_t)ctx->n_cu);
     HIPC(ctx, b->descs.alloc(count));
-    HIPC(ctx, b->items.alloc(std::max<uint64_t>(std::max(flat.size(), cand.size()), 1)));
+    HIPC(ctx, b->items.ensure(std::max<uint64_t>(std::max(flat.size(), cand.size()), 1)));
     HIPC(ctx, b->counter.alloc(kQueueCounterWords));
     BMC(upload(ctx, b->descs.p, descs.data(), count * sizeof(InstDesc)));
     if (tuned) {
@@ -2884,15 +2962,19 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         HIPC(ctx, e);
-        if (ms[1] < ms[0]) {
-            flat.swap(cand);
-            sp = sp2;
-            q_flat = q_cand;
-            r_flat.swap(r_cand);
-        }
         b->tuned_ms[0] = ms[0];
         b->tuned_ms[1] = ms[1];
     }
+    // the instances that the bitmap route is expected to count faster leave
+    // the work list; the trial above chose the speeds that plan the rest
+    batch_by_bits(b.get(), inst_work);
+    for (uint32_t q = 0; q < count; q++)
+        if (b->by_bits[q])
+            inst_work[q] = 0;
+    inst_target = shared_targets(inst_work, target_items(ctx), 8);
+    make_list(b->tuned_ms[1] < b->tuned_ms[0] ? &ctx->speeds : nullptr, flat, r_flat, q_flat, sp);
+    HIPC(ctx, hipStreamSynchronize(s));  // the trial's list is no longer read
+    HIPC(ctx, b->items.ensure(std::max<uint64_t>(flat.size(), 1)));
     b->slot_pairs = sp;
     b->n_items = (uint32_t)flat.size();
     b->queues = q_flat;

@@ -146,3 +146,28 @@ def test_cross_either_route(ctx, monkeypatch, route, m, na, nb):
     sigma = max(1, int(np.median(want)))
     i, j = np.nonzero(want >= sigma)
     assert np.array_equal(bm.cross_pairs(A, B, sigma), np.stack([i, j, want[i, j]], 1))
+
+
+@pytest.mark.parametrize("route", ["0", "1", None])
+def test_batch_either_route(ctx, monkeypatch, route):
+    """A batch of instances on both routes (None: the sparse one stays with slots), replayed between eager calls."""
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    shapes = [(30_000, 400, 0.05), (200_000, 900, 0.0002), (500, 1, 0.5), (9_000, 65, 0.2), (12_000, 700, 0.03),
+              (20_000, 130, 0.1), (50_000, 260, 0.02)]
+    sets = [datagen.bernoulli_sets(m, n, p, seed=q) for q, (m, n, p) in enumerate(shapes)]
+    idx = [bm.Index.from_sets(ctx, m, *s, max_loop=3) for (m, n, p), s in zip(shapes, sets)]
+    want = [oracle.all_pairs(*s) for s in sets]
+    outs = [torch.zeros(max(w.size, 1), dtype=torch.int32, device="cuda:0") for w in want]
+    torch.cuda.synchronize()
+    batch = bm.Batch(ctx, idx, outs)
+    for rep in range(4):
+        for o in outs:
+            o.fill_(-1)
+        torch.cuda.synchronize()
+        batch.run()
+        ctx.synchronize()
+        for (m, n, p), o, w, ix in zip(shapes, outs, want, idx):
+            assert np.array_equal(o.cpu().numpy().view(np.uint32)[:bm.n_pairs(n)], w[:bm.n_pairs(n)]), (m, n)
+            assert np.array_equal(ix.all_pair_supports()[:bm.n_pairs(n)], w[:bm.n_pairs(n)])
+    batch.close()
