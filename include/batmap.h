@@ -319,6 +319,10 @@ bm_status bm_batch_all_pair_supports(bm_context *ctx, bm_index *const *idx, uint
  * memory free up, overlapping those still running.  Results land in pinned host
  * memory; bm_server_wait copies one into the caller's buffer and releases
  * its memory.  Results are identical to bm_subset_pair_supports.
+ * bm_server_create makes the index's bit rows when the bitmap route is
+ * expected to count all its pairs faster (see bm_all_pair_supports); queries
+ * that it counts faster are then multiplied instead of compared, with up to
+ * 134 MB of scratch a launch slot.
  * The index must stay alive and must not be destroyed while the server
  * runs; other calls on the index may run from the thread that owns the
  * context.  A server's calls are thread-safe among themselves.

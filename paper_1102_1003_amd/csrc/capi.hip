@@ -1623,6 +1623,21 @@ bm_status ensure_bits(bm_index *idx)
     return BM_OK;
 }
 
+// Slot pairs of all pairs among k maps of widths r(0) .. r(k - 1) (powers of two).
+template <typename F>
+double slot_work(uint32_t k, F r)
+{
+    uint32_t of_width[64] = {};
+    for (uint32_t p = 0; p < k; p++)
+        of_width[__builtin_ctzll(r(p))]++;
+    double work = 0, narrower = 0;
+    for (uint32_t l = 0; l < 64; l++) {
+        work += 3.0 * (double)(1ull << l) * of_width[l] * (narrower + 0.5 * (of_width[l] - 1.0));
+        narrower += of_width[l];
+    }
+    return work;
+}
+
 BitMat whole_bits(const bm_index *idx)
 {
     BitMat a;
@@ -2658,25 +2673,22 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
         // a query that would be refused goes on to the checks below
         bool good = true;
         std::vector<bool> seen(idx->n);
-        uint32_t of_width[33] = {};  // maps by log2 r_i
         for (uint32_t p = 0; p < k && good; p++) {
-            const uint64_t sz = idx->h_off[q[p] + 1] - idx->h_off[q[p]];
-            good = !seen[q[p]] && sz >= idx->min_support;
+            good = !seen[q[p]] && idx->h_off[q[p] + 1] - idx->h_off[q[p]] >= idx->min_support;
             seen[q[p]] = true;
-            uint32_t l = 0;
-            while ((1ull << l) < std::max<uint64_t>(idx->r0, 2 * sz))
-                l++;
-            of_width[l]++;
         }
-        std::vector<Cls> cls;
-        for (uint32_t l = 0, at = 0; l < 33; at += of_width[l++])
-            if (of_width[l])
-                cls.push_back({(uint32_t)std::min<uint64_t>(1ull << l, UINT32_MAX), at, of_width[l]});
+        const double slots = slot_work(k, [&](uint32_t p) {
+            const uint64_t sz = idx->h_off[q[p] + 1] - idx->h_off[q[p]];
+            uint64_t r = idx->r0;
+            while (r < 2 * sz)
+                r <<= 1;
+            return r;
+        });
         bool taken = false;
         DevBuf<uint32_t> ids;
         // the slot compare plans its tiles on the host and uploads five lists: about 80 us
         if (good)
-            BMC(gram_pairs(idx, q.data(), k, compare_us(class_work(cls), idx->planes, 80), dst, ids, taken));
+            BMC(gram_pairs(idx, q.data(), k, compare_us(slots, idx->planes, 80), dst, ids, taken));
         if (taken) {
             if (host)
                 BMC(download(ctx, out, dst, np * 4));
@@ -2823,11 +2835,17 @@ void batch_by_bits(bm_batch *b, const std::vector<double> &inst_work)
         int l = 0;
         for (int c = 1; c < bm_batch::kLanes; c++)
             l = load[c] < load[l] ? c : l;
-        if (b->lane_ws[l].ensure(x.plan.ws_floats) != hipSuccess)
-            continue;
         load[l] += x.plan.us;
         b->lane[l].push_back(x);
-        b->by_bits[x.q] = 1;
+    }
+    for (int l = 0; l < bm_batch::kLanes; l++) {
+        uint64_t need = 0;
+        for (const bm_batch::Gram &x : b->lane[l])
+            need = std::max(need, x.plan.ws_floats);
+        if (need && b->lane_ws[l].ensure(need) != hipSuccess)
+            b->lane[l].clear();
+        for (const bm_batch::Gram &x : b->lane[l])
+            b->by_bits[x.q] = 1;
     }
 }
 
@@ -3456,6 +3474,7 @@ struct SrvLaunch {
     DevBuf<WorkItem> items;
     DevBuf<InstDesc> descs;
     DevBuf<uint32_t> flag;
+    DevBuf<float> ws;             // the bitmap route's scratch
     WorkItem *h_items = nullptr;  // pinned staging
     InstDesc *h_descs = nullptr;
     uint64_t cap_items = 0, cap_descs = 0;
@@ -3473,6 +3492,7 @@ struct bm_server {
     std::unordered_map<uint64_t, SrvRequest> reqs;
     std::vector<std::unique_ptr<SrvLaunch>> launches;
     std::vector<int32_t> sorted_pos;  // item -> sorted index (host copy)
+    BitMat bits;                      // the index's bit rows; bits.bits null: queries compare slots
     std::mutex mu;
     std::condition_variable cv_pump, cv_done;
     std::thread pump;
@@ -3543,10 +3563,31 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
             return e;
         L.cap_descs = nq;
     }
+    // queries that the bitmap route is expected to count faster (their launches,
+    // zero fills and corrections save about 30 us each); all of them compare slots
+    // when the largest one's scratch cannot be had
+    uint64_t ws_floats = 0;
+    std::vector<GramPlan> gram(nq);
+    std::vector<char> by_bits(nq, 0);
+    for (uint32_t j = 0; j < nq && bits.bits; j++) {
+        const SrvRequest &r = reqs[ids[j]];
+        gram[j] = plan_gram(r.k, r.k, true, bits.ld, (uint32_t)ix->ctx->n_cu, pinned_gram_tile());
+        const double slots = slot_work(r.k, [&](uint32_t p) { return ix->h_r_sorted[sorted_pos[r.items[p]]]; });
+        by_bits[j] = gram[j].us < compare_us(slots, 8, 30) || bitmap_route_env() == 1;
+        if (by_bits[j])
+            ws_floats = std::max(ws_floats, gram[j].ws_floats);
+    }
+    if (ws_floats && L.ws.ensure(ws_floats) != hipSuccess)
+        by_bits.assign(nq, 0);
     std::vector<std::vector<Cls>> q_cls(nq);
     for (uint32_t j = 0; j < nq; j++) {
         SrvRequest &r = reqs[ids[j]];
         const uint32_t k = r.k;
+        uint32_t *hit = reinterpret_cast<uint32_t *>(hpool + r.off + r.o_item);
+        for (uint32_t p = 0; p < k; p++)
+            hit[p] = r.items[p];
+        if (by_bits[j])
+            continue;
         // the query's maps in width order; output positions are query positions
         std::vector<uint32_t> ord(k);
         for (uint32_t p = 0; p < k; p++)
@@ -3555,7 +3596,6 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
                   [&](uint32_t a, uint32_t b) { return sorted_pos[r.items[a]] < sorted_pos[r.items[b]]; });
         uint64_t *hg = reinterpret_cast<uint64_t *>(hpool + r.off + r.o_goff);
         uint32_t *ho = reinterpret_cast<uint32_t *>(hpool + r.off + r.o_pos);
-        uint32_t *hi = reinterpret_cast<uint32_t *>(hpool + r.off + r.o_item);
         uint32_t *hc = reinterpret_cast<uint32_t *>(hpool + r.off + r.o_gcnt);
         std::vector<Cls> &cls = q_cls[j];
         for (uint32_t t = 0; t < k; t++) {
@@ -3569,8 +3609,6 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
                 cls.push_back({rr, t, 0});
             cls.back().count++;
         }
-        for (uint32_t p = 0; p < k; p++)
-            hi[p] = r.items[p];
         InstDesc &d = L.h_descs[j];
         d.arena = reinterpret_cast<const uint4 *>(ix->arena.p);
         d.goff = reinterpret_cast<const uint64_t *>(dpool + r.off + r.o_goff);
@@ -3582,6 +3620,10 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
         d.carena = d.arena;
         d.gcnt = reinterpret_cast<const uint32_t *>(dpool + r.off + r.o_gcnt);
     }
+    // every descriptor names the output layout, which selects the kernels
+    for (uint32_t j = 0; j < nq; j++)
+        if (by_bits[j])
+            L.h_descs[j] = packed_desc(ix->arena.p, nullptr, nullptr, nullptr, 0, ix->gb);
     // the launch's items shared among its queries in proportion to their work
     std::vector<double> q_work(nq);
     for (uint32_t j = 0; j < nq; j++)
@@ -3592,6 +3634,8 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
     // any item ends (a persistent launch would hold its units to the end)
     std::vector<std::vector<WorkItem>> by_variant(kVariantCount);
     for (uint32_t j = 0; j < nq; j++) {
+        if (by_bits[j])
+            continue;
         Plan plan;
         plan_classes(q_cls[j], j, q_target[j], plan, nullptr, 0, forced_variant(), false, 8, packed_rows());
         for (int v = 0; v < kVariantCount; v++)
@@ -3624,6 +3668,15 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
         e = hipMemcpyAsync(L.items.p, L.h_items, flat.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s);
     for (uint32_t j = 0; j < nq && e == hipSuccess; j++) {
         SrvRequest &r = reqs[ids[j]];
+        if (by_bits[j]) {
+            e = hipMemcpyAsync(dpool + r.off + r.o_item, hpool + r.off + r.o_item, 4ull * r.k, hipMemcpyHostToDevice, s);
+            BitMat a = bits;
+            a.rows = reinterpret_cast<const uint32_t *>(dpool + r.off + r.o_item);
+            a.n = r.k;
+            if (e == hipSuccess)
+                e = launch_gram(gram[j], a, a, reinterpret_cast<uint32_t *>(dpool + r.off + r.o_res), r.k, L.ws.p, s);
+            continue;
+        }
         // goff, outpos, items and group counts are contiguous in the range: one upload
         e = hipMemcpyAsync(dpool + r.off + r.o_goff, hpool + r.off + r.o_goff, r.o_gcnt + 4ull * r.k - r.o_goff,
                            hipMemcpyHostToDevice, s);
@@ -3639,6 +3692,8 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
         SrvRequest &r = reqs[ids[j]];
         if (ix->n_corr == 0)
             break;
+        if (by_bits[j])
+            continue;
         // item -> query position, then the index's corrections that fall inside the query
         uint32_t *pos_of_item = reinterpret_cast<uint32_t *>(dpool + r.off + r.need - align256(4ull * ix->n));
         e = fill_u32(pos_of_item, ix->n, kEmpty, s);
@@ -3811,6 +3866,17 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
         return fail(ctx, BM_EINVAL, "the server's launches compare the paper's 8-bit 2-of-3 maps; this index has "
                     "%u-bit slots or order-3 maps", idx->planes);
     HIPC(ctx, hipSetDevice(idx->device));
+    // bit rows for the queries that will be counted from them, when the whole
+    // index would be (each query then goes by its own expected time)
+    bool by_bits = false;
+    if (bitmap_route_on(ctx) && idx->n >= 2) {
+        AllocScope scope(ctx->as);
+        const uint64_t ld = bit_row_words(idx->m);
+        const double us = plan_gram(idx->n, idx->n, true, ld, (uint32_t)ctx->n_cu).us;
+        by_bits = idx->bits.p || ((us < compare_us(class_work(idx->classes), 8, 0) || bitmap_route_env() == 1) &&
+                                  bit_rows_fit(ctx, idx->n, ld) && ensure_bits(idx) == BM_OK);
+        ctx->err.clear();
+    }
     // the server's streams do not wait for the context's: whatever the index
     // still has queued there (a build's last corrections pass) ends first
     HIPC(ctx, hipStreamSynchronize(ctx->stream));
@@ -3818,6 +3884,8 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
     if (!srv)
         return fail(ctx, BM_ENOMEM, "host allocation");
     srv->idx = idx;
+    if (by_bits)
+        srv->bits = whole_bits(idx);
     srv->opts = o;
     srv->pool_bytes = align256(o.memory_budget);
     HIPC(ctx, hipMalloc(reinterpret_cast<void **>(&srv->dpool), srv->pool_bytes));

@@ -171,3 +171,22 @@ def test_batch_either_route(ctx, monkeypatch, route):
             assert np.array_equal(o.cpu().numpy().view(np.uint32)[:bm.n_pairs(n)], w[:bm.n_pairs(n)]), (m, n)
             assert np.array_equal(ix.all_pair_supports()[:bm.n_pairs(n)], w[:bm.n_pairs(n)])
     batch.close()
+
+
+@pytest.mark.parametrize("route", ["0", "1", None])
+@pytest.mark.parametrize("prune", [0, 600])
+def test_server_either_route(ctx, monkeypatch, route, prune):
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    m, n = 30_000, 300
+    rng = np.random.default_rng(11)
+    off, tids = datagen.sets_from_probs(m, rng.uniform(0.001, 0.1, n), seed=12)
+    items = np.flatnonzero(np.diff(off) >= prune)
+    idx = bm.Index.from_sets(ctx, m, off, tids, max_loop=2, min_support=prune)
+    srv = bm.Server(idx, streams=2, memory_budget=8 << 20, max_batch=5)
+    queries = [rng.choice(items, size=k, replace=False).astype(np.uint32) for k in (2, 64, 65, 200, 3, 130, 17, 200, 90)]
+    ids = [srv.submit(q) for q in queries]
+    for q, i in zip(queries, ids):
+        got, info = srv.wait(i, timeout_s=60.0)
+        assert np.array_equal(got, oracle.subset_pairs(off, tids, q))
+    srv.close()
