@@ -263,7 +263,8 @@ bm_status bm_cross_pairs(bm_index *a, bm_index *b, uint32_t min_support, bm_pair
  * device); out (host or device) receives count uint32 in the same order.
  * The index must be built with order 3.  Errors: BM_EINVAL for another
  * order, a repeated item in a triple or an item without a BatMap, BM_ERANGE
- * for an id >= n.  Every pair call (all pairs, frequent pairs, subsets,
+ * for an id >= n.  Counted by comparing slots or, where that is expected to be
+ * faster, by ANDing the items' bit rows (see bm_all_pair_supports).  Every pair call (all pairs, frequent pairs, subsets,
  * cross products, batches, the server) returns BM_EINVAL on an order-3
  * index. */
 bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t count, uint32_t *out);

@@ -508,7 +508,10 @@ hipError_t launch_encode3(const uint32_t *stage, const uint32_t *r_sorted, const
                           uint64_t n_groups, const PermSpec &P, uint32_t shift, uint32_t r0, uint32_t *arena,
                           hipStream_t s);
 hipError_t launch_check_triples(const uint32_t *triples, uint64_t count, uint32_t n, const int32_t *sorted_pos,
-                                uint32_t *flag, hipStream_t s);
+                                const uint32_t *r_sorted, uint32_t *flag, unsigned long long *slots, hipStream_t s);
+// The counts from bit rows (row i: item i, ld words), every item in range.
+hipError_t launch_triple_bits(const uint32_t *triples, uint64_t count, const uint32_t *bits, uint64_t ld,
+                              uint32_t n_cu, uint32_t *out, hipStream_t s);
 hipError_t launch_triple_compare(const uint32_t *triples, uint64_t count, const int32_t *sorted_pos,
                                  const uint64_t *goff, const uint32_t *r_sorted, const uint32_t *arena, uint32_t r0,
                                  uint32_t *out, hipStream_t s);

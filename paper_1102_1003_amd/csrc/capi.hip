@@ -2578,32 +2578,19 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
     hipStream_t s = ctx->stream;
     DevBuf<uint32_t> tri, flag, res;
     const uint32_t *d_tri = triples;
-    double slot_triples = 0;
     if (ptr_kind(triples) != PTR_DEVICE) {
-        // the compare's work, for the phase timings: 4 max(r) slots per triple
-        for (uint64_t t = 0; t < count; t++) {
-            uint32_t r = 0;
-            for (int u = 0; u < 3; u++) {
-                const uint32_t it = triples[3 * t + u];
-                if (it < idx->n) {
-                    const uint64_t sz = idx->h_off[it + 1] - idx->h_off[it];
-                    uint64_t rr = 1;
-                    while (rr < 2 * sz)
-                        rr <<= 1;
-                    r = std::max<uint32_t>(r, (uint32_t)std::max<uint64_t>(rr, idx->r0));
-                }
-            }
-            slot_triples += 4.0 * r;
-        }
         HIPC(ctx, tri.alloc(3 * count));
         BMC(upload(ctx, tri.p, triples, 12 * count));
         d_tri = tri.p;
     }
-    HIPC(ctx, flag.alloc(1));
-    HIPC(ctx, fill_u32(flag.p, 1, 0, s));
-    HIPC(ctx, launch_check_triples(d_tri, count, idx->n, idx->sorted_pos.p, flag.p, s));
-    uint32_t fl = 0;
-    BMC(read_back(ctx, &fl, flag.p, 4));
+    HIPC(ctx, flag.alloc(4));  // the flags, a pad, the slot compare's work (64-bit)
+    HIPC(ctx, fill_u32(flag.p, 4, 0, s));
+    HIPC(ctx, launch_check_triples(d_tri, count, idx->n, idx->sorted_pos.p, idx->r_sorted.p, flag.p,
+                                   reinterpret_cast<unsigned long long *>(flag.p + 2), s));
+    uint32_t h[4] = {0, 0, 0, 0};
+    BMC(read_back(ctx, h, flag.p, 16));
+    const uint32_t fl = h[0];
+    const double slot_triples = (double)(h[2] | (uint64_t)h[3] << 32);
     if (fl & 1u)
         return fail(ctx, BM_ERANGE, "an item id >= n");
     if (fl & 2u)
@@ -2616,13 +2603,36 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
         HIPC(ctx, res.alloc(count));
         dst = res.p;
     }
-    ctx->slot_pairs = slot_triples;
-    {
+    // slots: 1.3 * 10^7 slot triples a microsecond; bits: the rows at 12 TB/s,
+    // mostly one row a triple (41,664 triples of 64 items, 10^6 transactions, 500
+    // items at 2 %: 94 ms and 0.25 ms).  Rows not yet made are paid by the call or,
+    // item by item named, by the calls before it.
+    const uint64_t ld = bit_row_words(idx->m);
+    const double slots_us = 30 + slot_triples / 1.3e7, bits_us = 12 + (double)count * ld * 4 * 1.3 / 12e6;
+    const bool have = idx->bits.p != nullptr;
+    const uint64_t named = std::min<uint64_t>(idx->n, 3 * count);
+    bool by_bits = false;
+    if (bitmap_route_on(ctx) && (have || bit_rows_fit(ctx, idx->n, ld))) {
+        const bool cheaper = bits_us < slots_us || bitmap_route_env() == 1;
+        by_bits = cheaper && (have || bits_us + bit_rows_us(idx->n, ld, (double)idx->nnz) < slots_us ||
+                              idx->bit_rows_made + named > idx->n || bitmap_route_env() == 1);
+        if (cheaper && !by_bits)
+            idx->bit_rows_made += named;
+        if (by_bits && ensure_bits(idx) != BM_OK) {
+            ctx->err.clear();
+            by_bits = false;
+        }
+    }
+    ctx->slot_pairs = by_bits ? 0 : slot_triples;
+    if (by_bits) {
+        Span sp(ctx, PH_COMPARE);
+        HIPC(ctx, launch_triple_bits(d_tri, count, idx->bits.p, ld, (uint32_t)ctx->n_cu, dst, s));
+    } else {
         Span sp(ctx, PH_COMPARE);
         HIPC(ctx, launch_triple_compare(d_tri, count, idx->sorted_pos.p, idx->goff.p, idx->r_sorted.p, idx->arena.p,
                                         idx->r0, dst, s));
     }
-    {
+    if (!by_bits) {
         Span sp(ctx, PH_APPLY);
         HIPC(ctx, launch_triple_corrections(d_tri, count, idx->off.p, idx->tids.p, idx->failed_bits.p,
                                             idx->fail_off.p, idx->fail_tids.p, dst, s));

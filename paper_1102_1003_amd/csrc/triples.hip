@@ -11,6 +11,8 @@
 // one of the tables the three copies share, so each shared element counts
 // exactly once.  Elements whose insertion failed are added back per triple
 // (Sec. III-C).
+#include <algorithm>
+
 #include "bm_internal.h"
 
 namespace bm {
@@ -195,10 +197,12 @@ __global__ void encode3_kernel(const uint32_t *stage, const uint32_t *r_sorted, 
 }
 
 // Item ids of every triple: below n, distinct, with a map.  flag bit 0: an
-// id >= n; bit 1: a repeated id; bit 2: an item without a map.
+// id >= n; bit 1: a repeated id; bit 2: an item without a map.  *slots gets the
+// slot compare's work, the sum of 4 max(r) over the triples.
 __global__ void check_triples_kernel(const uint32_t *triples, uint64_t count, uint32_t n, const int32_t *sorted_pos,
-                                     uint32_t *flag)
+                                     const uint32_t *r_sorted, uint32_t *flag, unsigned long long *slots)
 {
+    unsigned long long sum = 0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count; t += stride) {
         const uint32_t a = triples[3 * t], b = triples[3 * t + 1], c = triples[3 * t + 2];
@@ -208,9 +212,16 @@ __global__ void check_triples_kernel(const uint32_t *triples, uint64_t count, ui
         }
         if (a == b || a == c || b == c)
             atomicOr(flag, 2u);
-        if (sorted_pos[a] < 0 || sorted_pos[b] < 0 || sorted_pos[c] < 0)
+        const int32_t pa = sorted_pos[a], pb = sorted_pos[b], pc = sorted_pos[c];
+        if (pa < 0 || pb < 0 || pc < 0)
             atomicOr(flag, 4u);
+        else  // sorted by size, so the last position is the widest map
+            sum += (unsigned long long)kTables3 * r_sorted[max(pa, max(pb, pc))];
     }
+    for (int o = 32; o > 0; o >>= 1)
+        sum += __shfl_xor(sum, o, 64);
+    if ((threadIdx.x & 63) == 0 && sum)
+        atomicAdd(slots, sum);
 }
 
 // Counts of the triple rule for 8 consecutive slots of table t (16-bit slots
@@ -269,6 +280,68 @@ __global__ __launch_bounds__(256) void triple_compare_kernel(const uint32_t *tri
             acc += __shfl_xor(acc, o, 64);
         if (lane == 0)
             out[t] = acc;
+    }
+}
+
+// The same counts from bit rows: |S_a cap S_b cap S_c| is the number of ones of
+// the AND of three rows.  A wavefront takes kTripleRun consecutive triples over
+// one segment of the rows: 16 bytes a lane and step of each third row, all of
+// them in flight together; the AND of the first two rows stays in registers while
+// the triples name the same two (lists in lexicographic order mostly do).
+// Segments are walked one after the other, so that the rows' current segment
+// stays in the L2s.  Bound by those loads: 4.2 GB of third rows for the 41,664
+// triples of 64 items over 10^6 transactions; the slot compare reads 8 r bytes
+// a map there at 14 VALU operations a slot, and adds the failed
+// insertions of each triple back after it (94 against 0.27 ms for the call).
+constexpr uint32_t kTripleRun = 8;
+
+__global__ __launch_bounds__(256) void triple_bits_kernel(const uint32_t *triples, uint64_t count,
+                                                          const uint32_t *bits, uint64_t ld, uint32_t seg_words,
+                                                          uint64_t n_runs, uint64_t n_work, uint32_t *out)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / 64u);
+    for (uint64_t w = uniform_u64((uint64_t)blockIdx.x * (blockDim.x / 64u) + threadIdx.x / 64u); w < n_work;
+         w += waves) {
+        const uint64_t run = w % n_runs, w0 = w / n_runs * seg_words;
+        const uint32_t len = (uint32_t)min((uint64_t)seg_words, ld - w0);  // a multiple of 16 words
+        const uint32_t *row[3][kTripleRun];
+        uint32_t fresh = 0;  // triples whose first two items are not the previous one's
+#pragma unroll
+        for (uint32_t u = 0; u < kTripleRun; u++) {
+            const uint64_t t = min(run * kTripleRun + u, count - 1);  // past the end: the last one again
+#pragma unroll
+            for (int k = 0; k < 3; k++)
+                row[k][u] = bits + (uint64_t)__builtin_amdgcn_readfirstlane(triples[3 * t + k]) * ld + w0;
+            if (u == 0 || row[0][u] != row[0][u - 1] || row[1][u] != row[1][u - 1])
+                fresh |= 1u << u;
+        }
+        uint32_t acc[kTripleRun] = {};
+        for (uint32_t v = lane * 4; v < len; v += 256) {
+            uint4 c[kTripleRun];
+#pragma unroll
+            for (uint32_t u = 0; u < kTripleRun; u++)
+                c[u] = *reinterpret_cast<const uint4 *>(row[2][u] + v);
+            uint4 ab = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (uint32_t u = 0; u < kTripleRun; u++) {
+                if (fresh >> u & 1u) {
+                    const uint4 a = *reinterpret_cast<const uint4 *>(row[0][u] + v);
+                    const uint4 b = *reinterpret_cast<const uint4 *>(row[1][u] + v);
+                    ab = make_uint4(a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w);
+                }
+                acc[u] += __popc(ab.x & c[u].x) + __popc(ab.y & c[u].y) + __popc(ab.z & c[u].z) +
+                          __popc(ab.w & c[u].w);
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kTripleRun; u++) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+                acc[u] += __shfl_xor(acc[u], o, 64);
+            if (lane == 0 && run * kTripleRun + u < count)
+                atomicAdd(&out[run * kTripleRun + u], acc[u]);
+        }
     }
 }
 
@@ -364,11 +437,11 @@ hipError_t launch_encode3(const uint32_t *stage, const uint32_t *r_sorted, const
 }
 
 hipError_t launch_check_triples(const uint32_t *triples, uint64_t count, uint32_t n, const int32_t *sorted_pos,
-                                uint32_t *flag, hipStream_t s)
+                                const uint32_t *r_sorted, uint32_t *flag, unsigned long long *slots, hipStream_t s)
 {
     if (count == 0)
         return hipSuccess;
-    check_triples_kernel<<<blocks_for(count, 65536), kBlock, 0, s>>>(triples, count, n, sorted_pos, flag);
+    check_triples_kernel<<<blocks_for(count, 65536), kBlock, 0, s>>>(triples, count, n, sorted_pos, r_sorted, flag, slots);
     return hipGetLastError();
 }
 
@@ -381,6 +454,25 @@ hipError_t launch_triple_compare(const uint32_t *triples, uint64_t count, const 
     const uint64_t blocks = (count + 3) / 4;  // four wavefronts per workgroup
     triple_compare_kernel<<<(uint32_t)(blocks > (1u << 20) ? (1u << 20) : blocks), kBlock, 0, s>>>(
         triples, count, sorted_pos, goff, r_sorted, reinterpret_cast<const uint16_t *>(arena), r0, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_triple_bits(const uint32_t *triples, uint64_t count, const uint32_t *bits, uint64_t ld,
+                              uint32_t n_cu, uint32_t *out, hipStream_t s)
+{
+    if (count == 0)
+        return hipSuccess;
+    hipError_t e = fill_u32(out, count, 0, s);
+    if (e != hipSuccess)
+        return e;
+    const uint64_t n_runs = (count + kTripleRun - 1) / kTripleRun;
+    // segments of at most 32 KB (64 rows of one are half an L2), more of them
+    // while there are fewer than 32 wavefronts a CU, down to four steps each
+    const uint64_t want = std::max<uint64_t>((ld + 8191) / 8192, (n_cu * 32ull + n_runs - 1) / n_runs);
+    const uint64_t seg = std::max<uint64_t>((ld / want + 255) / 256 * 256, 1024);
+    const uint64_t n_work = n_runs * ((ld + seg - 1) / seg);
+    const uint64_t blocks = std::min<uint64_t>((n_work + 3) / 4, 1u << 24);
+    triple_bits_kernel<<<(uint32_t)blocks, 256, 0, s>>>(triples, count, bits, ld, (uint32_t)seg, n_runs, n_work, out);
     return hipGetLastError();
 }
 

@@ -190,3 +190,24 @@ def test_server_either_route(ctx, monkeypatch, route, prune):
         got, info = srv.wait(i, timeout_s=60.0)
         assert np.array_equal(got, oracle.subset_pairs(off, tids, q))
     srv.close()
+
+
+@pytest.mark.parametrize("route", ["0", "1", None])
+@pytest.mark.parametrize("m,n,count", [(700, 3, 1), (5_000, 40, 9880), (200_000, 30, 15), (40_000, 60, 777)])
+def test_triples_either_route(ctx, monkeypatch, route, m, n, count):
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    rng = np.random.default_rng(m + count)
+    off, tids = datagen.sets_from_probs(m, rng.uniform(0.05, 0.9, n), seed=m)
+    every = np.array([(a, b, c) for a in range(n) for b in range(a + 1, n) for c in range(b + 1, n)], np.uint32)
+    pick = every if count == len(every) else rng.permuted(every[rng.integers(0, len(every), count)], axis=1)
+    idx = bm.Index.from_sets(ctx, m, off, tids, order=3, max_loop=2)
+    want = oracle.triples(off, tids, pick)
+    for rep in range(2):
+        assert np.array_equal(idx.triple_supports(pick, np.full(count, 3, np.uint32)), want)
+    out = torch.full((count,), -1, dtype=torch.int32, device="cuda:0")
+    dev = torch.from_numpy(pick.view(np.int32)).to("cuda:0")
+    torch.cuda.synchronize()
+    idx.triple_supports(dev, out)
+    ctx.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
