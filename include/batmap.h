@@ -118,7 +118,7 @@ typedef struct {
  * taken with HIP events on the context's stream while profiling is on.
  * compare_slot_pairs is the algorithmic work of the last query's compare:
  * the sum over its pairs of 3 max(r_i, r_j) slot comparisons; 0 when the
- * query took the bitmap route (see bm_all_pair_supports). */
+ * query did not compare slots (see bm_all_pair_supports). */
 typedef struct {
     double ingest_ms;     /* validation / transactions -> tidlists */
     double layout_ms;     /* permutations, size order, r_i and offsets */
@@ -209,9 +209,11 @@ void bm_index_destroy(bm_index *idx);
  * out_len >= n(n-1)/2.  BM_EINVAL if the index was built with min_support > 0.
  * The pairs are counted by comparing BatMaps or, where that is expected to be
  * faster (sets of more than about half a percent of the transactions), from
- * bit rows on the matrix cores as bm_all_pair_supports_dense does; the counts
- * are exact either way.  Bit rows take n m / 8 bytes, at most a sixteenth of
- * the device's memory, and the index keeps them until it is destroyed. */
+ * bit rows on the matrix cores as bm_all_pair_supports_dense does, or (very
+ * sparse sets, up to 16,384 of them) by walking the transactions of each set;
+ * the counts are exact whichever way.  Bit rows take n m / 8 bytes, at most a
+ * sixteenth of the device's memory; the index keeps them, and the incidences
+ * grouped by transaction, until it is destroyed. */
 bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len);
 
 /* Frequent pair mining (Sec. I: pairs with support at least sigma): every

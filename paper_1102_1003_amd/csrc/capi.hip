@@ -408,6 +408,10 @@ struct bm_index {
     DevBuf<uint32_t> bits;
     uint64_t bit_rows_made = 0;  // by calls that made the rows of their list alone
     DevBuf<float> gram_ws;       // bm_all_pair_supports_dense
+    // counting by transactions: items grouped by transaction, made at first use
+    DevBuf<uint32_t> txn_start, txn_items;
+    uint64_t txn_pairs = 0;   // sum over transactions of their pairs
+    bool txn_dense = false;   // more pairs than independent sets would have: made for nothing
 };
 
 struct bm_batch {
@@ -1562,11 +1566,12 @@ InstDesc whole_desc(const bm_index *idx, uint32_t *out)
 // rows costs m bits on the matrix cores whatever the sets.
 
 // BM_BITMAP_ROUTE=0 keeps every call on the slot compare, 1 takes the bitmap
-// route wherever it can be taken, whatever the expected times.
+// route and 2 the count by transactions wherever they can be taken, whatever
+// the expected times.
 int bitmap_route_env()
 {
     const char *e = getenv("BM_BITMAP_ROUTE");
-    return !e || !*e ? -1 : (e[0] != '0');
+    return !e || !*e ? -1 : atoi(e);
 }
 
 // Whether calls may take the bitmap route: not when the environment or the
@@ -1647,6 +1652,34 @@ BitMat whole_bits(const bm_index *idx)
     return a;
 }
 
+// How gram_pairs would count k listed items (or all, listed = false), and its
+// expected time: infinite where the route cannot be taken.
+struct GramChoice {
+    GramPlan plan;
+    bool whole = true;  // from every item's rows (else from the list's own)
+    double us = INFINITY;
+};
+
+GramChoice choose_gram(const bm_index *idx, bool listed, uint32_t k)
+{
+    const bm_context *ctx = idx->ctx;
+    GramChoice c;
+    if (!bitmap_route_on(ctx) || bitmap_route_env() == 2)
+        return c;
+    const uint64_t ld = bit_row_words(idx->m);
+    const bool have = idx->bits.p != nullptr;
+    const bool most = !listed || (uint64_t)k * 4 >= (uint64_t)idx->n * 3;
+    c.whole = have || ((most || idx->bit_rows_made + k > idx->n) && bit_rows_fit(ctx, idx->n, ld));
+    if (!c.whole && (!listed || !bit_rows_fit(ctx, k, ld)))
+        return c;
+    c.plan = plan_gram(k, k, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+    const uint32_t paid = most ? idx->n : k;  // rows this call accounts for
+    c.us = c.plan.us;
+    if (!have)
+        c.us += bit_rows_us(paid, ld, (double)idx->nnz * paid / idx->n);
+    return c;
+}
+
 // All pair counts of `list` (k item ids in host memory; null: all items, k =
 // n) into the packed triangle `out` (device, every entry written), when the
 // bitmap route is expected to beat a slot compare of other_us; `taken` says
@@ -1661,20 +1694,11 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
     taken = false;
     bm_context *ctx = idx->ctx;
     hipStream_t s = ctx->stream;
-    if (!bitmap_route_on(ctx))
-        return BM_OK;
+    const GramChoice c = choose_gram(idx, list != nullptr, k);
+    const GramPlan &p = c.plan;
     const uint64_t ld = bit_row_words(idx->m);
-    const GramPlan p = plan_gram(k, k, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
-    const bool have = idx->bits.p != nullptr;
-    const bool most = !list || (uint64_t)k * 4 >= (uint64_t)idx->n * 3;
-    const bool whole = have || ((most || idx->bit_rows_made + k > idx->n) && bit_rows_fit(ctx, idx->n, ld));
-    if (!whole && (!list || !bit_rows_fit(ctx, k, ld)))
-        return BM_OK;
-    const uint32_t paid = most ? idx->n : k;  // rows this call accounts for
-    double us = p.us;
-    if (!have)
-        us += bit_rows_us(paid, ld, (double)idx->nnz * paid / idx->n);
-    if ((us >= other_us && bitmap_route_env() != 1) || capturing(s))
+    const bool whole = c.whole;
+    if (!(c.us < other_us || (bitmap_route_env() == 1 && c.us < INFINITY)) || capturing(s))
         return BM_OK;
     DevBuf<float> ws;
     DevBuf<uint32_t> own;
@@ -1700,6 +1724,81 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
         idx->bit_rows_made += k;
     }
     HIPC(ctx, launch_gram(p, a, a, out, k, ws.p, s));
+    taken = true;
+    return BM_OK;
+}
+
+// Expected time of counting by transactions (us) with `pairs` pairs in all
+// transactions: the triangle written at 3 TB/s, 9 ps an incidence and 4.6 ps for
+// each item of its transaction; or the largest set, walked by one workgroup, 1 us
+// a round of its lanes and 0.25 us for each item of a transaction.  Measured
+// (MI355X, us, transactions / bits / slots): 2^20 x 8192 at 0.01 %: 53 / 9396 /
+// 802; 0.05 %: 189 / 9357 / 4718; 0.2 %: 1506 / 9400 / 12,888; 0.4 %: 5549 /
+// 9397 / 13,347; 10^6 x 4000 Zipf(1.0) at 0.05 % (largest set 225,199): 1741 /
+// 2530 / 3516; 10^6 x 8000 Zipf(1.0) at 0.1 % (836,079): 10,404 / 8914 / 12,818.
+double txn_us(const bm_index *idx, double pairs)
+{
+    const double nnz = std::max<double>((double)idx->nnz, 1), walked = 2 * pairs + nnz;
+    const double lanes = idx->n > 8192 ? 600 : 256;
+    return 10 + 4.0 * (double)n_pairs(idx->n) / 3e6 +
+           std::max(4.6e-6 * walked + 9e-6 * nnz, idx->h_sizes_sorted.back() / lanes * (1 + 0.25 * walked / nnz));
+}
+
+// All pair counts of the index into the packed triangle `out` (device, every
+// entry written) by transactions, when that is expected to take less than
+// other_us.  The grouped incidences are made at first use and kept; sets that
+// turn out to share far more than independent ones would are left to the others.
+bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
+{
+    taken = false;
+    bm_context *ctx = idx->ctx;
+    hipStream_t s = ctx->stream;
+    const bool forced = bitmap_route_env() == 2;
+    if (!bitmap_route_on(ctx) || bitmap_route_env() == 1 || idx->n > kTxnMaxItems || idx->txn_dense)
+        return BM_OK;
+    if (!idx->txn_items.p) {
+        // counted, scanned and grouped: a device atomic an incidence in two
+        // passes (4.3 * 10^6 incidences: 160 and 370 us)
+        const double nnz = (double)idx->nnz, make_us = 60 + nnz * 1.25e-4 + idx->m / 1e5;
+        if (!forced && txn_us(idx, 0) + make_us >= other_us)
+            return BM_OK;
+        double squares = 0;
+        for (uint32_t sz : idx->h_sizes_sorted)
+            squares += (double)sz * sz;
+        const double guess = std::max(0.0, (nnz * nnz - squares) / (2.0 * idx->m));  // independent sets
+        if (!forced && txn_us(idx, guess) + make_us >= other_us)
+            return BM_OK;
+        if (2 * ((uint64_t)idx->m + idx->nnz) * 4 > ctx->mem_bytes / 16 || capturing(s))
+            return BM_OK;
+        Span sp(ctx, PH_ENCODE);
+        DevBuf<uint32_t> count, start, items;
+        DevBuf<char> tmp;
+        const uint64_t mm = (uint64_t)idx->m + 1;
+        // [m + 1 counts | the pair total, 64-bit]
+        const uint64_t at = (mm + 1) / 2 * 2;
+        if (count.alloc(at + 2) != hipSuccess || start.alloc(mm) != hipSuccess ||
+            items.alloc(idx->nnz) != hipSuccess || tmp.alloc(scan_tmp_bytes(mm)) != hipSuccess)
+            return BM_OK;
+        HIPC(ctx, fill_u32(count.p, at + 2, 0, s));
+        HIPC(ctx, launch_txn_count(idx->tids.p, idx->nnz, idx->m, count.p,
+                                   reinterpret_cast<unsigned long long *>(count.p + at), s));
+        uint64_t pairs = 0;
+        BMC(read_back(ctx, &pairs, count.p + at, 8));
+        if (!forced && txn_us(idx, (double)pairs) >= other_us) {
+            idx->txn_dense = true;
+            return BM_OK;
+        }
+        HIPC(ctx, exclusive_scan_u32(count.p, start.p, mm, tmp.p, s));
+        HIPC(ctx, hipMemcpyAsync(count.p, start.p, mm * 4, hipMemcpyDeviceToDevice, s));
+        HIPC(ctx, launch_txn_scatter(idx->off.p, idx->tids.p, idx->n, count.p, items.p, s));
+        idx->txn_start.swap(start);
+        idx->txn_items.swap(items);
+        idx->txn_pairs = pairs;
+    } else if ((!forced && txn_us(idx, (double)idx->txn_pairs) >= other_us) || capturing(s)) {
+        return BM_OK;
+    }
+    Span sp(ctx, PH_COMPARE);
+    HIPC(ctx, launch_txn_rows(idx->off.p, idx->tids.p, idx->txn_start.p, idx->txn_items.p, idx->n, out, s));
     taken = true;
     return BM_OK;
 }
@@ -2382,7 +2481,10 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
     }
     bool taken = false;
     DevBuf<uint32_t> ids;
-    BMC(gram_pairs(idx, nullptr, idx->n, compare_us(class_work(idx->classes), idx->planes, 40), dst, ids, taken));
+    const double slots_us = compare_us(class_work(idx->classes), idx->planes, 40);
+    BMC(txn_pairs(idx, std::min(slots_us, choose_gram(idx, false, idx->n).us), dst, taken));
+    if (!taken)
+        BMC(gram_pairs(idx, nullptr, idx->n, slots_us, dst, ids, taken));
     if (!taken)
         BMC(count_pairs(idx, 0, dst));
     if (host) {
@@ -2426,18 +2528,20 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
         ids.assign(idx->h_sorted_items.begin() + first, idx->h_sorted_items.end());
         std::sort(ids.begin(), ids.end());
     }
-    const double slots = class_work(first ? classes_from(idx->classes, first) : idx->classes);
+    const double slots_us =
+        compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes, 40);
     DevBuf<uint32_t> d_ids;
-    bool taken = false;
+    bool by_txn = false, by_bits = false;
     HIPC(ctx, idx->pairbuf.ensure(np));
-    BMC(gram_pairs(idx, first ? ids.data() : nullptr, live, compare_us(slots, idx->planes, 40), idx->pairbuf.p, d_ids,
-                   taken));
+    BMC(txn_pairs(idx, std::min(slots_us, choose_gram(idx, first > 0, live).us), idx->pairbuf.p, by_txn));
+    if (!by_txn)
+        BMC(gram_pairs(idx, first ? ids.data() : nullptr, live, slots_us, idx->pairbuf.p, d_ids, by_bits));
     uint32_t n_eff = idx->n;
-    if (!taken) {
-        BMC(count_pairs(idx, first, idx->pairbuf.p));
-    } else if (first) {
+    if (by_bits && first) {
         n_eff = live;
         np = n_pairs(live);
+    } else if (!by_txn && !by_bits) {
+        BMC(count_pairs(idx, first, idx->pairbuf.p));
     }
     const uint32_t *thr_ids = n_eff < idx->n ? d_ids.p : nullptr;
     uint32_t nb = threshold_blocks(np);

@@ -46,15 +46,17 @@ def test_counts_past_fp32(ctx):
     assert np.array_equal(idx.all_pair_supports_dense(), np.full(3, m, np.uint32))
 
 
-@pytest.mark.parametrize("route", ["0", "1", None])
+@pytest.mark.parametrize("route", ["0", "1", "2", None])       # slots, bits, transactions, by time
 @pytest.mark.parametrize("m,n,p,opts", [
     (10_000, 200, 0.02, {}),
     (20_000, 90, 0.3, dict(max_loop=0)),             # every insertion fails: slot counts are all corrections
     (60_000, 150, 0.002, dict(slot_bits=16)),
     (5_000, 2, 0.5, {}),
+    (300_000, 1500, 0.0005, dict(slot_bits=0)),
+    (1_000, 9000, 0.001, dict(slot_bits=0)),         # rows past 32 KB of counters
 ])
 def test_pairs_either_route(ctx, monkeypatch, route, m, n, p, opts):
-    """All pairs and frequent pairs give the same counts by slots and by bits."""
+    """All pairs and frequent pairs give the same counts by slots, bits and transactions."""
     if route is not None:
         monkeypatch.setenv("BM_BITMAP_ROUTE", route)
     rng = np.random.default_rng(m)
@@ -66,7 +68,7 @@ def test_pairs_either_route(ctx, monkeypatch, route, m, n, p, opts):
         assert np.array_equal(idx.all_pair_supports(np.full(want.size, 9, np.uint32)), want)
         ctx.set_profiling(True)
         idx.all_pair_supports()
-        assert (ctx.timings()["compare_slot_pairs"] == 0) == (route == "1") or route is None
+        assert (ctx.timings()["compare_slot_pairs"] == 0) == (route in ("1", "2")) or route is None
         ctx.set_profiling(False)
     for sigma in (0, 1, int(np.median(want)) + 1, int(sizes[n // 2]), int(sizes[-1]), int(sizes[-1]) + 1):
         fresh = bm.Index.from_sets(ctx, m, off, tids, **opts)          # rows of the live items alone
