@@ -407,6 +407,9 @@ struct bm_index {
     // bitmap route: a bit row per item and the zero row, made at first use
     DevBuf<uint32_t> bits;
     uint64_t bit_rows_made = 0;  // by calls that made the rows of their list alone
+    // what calls would have saved (us) with all bit rows, or with the incidences
+    // grouped by transaction, in place: once that pays for making them, they are made
+    double bits_saved_us = 0, txn_saved_us = 0;
     DevBuf<float> gram_ws;       // bm_all_pair_supports_dense
     // counting by transactions: items grouped by transaction, made at first use
     DevBuf<uint32_t> txn_start, txn_items;
@@ -1583,14 +1586,19 @@ bool bitmap_route_on(const bm_context *ctx)
 }
 
 // Expected time of a slot compare (us): W + 1 VALU operations per 32 slot
-// pairs, 30 * 10^12 a second with 8-bit slots and 20 with wider ones; fixed_us
-// for its launches, zero fill and corrections.  Both sides measured (MI355X,
-// us, rows built in the call included): 10^4 x 200 at 2 %: 85 slots, 25 bits;
-// 50,000 x 4000 at 5 %: 1818 and 175; 10^6 x 2000 Zipf at 2 %: 4700 and 760;
-// 2^20 x 8192 at 0.05 % (16-bit slots): 4806 and 9900, which stays with slots.
-double compare_us(double slot_pairs, uint32_t planes, double fixed_us)
+// pairs, 30 * 10^12 a second with 8-bit slots and 20 with wider ones; a work
+// item's walk over up to 256 groups of the widest map (r_max slots a table),
+// about 1 us a group (2 with wider slots), which is what a compare takes that
+// does not fill the chip; fixed_us for launches, zero fill, corrections and
+// planning.  Slots and bits measured (MI355X, us, rows kept): 10^4 x 100 at 0.5 %:
+// 111 and 14; 200,000 x 300 at 0.5 %: 261 and 20; 50,000 x 1500 at 0.05 %
+// (16-bit slots, r = 128): 31 and 44; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x
+// 2000 Zipf at 2 %: 4700 and 670; 10^6 x 1500 at 0.05 % (16-bit): 332 and 390.
+double compare_us(double slot_pairs, uint32_t planes, double r_max, double fixed_us)
 {
-    return fixed_us + slot_pairs / 32 * (planes + 1) / (planes == 8 ? 30e6 : 20e6);
+    const bool wide = planes != 8;
+    return fixed_us + std::min(256.0, 3 * r_max / 32) * (wide ? 2 : 1) +
+           slot_pairs / 32 * (planes + 1) / (wide ? 20e6 : 30e6);
 }
 
 // Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
@@ -1698,7 +1706,12 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
     const GramPlan &p = c.plan;
     const uint64_t ld = bit_row_words(idx->m);
     const bool whole = c.whole;
-    if (!(c.us < other_us || (bitmap_route_env() == 1 && c.us < INFINITY)) || capturing(s))
+    bool go = c.us < other_us || (bitmap_route_env() == 1 && c.us < INFINITY);
+    if (!go && c.whole && c.us < INFINITY && p.us < other_us) {
+        idx->bits_saved_us += other_us - p.us;
+        go = idx->bits_saved_us > c.us - p.us;
+    }
+    if (!go || capturing(s))
         return BM_OK;
     DevBuf<float> ws;
     DevBuf<uint32_t> own;
@@ -1760,14 +1773,19 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
         // counted, scanned and grouped: a device atomic an incidence in two
         // passes (4.3 * 10^6 incidences: 160 and 370 us)
         const double nnz = (double)idx->nnz, make_us = 60 + nnz * 1.25e-4 + idx->m / 1e5;
-        if (!forced && txn_us(idx, 0) + make_us >= other_us)
+        if (!forced && txn_us(idx, 0) >= other_us)
             return BM_OK;
         double squares = 0;
         for (uint32_t sz : idx->h_sizes_sorted)
             squares += (double)sz * sz;
         const double guess = std::max(0.0, (nnz * nnz - squares) / (2.0 * idx->m));  // independent sets
-        if (!forced && txn_us(idx, guess) + make_us >= other_us)
-            return BM_OK;
+        const double us = txn_us(idx, guess);
+        if (!forced && us + make_us >= other_us) {
+            if (us < other_us)
+                idx->txn_saved_us += other_us - us;
+            if (idx->txn_saved_us <= make_us)
+                return BM_OK;
+        }
         if (2 * ((uint64_t)idx->m + idx->nnz) * 4 > ctx->mem_bytes / 16 || capturing(s))
             return BM_OK;
         Span sp(ctx, PH_ENCODE);
@@ -2481,7 +2499,7 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
     }
     bool taken = false;
     DevBuf<uint32_t> ids;
-    const double slots_us = compare_us(class_work(idx->classes), idx->planes, 40);
+    const double slots_us = compare_us(class_work(idx->classes), idx->planes, idx->h_r_sorted.back(), 20);
     BMC(txn_pairs(idx, std::min(slots_us, choose_gram(idx, false, idx->n).us), dst, taken));
     if (!taken)
         BMC(gram_pairs(idx, nullptr, idx->n, slots_us, dst, ids, taken));
@@ -2529,7 +2547,8 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
         std::sort(ids.begin(), ids.end());
     }
     const double slots_us =
-        compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes, 40);
+        compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes,
+                   idx->h_r_sorted.back(), 20);
     DevBuf<uint32_t> d_ids;
     bool by_txn = false, by_bits = false;
     HIPC(ctx, idx->pairbuf.ensure(np));
@@ -2791,18 +2810,20 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
             good = !seen[q[p]] && idx->h_off[q[p] + 1] - idx->h_off[q[p]] >= idx->min_support;
             seen[q[p]] = true;
         }
+        uint64_t r_max = 0;
         const double slots = slot_work(k, [&](uint32_t p) {
             const uint64_t sz = idx->h_off[q[p] + 1] - idx->h_off[q[p]];
             uint64_t r = idx->r0;
             while (r < 2 * sz)
                 r <<= 1;
+            r_max = std::max(r_max, r);
             return r;
         });
         bool taken = false;
         DevBuf<uint32_t> ids;
-        // the slot compare plans its tiles on the host and uploads five lists: about 80 us
+        // the slot compare plans its tiles on the host and uploads five lists: about 60 us
         if (good)
-            BMC(gram_pairs(idx, q.data(), k, compare_us(slots, idx->planes, 80), dst, ids, taken));
+            BMC(gram_pairs(idx, q.data(), k, compare_us(slots, idx->planes, (double)r_max, 60), dst, ids, taken));
         if (taken) {
             if (host)
                 BMC(download(ctx, out, dst, np * 4));
@@ -2912,8 +2933,8 @@ namespace {
 // faster to its lanes (the least loaded one, longest instance first), with
 // their rows made and the lanes' scratch in place; an instance whose memory
 // cannot be had stays in the work list.  All of a batch's new rows take at most
-// an eighth of the device's memory.
-void batch_by_bits(bm_batch *b, const std::vector<double> &inst_work)
+// an eighth of the device's memory.  once: the batch runs one time.
+void batch_by_bits(bm_batch *b, const std::vector<double> &inst_work, bool once)
 {
     bm_context *ctx = b->ctx;
     if (!bitmap_route_on(ctx))
@@ -2926,9 +2947,9 @@ void batch_by_bits(bm_batch *b, const std::vector<double> &inst_work)
         const uint64_t ld = bit_row_words(ix->m);
         const GramPlan p = plan_gram(ix->n, ix->n, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
         double us = p.us;
-        if (!ix->bits.p)
+        if (once && !ix->bits.p)  // a batch to be replayed keeps its rows
             us += bit_rows_us(ix->n, ld, (double)ix->nnz);
-        if ((us < compare_us(inst_work[q], ix->planes, 20) || bitmap_route_env() == 1) &&
+        if ((us < compare_us(inst_work[q], ix->planes, ix->h_r_sorted.back(), 10) || bitmap_route_env() == 1) &&
             (ix->bits.p || bit_rows_fit(ctx, ix->n, ld)))
             g.push_back({q, p});
     }
@@ -3099,7 +3120,7 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
     }
     // the instances that the bitmap route is expected to count faster leave
     // the work list; the trial above chose the speeds that plan the rest
-    batch_by_bits(b.get(), inst_work);
+    batch_by_bits(b.get(), inst_work, !trial);
     for (uint32_t q = 0; q < count; q++)
         if (b->by_bits[q])
             inst_work[q] = 0;
@@ -3320,8 +3341,9 @@ bm_status cross_gram(bm_index *a, bm_index *b, uint32_t *out, bool &taken)
     for (const Cls &x : a->classes)
         for (const Cls &y : b->classes)
             slots += 3.0 * std::max(x.r, y.r) * x.count * y.count;
-    // planning, the uploads and the launches of the slot compare: about 150 us
-    if ((us >= compare_us(slots, a->planes, 150) && bitmap_route_env() != 1) || capturing(ctx->stream))
+    // planning, the uploads and the launches of the slot compare: about 130 us
+    const double r_max = std::max(a->h_r_sorted.back(), b->h_r_sorted.back());
+    if ((us >= compare_us(slots, a->planes, r_max, 130) && bitmap_route_env() != 1) || capturing(ctx->stream))
         return BM_OK;
     DevBuf<float> ws;
     if (ws.alloc(p.ws_floats) != hipSuccess)
@@ -3687,7 +3709,7 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<uint64_t> &id
         const SrvRequest &r = reqs[ids[j]];
         gram[j] = plan_gram(r.k, r.k, true, bits.ld, (uint32_t)ix->ctx->n_cu, pinned_gram_tile());
         const double slots = slot_work(r.k, [&](uint32_t p) { return ix->h_r_sorted[sorted_pos[r.items[p]]]; });
-        by_bits[j] = gram[j].us < compare_us(slots, 8, 30) || bitmap_route_env() == 1;
+        by_bits[j] = gram[j].us < compare_us(slots, 8, 0, 50) || bitmap_route_env() == 1;
         if (by_bits[j])
             ws_floats = std::max(ws_floats, gram[j].ws_floats);
     }
@@ -3987,7 +4009,7 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
         AllocScope scope(ctx->as);
         const uint64_t ld = bit_row_words(idx->m);
         const double us = plan_gram(idx->n, idx->n, true, ld, (uint32_t)ctx->n_cu).us;
-        by_bits = idx->bits.p || ((us < compare_us(class_work(idx->classes), 8, 0) || bitmap_route_env() == 1) &&
+        by_bits = idx->bits.p || ((us < compare_us(class_work(idx->classes), 8, 0, 0) || bitmap_route_env() == 1) &&
                                   bit_rows_fit(ctx, idx->n, ld) && ensure_bits(idx) == BM_OK);
         ctx->err.clear();
     }
