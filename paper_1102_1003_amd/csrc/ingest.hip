@@ -1,7 +1,10 @@
 // Ingest (Sec. I, "Set representations"): validation of the vertical format
 // (sorted tidlists) and conversion of the horizontal format (transactions) to
 // it.  The conversion is a stable sort of (item, tid) pairs by item: pairs
-// arrive in tid order, so every tidlist comes out sorted.
+// arrive in tid order, so every tidlist comes out sorted.  Where the incidences
+// are not too sparse it goes through bit rows instead (txn_bits_kernel).
+#include <algorithm>
+
 #include "bm_internal.h"
 
 namespace bm {
@@ -211,6 +214,195 @@ __global__ void offsets_and_dups_kernel(const uint32_t *keys, const uint32_t *va
         atomicAdd(n_dup, dups);
 }
 
+// ------------------------------------------------- transactions -> bit rows
+// A workgroup takes 32 TW consecutive transactions, sets one bit per incidence
+// in an LDS block of (n + 1) x TW words (the row of no item stays zero) and
+// writes the block into the bit rows, 4 TW bytes of every row.  The rows are
+// what the tidlists are then read from, in order and without repeats, so that
+// no sort is needed: the incidences are read once and the rows move three
+// times (written, counted, expanded) where each pass of the radix sort moves 16
+// bytes an incidence.  LDS rows are TW + 1 words apart: the incidences of a
+// transaction (same word, other items) spread over the banks.  Consecutive
+// chunks run on one XCD, whose L2 puts the pieces of a line together.  Bound by
+// memory: m = 10^6, n = 2000, 4 * 10^7 incidences (160 MB in, 250 MB out).
+constexpr int kTxnBitsThreads = 1024;
+
+template <int TW>
+__global__ void __launch_bounds__(kTxnBitsThreads)
+    txn_bits_kernel(const uint64_t *__restrict__ row_off, const uint32_t *__restrict__ items, uint32_t m, uint32_t n,
+                    uint64_t ld, uint32_t n_chunks, uint32_t per_xcd, uint32_t *__restrict__ bits, uint32_t *flag)
+{
+    extern __shared__ uint32_t blk[];  // (n + 1) (TW + 1) words
+    __shared__ uint32_t offs[32 * TW + 1];
+    const uint32_t c = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
+    if (blockIdx.x / kXcds >= per_xcd || c >= n_chunks)
+        return;
+    const uint32_t t0 = c * (32 * TW), rows = min(32u * TW, m > t0 ? m - t0 : 0u);
+    for (uint32_t i = threadIdx.x; i < (n + 1) * (TW + 1); i += kTxnBitsThreads)
+        blk[i] = 0;
+    const uint64_t base = row_off[min(t0, m)];
+    for (uint32_t i = threadIdx.x; i <= rows; i += kTxnBitsThreads)
+        offs[i] = (uint32_t)(row_off[min(t0, m) + i] - base);
+    __syncthreads();
+    const uint32_t total = offs[rows];
+    bool bad = false;
+    // four consecutive incidences a thread: one search for the first one's
+    // transaction (the last offset <= e, which skips empty ones), then steps forward
+    for (uint64_t e4 = threadIdx.x * 4; e4 < total; e4 += kTxnBitsThreads * 4) {
+        const uint32_t e = (uint32_t)e4;
+        uint32_t it[4];
+        const uint32_t cnt = min(4u, total - e);
+        if (cnt == 4) {
+            __builtin_memcpy(it, items + base + e, 16);
+        } else {
+            for (uint32_t q = 0; q < 4; q++)
+                it[q] = items[base + e + (q < cnt ? q : 0)];
+        }
+        uint32_t lo = 0, hi = rows;  // offs[lo] <= e < offs[hi]
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (offs[mid] <= e)
+                lo = mid;
+            else
+                hi = mid;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; q++) {
+            if (q < cnt) {
+                while (offs[lo + 1] <= e + q)
+                    lo++;
+                if (it[q] < n)
+                    atomicOr(&blk[it[q] * (TW + 1) + (lo >> 5)], 1u << (lo & 31));
+                else
+                    bad = true;
+            }
+        }
+    }
+    if (bad)
+        atomicOr(flag, 1u);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < (n + 1) * (TW / 4); i += kTxnBitsThreads) {
+        const uint32_t item = i / (TW / 4), w = i % (TW / 4) * 4;
+        const uint64_t at = (uint64_t)c * TW + w;
+        if (at < ld) {  // a multiple of 16 words
+            const uint32_t *src = &blk[item * (TW + 1) + w];
+            *reinterpret_cast<uint4 *>(bits + item * ld + at) = make_uint4(src[0], src[1], src[2], src[3]);
+        }
+    }
+}
+
+// Ones of every (row, segment of kSegWords words).
+constexpr uint32_t kSegWords = 4096;
+
+__global__ void __launch_bounds__(256) bit_count_kernel(const uint32_t *__restrict__ bits, uint64_t ld,
+                                                        uint32_t n_seg, uint32_t *count)
+{
+    __shared__ uint32_t part[4];
+    const uint32_t item = blockIdx.x / n_seg, seg = blockIdx.x % n_seg;
+    const uint32_t len = (uint32_t)min((uint64_t)kSegWords, ld - (uint64_t)seg * kSegWords);
+    const uint32_t *row = bits + item * ld + (uint64_t)seg * kSegWords;
+    uint32_t sum = 0;
+    for (uint32_t w = threadIdx.x * 4; w < len; w += 1024) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(row + w);
+        sum += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        sum += __shfl_xor(sum, o, 64);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x / 64] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        count[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+// The tids of one (row, segment), in order, at tids[start[row n_seg + seg] ..).
+// W consecutive words a thread and round: their ones are counted, ranked over
+// the workgroup and set down in LDS, then written out coalesced.  W is chosen
+// so that a round's tids mostly fit the LDS buffer (the rest go out directly).
+constexpr uint32_t kExpandBuf = 8192;
+
+template <int W>
+__device__ void expand_segment(const uint32_t *row, uint32_t len, uint32_t t0, uint32_t *out, uint32_t *buf,
+                               uint32_t *part)
+{
+    uint32_t done = 0;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    for (uint32_t r0 = 0; r0 < len; r0 += 256 * W) {
+        const uint32_t w0 = r0 + threadIdx.x * W;
+        uint32_t v[W];
+        uint32_t ones = 0;
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            v[k] = w0 < len ? row[w0 + k] : 0u;  // len is a multiple of 16
+            ones += __popc(v[k]);
+        }
+        uint32_t incl = ones;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t up = __shfl_up(incl, o, 64);
+            incl += lane >= (uint32_t)o ? up : 0u;
+        }
+        if (lane == 63)
+            part[wave] = incl;
+        __syncthreads();
+        uint32_t pos = incl - ones, total = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) {
+            pos += k < wave ? part[k] : 0u;
+            total += part[k];
+        }
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            const uint32_t t = t0 + (w0 + k) * 32;
+            for (uint32_t b = v[k]; b; b &= b - 1, pos++) {
+                const uint32_t x = t + __builtin_ctz(b);
+                if (pos < kExpandBuf)
+                    buf[pos] = x;
+                else
+                    out[done + pos] = x;
+            }
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < min(total, kExpandBuf); i += 256)
+            out[done + i] = buf[i];
+        done += total;
+        __syncthreads();  // buf and part are written again
+    }
+}
+
+__global__ void __launch_bounds__(256) bit_expand_kernel(const uint32_t *__restrict__ bits, uint64_t ld, uint32_t n,
+                                                         uint32_t n_seg, const uint64_t *__restrict__ start,
+                                                         uint64_t *__restrict__ off, uint32_t *__restrict__ tids)
+{
+    __shared__ uint32_t buf[kExpandBuf];
+    __shared__ uint32_t part[4];
+    const uint32_t item = blockIdx.x / n_seg, seg = blockIdx.x % n_seg;
+    const uint64_t s0 = start[blockIdx.x], s1 = start[blockIdx.x + 1];
+    if (threadIdx.x == 0 && seg == 0)
+        off[item] = s0;
+    if (threadIdx.x == 0 && blockIdx.x + 1 == gridDim.x)
+        off[n] = s1;
+    if (s1 == s0)
+        return;
+    const uint32_t len = (uint32_t)min((uint64_t)kSegWords, ld - (uint64_t)seg * kSegWords);
+    const uint32_t *row = bits + item * ld + (uint64_t)seg * kSegWords;
+    const uint32_t t0 = seg * (kSegWords * 32);
+    uint32_t *out = tids + s0;
+    // about kExpandBuf / 2 tids a round, and every thread at work on short rows
+    const uint32_t ones = (uint32_t)(s1 - s0);
+    const uint32_t rounds = max(ones / (kExpandBuf / 2), 1u);
+    const uint32_t w = min((len + 255) / 256, max(len / (256 * rounds), 1u));
+    if (w > 8)
+        expand_segment<16>(row, len, t0, out, buf, part);
+    else if (w > 4)
+        expand_segment<8>(row, len, t0, out, buf, part);
+    else if (w > 1)
+        expand_segment<4>(row, len, t0, out, buf, part);
+    else
+        expand_segment<1>(row, len, t0, out, buf, part);
+}
+
 // One block per set: every tid < m and strictly increasing.
 // flags[0] |= 1 on a range error, flags[1] |= 1 on an order error.
 __global__ void validate_sets_kernel(const uint64_t *off, const uint32_t *tids, uint32_t n, uint32_t m,
@@ -296,6 +488,77 @@ hipError_t launch_validate_sets(const uint64_t *off, const uint32_t *tids, uint3
     (void)nnz;
     uint32_t g = n < 65536 ? n : 65536;
     validate_sets_kernel<<<g, kBlock, 0, s>>>(off, tids, n, m, flags);
+    return hipGetLastError();
+}
+
+// Words of a row that one workgroup of txn_bits_kernel covers, for n items: the
+// most (whole 128-byte lines, at best) whose block fits lds bytes, but enough
+// workgroups for the chip; 0: too many items.
+static uint32_t txn_bits_words(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
+{
+    uint32_t best = 0;
+    for (uint32_t tw : {8u, 16u, 32u}) {
+        const uint64_t need = ((uint64_t)n + 1) * (tw + 1) * 4 + (32 * tw + 1) * 4;
+        if (need <= lds && (best == 0 || (uint64_t)m / (32 * tw) >= n_cu))
+            best = tw;
+    }
+    return best;
+}
+
+bool bit_ingest_fits(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
+{
+    const uint64_t n_seg = (bit_row_words(m) + kSegWords - 1) / kSegWords;
+    return txn_bits_words(m, n, lds, n_cu) != 0 && n * n_seg <= 0x7FFFFFFFull;
+}
+
+uint64_t bit_ingest_segments(uint32_t m, uint32_t n)
+{
+    return n * ((bit_row_words(m) + kSegWords - 1) / kSegWords);
+}
+
+hipError_t launch_txn_bits(const uint64_t *row_off, const uint32_t *items, uint32_t m, uint32_t n, uint32_t lds,
+                           uint32_t n_cu, uint32_t *bits, uint32_t *flag, hipStream_t s)
+{
+    const uint64_t ld = bit_row_words(m);
+    const uint32_t tw = txn_bits_words(m, n, lds, n_cu);
+    if (tw == 0)
+        return hipErrorInvalidValue;
+    const uint32_t n_chunks = (uint32_t)((ld + tw - 1) / tw), per_xcd = (n_chunks + kXcds - 1) / kXcds;
+    const uint32_t bytes = (n + 1) * (tw + 1) * 4;
+    const void *f = tw == 8    ? reinterpret_cast<const void *>(txn_bits_kernel<8>)
+                    : tw == 16 ? reinterpret_cast<const void *>(txn_bits_kernel<16>)
+                               : reinterpret_cast<const void *>(txn_bits_kernel<32>);
+    if (bytes > 32768) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess)
+            return e;
+    }
+    const uint32_t grid = per_xcd * kXcds;
+    if (tw == 8)
+        txn_bits_kernel<8><<<grid, kTxnBitsThreads, bytes, s>>>(row_off, items, m, n, ld, n_chunks, per_xcd, bits, flag);
+    else if (tw == 16)
+        txn_bits_kernel<16><<<grid, kTxnBitsThreads, bytes, s>>>(row_off, items, m, n, ld, n_chunks, per_xcd, bits,
+                                                                 flag);
+    else
+        txn_bits_kernel<32><<<grid, kTxnBitsThreads, bytes, s>>>(row_off, items, m, n, ld, n_chunks, per_xcd, bits,
+                                                                 flag);
+    return hipGetLastError();
+}
+
+hipError_t launch_bit_count(const uint32_t *bits, uint32_t m, uint32_t n, uint32_t *count, hipStream_t s)
+{
+    const uint64_t ld = bit_row_words(m);
+    const uint32_t n_seg = (uint32_t)((ld + kSegWords - 1) / kSegWords);
+    bit_count_kernel<<<n * n_seg, 256, 0, s>>>(bits, ld, n_seg, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_bit_expand(const uint32_t *bits, uint32_t m, uint32_t n, const uint64_t *start, uint64_t *off,
+                             uint32_t *tids, hipStream_t s)
+{
+    const uint64_t ld = bit_row_words(m);
+    const uint32_t n_seg = (uint32_t)((ld + kSegWords - 1) / kSegWords);
+    bit_expand_kernel<<<n * n_seg, 256, 0, s>>>(bits, ld, n, n_seg, start, off, tids);
     return hipGetLastError();
 }
 

@@ -213,3 +213,35 @@ def test_triples_either_route(ctx, monkeypatch, route, m, n, count):
     idx.triple_supports(dev, out)
     ctx.synchronize()
     assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+
+
+@pytest.mark.parametrize("ingest", ["0", "1", None])       # radix sort, bit rows, by time
+@pytest.mark.parametrize("m,n,deg", [
+    (1, 3, 2), (255, 40, 3), (256, 41, 9), (257, 200, 0.3), (5_000, 1300, 20), (140_000, 37, 6), (9_000, 2400, 50),
+    (300_000, 300, 10), (2_000, 5_000, 30),                  # the last: too many items for the bit rows' block
+])
+def test_transactions_either_ingest(ctx, monkeypatch, ingest, m, n, deg):
+    """Transactions in any order with repeats and empty ones; the tidlists through both ways of counting."""
+    if ingest is not None:
+        monkeypatch.setenv("BM_BIT_INGEST", ingest)
+    rng = np.random.default_rng(m + n)
+    sizes = rng.poisson(deg, m) * (rng.random(m) < 0.9)
+    sizes[-1] = 2
+    hot = np.minimum((rng.random(int(sizes.sum())) ** 4 * n).astype(np.uint32), n - 1)   # a few items in most rows
+    rows = np.zeros(m + 1, np.uint64)
+    np.cumsum(sizes, out=rows[1:])
+    off, tids = oracle.transpose(m, rows, hot, n)
+    want = oracle.all_pairs(off, tids)
+    dev = [torch.from_numpy(a).to("cuda:0") for a in (rows.view(np.int64), hot.view(np.int32))]
+    torch.cuda.synchronize()
+    for r, it in ((rows, hot), dev):
+        idx = bm.Index.from_transactions(ctx, n, r, it)
+        assert idx.stats()["nnz"] == tids.size
+        for route in ("0", "1"):
+            monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+            assert np.array_equal(idx.all_pair_supports(), want)
+    bad = hot.copy()
+    bad[bad.size // 2] = n
+    with pytest.raises(bm.BatmapError) as e:
+        bm.Index.from_transactions(ctx, n, rows, bad)
+    assert e.value.status == bm.BM_ERANGE
