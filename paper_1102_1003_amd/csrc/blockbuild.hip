@@ -18,6 +18,7 @@ namespace bm {
 namespace {
 
 constexpr uint32_t kEmptyCode = 0x7Fu;
+constexpr uint32_t kMaxBlocksH = kBlockKeysH;
 constexpr uint32_t kBlockFailCap = 1024;  // nestless elements one block may leave
 constexpr int kBucketThreads = 256;
 constexpr int kBucketPer = kBucketChunk / kBucketThreads;
@@ -33,12 +34,10 @@ size_t block_lds_bytes(uint32_t r0)
     return sizeof(BlockHead) + 3ull * r0 + 3ull * r0 / 8;
 }
 
-// beta_{t,H}'s keys of every block (H < 128: m <= 127 r_0) and table, kept
-// in LDS by each workgroup of the build: x = m1 | m2 << 16, y = c1 | c2 << 16,
-// z = i1 | i2 << 16 (all below 2^15).
-constexpr uint32_t kMaxBlocksH = 128;
-
-__device__ inline uint4 pack_key(const BetaKey &k)
+// beta_{t,H}'s keys of every block (H < 128: m <= 127 r_0) and table, made on
+// the host and kept in LDS by each workgroup of the build: x = m1 | m2 << 16,
+// y = c1 | c2 << 16, z = i1 | i2 << 16 (all below 2^15).
+inline uint4 pack_key(const BetaKey &k)
 {
     return make_uint4(k.m1 | (k.m2 << 16), k.c1 | (k.c2 << 16), k.i1 | (k.i2 << 16), 0u);
 }
@@ -55,18 +54,21 @@ __device__ inline BetaKey unpack_key(uint4 w)
     return k;
 }
 
-// Byte i of the LDS tables set to v; returns the byte it held.
+// Byte i of the LDS tables set to v; returns the byte it held.  One masked
+// exchange (clear the mask's bits, set v's, return the word): a compare-and-swap
+// loop needs a read before it and a round for every neighbour that changed (large
+// Zipf build 663 us; with this, keys from the host, the next copy loaded ahead and
+// byte reads 530).
 __device__ inline uint32_t lds_swap_byte(uint32_t *W, uint32_t i, uint32_t v)
 {
-    uint32_t *w = W + (i >> 2);
-    const uint32_t sh = (i & 3u) * 8u;
-    uint32_t old = *w;
-    for (;;) {
-        const uint32_t prev = atomicCAS(w, old, (old & ~(0xFFu << sh)) | (v << sh));
-        if (prev == old)
-            return (old >> sh) & 0xFFu;
-        old = prev;
-    }
+    typedef __attribute__((address_space(3))) uint32_t LdsWord;
+    const uint32_t at = (uint32_t)(uintptr_t)(LdsWord *)W + (i & ~3u), sh = (i & 3u) * 8u;
+    uint32_t old;
+    asm volatile("ds_mskor_rtn_b32 %0, %1, %2, %3\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(old)
+                 : "v"(at), "v"(0xFFu << sh), "v"(v << sh)
+                 : "memory");
+    return (old >> sh) & 0xFFu;
 }
 
 // Byte i emptied if it holds v.
@@ -85,7 +87,7 @@ __device__ inline void lds_clear_byte(uint32_t *W, uint32_t i, uint32_t v)
 
 __device__ inline uint32_t lds_get_byte(const uint32_t *W, uint32_t i)
 {
-    return (W[i >> 2] >> ((i & 3u) * 8u)) & 0xFFu;
+    return reinterpret_cast<const uint8_t *>(W)[i];
 }
 
 __device__ inline int64_t find_sorted(const uint32_t *a, uint64_t n, uint32_t x)
@@ -160,40 +162,62 @@ __global__ void __launch_bounds__(kBucketThreads)
             atomicAdd(&count[v.b0 + j], hist[j]);
 }
 
-// The chunk's y values into their blocks' runs: the chunk reserves its part
-// of each run with one atomic, then ranks its elements in LDS.
+// The chunk's y values into their blocks' runs: ranked per block and put in
+// block order in LDS, the chunk reserves its part of each run with one atomic,
+// and the values leave in that order, neighbouring lanes to neighbouring words
+// (large Zipf 100 us; written straight from the tidlist's order, a wavefront's 64
+// stores went to as many lines: 160).
 template <bool K24>
 __global__ void __launch_bounds__(kBucketThreads)
     bucket_scatter_kernel(const BucketChunk *chunks, const uint32_t *__restrict__ tids, const uint64_t *off,
                           const uint32_t *sorted_items, const uint32_t *r_sorted, const uint64_t *goff, uint32_t gb,
                           BlockPerm B, uint32_t *cursor, uint32_t *__restrict__ bk)
 {
-    __shared__ uint32_t hist[256], start[256];
+    __shared__ uint32_t hist[256], shift[256];  // shift: run position minus position in `vals`
+    __shared__ uint32_t wsum[kBucketThreads / 64];
+    __shared__ uint32_t vals[kBucketChunk];
+    static_assert(kBucketThreads == 256, "one thread per block of a map");
     const ChunkView v = chunk_view(chunks[blockIdx.x], tids, off, sorted_items, r_sorted, goff, gb, B.l0);
-    for (uint32_t j = threadIdx.x; j < v.R; j += blockDim.x)
-        hist[j] = 0;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x / 64u;
+    hist[threadIdx.x] = 0;
     __syncthreads();
-    uint32_t ys[kBucketPer];
-#pragma unroll
-    for (int k = 0; k < kBucketPer; k++) {
-        const uint32_t e = v.e0 + k * kBucketThreads + threadIdx.x;
-        ys[k] = e < v.e1 ? perm_eval_k<K24>(B.sig, 0, v.T[e]) : 0u;
-        if (e < v.e1)
-            atomicAdd(&hist[(ys[k] >> B.l0) & (v.R - 1u)], 1u);
-    }
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < v.R; j += blockDim.x) {
-        start[j] = hist[j] ? atomicAdd(&cursor[v.b0 + j], hist[j]) : 0u;
-        hist[j] = 0;
-    }
-    __syncthreads();
+    uint32_t ys[kBucketPer], rank[kBucketPer];
 #pragma unroll
     for (int k = 0; k < kBucketPer; k++) {
         const uint32_t e = v.e0 + k * kBucketThreads + threadIdx.x;
         if (e < v.e1) {
-            const uint32_t j = (ys[k] >> B.l0) & (v.R - 1u);
-            bk[start[j] + atomicAdd(&hist[j], 1u)] = ys[k];
+            ys[k] = perm_eval_k<K24>(B.sig, 0, v.T[e]);
+            rank[k] = atomicAdd(&hist[(ys[k] >> B.l0) & (v.R - 1u)], 1u);
         }
+    }
+    __syncthreads();
+    const uint32_t mine = hist[threadIdx.x];
+    uint32_t incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(incl, o, 64);
+        incl += lane >= (uint32_t)o ? up : 0u;
+    }
+    if (lane == 63)
+        wsum[wave] = incl;
+    __syncthreads();
+    uint32_t first = incl - mine;
+#pragma unroll
+    for (uint32_t w = 0; w < kBucketThreads / 64; w++)
+        first += w < wave ? wsum[w] : 0u;
+    shift[threadIdx.x] = (mine ? atomicAdd(&cursor[v.b0 + threadIdx.x], mine) : 0u) - first;
+    hist[threadIdx.x] = first;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kBucketPer; k++) {
+        const uint32_t e = v.e0 + k * kBucketThreads + threadIdx.x;
+        if (e < v.e1)
+            vals[hist[(ys[k] >> B.l0) & (v.R - 1u)] + rank[k]] = ys[k];
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < v.e1 - v.e0; i += kBucketThreads) {
+        const uint32_t y = vals[i];
+        bk[shift[(y >> B.l0) & (v.R - 1u)] + i] = y;
     }
 }
 
@@ -206,8 +230,9 @@ __global__ void __launch_bounds__(1024)
                        const uint32_t *__restrict__ bucket_map, const uint64_t *__restrict__ goff,
                        const uint32_t *__restrict__ sorted_items, const uint32_t *__restrict__ r_sorted,
                        const uint32_t *__restrict__ tids, const uint64_t *__restrict__ off, BlockPerm B,
-                       uint32_t shift, uint32_t max_loop, uint32_t *__restrict__ arena, uint32_t *failed_bits,
-                       uint32_t *failed, uint32_t *n_failed, uint32_t fail_cap, uint32_t *overflow)
+                       const uint4 *__restrict__ keys, uint32_t shift, uint32_t max_loop,
+                       uint32_t *__restrict__ arena, uint32_t *failed_bits, uint32_t *failed, uint32_t *n_failed,
+                       uint32_t fail_cap, uint32_t *overflow)
 {
     extern __shared__ uint32_t lds_dyn[];
     __shared__ uint4 KT[3 * kMaxBlocksH];  // beta_{t,H}'s keys at t * kMaxBlocksH + H
@@ -222,36 +247,38 @@ __global__ void __launch_bounds__(1024)
     const uint32_t n_el = bstart[b + 1] - bstart[b];
     const uint32_t csh = B.l0 - shift;  // code = H << csh | pos >> shift
 
-    for (uint32_t i = threadIdx.x; i < 3u * r0 / 4u; i += blockDim.x)
-        W[i] = 0x7F7F7F7Fu;
-    for (uint32_t i = threadIdx.x; i < 3u * r0 / 32u; i += blockDim.x)
+    // the lanes' first copies and the keys are on their way while the tables are cleared
+    const uint32_t nt = blockDim.x, copies = 2u * n_el;
+    uint32_t c = threadIdx.x, y_next = c < copies ? Y[c >> 1] : 0u;
+    for (uint32_t i = threadIdx.x; i < 3u * kMaxBlocksH; i += nt)
+        KT[i] = keys[i];
+    for (uint32_t i = threadIdx.x * 4; i < 3u * r0 / 4u; i += nt * 4)
+        *reinterpret_cast<uint4 *>(W + i) = make_uint4(0x7F7F7F7Fu, 0x7F7F7F7Fu, 0x7F7F7F7Fu, 0x7F7F7F7Fu);
+    for (uint32_t i = threadIdx.x; i < 3u * r0 / 32u; i += nt)
         IND[i] = 0;
-    for (uint32_t i = threadIdx.x; i < 3u * kMaxBlocksH; i += blockDim.x) {
-        const uint32_t t = i / kMaxBlocksH, H = i % kMaxBlocksH;
-        if (H < B.n_blocks)
-            KT[i] = pack_key(beta_key(B, H, B.key1[t], B.key2[t]));
-    }
     if (threadIdx.x == 0)
         Hd.count = 0;
     __syncthreads();
 
     // Insertion (Sec. II-A).  Copy c of the block is chain c mod 2 of element
     // c / 2, entering at A_1 or A_2 and then cycling through the tables; a
-    // lane takes its next copy as soon as its chain ends.  An exchange with
-    // the element's own other copy just passes the chain on.
+    // lane takes its next copy (loaded while it worked on the one before) as
+    // soon as its chain ends.  An exchange with the element's own other copy
+    // just passes the chain on.
     {
         const uint32_t steps = 3u * max_loop;
-        uint32_t c = threadIdx.x, y = 0, tb = 0, left = 0;
+        uint32_t y = 0, tb = 0, left = 0;
         bool busy = false;
         for (;;) {
             if (!busy) {
-                if (c >= 2u * n_el)
+                if (c >= copies)
                     break;
-                y = Y[c >> 1];
+                y = y_next;
                 tb = c & 1u;
                 left = steps;
                 busy = true;
-                c += blockDim.x;
+                c += nt;
+                y_next = c < copies ? Y[c >> 1] : 0u;
             }
             if (left == 0) {
                 const uint32_t slot = atomicAdd(&Hd.count, 1u);
@@ -335,8 +362,9 @@ __global__ void __launch_bounds__(1024)
     __syncthreads();
 
     // Encoding: a wavefront per 8 groups (256 slots), lane = (group, plane).
-    // Plane b < 7 gathers bit b of the group's 32 code bytes, four at a time by
-    // a dot product with 1, 2, 4, 8; plane 7 is the group's indicator word.
+    // Plane b < 7 gathers bit b of the group's 32 code bytes, eight at a time by
+    // two dot products with 1, 2, 4, 8 and 16 .. 128 (2^b times the eight bits);
+    // plane 7 is the group's indicator word.
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
     const uint32_t n_waves = blockDim.x / 64u;
@@ -350,10 +378,13 @@ __global__ void __launch_bounds__(1024)
             const uint4 lo = *reinterpret_cast<const uint4 *>(src);
             const uint4 hi = *reinterpret_cast<const uint4 *>(src + 16);
             const uint32_t d[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            const uint32_t bit = 0x01010101u << plane;
             uint32_t word = 0;
 #pragma unroll
-            for (int k = 0; k < 8; k++)
-                word |= __builtin_amdgcn_udot4((d[k] >> plane) & 0x01010101u, 0x08040201u, 0u, false) << (4 * k);
+            for (int k = 0; k < 8; k += 2) {
+                const uint32_t low = __builtin_amdgcn_udot4(d[k] & bit, 0x08040201u, 0u, false);
+                word |= __builtin_amdgcn_udot4(d[k + 1] & bit, 0x80402010u, low, false) >> plane << (4 * k);
+            }
             if (plane == 7u)
                 word = IND[v >> 5];
             out[(uint64_t)(v / kSlotsPerGroup) * kWordsPerGroup + plane] = word;
@@ -430,6 +461,14 @@ BlockPerm make_block_perm(uint32_t m, uint32_t l0, uint64_t seed)
     return B;
 }
 
+void make_block_keys(const BlockPerm &B, uint4 *keys)
+{
+    for (uint32_t t = 0; t < 3; t++)
+        for (uint32_t H = 0; H < kMaxBlocksH; H++)
+            keys[t * kMaxBlocksH + H] =
+                H < B.n_blocks ? pack_key(beta_key(B, H, B.key1[t], B.key2[t])) : make_uint4(0, 0, 0, 0);
+}
+
 hipError_t launch_bucket_map(const uint64_t *goff, uint32_t p_first, uint32_t n, uint32_t gb, uint32_t *bucket_map,
                              hipStream_t s)
 {
@@ -473,7 +512,8 @@ hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, c
 hipError_t launch_block_build(const uint32_t *bk, const uint32_t *bstart, const uint32_t *bucket_map,
                               uint32_t n_blocks, const uint64_t *goff, const uint32_t *sorted_items,
                               const uint32_t *r_sorted, const uint32_t *tids, const uint64_t *off, const BlockPerm &B,
-                              uint32_t shift, uint32_t max_loop, uint32_t *arena, uint32_t *failed_bits,
+                              const uint4 *keys, uint32_t shift, uint32_t max_loop, uint32_t *arena,
+                              uint32_t *failed_bits,
                               uint32_t *failed, uint32_t *n_failed, uint32_t fail_cap, uint32_t *overflow,
                               hipStream_t s)
 {
@@ -486,7 +526,7 @@ hipError_t launch_block_build(const uint32_t *bk, const uint32_t *bstart, const 
     // 3 r_0 / 256 wavefront steps of the encoding; about r_0 / 2 elements
     const int threads = r0 >= 32768 ? 1024 : (r0 >= 8192 ? 512 : 256);
     block_build_kernel<<<n_blocks, threads, lds, s>>>(bk, bstart, bucket_map, goff, sorted_items, r_sorted, tids, off,
-                                                      B, shift, max_loop, arena, failed_bits, failed, n_failed,
+                                                      B, keys, shift, max_loop, arena, failed_bits, failed, n_failed,
                                                       fail_cap, overflow);
     return hipGetLastError();
 }

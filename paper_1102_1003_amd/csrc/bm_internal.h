@@ -222,6 +222,9 @@ struct BlockPerm {
 };
 
 BlockPerm make_block_perm(uint32_t m, uint32_t l0, uint64_t seed);
+// The packed keys of beta_{t,H} for launch_block_build, at t kBlockKeysH + H.
+constexpr uint32_t kBlockKeysH = 128;
+void make_block_keys(const BlockPerm &B, uint4 *keys);
 
 __host__ __device__ inline uint32_t block_hash(uint32_t H, uint32_t key)
 {
@@ -576,7 +579,7 @@ hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, c
 hipError_t launch_block_build(const uint32_t *bk, const uint32_t *bstart, const uint32_t *bucket_map,
                               uint32_t n_blocks, const uint64_t *goff, const uint32_t *sorted_items,
                               const uint32_t *r_sorted, const uint32_t *tids, const uint64_t *off, const BlockPerm &B,
-                              uint32_t shift, uint32_t max_loop, uint32_t *arena, uint32_t *failed_bits,
+                              const uint4 *keys, uint32_t shift, uint32_t max_loop, uint32_t *arena, uint32_t *failed_bits,
                               uint32_t *failed, uint32_t *n_failed, uint32_t fail_cap, uint32_t *overflow,
                               hipStream_t s);
 // Largest r_0 whose blocks fit the device's LDS (0 if none).

@@ -1030,6 +1030,7 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
     }
     Span span_construct(ctx, PH_CONSTRUCT);
     DevBuf<BucketChunk> chunks;
+    DevBuf<uint4> keys;
     DevBuf<uint32_t> count, bstart, cursor, bmap, bk, counters;
     DevBuf<char> tmp;
     HIPC(ctx, chunks.alloc(std::max<size_t>(h_chunks.size(), 1)));
@@ -1046,8 +1047,11 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
     if (corr_here)
         HIPC(ctx, idx->corr.alloc(2 * corr_cap));
     HIPC(ctx, tmp.alloc(scan_tmp_bytes(n_blocks + 1)));
-    if (!h_chunks.empty())
-        BMC(upload(ctx, chunks.p, h_chunks.data(), h_chunks.size() * sizeof(BucketChunk)));
+    HIPC(ctx, keys.alloc(3 * kBlockKeysH));
+    uint4 h_keys[3 * kBlockKeysH];
+    make_block_keys(idx->bperm, h_keys);
+    BMC(upload_many(ctx, {{keys.p, h_keys, sizeof h_keys},
+                          {chunks.p, h_chunks.data(), h_chunks.size() * sizeof(BucketChunk)}}));
     HIPC(ctx, fill_u32(count.p, n_blocks + 1, 0, s));
     HIPC(ctx, launch_bucket_map(idx->goff.p, first, n, gb, bmap.p, s));
     HIPC(ctx, launch_bucket_count(chunks.p, (uint32_t)h_chunks.size(), idx->tids.p, idx->off.p, idx->sorted_items.p,
@@ -1071,7 +1075,7 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
             HIPC(ctx, hipEventRecord(ctx->fork, s));
         }
         HIPC(ctx, launch_block_build(bk.p, bstart.p, bmap.p, (uint32_t)n_blocks, idx->goff.p, idx->sorted_items.p,
-                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, idx->shift, o->max_loop,
+                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, keys.p, idx->shift, o->max_loop,
                                      idx->arena.p, failed_bits.p, idx->failed.p, counters.p, (uint32_t)fail_cap,
                                      counters.p + 1, s));
         // the corrections of the failures the build lists (it stops listing
