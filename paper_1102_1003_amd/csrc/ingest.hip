@@ -224,7 +224,8 @@ __global__ void offsets_and_dups_kernel(const uint32_t *keys, const uint32_t *va
 // bytes an incidence.  LDS rows are TW + 1 words apart: the incidences of a
 // transaction (same word, other items) spread over the banks.  Consecutive
 // chunks run on one XCD, whose L2 puts the pieces of a line together.  Bound by
-// memory: m = 10^6, n = 2000, 4 * 10^7 incidences (160 MB in, 250 MB out).
+// memory: m = 10^6, n = 2000, 4 * 10^7 incidences (160 MB in, 250 MB out) 125 us,
+// and 39 us to count them.
 constexpr int kTxnBitsThreads = 1024;
 
 template <int TW>
@@ -292,7 +293,7 @@ __global__ void __launch_bounds__(kTxnBitsThreads)
 }
 
 // Ones of every (row, segment of kSegWords words).
-constexpr uint32_t kSegWords = 4096;
+constexpr uint32_t kSegWords = 1024;
 
 __global__ void __launch_bounds__(256) bit_count_kernel(const uint32_t *__restrict__ bits, uint64_t ld,
                                                         uint32_t n_seg, uint32_t *count)
@@ -319,11 +320,15 @@ __global__ void __launch_bounds__(256) bit_count_kernel(const uint32_t *__restri
 // The tids of one (row, segment), in order, at tids[start[row n_seg + seg] ..).
 // W consecutive words a thread and round: their ones are counted, ranked over
 // the workgroup and set down in LDS, then written out coalesced.  W is chosen
-// so that a round's tids mostly fit the LDS buffer (the rest go out directly).
+// so that a round's tids mostly fit the LDS buffer (the rest go out directly),
+// as 16-bit offsets in the round (W <= 4); the buffer skips a word after every 32
+// of them, since in a dense row the lanes write 32 apart.  Large Zipf (410 MB
+// moved): 123 us; with segments of 4096 words, whose dense ones end the launch,
+// 183, and with 32-bit offsets, which halve the workgroups a CU, 209.
 constexpr uint32_t kExpandBuf = 8192;
 
-template <int W>
-__device__ void expand_segment(const uint32_t *row, uint32_t len, uint32_t t0, uint32_t *out, uint32_t *buf,
+template <int W>  // 256 W 32 tids a round: 16 bits
+__device__ void expand_segment(const uint32_t *row, uint32_t len, uint32_t t0, uint32_t *out, uint16_t *buf,
                                uint32_t *part)
 {
     uint32_t done = 0;
@@ -354,18 +359,18 @@ __device__ void expand_segment(const uint32_t *row, uint32_t len, uint32_t t0, u
         }
 #pragma unroll
         for (int k = 0; k < W; k++) {
-            const uint32_t t = t0 + (w0 + k) * 32;
+            const uint32_t t = (threadIdx.x * W + k) * 32;  // within the round
             for (uint32_t b = v[k]; b; b &= b - 1, pos++) {
                 const uint32_t x = t + __builtin_ctz(b);
                 if (pos < kExpandBuf)
-                    buf[pos] = x;
+                    buf[pos + pos / 32 * 2] = (uint16_t)x;
                 else
-                    out[done + pos] = x;
+                    out[done + pos] = t0 + r0 * 32 + x;
             }
         }
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < min(total, kExpandBuf); i += 256)
-            out[done + i] = buf[i];
+            out[done + i] = t0 + r0 * 32 + buf[i + i / 32 * 2];
         done += total;
         __syncthreads();  // buf and part are written again
     }
@@ -375,7 +380,7 @@ __global__ void __launch_bounds__(256) bit_expand_kernel(const uint32_t *__restr
                                                          uint32_t n_seg, const uint64_t *__restrict__ start,
                                                          uint64_t *__restrict__ off, uint32_t *__restrict__ tids)
 {
-    __shared__ uint32_t buf[kExpandBuf];
+    __shared__ uint16_t buf[kExpandBuf + kExpandBuf / 16];
     __shared__ uint32_t part[4];
     const uint32_t item = blockIdx.x / n_seg, seg = blockIdx.x % n_seg;
     const uint64_t s0 = start[blockIdx.x], s1 = start[blockIdx.x + 1];
@@ -393,11 +398,7 @@ __global__ void __launch_bounds__(256) bit_expand_kernel(const uint32_t *__restr
     const uint32_t ones = (uint32_t)(s1 - s0);
     const uint32_t rounds = max(ones / (kExpandBuf / 2), 1u);
     const uint32_t w = min((len + 255) / 256, max(len / (256 * rounds), 1u));
-    if (w > 8)
-        expand_segment<16>(row, len, t0, out, buf, part);
-    else if (w > 4)
-        expand_segment<8>(row, len, t0, out, buf, part);
-    else if (w > 1)
+    if (w > 1)
         expand_segment<4>(row, len, t0, out, buf, part);
     else
         expand_segment<1>(row, len, t0, out, buf, part);
