@@ -526,6 +526,80 @@ bool packed_rows()
     return !(e && e[0] == '0');
 }
 
+// ------------------------------------------------------------ bitmap route
+// Which way a call's pairs are counted is a matter of time alone: the counts
+// are exact either way.  A pair of maps costs 3 max(r_i, r_j) slot compares,
+// so the slot compare is the faster one where sets are sparse; a pair of bit
+// rows costs m bits on the matrix cores whatever the sets.
+
+// BM_BITMAP_ROUTE=0 keeps every call on the slot compare, 1 takes the bitmap
+// route and 2 the count by transactions wherever they can be taken, whatever
+// the expected times.
+int bitmap_route_env()
+{
+    const char *e = getenv("BM_BITMAP_ROUTE");
+    return !e || !*e ? -1 : atoi(e);
+}
+
+// Whether calls may take the bitmap route: not when the environment or the
+// context pins how slots are compared (those calls are there to run that
+// compare).
+bool bitmap_route_on(const bm_context *ctx)
+{
+    return bitmap_route_env() != 0 && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
+}
+
+// Expected time of a slot compare (us): W + 1 VALU operations per 32 slot
+// pairs, 30 * 10^12 a second with 8-bit slots and 20 with wider ones; a work
+// item's walk over up to 256 groups of the widest map (r_max slots a table),
+// about 1 us a group (2 with wider slots), which is what a compare takes that
+// does not fill the chip; fixed_us for launches, zero fill, corrections and
+// planning.  Slots and bits measured (MI355X, us, rows kept): 10^4 x 100 at 0.5 %:
+// 111 and 14; 200,000 x 300 at 0.5 %: 261 and 20; 50,000 x 1500 at 0.05 %
+// (16-bit slots, r = 128): 31 and 44; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x
+// 2000 Zipf at 2 %: 4700 and 670; 10^6 x 1500 at 0.05 % (16-bit): 332 and 390.
+double compare_us(double slot_pairs, uint32_t planes, double r_max, double fixed_us)
+{
+    const bool wide = planes != 8;
+    return fixed_us + std::min(256.0, 3 * r_max / 32) * (wide ? 2 : 1) +
+           slot_pairs / 32 * (planes + 1) / (wide ? 20e6 : 30e6);
+}
+
+// Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
+double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (rows * row_words + tids) * 4 / 2.5e6; }
+
+// Whether `rows` bit rows may be made: at most a sixteenth of the device's memory.
+bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
+{
+    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16;
+}
+
+// A stream being captured takes the slot compare, as ever (the bitmap route's
+// rows and scratch would become part of the graph), unless the index was built
+// without a plan because its rows are there: then each tile is one workgroup's.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Whether all pairs of an index that holds its bit rows will be counted from
+// them (with no scratch too, should a stream be captured).
+bool pairs_by_kept_bits(const bm_index *idx)
+{
+    const bm_context *ctx = idx->ctx;
+    if (!idx->bits.p || !bitmap_route_on(ctx) || bitmap_route_env() == 2 || idx->classes.empty() ||
+        bit_row_words(idx->m) > kGramMaxStages * (kGramStage / 32))
+        return false;
+    return bitmap_route_env() == 1 ||
+           plan_gram(idx->n, idx->n, true, bit_row_words(idx->m), (uint32_t)ctx->n_cu, pinned_gram_tile()).us <
+               compare_us(class_work(idx->classes), idx->planes, idx->h_r_sorted.back(), 20);
+}
+
 // Persistent plans run as one single-launch list: range (-1, all items),
 // longest first.
 bool use_persistent(const bm_context *ctx) { return ctx->persistent && forced_variant() < 0; }
@@ -1069,7 +1143,7 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
         // uploaded on a side stream beside the build: after everything queued
         // before it (its buffer comes from this stream's pool), and before
         // anything queued after it
-        const bool plan_here = attempt == 0 && n - first <= kPlanAtBuild;
+        const bool plan_here = attempt == 0 && early;
         if (plan_here) {
             BMC(create_side(ctx));
             HIPC(ctx, hipEventRecord(ctx->fork, s));
@@ -1352,8 +1426,11 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
     // makes it from here on while the construction's kernels run (indexes of
     // up to kPlanAtBuild maps; larger ones are mostly queried by subsets, and
     // planning all their pairs takes longer than building them)
+    // Not where the pairs will be counted from the bit rows that the ingest
+    // left: the build waited for its plan (large Zipf: 0.3 ms past its kernels).
+    const bool plan_here = !order3 && n - first_built <= kPlanAtBuild && !pairs_by_kept_bits(idx);
     std::future<Plan> early_plan;
-    if (!order3 && n - first_built <= kPlanAtBuild)
+    if (plan_here)
         early_plan = start_plan(idx, first_built);
 
     // construction, in batches of maps whose staging fits the budget
@@ -1373,7 +1450,8 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
         const char *bb_env = getenv("BM_BLOCK_BUILD");
         if (!(bb_env && atoi(bb_env) == 0) && !order3 && idx->planes == 8 && !o->perm[0] && first_built < n &&
             idx->r0 <= block_build_max_r0()) {
-            st = block_construct(idx, o, failed_bits, fb_words, has_map.p, &early_plan, block_done, corr_done);
+            st = block_construct(idx, o, failed_bits, fb_words, has_map.p, plan_here ? &early_plan : nullptr, block_done,
+                                 corr_done);
             if (st != BM_OK)
                 return st;
         }
@@ -1512,7 +1590,7 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
             if (st != BM_OK)
                 return st;
             // the all-pairs plan, uploaded while the construction kernels run
-            if (attempt == 0 && !order3 && n - idx->first_built <= kPlanAtBuild) {
+            if (attempt == 0 && plan_here) {
                 st = ensure_plan(idx, idx->first_built, nullptr, &early_plan);
                 if (st != BM_OK)
                     return st;
@@ -1617,66 +1695,6 @@ InstDesc whole_desc(const bm_index *idx, uint32_t *out)
     return d;
 }
 
-// ------------------------------------------------------------ bitmap route
-// Which way a call's pairs are counted is a matter of time alone: the counts
-// are exact either way.  A pair of maps costs 3 max(r_i, r_j) slot compares,
-// so the slot compare is the faster one where sets are sparse; a pair of bit
-// rows costs m bits on the matrix cores whatever the sets.
-
-// BM_BITMAP_ROUTE=0 keeps every call on the slot compare, 1 takes the bitmap
-// route and 2 the count by transactions wherever they can be taken, whatever
-// the expected times.
-int bitmap_route_env()
-{
-    const char *e = getenv("BM_BITMAP_ROUTE");
-    return !e || !*e ? -1 : atoi(e);
-}
-
-// Whether calls may take the bitmap route: not when the environment or the
-// context pins how slots are compared (those calls are there to run that
-// compare).
-bool bitmap_route_on(const bm_context *ctx)
-{
-    return bitmap_route_env() != 0 && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
-}
-
-// Expected time of a slot compare (us): W + 1 VALU operations per 32 slot
-// pairs, 30 * 10^12 a second with 8-bit slots and 20 with wider ones; a work
-// item's walk over up to 256 groups of the widest map (r_max slots a table),
-// about 1 us a group (2 with wider slots), which is what a compare takes that
-// does not fill the chip; fixed_us for launches, zero fill, corrections and
-// planning.  Slots and bits measured (MI355X, us, rows kept): 10^4 x 100 at 0.5 %:
-// 111 and 14; 200,000 x 300 at 0.5 %: 261 and 20; 50,000 x 1500 at 0.05 %
-// (16-bit slots, r = 128): 31 and 44; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x
-// 2000 Zipf at 2 %: 4700 and 670; 10^6 x 1500 at 0.05 % (16-bit): 332 and 390.
-double compare_us(double slot_pairs, uint32_t planes, double r_max, double fixed_us)
-{
-    const bool wide = planes != 8;
-    return fixed_us + std::min(256.0, 3 * r_max / 32) * (wide ? 2 : 1) +
-           slot_pairs / 32 * (planes + 1) / (wide ? 20e6 : 30e6);
-}
-
-// Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
-double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (rows * row_words + tids) * 4 / 2.5e6; }
-
-// Whether `rows` bit rows may be made: at most a sixteenth of the device's memory.
-bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
-{
-    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16;
-}
-
-// A stream being captured takes the slot compare, as ever: the bitmap
-// route's rows and scratch would become part of the graph.
-bool capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 // The index's bit rows (every item's), made at the first call that needs them.
 bm_status ensure_bits(bm_index *idx)
 {
@@ -1766,8 +1784,20 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
         idx->bits_saved_us += other_us - p.us;
         go = idx->bits_saved_us > c.us - p.us;
     }
-    if (!go || capturing(s))
+    if (!go)
         return BM_OK;
+    if (capturing(s)) {
+        if (list || !idx->bits.p || idx->planned_first != UINT32_MAX)
+            return BM_OK;
+        const GramPlan one = plan_gram(k, k, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile(), 0);
+        if (one.ws_floats)
+            return BM_OK;
+        Span sp(ctx, PH_COMPARE);
+        const BitMat a = whole_bits(idx);
+        HIPC(ctx, launch_gram(one, a, a, out, k, nullptr, s));
+        taken = true;
+        return BM_OK;
+    }
     DevBuf<float> ws;
     DevBuf<uint32_t> own;
     if (ws.alloc(p.ws_floats) != hipSuccess || (list && ids.alloc(k) != hipSuccess))
@@ -2692,6 +2722,25 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     uint32_t first = (uint32_t)(std::lower_bound(idx->h_sizes_sorted.begin(), idx->h_sizes_sorted.end(), min_support) -
                                 idx->h_sizes_sorted.begin());
     first = std::max(first, idx->first_built);
+    // scratch: counts | per-block counts | their offsets | scan workspace | work list, or parts of the product
+    const uint32_t nb = threshold_blocks(np);
+    const uint64_t o_cnt = align_up(np * 4, 256);
+    const uint64_t o_off = o_cnt + align_up(((uint64_t)nb + 1) * 4, 256);
+    const uint64_t o_tmp = o_off + align_up(((uint64_t)nb + 1) * 8, 256);
+    const uint64_t o_work = o_tmp + align_up(scan_tmp_bytes((uint64_t)nb + 1), 256);
+    // From the index's bit rows, when it holds them and their product (with
+    // the scratch that is left) is expected to be faster.
+    const uint64_t room = o_work < kNoAllocScratchBytes ? (kNoAllocScratchBytes - o_work) / 4 : 0;
+    GramPlan gram;
+    bool by_bits = false;
+    if (idx->bits.p && o_work <= kNoAllocScratchBytes && bitmap_route_on(ctx) && bitmap_route_env() != 2 &&
+        !capturing(s)) {
+        gram = plan_gram(idx->n, idx->n, true, bit_row_words(idx->m), (uint32_t)ctx->n_cu, pinned_gram_tile(), room);
+        by_bits = gram.ws_floats <= room &&
+                  (bitmap_route_env() == 1 ||
+                   gram.us < compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes),
+                                        idx->planes, idx->h_r_sorted.back(), 20));
+    }
     // The index's resident plan serves when it covers every pair among sorted
     // indices >= first (it was made for a prefix no longer than that; tile
     // speeds only weigh shapes, every plan is complete).  Pairs it adds among
@@ -2701,7 +2750,7 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     std::vector<WorkItem> flat;
     std::vector<std::pair<int, uint32_t>> ranges;
     double slot_pairs = idx->planned_slot_pairs;
-    if (!own) {
+    if (!own && !by_bits) {
         Plan plan;
         plan_classes(classes_from(idx->classes, first), 0, target_items(ctx), plan, nullptr,
                      single_launch(ctx, idx->planes) ? 1 : 0, forced_variant(), false, idx->planes, packed_rows());
@@ -2710,12 +2759,6 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
         flatten_plan(plan, single_launch(ctx, idx->planes), flat, ranges);
         slot_pairs = plan.slot_pairs;
     }
-    // scratch: counts | per-block counts | their offsets | scan workspace | work list
-    const uint32_t nb = threshold_blocks(np);
-    const uint64_t o_cnt = align_up(np * 4, 256);
-    const uint64_t o_off = o_cnt + align_up(((uint64_t)nb + 1) * 4, 256);
-    const uint64_t o_tmp = o_off + align_up(((uint64_t)nb + 1) * 8, 256);
-    const uint64_t o_work = o_tmp + align_up(scan_tmp_bytes((uint64_t)nb + 1), 256);
     const uint64_t end = o_work + flat.size() * sizeof(WorkItem);
     if (end > kNoAllocScratchBytes)
         return fail(ctx, BM_EINVAL, "%u items need %llu bytes of scratch; the allocation-free call has %llu", idx->n,
@@ -2725,14 +2768,20 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     uint32_t *thr_counts = reinterpret_cast<uint32_t *>(sc + o_cnt);
     uint64_t *thr_off = reinterpret_cast<uint64_t *>(sc + o_off);
     WorkItem *work = own ? idx->work.p : reinterpret_cast<WorkItem *>(sc + o_work);
-    if (!own && !flat.empty())
+    if (!flat.empty())
         BMC(upload(ctx, work, flat.data(), flat.size() * sizeof(WorkItem), /*grow=*/false));
     // the scratch keeps the last call's contents: counts and the block-count
-    // tail start from zero here (fill kernels, no memset nodes)
-    HIPC(ctx, fill_u32(counts, np, 0, s));
-    ctx->slot_pairs = slot_pairs;
-    BMC(run_compare(ctx, work, own ? idx->work_ranges : ranges, whole_desc(idx, counts)));
-    HIPC(ctx, launch_apply_corrections(idx->corr.p, idx->n_corr, counts, idx->n, s));
+    // tail start from zero here (fill kernels, no memset nodes; the product
+    // writes every count)
+    if (by_bits) {
+        const BitMat a = whole_bits(idx);
+        HIPC(ctx, launch_gram(gram, a, a, counts, idx->n, reinterpret_cast<float *>(sc + o_work), s));
+    } else {
+        HIPC(ctx, fill_u32(counts, np, 0, s));
+        ctx->slot_pairs = slot_pairs;
+        BMC(run_compare(ctx, work, own ? idx->work_ranges : ranges, whole_desc(idx, counts)));
+        HIPC(ctx, launch_apply_corrections(idx->corr.p, idx->n_corr, counts, idx->n, s));
+    }
     HIPC(ctx, fill_u32(thr_counts + nb, 1, 0, s));
     HIPC(ctx, launch_threshold_count(counts, np, min_support, thr_counts, nb, s));
     HIPC(ctx, exclusive_scan_u32_to_u64(thr_counts, thr_off, (uint64_t)nb + 1, sc + o_tmp, s));

@@ -845,7 +845,7 @@ std::vector<Cls> classes_from(const std::vector<Cls> &cls, uint32_t first)
 // / 5435 / 4573.  A group of 64-wide tiles takes at least 8 stages, one of
 // 128-wide ones 4: fewer only add parts (10^6 x 48 with 768 groups of 64-wide
 // tiles 21 us).
-GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned)
+GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned, uint64_t max_ws)
 {
     GramPlan best;
     for (int tile : {256, 128, 64}) {
@@ -867,14 +867,21 @@ GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint3
             per_cu = std::min<uint64_t>(std::max<uint64_t>(U / ((uint64_t)n_cu * (tile == 64 ? 8 : 4)), 1), 3);
         // enough groups that none adds more than kGramMaxStages stages
         const uint64_t least = std::max<uint64_t>((U + kGramMaxStages - 1) / kGramMaxStages, 1);
-        p.groups = (uint32_t)std::max<uint64_t>(std::min<uint64_t>(U, n_cu * per_cu), least);
+        const uint64_t full = std::min<uint64_t>(U, n_cu * per_cu), room = max_ws / (2ull * tile * tile);
+        p.groups = (uint32_t)std::max(std::min(full, room ? room : tiles), least);
+        if (room == 0 && least <= tiles)
+            p.groups = (uint32_t)tiles;
+        // fewer groups than fill the chip
+        const double idle = p.groups < full ? 1.3 * std::max(1.0, (double)std::min<uint64_t>(U, n_cu) / p.groups) : 1;
         const double part = 4.0 * tile * tile;
-        p.us = 10 + (double)U * stage_us / n_cu;
+        p.us = 10 + (double)U * stage_us / n_cu * idle;
         if (p.groups && (U % p.groups != 0 || (U / p.groups) % p.stages != 0)) {
             p.ws_floats = (uint64_t)p.groups * 2 * tile * tile;
             p.us += (double)std::min<uint64_t>(2ull * p.groups, p.groups + tiles) * part * 2 / 4e6;
         }
-        if (!best.groups || p.us < best.us)
+        // one that keeps within max_ws, where there is one
+        const bool fits = p.ws_floats <= max_ws, best_fits = best.ws_floats <= max_ws;
+        if (!best.groups || (fits && !best_fits) || (fits == best_fits && p.us < best.us))
             best = p;
     }
     return best;

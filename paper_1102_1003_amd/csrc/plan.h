@@ -198,7 +198,10 @@ struct GramPlan {
 
 // The tile size with the least expected time for na x nb counts (tri: the
 // pairs i < j of one family, na == nb) over rows of row_words words.  pinned:
-// 64, 128 or 256 takes that tile.
-GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0);
+// 64, 128 or 256 takes that tile.  max_ws: floats of scratch at most (fewer
+// groups share the tiles then; 0: every tile is one group's, unless its rows are
+// longer than kGramMaxStages, where ws_floats says what it takes all the same).
+GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0,
+                   uint64_t max_ws = UINT64_MAX);
 
 }  // namespace bm

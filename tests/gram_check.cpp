@@ -8,10 +8,10 @@
 // Walks every group's run as the Gram kernel does: 0, or a message.  Each
 // (tile, stage) is visited once, no run part passes the fp32 bound, each shared
 // part has a place of its own inside ws, and gram_reduce_kernel's rule finds it.
-extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned, char *msg,
-                          uint32_t len)
+extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned, uint64_t max_ws,
+                          char *msg, uint32_t len)
 {
-    const bm::GramPlan p = bm::plan_gram(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned);
+    const bm::GramPlan p = bm::plan_gram(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned, max_ws);
     const uint64_t U = (uint64_t)p.tiles * p.stages, W = p.groups;
     auto bad = [&](const char *what) {
         snprintf(msg, len, "%s: tile %d tiles %u stages %u groups %u", what, p.tile, p.tiles, p.stages, p.groups);
@@ -21,6 +21,10 @@ extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_
         return bad("counts left out");
     if ((uint64_t)p.stages * bm::kGramStage < m || W == 0 || W > U)
         return bad("bad cut");
+    if (p.ws_floats > max_ws && p.stages <= bm::kGramMaxStages && max_ws == 0)
+        return bad("scratch where none was to be used");
+    if (p.ws_floats > max_ws && (uint64_t)p.stages * p.tiles <= bm::kGramMaxStages && max_ws >= 2ull * 256 * 256)
+        return bad("more scratch than allowed");
     uint64_t seen = 0;
     std::set<uint64_t> places;
     for (uint64_t w = 0; w < W; w++) {

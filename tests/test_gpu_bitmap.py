@@ -245,3 +245,43 @@ def test_transactions_either_ingest(ctx, monkeypatch, ingest, m, n, deg):
     with pytest.raises(bm.BatmapError) as e:
         bm.Index.from_transactions(ctx, n, rows, bad)
     assert e.value.status == bm.BM_ERANGE
+
+
+def test_rows_kept_by_the_build(monkeypatch):
+    """An index built through its bit rows has no slot plan: a capture before any eager call, and the
+    allocation-free call, count from the rows."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    monkeypatch.setenv("BM_BIT_INGEST", "1")
+    stream = torch.cuda.Stream()
+    c = bm.Context(0, stream)
+    for m, n, p in ((40_000, 300, 0.05), (3_000, 900, 0.1)):
+        off, tids = datagen.bernoulli_sets(m, n, p, seed=n)
+        rows, items = datagen.sets_to_transactions(m, off, tids)
+        want = oracle.all_pairs(off, tids)
+        idx = bm.Index.from_transactions(c, n, rows, items)
+        out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+            idx.all_pair_supports(out)
+        for rep in range(3):
+            out.fill_(-1)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+            assert np.array_equal(idx.all_pair_supports(), want)
+        sigma = int(np.median(want)) + 1
+        fp = torch.zeros(3 * want.size, dtype=torch.int32, device="cuda:0")
+        torch.cuda.synchronize()
+        for route in (None, "0", "1"):
+            if route:
+                monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+            k = idx.frequent_pairs_noalloc(sigma, fp)
+            c.synchronize()
+            got = fp.cpu().numpy().view(np.uint32)[:3 * k].reshape(k, 3)
+            assert np.array_equal(got, oracle.frequent_pairs(off, tids, sigma))
+        monkeypatch.delenv("BM_BITMAP_ROUTE")
+        del g
+    c.close()

@@ -17,9 +17,10 @@ def check(tmp_path_factory):
                     os.path.join(ROOT, "tests", "gram_check.cpp"), "-o", out], check=True)
     lib = ctypes.CDLL(out)
 
-    def run(na, nb, tri, m, n_cu=256, pinned=0):
+    def run(na, nb, tri, m, n_cu=256, pinned=0, max_ws=2**64 - 1):
         msg = ctypes.create_string_buffer(256)
-        assert lib.gram_check(na, nb, int(tri), ctypes.c_uint32(m), n_cu, pinned, msg, 256) == 0, msg.value.decode()
+        assert lib.gram_check(na, nb, int(tri), ctypes.c_uint32(m), n_cu, pinned, ctypes.c_uint64(max_ws), msg,
+                              256) == 0, msg.value.decode()
     return run
 
 
@@ -31,3 +32,5 @@ def test_cut(check, m, pinned):
             check(n, n, True, m, pinned=pinned)
             check(n, 31, False, m, pinned=pinned)
     check(300, 1, False, m, n_cu=8, pinned=pinned)
+    for max_ws in (0, 10_000, 200_000, 9_000_000):          # less scratch than the full cut takes
+        check(200, 200, True, m, pinned=pinned, max_ws=max_ws)
