@@ -225,13 +225,20 @@ __global__ void __launch_bounds__(kBucketThreads)
 // each, in the order of the Fig. 4 layout).  LDS holds the block's code bytes
 // (0x7F when empty): the code pi >> s and the position fix pi, so an evicted
 // element is recovered by inverting beta, with no staging of tids.
+//
+// kHops: `hops` holds, for a copy at position pos of table t in a block of H's,
+// its position in the next table (launch_block_hops); one load then takes the
+// place of two keys, beta's inverse and beta.  A chain's moves wait for one
+// another, so in small builds, where the longest chains (failures: 3 MaxLoop moves)
+// are what the launch takes, a move's latency is all that counts.
+template <bool kHops>
 __global__ void __launch_bounds__(1024)
     block_build_kernel(const uint32_t *__restrict__ bk, const uint32_t *__restrict__ bstart,
                        const uint32_t *__restrict__ bucket_map, const uint64_t *__restrict__ goff,
                        const uint32_t *__restrict__ sorted_items, const uint32_t *__restrict__ r_sorted,
                        const uint32_t *__restrict__ tids, const uint64_t *__restrict__ off, BlockPerm B,
-                       const uint4 *__restrict__ keys, uint32_t shift, uint32_t max_loop,
-                       uint32_t *__restrict__ arena, uint32_t *failed_bits, uint32_t *failed, uint32_t *n_failed,
+                       const uint4 *__restrict__ keys, const uint16_t *__restrict__ hops, uint32_t shift,
+                       uint32_t max_loop, uint32_t *__restrict__ arena, uint32_t *failed_bits, uint32_t *failed, uint32_t *n_failed,
                        uint32_t fail_cap, uint32_t *overflow)
 {
     extern __shared__ uint32_t lds_dyn[];
@@ -267,14 +274,15 @@ __global__ void __launch_bounds__(1024)
     // just passes the chain on.
     {
         const uint32_t steps = 3u * max_loop;
-        uint32_t y = 0, tb = 0, left = 0;
+        uint32_t H = 0, pos = 0, tb = 0, left = 0;  // the copy in hand: its block and position in table tb
         bool busy = false;
         for (;;) {
             if (!busy) {
                 if (c >= copies)
                     break;
-                y = y_next;
+                H = y_next >> B.l0;
                 tb = c & 1u;
+                pos = beta_fwd(B, unpack_key(KT[tb * kMaxBlocksH + H]), y_next & B.mask, block_len(B, H));
                 left = steps;
                 busy = true;
                 c += nt;
@@ -283,20 +291,25 @@ __global__ void __launch_bounds__(1024)
             if (left == 0) {
                 const uint32_t slot = atomicAdd(&Hd.count, 1u);
                 if (slot < kBlockFailCap)
-                    Hd.elem[slot] = y;
+                    Hd.elem[slot] = (H << B.l0) | beta_inv(B, unpack_key(KT[tb * kMaxBlocksH + H]), pos,
+                                                           block_len(B, H));
                 busy = false;
                 continue;
             }
-            const uint32_t H = y >> B.l0;
-            const uint32_t pos = beta_fwd(B, unpack_key(KT[tb * kMaxBlocksH + H]), y & B.mask, block_len(B, H));
             const uint32_t old = lds_swap_byte(W, tb * r0 + pos, (H << csh) | (pos >> shift));
             if (old == kEmptyCode) {
                 busy = false;
             } else {
-                const uint32_t H2 = old >> csh;
-                const uint32_t a2 = beta_inv(B, unpack_key(KT[tb * kMaxBlocksH + H2]), pos, block_len(B, H2));
-                y = (H2 << B.l0) | a2;
-                tb = tb == 2u ? 0u : tb + 1u;
+                const uint32_t tn = tb == 2u ? 0u : tb + 1u;
+                H = old >> csh;
+                if constexpr (kHops) {
+                    pos = hops[((tb * B.n_blocks + H) << B.l0) + pos];
+                } else {
+                    const uint32_t len = block_len(B, H);
+                    const uint32_t a = beta_inv(B, unpack_key(KT[tb * kMaxBlocksH + H]), pos, len);
+                    pos = beta_fwd(B, unpack_key(KT[tn * kMaxBlocksH + H]), a, len);
+                }
+                tb = tn;
                 left--;
             }
         }
@@ -392,6 +405,22 @@ __global__ void __launch_bounds__(1024)
     }
 }
 
+// hops[(t n_blocks + H) r_0 + beta_{t,H}(a)] = beta_{t+1,H}(a)
+__global__ void block_hops_kernel(BlockPerm B, const uint4 *__restrict__ keys, uint16_t *hops)
+{
+    const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;  // H r_0 + a
+    if (x >= B.m)
+        return;
+    const uint32_t H = x >> B.l0, len = block_len(B, H);
+    uint32_t pos[3];
+#pragma unroll
+    for (uint32_t t = 0; t < 3; t++)
+        pos[t] = beta_fwd(B, unpack_key(keys[t * kMaxBlocksH + H]), x & B.mask, len);
+#pragma unroll
+    for (uint32_t t = 0; t < 3; t++)
+        hops[((t * B.n_blocks + H) << B.l0) + pos[t]] = (uint16_t)pos[t == 2 ? 0 : t + 1];
+}
+
 __global__ void gen_block_perms_kernel(BlockPerm B, uint32_t *out)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -407,17 +436,24 @@ int block_lds_limit()
 {
     static int limit = -1;
     if (limit < 0) {
-        // the kernel's static LDS (its key table) comes out of the same budget
+        // the kernels' static LDS (their key table) comes out of the same budget
         int dev = 0, bytes = 0;
-        hipFuncAttributes attr;
         limit = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
-            hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(block_build_kernel)) == hipSuccess &&
-            bytes > (int)attr.sharedSizeBytes) {
-            const int dyn = bytes - (int)attr.sharedSizeBytes;
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(block_build_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, dyn) == hipSuccess)
+            hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) {
+            int dyn = bytes;
+            bool good = true;
+            for (const void *f : {reinterpret_cast<const void *>(block_build_kernel<false>),
+                                  reinterpret_cast<const void *>(block_build_kernel<true>)}) {
+                hipFuncAttributes attr;
+                good = good && hipFuncGetAttributes(&attr, f) == hipSuccess && bytes > (int)attr.sharedSizeBytes;
+                if (good)
+                    dyn = std::min(dyn, bytes - (int)attr.sharedSizeBytes);
+            }
+            for (const void *f : {reinterpret_cast<const void *>(block_build_kernel<false>),
+                                  reinterpret_cast<const void *>(block_build_kernel<true>)})
+                good = good && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) == hipSuccess;
+            if (good)
                 limit = dyn;
         }
         (void)hipGetLastError();
@@ -469,6 +505,14 @@ void make_block_keys(const BlockPerm &B, uint4 *keys)
                 H < B.n_blocks ? pack_key(beta_key(B, H, B.key1[t], B.key2[t])) : make_uint4(0, 0, 0, 0);
 }
 
+uint64_t block_hops_entries(const BlockPerm &B) { return 3ull * B.n_blocks << B.l0; }
+
+hipError_t launch_block_hops(const BlockPerm &B, const uint4 *keys, uint16_t *hops, hipStream_t s)
+{
+    block_hops_kernel<<<(B.m + 255) / 256, 256, 0, s>>>(B, keys, hops);
+    return hipGetLastError();
+}
+
 hipError_t launch_bucket_map(const uint64_t *goff, uint32_t p_first, uint32_t n, uint32_t gb, uint32_t *bucket_map,
                              hipStream_t s)
 {
@@ -512,8 +556,8 @@ hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, c
 hipError_t launch_block_build(const uint32_t *bk, const uint32_t *bstart, const uint32_t *bucket_map,
                               uint32_t n_blocks, const uint64_t *goff, const uint32_t *sorted_items,
                               const uint32_t *r_sorted, const uint32_t *tids, const uint64_t *off, const BlockPerm &B,
-                              const uint4 *keys, uint32_t shift, uint32_t max_loop, uint32_t *arena,
-                              uint32_t *failed_bits,
+                              const uint4 *keys, const uint16_t *hops, uint32_t shift, uint32_t max_loop,
+                              uint32_t *arena, uint32_t *failed_bits,
                               uint32_t *failed, uint32_t *n_failed, uint32_t fail_cap, uint32_t *overflow,
                               hipStream_t s)
 {
@@ -525,9 +569,10 @@ hipError_t launch_block_build(const uint32_t *bk, const uint32_t *bstart, const 
     const size_t lds = block_lds_bytes(r0);
     // 3 r_0 / 256 wavefront steps of the encoding; about r_0 / 2 elements
     const int threads = r0 >= 32768 ? 1024 : (r0 >= 8192 ? 512 : 256);
-    block_build_kernel<<<n_blocks, threads, lds, s>>>(bk, bstart, bucket_map, goff, sorted_items, r_sorted, tids, off,
-                                                      B, keys, shift, max_loop, arena, failed_bits, failed, n_failed,
-                                                      fail_cap, overflow);
+    auto *kernel = hops ? block_build_kernel<true> : block_build_kernel<false>;
+    kernel<<<n_blocks, threads, lds, s>>>(bk, bstart, bucket_map, goff, sorted_items, r_sorted, tids, off, B, keys,
+                                          hops, shift, max_loop, arena, failed_bits, failed, n_failed, fail_cap,
+                                          overflow);
     return hipGetLastError();
 }
 

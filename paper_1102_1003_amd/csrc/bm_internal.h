@@ -571,15 +571,19 @@ hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, c
                                  const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
                                  const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *cursor,
                                  uint32_t *bk, hipStream_t s);
+// Where a copy goes when it is evicted: from (table, H, position) to its position
+// in the next table, block_hops_entries() of them.
+uint64_t block_hops_entries(const BlockPerm &B);
+hipError_t launch_block_hops(const BlockPerm &B, const uint4 *keys, uint16_t *hops, hipStream_t s);
 // One workgroup per block: 2-of-3 insertion (Sec. II-A) in LDS, failures,
 // indicators (Fig. 3) and the bit-sliced bytes of the block written to the
 // arena.  Failed elements go to failed[] as (item, x) with x the caller's
 // tid; *overflow is set when a block leaves more nestless elements than the
-// kernel holds (the caller then builds with the chain family).
+// kernel holds (the caller then builds with the chain family).  hops may be null.
 hipError_t launch_block_build(const uint32_t *bk, const uint32_t *bstart, const uint32_t *bucket_map,
                               uint32_t n_blocks, const uint64_t *goff, const uint32_t *sorted_items,
                               const uint32_t *r_sorted, const uint32_t *tids, const uint64_t *off, const BlockPerm &B,
-                              const uint4 *keys, uint32_t shift, uint32_t max_loop, uint32_t *arena, uint32_t *failed_bits,
+                              const uint4 *keys, const uint16_t *hops, uint32_t shift, uint32_t max_loop, uint32_t *arena, uint32_t *failed_bits,
                               uint32_t *failed, uint32_t *n_failed, uint32_t fail_cap, uint32_t *overflow,
                               hipStream_t s);
 // Largest r_0 whose blocks fit the device's LDS (0 if none).

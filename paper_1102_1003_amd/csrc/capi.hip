@@ -1076,6 +1076,12 @@ bm_status corr_finish(bm_index *idx, const uint32_t *failed_bits, const uint8_t 
     return BM_OK;
 }
 
+// Universes up to here build with the hops' table (6 m bytes).  Block build in us
+// without and with it (the table's kernel included): m = 10^4, n = 200: 77 and 50;
+// 30,011 x 613: 109 and 75; 50,000 x 2000 at 3 %: 131 and 101; 400,000 x 1500 at 2 %:
+// 316 and 253; 10^6 x 2000 Zipf: 552 and 546 (the table is past an XCD's L2).
+constexpr uint32_t kHopsMaxM = 1u << 19;
+
 // The block family's construction.  done: the maps are built (else the chain
 // family builds them); corr_done: the corrections are made too (queued right
 // behind the build and read back with its counters, one wait for both).
@@ -1126,6 +1132,11 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
     make_block_keys(idx->bperm, h_keys);
     BMC(upload_many(ctx, {{keys.p, h_keys, sizeof h_keys},
                           {chunks.p, h_chunks.data(), h_chunks.size() * sizeof(BucketChunk)}}));
+    DevBuf<uint16_t> hops;
+    if (idx->m <= kHopsMaxM) {
+        HIPC(ctx, hops.alloc(block_hops_entries(idx->bperm)));
+        HIPC(ctx, launch_block_hops(idx->bperm, keys.p, hops.p, s));
+    }
     HIPC(ctx, fill_u32(count.p, n_blocks + 1, 0, s));
     HIPC(ctx, launch_bucket_map(idx->goff.p, first, n, gb, bmap.p, s));
     HIPC(ctx, launch_bucket_count(chunks.p, (uint32_t)h_chunks.size(), idx->tids.p, idx->off.p, idx->sorted_items.p,
@@ -1149,7 +1160,7 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
             HIPC(ctx, hipEventRecord(ctx->fork, s));
         }
         HIPC(ctx, launch_block_build(bk.p, bstart.p, bmap.p, (uint32_t)n_blocks, idx->goff.p, idx->sorted_items.p,
-                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, keys.p, idx->shift, o->max_loop,
+                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, keys.p, hops.p, idx->shift, o->max_loop,
                                      idx->arena.p, failed_bits.p, idx->failed.p, counters.p, (uint32_t)fail_cap,
                                      counters.p + 1, s));
         // the corrections of the failures the build lists (it stops listing
