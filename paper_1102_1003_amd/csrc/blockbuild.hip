@@ -171,7 +171,8 @@ template <bool K24>
 __global__ void __launch_bounds__(kBucketThreads)
     bucket_scatter_kernel(const BucketChunk *chunks, const uint32_t *__restrict__ tids, const uint64_t *off,
                           const uint32_t *sorted_items, const uint32_t *r_sorted, const uint64_t *goff, uint32_t gb,
-                          BlockPerm B, uint32_t *cursor, uint32_t *__restrict__ bk)
+                          BlockPerm B, const uint32_t *__restrict__ bstart, uint32_t *cursor,
+                          uint32_t *__restrict__ bk)
 {
     __shared__ uint32_t hist[256], shift[256];  // shift: run position minus position in `vals`
     __shared__ uint32_t wsum[kBucketThreads / 64];
@@ -205,7 +206,8 @@ __global__ void __launch_bounds__(kBucketThreads)
 #pragma unroll
     for (uint32_t w = 0; w < kBucketThreads / 64; w++)
         first += w < wave ? wsum[w] : 0u;
-    shift[threadIdx.x] = (mine ? atomicAdd(&cursor[v.b0 + threadIdx.x], mine) : 0u) - first;
+    shift[threadIdx.x] =
+        (mine ? bstart[v.b0 + threadIdx.x] + atomicAdd(&cursor[v.b0 + threadIdx.x], mine) : 0u) - first;
     hist[threadIdx.x] = first;
     __syncthreads();
 #pragma unroll
@@ -539,17 +541,17 @@ hipError_t launch_bucket_count(const BucketChunk *chunks, uint32_t n_chunks, con
 
 hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, const uint32_t *tids,
                                  const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
-                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *cursor,
-                                 uint32_t *bk, hipStream_t s)
+                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, const uint32_t *bstart,
+                                 uint32_t *cursor, uint32_t *bk, hipStream_t s)
 {
     if (n_chunks == 0)
         return hipSuccess;
     if (B.sig.mask <= 0xFFFFFFu)
         bucket_scatter_kernel<true><<<n_chunks, kBucketThreads, 0, s>>>(chunks, tids, off, sorted_items, r_sorted,
-                                                                        goff, gb, B, cursor, bk);
+                                                                        goff, gb, B, bstart, cursor, bk);
     else
         bucket_scatter_kernel<false><<<n_chunks, kBucketThreads, 0, s>>>(chunks, tids, off, sorted_items, r_sorted,
-                                                                         goff, gb, B, cursor, bk);
+                                                                         goff, gb, B, bstart, cursor, bk);
     return hipGetLastError();
 }
 

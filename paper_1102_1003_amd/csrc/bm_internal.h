@@ -320,6 +320,16 @@ __host__ __device__ inline uint32_t block_pi(const BlockPerm &B, int t, uint32_t
 // ------------------------------------------------------------------ device
 // Host-side launchers.  All take a stream; none synchronises.
 hipError_t fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
+// Up to kMax pieces of 4-byte words copied by one launch (a copy command costs
+// the host and the stream about as much as a launch each).  Pinned host memory may
+// stand on either side.
+struct CopyPieces {
+    static constexpr int kMax = 4;
+    void *dst[kMax] = {};
+    const void *src[kMax] = {};
+    uint32_t words[kMax] = {};
+};
+hipError_t launch_copy_pieces(const CopyPieces &c, hipStream_t s);
 // *flag |= 1 when a[i] != b[i] for some i < n.
 hipError_t launch_words_differ(const uint32_t *a, const uint32_t *b, uint64_t n, uint32_t *flag, hipStream_t s);
 hipError_t fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s);
@@ -569,8 +579,8 @@ hipError_t launch_bucket_count(const BucketChunk *chunks, uint32_t n_chunks, con
 // the first position of block b's run and ends at the next block's.
 hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, const uint32_t *tids,
                                  const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
-                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *cursor,
-                                 uint32_t *bk, hipStream_t s);
+                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, const uint32_t *bstart,
+                                 uint32_t *cursor, uint32_t *bk, hipStream_t s);
 // Where a copy goes when it is evicted: from (table, H, position) to its position
 // in the next table, block_hops_entries() of them.
 uint64_t block_hops_entries(const BlockPerm &B);

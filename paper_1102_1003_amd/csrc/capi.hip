@@ -837,10 +837,14 @@ bm_status copy_in(bm_context *ctx, void *dst, const void *src, uint64_t bytes)
 struct ReadBack {
     void *dst;
     const void *src;
-    uint64_t bytes;
+    uint64_t bytes;  // a multiple of 4
 };
 
-bm_status read_back_many(bm_context *ctx, std::initializer_list<ReadBack> reads)
+// Up to here small pieces go to and from pinned memory by one kernel.
+constexpr uint64_t kPieceBytes = 64u << 10;
+
+// callers: a source is the caller's memory, which only copy commands touch.
+bm_status read_back_many(bm_context *ctx, std::initializer_list<ReadBack> reads, bool callers = false)
 {
     uint64_t total = 0;
     for (const ReadBack &r : reads)
@@ -858,10 +862,22 @@ bm_status read_back_many(bm_context *ctx, std::initializer_list<ReadBack> reads)
     }
     char *h = static_cast<char *>(ctx->h_rb);
     uint64_t at = 0;
-    for (const ReadBack &r : reads) {
-        if (r.bytes)
-            HIPC(ctx, hipMemcpyAsync(h + at, r.src, r.bytes, hipMemcpyDeviceToHost, ctx->stream));
-        at += (r.bytes + 15) / 16 * 16;
+    if (!callers && total <= kPieceBytes && reads.size() <= CopyPieces::kMax) {
+        CopyPieces c;
+        int k = 0;
+        for (const ReadBack &r : reads) {
+            c.dst[k] = h + at;
+            c.src[k] = r.src;
+            c.words[k++] = (uint32_t)(r.bytes / 4);
+            at += (r.bytes + 15) / 16 * 16;
+        }
+        HIPC(ctx, launch_copy_pieces(c, ctx->stream));
+    } else {
+        for (const ReadBack &r : reads) {
+            if (r.bytes)
+                HIPC(ctx, hipMemcpyAsync(h + at, r.src, r.bytes, hipMemcpyDeviceToHost, ctx->stream));
+            at += (r.bytes + 15) / 16 * 16;
+        }
     }
     HIPC(ctx, hipStreamSynchronize(ctx->stream));
     at = 0;
@@ -873,9 +889,9 @@ bm_status read_back_many(bm_context *ctx, std::initializer_list<ReadBack> reads)
     return BM_OK;
 }
 
-bm_status read_back(bm_context *ctx, void *dst, const void *src, uint64_t bytes)
+bm_status read_back(bm_context *ctx, void *dst, const void *src, uint64_t bytes, bool callers = false)
 {
-    return read_back_many(ctx, {{dst, src, bytes}});
+    return read_back_many(ctx, {{dst, src, bytes}}, callers);
 }
 
 // Chunks of host data through the context's pinned staging buffer; a chunk
@@ -924,7 +940,7 @@ bm_status upload(bm_context *ctx, void *dst, const void *src, uint64_t bytes, bo
 struct UploadPiece {
     void *dst;
     const void *src;
-    uint64_t bytes;
+    uint64_t bytes;  // a multiple of 4
 };
 
 bm_status upload_many(bm_context *ctx, std::initializer_list<UploadPiece> pieces)
@@ -954,13 +970,24 @@ bm_status upload_many(bm_context *ctx, std::initializer_list<UploadPiece> pieces
     }
     char *h = static_cast<char *>(ctx->h_stage);
     uint64_t at = 0;
+    const bool by_kernel = total <= kPieceBytes && pieces.size() <= CopyPieces::kMax;
+    CopyPieces c;
+    int k = 0;
     for (const UploadPiece &u : pieces) {
         if (u.bytes) {
             memcpy(h + at, u.src, u.bytes);
-            HIPC(ctx, hipMemcpyAsync(u.dst, h + at, u.bytes, hipMemcpyHostToDevice, ctx->stream));
+            if (by_kernel) {
+                c.dst[k] = u.dst;
+                c.src[k] = h + at;
+                c.words[k++] = (uint32_t)(u.bytes / 4);
+            } else {
+                HIPC(ctx, hipMemcpyAsync(u.dst, h + at, u.bytes, hipMemcpyHostToDevice, ctx->stream));
+            }
         }
         at += (u.bytes + 15) / 16 * 16;
     }
+    if (by_kernel)
+        HIPC(ctx, launch_copy_pieces(c, ctx->stream));
     HIPC(ctx, hipEventRecord(ctx->staged, ctx->stream));
     return BM_OK;
 }
@@ -1111,17 +1138,17 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
     Span span_construct(ctx, PH_CONSTRUCT);
     DevBuf<BucketChunk> chunks;
     DevBuf<uint4> keys;
-    DevBuf<uint32_t> count, bstart, cursor, bmap, bk, counters;
+    DevBuf<uint32_t> zeroed, bstart, bmap, bk;
     DevBuf<char> tmp;
     HIPC(ctx, chunks.alloc(std::max<size_t>(h_chunks.size(), 1)));
-    HIPC(ctx, count.alloc(n_blocks + 1));
+    // cleared by one fill: failures, the give-up flag, the corrections count
+    // (64-bit); elements per block (and the scan's last entry); elements placed per block
+    HIPC(ctx, zeroed.alloc(4 + 2 * (n_blocks + 1)));
+    uint32_t *const counters = zeroed.p, *const count = zeroed.p + 4, *const cursor = count + n_blocks + 1;
     HIPC(ctx, bstart.alloc(n_blocks + 1));
-    HIPC(ctx, cursor.alloc(n_blocks + 1));
     HIPC(ctx, bmap.alloc(n_blocks + 1));
     HIPC(ctx, bk.alloc(std::max<uint64_t>(idx->nnz, 1)));
-    // failures, the give-up flag, the corrections count (64-bit)
-    HIPC(ctx, counters.alloc(4));
-    unsigned long long *corr_cnt = reinterpret_cast<unsigned long long *>(counters.p + 2);
+    unsigned long long *corr_cnt = reinterpret_cast<unsigned long long *>(counters + 2);
     const bool corr_here = n > 1;
     const uint64_t corr_cap = corr_first_cap(std::max<uint64_t>(1u << 16, idx->nnz / 256));
     if (corr_here)
@@ -1137,19 +1164,19 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
         HIPC(ctx, hops.alloc(block_hops_entries(idx->bperm)));
         HIPC(ctx, launch_block_hops(idx->bperm, keys.p, hops.p, s));
     }
-    HIPC(ctx, fill_u32(count.p, n_blocks + 1, 0, s));
+    HIPC(ctx, fill_u32(zeroed.p, 4 + 2 * (n_blocks + 1), 0, s));
     HIPC(ctx, launch_bucket_map(idx->goff.p, first, n, gb, bmap.p, s));
     HIPC(ctx, launch_bucket_count(chunks.p, (uint32_t)h_chunks.size(), idx->tids.p, idx->off.p, idx->sorted_items.p,
-                                  idx->r_sorted.p, idx->goff.p, gb, idx->bperm, count.p, s));
-    HIPC(ctx, exclusive_scan_u32(count.p, bstart.p, n_blocks + 1, tmp.p, s));
-    HIPC(ctx, hipMemcpyAsync(cursor.p, bstart.p, (n_blocks + 1) * 4, hipMemcpyDeviceToDevice, s));
+                                  idx->r_sorted.p, idx->goff.p, gb, idx->bperm, count, s));
+    HIPC(ctx, exclusive_scan_u32(count, bstart.p, n_blocks + 1, tmp.p, s));
     HIPC(ctx, launch_bucket_scatter(chunks.p, (uint32_t)h_chunks.size(), idx->tids.p, idx->off.p,
-                                    idx->sorted_items.p, idx->r_sorted.p, idx->goff.p, gb, idx->bperm, cursor.p, bk.p,
-                                    s));
+                                    idx->sorted_items.p, idx->r_sorted.p, idx->goff.p, gb, idx->bperm, bstart.p, cursor,
+                                    bk.p, s));
     uint64_t fail_cap = std::max<uint64_t>(1u << 16, idx->nnz / 64);
     for (int attempt = 0;; attempt++) {
         HIPC(ctx, idx->failed.alloc(2 * fail_cap));
-        HIPC(ctx, fill_u32(counters.p, 4, 0, s));
+        if (attempt > 0)
+            HIPC(ctx, fill_u32(counters, 4, 0, s));
         // the all-pairs plan (made on the host while the kernels run) is
         // uploaded on a side stream beside the build: after everything queued
         // before it (its buffer comes from this stream's pool), and before
@@ -1160,13 +1187,13 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
             HIPC(ctx, hipEventRecord(ctx->fork, s));
         }
         HIPC(ctx, launch_block_build(bk.p, bstart.p, bmap.p, (uint32_t)n_blocks, idx->goff.p, idx->sorted_items.p,
-                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, keys.p, hops.p, idx->shift, o->max_loop,
-                                     idx->arena.p, failed_bits.p, idx->failed.p, counters.p, (uint32_t)fail_cap,
-                                     counters.p + 1, s));
+                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, keys.p, hops.p, idx->shift,
+                                     o->max_loop, idx->arena.p, failed_bits.p, idx->failed.p, counters,
+                                     (uint32_t)fail_cap, counters + 1, s));
         // the corrections of the failures the build lists (it stops listing
         // at fail_cap; past that the attempt is repeated anyway)
         if (corr_here)
-            HIPC(ctx, launch_corrections(idx->failed.p, (uint32_t)fail_cap, counters.p, idx->off.p, idx->tids.p,
+            HIPC(ctx, launch_corrections(idx->failed.p, (uint32_t)fail_cap, counters, idx->off.p, idx->tids.p,
                                          failed_bits.p, has_map, n, idx->corr.p, corr_cap, corr_cnt, s));
         if (plan_here) {
             HIPC(ctx, hipStreamWaitEvent(ctx->side[0], ctx->fork, 0));
@@ -1177,7 +1204,7 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
             HIPC(ctx, hipStreamWaitEvent(s, ctx->join[0], 0));
         }
         uint32_t h[4] = {0, 0, 0, 0};
-        BMC(read_back(ctx, h, counters.p, 16));
+        BMC(read_back(ctx, h, counters, 16));
         if (h[1]) {
             HIPC(ctx, fill_u32(failed_bits.p, fb_words + 1, 0, s));
             return BM_OK;
@@ -1199,9 +1226,9 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
 
 // Transactions to tidlists through the index's bit rows (launch_txn_bits),
 // when that is expected to beat the radix sort; `taken` says whether it was.
-// The rows stay in the index.  row_off is in device memory.
+// The rows stay in the index.  row_off is in device memory; flag: a cleared word there.
 bm_status ingest_by_bits(bm_index *idx, const uint64_t *row_off, const uint32_t *items, bool dev_items, uint64_t nnz,
-                         bool &taken)
+                         uint32_t *flag, bool &taken)
 {
     taken = false;
     bm_context *ctx = idx->ctx;
@@ -1219,25 +1246,24 @@ bm_status ingest_by_bits(bm_index *idx, const uint64_t *row_off, const uint32_t 
         words * 4 > ctx->mem_bytes / 16 || !bit_ingest_fits(m, n, ctx->lds_bytes, (uint32_t)ctx->n_cu))
         return BM_OK;
     const uint64_t segs = bit_ingest_segments(m, n);
-    DevBuf<uint32_t> bits, in, count, tids;  // count: [ones per (item, segment) | 0 | flag]
+    DevBuf<uint32_t> bits, in, count, tids;  // count: [ones per (item, segment) | 0]
     DevBuf<uint64_t> start;
     DevBuf<char> tmp;
-    if (bits.alloc(words) != hipSuccess || tids.alloc(nnz) != hipSuccess || count.alloc(segs + 2) != hipSuccess ||
+    if (bits.alloc(words) != hipSuccess || tids.alloc(nnz) != hipSuccess || count.alloc(segs + 1) != hipSuccess ||
         start.alloc(segs + 1) != hipSuccess || tmp.alloc(scan_tmp_bytes(segs + 1)) != hipSuccess ||
         (!dev_items && in.alloc(nnz) != hipSuccess))
         return BM_OK;
     if (!dev_items)
         BMC(copy_in(ctx, in.p, items, nnz * 4));
     HIPC(ctx, idx->off.alloc((uint64_t)n + 1));
-    HIPC(ctx, fill_u32(count.p + segs, 2, 0, s));
     HIPC(ctx, launch_txn_bits(row_off, dev_items ? items : in.p, m, n, ctx->lds_bytes, (uint32_t)ctx->n_cu, bits.p,
-                              count.p + segs + 1, s));
+                              flag, s));
     HIPC(ctx, launch_bit_count(bits.p, m, n, count.p, s));
     HIPC(ctx, exclusive_scan_u32_to_u64(count.p, start.p, segs + 1, tmp.p, s));
     HIPC(ctx, launch_bit_expand(bits.p, m, n, start.p, idx->off.p, tids.p, s));
     uint32_t bad = 0;
     idx->h_off.resize((size_t)n + 1);
-    BMC(read_back_many(ctx, {{&bad, count.p + segs + 1, 4}, {idx->h_off.data(), idx->off.p, ((uint64_t)n + 1) * 8}}));
+    BMC(read_back_many(ctx, {{&bad, flag, 4}, {idx->h_off.data(), idx->off.p, ((uint64_t)n + 1) * 8}}));
     if (bad)
         return fail(ctx, BM_ERANGE, "an item id is >= n_items");
     idx->nnz = idx->h_off[n];
@@ -2346,7 +2372,7 @@ bm_status bm_index_build_sets(bm_context *ctx, uint32_t m, uint32_t n_sets, cons
 
     idx->h_off.resize((size_t)n_sets + 1);
     if (ptr_kind(offsets) == PTR_DEVICE) {
-        st = read_back(ctx, idx->h_off.data(), offsets, ((uint64_t)n_sets + 1) * 8);
+        st = read_back(ctx, idx->h_off.data(), offsets, ((uint64_t)n_sets + 1) * 8, true);
         if (st != BM_OK)
             return st;
     } else {
@@ -2429,13 +2455,13 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
     const bool dev_off = ptr_kind(offsets) == PTR_DEVICE;
     uint64_t nnz_in = 0;
     std::vector<uint64_t> roff;
+    DevBuf<uint32_t> flags;  // bad offsets; items out of range
+    HIPC(ctx, flags.alloc(2));
+    HIPC(ctx, fill_u32(flags.p, 2, 0, s));
     if (dev_off) {
-        DevBuf<uint32_t> oflag;
-        HIPC(ctx, oflag.alloc(1));
-        HIPC(ctx, fill_u32(oflag.p, 1, 0, s));
-        HIPC(ctx, launch_check_offsets(offsets, m_txn, oflag.p, s));
+        HIPC(ctx, launch_check_offsets(offsets, m_txn, flags.p, s));
         uint32_t hflag = 0;
-        st = read_back_many(ctx, {{&nnz_in, offsets + m_txn, 8}, {&hflag, oflag.p, 4}});
+        st = read_back_many(ctx, {{&nnz_in, offsets + m_txn, 8}, {&hflag, flags.p, 4}});
         if (st != BM_OK)
             return st;
         if (hflag & 2u)
@@ -2469,7 +2495,7 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
     }
     const bool dev_items = ptr_kind(items) == PTR_DEVICE;
     bool by_bits = false;
-    BMC(ingest_by_bits(idx.get(), row_off, items, dev_items, nnz_in, by_bits));
+    BMC(ingest_by_bits(idx.get(), row_off, items, dev_items, nnz_in, flags.p + 1, by_bits));
     if (by_bits) {
         span_ingest.end();
         BMC(build_common(idx.get(), &o));
@@ -2673,7 +2699,6 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
     HIPC(ctx, idx->thr_off.ensure((uint64_t)nb + 1));
     HIPC(ctx, idx->scan_tmp.ensure(scan_tmp_bytes((uint64_t)nb + 1)));
     Span span_thr(ctx, PH_THRESHOLD);
-    HIPC(ctx, fill_u32(idx->thr_counts.p + nb, 1, 0, s));
     HIPC(ctx, launch_threshold_count(idx->pairbuf.p, np, min_support, idx->thr_counts.p, nb, s));
     HIPC(ctx, exclusive_scan_u32_to_u64(idx->thr_counts.p, idx->thr_off.p, (uint64_t)nb + 1, idx->scan_tmp.p, s));
     // a device buffer is written before the total comes back (the kernel
@@ -2793,7 +2818,6 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
         BMC(run_compare(ctx, work, own ? idx->work_ranges : ranges, whole_desc(idx, counts)));
         HIPC(ctx, launch_apply_corrections(idx->corr.p, idx->n_corr, counts, idx->n, s));
     }
-    HIPC(ctx, fill_u32(thr_counts + nb, 1, 0, s));
     HIPC(ctx, launch_threshold_count(counts, np, min_support, thr_counts, nb, s));
     HIPC(ctx, exclusive_scan_u32_to_u64(thr_counts, thr_off, (uint64_t)nb + 1, sc + o_tmp, s));
     if (out)
@@ -2911,7 +2935,7 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
     std::vector<uint32_t> q(k);
     bm_status st;
     if (ptr_kind(items) == PTR_DEVICE) {
-        st = read_back(ctx, q.data(), items, (uint64_t)k * 4);
+        st = read_back(ctx, q.data(), items, (uint64_t)k * 4, true);
         if (st != BM_OK)
             return st;
     } else {
@@ -3598,7 +3622,6 @@ bm_status bm_cross_pairs(bm_index *a, bm_index *b, uint32_t min_support, bm_pair
     HIPC(ctx, offs.alloc((uint64_t)nbk + 1));
     HIPC(ctx, tmp.alloc(scan_tmp_bytes((uint64_t)nbk + 1)));
     Span span_thr(ctx, PH_THRESHOLD);
-    HIPC(ctx, fill_u32(counts.p + nbk, 1, 0, s));
     HIPC(ctx, launch_threshold_count(a->x_out.p, cells, min_support, counts.p, nbk, s));
     HIPC(ctx, exclusive_scan_u32_to_u64(counts.p, offs.p, (uint64_t)nbk + 1, tmp.p, s));
     const bool host = out && ptr_kind(out) == PTR_HOST;

@@ -155,6 +155,8 @@ __global__ void threshold_count_kernel(const uint32_t *sup, uint64_t n_pairs, ui
     block_excl_scan_u32(c, &total);
     if (threadIdx.x == 0)
         block_counts[blockIdx.x] = total;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        block_counts[gridDim.x] = 0;  // where the scan leaves the sum
 }
 
 // Row of packed index k in an n-item upper triangle.

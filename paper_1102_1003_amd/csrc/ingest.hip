@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(kTxnBitsThreads)
     }
 }
 
-// Ones of every (row, segment of kSegWords words).
+// Ones of every (row, segment of kSegWords words), and a 0 behind them.
 constexpr uint32_t kSegWords = 1024;
 
 __global__ void __launch_bounds__(256) bit_count_kernel(const uint32_t *__restrict__ bits, uint64_t ld,
@@ -315,6 +315,8 @@ __global__ void __launch_bounds__(256) bit_count_kernel(const uint32_t *__restri
     __syncthreads();
     if (threadIdx.x == 0)
         count[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        count[gridDim.x] = 0;  // where the scan leaves the sum
 }
 
 // The tids of one (row, segment), in order, at tids[start[row n_seg + seg] ..).

@@ -1,5 +1,7 @@
 // Generic device primitives: fills, exclusive scans, stable LSD radix sort.
 // Wave64 throughout (gfx950).
+#include <algorithm>
+
 #include "bm_internal.h"
 
 namespace bm {
@@ -19,13 +21,26 @@ __global__ void fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v)
         p[i] = v;
 }
 
-__global__ void fill_u32x4_kernel(uint4 *p, uint64_t n4, uint32_t v)
+__global__ void fill_u32x4_kernel(uint32_t *p, uint64_t n, uint32_t v)
 {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint4 w = make_uint4(v, v, v, v);
+    const uint64_t n4 = n / 4;
+    if (i < n % 4)
+        p[n4 * 4 + i] = v;
     for (; i < n4; i += stride)
-        p[i] = w;
+        reinterpret_cast<uint4 *>(p)[i] = w;
+}
+
+// Small pieces between device memory and pinned host memory, all in one launch.
+__global__ void copy_pieces_kernel(CopyPieces c)
+{
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+#pragma unroll
+    for (int k = 0; k < CopyPieces::kMax; k++)
+        for (uint32_t i = i0; i < c.words[k]; i += stride)
+            static_cast<uint32_t *>(c.dst[k])[i] = static_cast<const uint32_t *>(c.src[k])[i];
 }
 
 __global__ void words_differ_kernel(const uint32_t *a, const uint32_t *b, uint64_t n, uint32_t *flag)
@@ -326,13 +341,21 @@ hipError_t fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s)
         return hipSuccess;
     // large 16-byte aligned fills store 16 bytes per lane
     if (n >= 4096 && (reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
-        const uint64_t n4 = n / 4;
-        fill_u32x4_kernel<<<grid_for(n4), kBlock, 0, s>>>(reinterpret_cast<uint4 *>(p), n4, v);
-        if (n % 4)
-            fill_u32_kernel<<<1, kBlock, 0, s>>>(p + n4 * 4, n % 4, v);
+        fill_u32x4_kernel<<<grid_for(n / 4), kBlock, 0, s>>>(p, n, v);
         return hipGetLastError();
     }
     fill_u32_kernel<<<grid_for(n), kBlock, 0, s>>>(p, n, v);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_pieces(const CopyPieces &c, hipStream_t s)
+{
+    uint32_t most = 0;
+    for (uint32_t w : c.words)
+        most = std::max(most, w);
+    if (most == 0)
+        return hipSuccess;
+    copy_pieces_kernel<<<std::min<uint32_t>((most + kBlock - 1) / kBlock, 64), kBlock, 0, s>>>(c);
     return hipGetLastError();
 }
 
