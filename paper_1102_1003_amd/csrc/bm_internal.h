@@ -330,6 +330,13 @@ struct CopyPieces {
     uint32_t words[kMax] = {};
 };
 hipError_t launch_copy_pieces(const CopyPieces &c, hipStream_t s);
+// Any number of pieces, listed in device memory (16-byte aligned; most: the largest one's words).
+struct CopyPiece {
+    void *dst;
+    const void *src;
+    uint64_t words;
+};
+hipError_t launch_copy_list(const CopyPiece *pieces, uint32_t n, uint64_t most, hipStream_t s);
 // *flag |= 1 when a[i] != b[i] for some i < n.
 hipError_t launch_words_differ(const uint32_t *a, const uint32_t *b, uint64_t n, uint32_t *flag, hipStream_t s);
 hipError_t fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s);
@@ -524,6 +531,29 @@ struct BitMat {
 // positions; else rows of n_out.  Every count is written (none is read).
 hipError_t launch_gram(const GramPlan &p, const BitMat &a, const BitMat &b, uint32_t *out, uint64_t n_out, float *ws,
                        hipStream_t s);
+
+// What the Gram kernels take; a job is one family's part of a launch over several.
+struct GramArgs {
+    BitMat a, b;
+    uint32_t TR, TC, S, W;  // tile rows and columns, stages per tile, workgroups
+    uint64_t U;             // stages in all: tiles * S
+    uint32_t tri;
+    uint32_t *out;
+    uint64_t n_out;
+    float *ws;
+};
+struct GramJob {
+    GramArgs g;
+    uint32_t tile, fold;  // fold: threads that share the parts of a count
+    uint32_t w0, r0;      // the job's first workgroup in the two launches
+};
+struct GramJobs {
+    uint32_t n = 0, groups = 0, reduce_blocks = 0;
+};
+// Fills jobs (host, room for set.plan.size()) with the joint families of `set`, a[q] counted into out[q];
+// launch_gram_jobs takes them from device memory.
+GramJobs gram_jobs(const GramSetPlan &set, const BitMat *a, uint32_t *const *out, float *ws, GramJob *jobs);
+hipError_t launch_gram_jobs(const GramJob *jobs, const GramJobs &j, hipStream_t s);
 
 }  // namespace bm
 

@@ -887,4 +887,67 @@ GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint3
     return best;
 }
 
+// One launch holds every family's tiles, of 64 or 128 counts whichever takes a
+// family less time: a small family alone is mostly the two launches' 10 us and a
+// chip that fills and drains, and several launches side by side share the
+// compute units unevenly (see bit_gram_jobs_kernel).  Every workgroup takes about the same
+// time, the total over three workgroups a CU; families that 256-wide tiles count
+// in over 1 ms go alone (2^20 x 4096: 2.46 ms against 2.73; 10^6 x 2000: 653 us
+// against 668, less than the launch and the larger parts cost).
+GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, int pinned)
+{
+    GramSetPlan set;
+    double total = 0;  // us of one CU
+    std::vector<double> stage_us(shapes.size(), 0);
+    for (size_t q = 0; q < shapes.size(); q++) {
+        const GramShape &f = shapes[q];
+        GramPlan p = plan_gram(f.n, f.n, true, f.row_words, n_cu, pinned);
+        const bool alone = p.tile == 256 && (p.us > 1000 || pinned);
+        if (!alone) {
+            auto cost = [&](uint64_t t, double us) { return (f.n + t - 1) / t * ((f.n + t - 1) / t + 1) / 2 * us; };
+            p.tile = pinned ? pinned : cost(128, 0.62) <= cost(64, 0.27) ? 128 : 64;
+            p.tile_rows = p.tile_cols = (f.n + p.tile - 1) / p.tile;
+            p.tiles = (uint32_t)((uint64_t)p.tile_rows * (p.tile_rows + 1) / 2);
+            stage_us[q] = p.tile == 128 ? 0.62 : 0.27;
+            total += (double)p.tiles * p.stages * stage_us[q];
+        } else {
+            set.ws_floats = std::max(set.ws_floats, p.ws_floats);
+        }
+        set.plan.push_back(p);
+        set.joint.push_back(!alone);
+    }
+    // the shortest run that needs no more than three workgroups a CU
+    double run = total / (3.0 * n_cu);
+    for (int round = 0;; round++, run *= 1.03) {
+        uint64_t groups = 0;
+        bool least = true;
+        for (size_t q = 0; q < shapes.size(); q++) {
+            if (!set.joint[q])
+                continue;
+            GramPlan &p = set.plan[q];
+            const uint64_t U = (uint64_t)p.tiles * p.stages;
+            const uint64_t stages = std::max<uint64_t>((uint64_t)(run / stage_us[q]), p.tile == 64 ? 8 : 4);
+            const uint64_t floor = std::max<uint64_t>((U + kGramMaxStages - 1) / kGramMaxStages, 1);
+            p.groups = (uint32_t)std::max((U + stages - 1) / stages, floor);
+            least = least && p.groups == floor;
+            groups += p.groups;
+        }
+        set.groups = (uint32_t)groups;
+        if (groups <= 3ull * n_cu || least || round == 400)
+            break;
+    }
+    uint64_t ws = 0;
+    for (size_t q = 0; q < shapes.size(); q++) {
+        if (!set.joint[q])
+            continue;
+        GramPlan &p = set.plan[q];
+        const uint64_t U = (uint64_t)p.tiles * p.stages;
+        const bool split = p.groups && (U % p.groups != 0 || (U / p.groups) % p.stages != 0);
+        p.ws_floats = split ? 2ull * p.groups * p.tile * p.tile : 0;
+        ws += p.ws_floats;
+    }
+    set.ws_floats = std::max(set.ws_floats, ws);
+    return set;
+}
+
 }  // namespace bm

@@ -204,4 +204,17 @@ struct GramPlan {
 GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0,
                    uint64_t max_ws = UINT64_MAX);
 
+// The pairs of several families, counted by one launch where that pays.
+struct GramShape {
+    uint32_t n;
+    uint64_t row_words;
+};
+struct GramSetPlan {
+    std::vector<GramPlan> plan;  // per family
+    std::vector<char> joint;     // its tiles run in the joint launch (64 or 128 wide)
+    uint32_t groups = 0;         // workgroups of the joint launch
+    uint64_t ws_floats = 0;      // scratch: the joint launch's, or the largest single one's
+};
+GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, int pinned = 0);
+
 }  // namespace bm

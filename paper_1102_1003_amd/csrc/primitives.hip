@@ -43,6 +43,16 @@ __global__ void copy_pieces_kernel(CopyPieces c)
             static_cast<uint32_t *>(c.dst[k])[i] = static_cast<const uint32_t *>(c.src[k])[i];
 }
 
+__global__ void copy_list_kernel(const CopyPiece *pieces)
+{
+    const CopyPiece c = pieces[blockIdx.y];
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = i0; i < c.words / 4; i += stride)
+        static_cast<uint4 *>(c.dst)[i] = static_cast<const uint4 *>(c.src)[i];
+    if (i0 < c.words % 4)
+        static_cast<uint32_t *>(c.dst)[c.words / 4 * 4 + i0] = static_cast<const uint32_t *>(c.src)[c.words / 4 * 4 + i0];
+}
+
 __global__ void words_differ_kernel(const uint32_t *a, const uint32_t *b, uint64_t n, uint32_t *flag)
 {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
@@ -356,6 +366,17 @@ hipError_t launch_copy_pieces(const CopyPieces &c, hipStream_t s)
     if (most == 0)
         return hipSuccess;
     copy_pieces_kernel<<<std::min<uint32_t>((most + kBlock - 1) / kBlock, 64), kBlock, 0, s>>>(c);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_list(const CopyPiece *pieces, uint32_t n, uint64_t most, hipStream_t s)
+{
+    if (n == 0 || most == 0)
+        return hipSuccess;
+    if (n > 65535)
+        return hipErrorInvalidValue;
+    const uint64_t blocks = (most / 4 + kBlock) / kBlock;
+    copy_list_kernel<<<dim3((uint32_t)std::min<uint64_t>(blocks, 64), n), kBlock, 0, s>>>(pieces);
     return hipGetLastError();
 }
 

@@ -2,16 +2,16 @@
 #include <cstdint>
 #include <cstdio>
 #include <set>
+#include <vector>
 
 #include "../paper_1102_1003_amd/csrc/plan.h"
 
 // Walks every group's run as the Gram kernel does: 0, or a message.  Each
 // (tile, stage) is visited once, no run part passes the fp32 bound, each shared
 // part has a place of its own inside ws, and gram_reduce_kernel's rule finds it.
-extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned, uint64_t max_ws,
-                          char *msg, uint32_t len)
+static int check_plan(const bm::GramPlan &p, uint32_t na, uint32_t nb, uint32_t m, uint64_t max_ws, char *msg,
+                      uint32_t len)
 {
-    const bm::GramPlan p = bm::plan_gram(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned, max_ws);
     const uint64_t U = (uint64_t)p.tiles * p.stages, W = p.groups;
     auto bad = [&](const char *what) {
         snprintf(msg, len, "%s: tile %d tiles %u stages %u groups %u", what, p.tile, p.tiles, p.stages, p.groups);
@@ -50,4 +50,53 @@ extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_
         seen = u1;
     }
     return seen == U ? 0 : bad("stages left out");
+}
+
+extern "C" int gram_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned, uint64_t max_ws,
+                          char *msg, uint32_t len)
+{
+    const bm::GramPlan p = bm::plan_gram(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned, max_ws);
+    return check_plan(p, na, nb, m, max_ws, msg, len);
+}
+
+// The families of a joint launch: each cut as above, the scratch enough for all
+// of them, the workgroups no more than three a compute unit unless every family
+// is down to the fewest it can have.
+extern "C" int gram_set_check(const uint32_t *n, const uint32_t *m, uint32_t count, uint32_t n_cu, int pinned,
+                              uint32_t *joint, uint32_t *groups, char *msg, uint32_t len)
+{
+    std::vector<bm::GramShape> shapes;
+    for (uint32_t q = 0; q < count; q++)
+        shapes.push_back({n[q], bm::bit_row_words(m[q])});
+    const bm::GramSetPlan set = bm::plan_gram_set(shapes, n_cu, pinned);
+    uint64_t ws = 0, w = 0;
+    bool least = true;
+    *joint = 0;
+    for (uint32_t q = 0; q < count; q++) {
+        const bm::GramPlan &p = set.plan[q];
+        if (check_plan(p, n[q], n[q], m[q], UINT64_MAX, msg, len))
+            return 1;
+        if (!set.joint[q]) {
+            if (p.ws_floats > set.ws_floats) {
+                snprintf(msg, len, "a single family's scratch");
+                return 1;
+            }
+            continue;
+        }
+        ++*joint;
+        ws += p.ws_floats;
+        w += p.groups;
+        least = least && ((uint64_t)p.groups - 1) * bm::kGramMaxStages < (uint64_t)p.tiles * p.stages;
+        if (p.tile != 64 && p.tile != 128) {
+            snprintf(msg, len, "a joint tile of %d", p.tile);
+            return 1;
+        }
+    }
+    *groups = set.groups;
+    if (ws > set.ws_floats || w != set.groups || (w > 3ull * n_cu && !least)) {
+        snprintf(msg, len, "%llu groups, %llu floats of %llu", (unsigned long long)w, (unsigned long long)ws,
+                 (unsigned long long)set.ws_floats);
+        return 1;
+    }
+    return 0;
 }

@@ -175,6 +175,24 @@ def test_batch_either_route(ctx, monkeypatch, route):
     batch.close()
 
 
+@pytest.mark.parametrize("tile", ["64", "128", "256"])
+def test_joint_launch_tiles(ctx, monkeypatch, tile):
+    """Families around tile edges in one launch (256: one launch each)."""
+    monkeypatch.setenv("BM_BITMAP_ROUTE", "1")
+    monkeypatch.setenv("BM_GRAM_TILE", tile)
+    shapes = [(511, 2), (70_000, 64), (513, 65), (30_000, 128), (10_000, 257), (1, 3), (40_000, 129)]
+    sets = [datagen.bernoulli_sets(m, n, 0.3, seed=50 + q) for q, (m, n) in enumerate(shapes)]
+    idx = [bm.Index.from_sets(ctx, m, *s) for (m, n), s in zip(shapes, sets)]
+    outs = [torch.full((bm.n_pairs(n),), -1, dtype=torch.int32, device="cuda:0") for m, n in shapes]
+    torch.cuda.synchronize()
+    batch = bm.Batch(ctx, idx, outs)
+    batch.run()
+    ctx.synchronize()
+    batch.close()
+    for shape, s, o in zip(shapes, sets, outs):
+        assert np.array_equal(o.cpu().numpy().view(np.uint32), oracle.all_pairs(*s)), shape
+
+
 @pytest.mark.parametrize("route", ["0", "1", None])
 @pytest.mark.parametrize("prune", [0, 600])
 def test_server_either_route(ctx, monkeypatch, route, prune):

@@ -21,6 +21,7 @@ def check(tmp_path_factory):
         msg = ctypes.create_string_buffer(256)
         assert lib.gram_check(na, nb, int(tri), ctypes.c_uint32(m), n_cu, pinned, ctypes.c_uint64(max_ws), msg,
                               256) == 0, msg.value.decode()
+    run.lib = lib
     return run
 
 
@@ -34,3 +35,17 @@ def test_cut(check, m, pinned):
     check(300, 1, False, m, n_cu=8, pinned=pinned)
     for max_ws in (0, 10_000, 200_000, 9_000_000):          # less scratch than the full cut takes
         check(200, 200, True, m, pinned=pinned, max_ws=max_ws)
+
+
+@pytest.mark.parametrize("pinned", [0, 64, 128, 256])
+def test_set(check, pinned):
+    """Families of a joint launch: one, many small, small beside large, more than workgroups."""
+    for fam in ([(2, 1)], [(64, 1000), (65, 513), (700, 100_000)], [(3000, 400_000), (16, 16)],
+                [(4096, 2**20), (100, 100_000), (2, 2**32 - 1)], [(20, 5000)] * 1000):
+        n = (ctypes.c_uint32 * len(fam))(*[f[0] for f in fam])
+        m = (ctypes.c_uint32 * len(fam))(*[f[1] for f in fam])
+        joint, groups, msg = ctypes.c_uint32(), ctypes.c_uint32(), ctypes.create_string_buffer(256)
+        assert check.lib.gram_set_check(n, m, len(fam), 256, pinned, ctypes.byref(joint), ctypes.byref(groups), msg,
+                                        256) == 0, (fam[:4], msg.value.decode())
+        # a family alone needs the 256-wide tiles' better rate over a millisecond
+        assert joint.value == (0 if pinned == 256 else len(fam) - (pinned == 0 and (4096, 2**20) in fam))
