@@ -103,15 +103,38 @@ __device__ inline int64_t find_sorted(const uint32_t *a, uint64_t n, uint32_t x)
     return (lo < n && a[lo] == x) ? (int64_t)lo : -1;
 }
 
-__global__ void bucket_map_kernel(const uint64_t *goff, uint32_t p_first, uint32_t n, uint32_t gb,
-                                  uint32_t *bucket_map)
+// What the build's other kernels start from, in one launch (five took 10 us of
+// a build's 90 at m = 10^4, n = 200, each over in 2 us): see BlockPrep.  The last
+// threads of the grid take the maps, the first ones the first hops.
+__global__ void block_prep_kernel(BlockPrep a, BlockPerm B)
 {
-    const uint32_t p = p_first + blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n)
-        return;
-    const uint64_t b0 = goff[p] / gb, b1 = goff[p + 1] / gb;
-    for (uint64_t b = b0; b < b1; b++)
-        bucket_map[b] = p;
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t w = i0; w < a.failed_words; w += nt)
+        a.failed_bits[w] = 0;
+    for (uint64_t w = i0; w < a.zeroed_words; w += nt)
+        a.zeroed[w] = 0;
+    for (uint64_t p = nt - 1 - i0; p < a.n; p += nt) {
+        const uint32_t item = a.sorted_items[p];
+        const bool built = p >= a.first;
+        a.sorted_pos[item] = built ? (int32_t)p : -1;
+        a.has_map[item] = built;
+        if (built && a.bucket_map) {
+            const uint64_t b1 = a.goff[p + 1] / a.gb;
+            for (uint64_t b = a.goff[p] / a.gb; b < b1; b++)
+                a.bucket_map[b] = (uint32_t)p;
+        }
+    }
+    // hops[(t n_blocks + H) r_0 + beta_{t,H}(a)] = beta_{t+1,H}(a)
+    for (uint64_t x = a.hops ? i0 : B.m; x < B.m; x += nt) {  // H r_0 + a
+        const uint32_t H = (uint32_t)x >> B.l0, len = block_len(B, H);
+        uint32_t pos[3];
+#pragma unroll
+        for (uint32_t t = 0; t < 3; t++)
+            pos[t] = beta_fwd(B, unpack_key(a.keys[t * kMaxBlocksH + H]), (uint32_t)x & B.mask, len);
+#pragma unroll
+        for (uint32_t t = 0; t < 3; t++)
+            a.hops[((t * B.n_blocks + H) << B.l0) + pos[t]] = (uint16_t)pos[t == 2 ? 0 : t + 1];
+    }
 }
 
 // The chunk's elements, relabelled, and their blocks within the map.
@@ -167,18 +190,23 @@ __global__ void __launch_bounds__(kBucketThreads)
 // and the values leave in that order, neighbouring lanes to neighbouring words
 // (large Zipf 100 us; written straight from the tidlist's order, a wavefront's 64
 // stores went to as many lines: 160).
-template <bool K24>
+//
+// kWhole: every map is one chunk (its elements from ebase[p] on), so the chunk's own
+// counts are the runs: nothing is counted or scanned before, and the blocks' starts
+// and maps are written here (30,011 x 613: 6 us, against 22 for the five launches).
+template <bool K24, bool kWhole>
 __global__ void __launch_bounds__(kBucketThreads)
-    bucket_scatter_kernel(const BucketChunk *chunks, const uint32_t *__restrict__ tids, const uint64_t *off,
-                          const uint32_t *sorted_items, const uint32_t *r_sorted, const uint64_t *goff, uint32_t gb,
-                          BlockPerm B, const uint32_t *__restrict__ bstart, uint32_t *cursor,
-                          uint32_t *__restrict__ bk)
+    bucket_scatter_kernel(const BucketChunk *chunks, const uint32_t *ebase, uint32_t p_first,
+                          const uint32_t *__restrict__ tids, const uint64_t *off, const uint32_t *sorted_items,
+                          const uint32_t *r_sorted, const uint64_t *goff, uint32_t gb, BlockPerm B, uint32_t *bstart,
+                          uint32_t *cursor, uint32_t *bucket_map, uint32_t *__restrict__ bk)
 {
     __shared__ uint32_t hist[256], shift[256];  // shift: run position minus position in `vals`
     __shared__ uint32_t wsum[kBucketThreads / 64];
     __shared__ uint32_t vals[kBucketChunk];
     static_assert(kBucketThreads == 256, "one thread per block of a map");
-    const ChunkView v = chunk_view(chunks[blockIdx.x], tids, off, sorted_items, r_sorted, goff, gb, B.l0);
+    const BucketChunk c = kWhole ? BucketChunk{p_first + blockIdx.x, 0} : chunks[blockIdx.x];
+    const ChunkView v = chunk_view(c, tids, off, sorted_items, r_sorted, goff, gb, B.l0);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x / 64u;
     hist[threadIdx.x] = 0;
     __syncthreads();
@@ -206,8 +234,19 @@ __global__ void __launch_bounds__(kBucketThreads)
 #pragma unroll
     for (uint32_t w = 0; w < kBucketThreads / 64; w++)
         first += w < wave ? wsum[w] : 0u;
-    shift[threadIdx.x] =
-        (mine ? bstart[v.b0 + threadIdx.x] + atomicAdd(&cursor[v.b0 + threadIdx.x], mine) : 0u) - first;
+    if constexpr (kWhole) {
+        const uint32_t e0 = ebase[c.p];
+        if (threadIdx.x < v.R) {
+            bstart[v.b0 + threadIdx.x] = e0 + first;
+            bucket_map[v.b0 + threadIdx.x] = c.p;
+        }
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+            bstart[v.b0 + v.R] = e0 + v.e1;
+        shift[threadIdx.x] = e0;
+    } else {
+        shift[threadIdx.x] =
+            (mine ? bstart[v.b0 + threadIdx.x] + atomicAdd(&cursor[v.b0 + threadIdx.x], mine) : 0u) - first;
+    }
     hist[threadIdx.x] = first;
     __syncthreads();
 #pragma unroll
@@ -407,22 +446,6 @@ __global__ void __launch_bounds__(1024)
     }
 }
 
-// hops[(t n_blocks + H) r_0 + beta_{t,H}(a)] = beta_{t+1,H}(a)
-__global__ void block_hops_kernel(BlockPerm B, const uint4 *__restrict__ keys, uint16_t *hops)
-{
-    const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;  // H r_0 + a
-    if (x >= B.m)
-        return;
-    const uint32_t H = x >> B.l0, len = block_len(B, H);
-    uint32_t pos[3];
-#pragma unroll
-    for (uint32_t t = 0; t < 3; t++)
-        pos[t] = beta_fwd(B, unpack_key(keys[t * kMaxBlocksH + H]), x & B.mask, len);
-#pragma unroll
-    for (uint32_t t = 0; t < 3; t++)
-        hops[((t * B.n_blocks + H) << B.l0) + pos[t]] = (uint16_t)pos[t == 2 ? 0 : t + 1];
-}
-
 __global__ void gen_block_perms_kernel(BlockPerm B, uint32_t *out)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -509,18 +532,10 @@ void make_block_keys(const BlockPerm &B, uint4 *keys)
 
 uint64_t block_hops_entries(const BlockPerm &B) { return 3ull * B.n_blocks << B.l0; }
 
-hipError_t launch_block_hops(const BlockPerm &B, const uint4 *keys, uint16_t *hops, hipStream_t s)
+hipError_t launch_block_prep(const BlockPrep &a, const BlockPerm &B, hipStream_t s)
 {
-    block_hops_kernel<<<(B.m + 255) / 256, 256, 0, s>>>(B, keys, hops);
-    return hipGetLastError();
-}
-
-hipError_t launch_bucket_map(const uint64_t *goff, uint32_t p_first, uint32_t n, uint32_t gb, uint32_t *bucket_map,
-                             hipStream_t s)
-{
-    if (p_first >= n)
-        return hipSuccess;
-    bucket_map_kernel<<<(n - p_first + 255) / 256, 256, 0, s>>>(goff, p_first, n, gb, bucket_map);
+    const uint64_t most = std::max({(uint64_t)a.n, a.failed_words / 4, a.zeroed_words / 4, a.hops ? (uint64_t)B.m : 0});
+    block_prep_kernel<<<(uint32_t)std::min<uint64_t>((most + 255) / 256, 2048), 256, 0, s>>>(a, B);
     return hipGetLastError();
 }
 
@@ -541,17 +556,28 @@ hipError_t launch_bucket_count(const BucketChunk *chunks, uint32_t n_chunks, con
 
 hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, const uint32_t *tids,
                                  const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
-                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, const uint32_t *bstart,
+                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *bstart,
                                  uint32_t *cursor, uint32_t *bk, hipStream_t s)
 {
     if (n_chunks == 0)
         return hipSuccess;
-    if (B.sig.mask <= 0xFFFFFFu)
-        bucket_scatter_kernel<true><<<n_chunks, kBucketThreads, 0, s>>>(chunks, tids, off, sorted_items, r_sorted,
-                                                                        goff, gb, B, bstart, cursor, bk);
-    else
-        bucket_scatter_kernel<false><<<n_chunks, kBucketThreads, 0, s>>>(chunks, tids, off, sorted_items, r_sorted,
-                                                                         goff, gb, B, bstart, cursor, bk);
+    auto *kernel =
+        B.sig.mask <= 0xFFFFFFu ? bucket_scatter_kernel<true, false> : bucket_scatter_kernel<false, false>;
+    kernel<<<n_chunks, kBucketThreads, 0, s>>>(chunks, nullptr, 0, tids, off, sorted_items, r_sorted, goff, gb, B,
+                                               bstart, cursor, nullptr, bk);
+    return hipGetLastError();
+}
+
+hipError_t launch_bucket_whole(const uint32_t *ebase, uint32_t p_first, uint32_t n, const uint32_t *tids,
+                               const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
+                               const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *bstart,
+                               uint32_t *bucket_map, uint32_t *bk, hipStream_t s)
+{
+    if (p_first >= n)
+        return hipSuccess;
+    auto *kernel = B.sig.mask <= 0xFFFFFFu ? bucket_scatter_kernel<true, true> : bucket_scatter_kernel<false, true>;
+    kernel<<<n - p_first, kBucketThreads, 0, s>>>(nullptr, ebase, p_first, tids, off, sorted_items, r_sorted, goff,
+                                                  gb, B, bstart, nullptr, bucket_map, bk);
     return hipGetLastError();
 }
 

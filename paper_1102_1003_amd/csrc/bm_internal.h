@@ -324,7 +324,7 @@ hipError_t fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 // the host and the stream about as much as a launch each).  Pinned host memory may
 // stand on either side.
 struct CopyPieces {
-    static constexpr int kMax = 4;
+    static constexpr int kMax = 5;
     void *dst[kMax] = {};
     const void *src[kMax] = {};
     uint32_t words[kMax] = {};
@@ -373,8 +373,8 @@ hipError_t launch_bit_expand(const uint32_t *bits, uint32_t m, uint32_t n, const
                              uint32_t *tids, hipStream_t s);
 // Sets bit 0 of *flag when an item id is >= n.
 hipError_t launch_check_items(const uint32_t *items, uint64_t nnz, uint32_t n, uint32_t *flag, hipStream_t s);
-// Sets bit 1 of *flag when off[0] != 0, bit 2 when off[0..m] decreases.
-hipError_t launch_check_offsets(const uint64_t *off, uint32_t m, uint32_t *flag, hipStream_t s);
+// flags[0]: bit 1 when off[0] != 0, bit 2 when off[0..m] decreases; flags[1]: 0.
+hipError_t launch_check_offsets(const uint64_t *off, uint32_t m, uint32_t *flags, hipStream_t s);
 hipError_t launch_mark_dups(const uint32_t *keys, const uint32_t *vals, uint64_t nnz, uint32_t *keep,
                             uint32_t *n_dup, hipStream_t s);
 hipError_t launch_compact_pairs(const uint32_t *keys, const uint32_t *vals, const uint32_t *keep,
@@ -491,9 +491,12 @@ hipError_t launch_threshold_count(const uint32_t *sup, uint64_t n_pairs, uint32_
 // Writes the pairs only when the total, block_off[n_blocks], is at most
 // capacity (so it may be queued before the host reads the total).
 // ids (device, optional): the item of each of the n packed positions.
+// block_counts (at most kThresholdSums blocks, their offsets not scanned; else null): the
+// offsets are summed on the way and the total left in block_off[n_blocks].
+constexpr uint32_t kThresholdSums = 1024;
 hipError_t launch_threshold_write(const uint32_t *sup, uint64_t n_pairs, uint64_t n, const uint32_t *ids,
-                                  uint32_t sigma, const uint64_t *block_off, uint32_t n_blocks, uint64_t capacity,
-                                  bm_pair *out, hipStream_t s);
+                                  uint32_t sigma, const uint32_t *block_counts, uint64_t *block_off, uint32_t n_blocks,
+                                  uint64_t capacity, bm_pair *out, hipStream_t s);
 uint32_t threshold_blocks(uint64_t n_pairs);
 
 // Subset queries.
@@ -598,9 +601,26 @@ struct BucketChunk {
     uint32_t p;   // sorted index of the map
     uint32_t e0;  // first element (offset in the map's tidlist)
 };
-// bucket_map[b] = sorted index of the map owning block b.
-hipError_t launch_bucket_map(const uint64_t *goff, uint32_t p_first, uint32_t n, uint32_t gb, uint32_t *bucket_map,
-                             hipStream_t s);
+// One launch before the others: sorted_pos[item] = sorted index (-1: unbuilt, below
+// `first`) and has_map[item] of every item; failed_bits and zeroed cleared;
+// bucket_map[b] = sorted index of the map owning block b; hops, where a copy goes
+// when it is evicted: from (table, H, position) to its position in the next table,
+// block_hops_entries() of them.  bucket_map and hops may be null.
+struct BlockPrep {
+    const uint32_t *sorted_items;
+    uint32_t n, first;
+    int32_t *sorted_pos;
+    uint8_t *has_map;
+    uint32_t *failed_bits, *zeroed;
+    uint64_t failed_words, zeroed_words;
+    const uint64_t *goff;
+    uint32_t gb;
+    uint32_t *bucket_map;
+    const uint4 *keys;
+    uint16_t *hops;
+};
+uint64_t block_hops_entries(const BlockPerm &B);
+hipError_t launch_block_prep(const BlockPrep &a, const BlockPerm &B, hipStream_t s);
 // Counts of the elements of each block (count[b] += ...; zeroed by the caller).
 hipError_t launch_bucket_count(const BucketChunk *chunks, uint32_t n_chunks, const uint32_t *tids,
                                const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
@@ -609,12 +629,14 @@ hipError_t launch_bucket_count(const BucketChunk *chunks, uint32_t n_chunks, con
 // the first position of block b's run and ends at the next block's.
 hipError_t launch_bucket_scatter(const BucketChunk *chunks, uint32_t n_chunks, const uint32_t *tids,
                                  const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
-                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, const uint32_t *bstart,
+                                 const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *bstart,
                                  uint32_t *cursor, uint32_t *bk, hipStream_t s);
-// Where a copy goes when it is evicted: from (table, H, position) to its position
-// in the next table, block_hops_entries() of them.
-uint64_t block_hops_entries(const BlockPerm &B);
-hipError_t launch_block_hops(const BlockPerm &B, const uint4 *keys, uint16_t *hops, hipStream_t s);
+// Where no map has more than kBucketChunk elements: count, starts, map of the blocks
+// and scatter in one, ebase[p] the elements before map p (and bstart's last entry).
+hipError_t launch_bucket_whole(const uint32_t *ebase, uint32_t p_first, uint32_t n, const uint32_t *tids,
+                               const uint64_t *off, const uint32_t *sorted_items, const uint32_t *r_sorted,
+                               const uint64_t *goff, uint32_t gb, const BlockPerm &B, uint32_t *bstart,
+                               uint32_t *bucket_map, uint32_t *bk, hipStream_t s);
 // One workgroup per block: 2-of-3 insertion (Sec. II-A) in LDS, failures,
 // indicators (Fig. 3) and the bit-sliced bytes of the block written to the
 // arena.  Failed elements go to failed[] as (item, x) with x the caller's

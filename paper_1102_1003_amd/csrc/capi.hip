@@ -1106,41 +1106,65 @@ bm_status corr_finish(bm_index *idx, const uint32_t *failed_bits, const uint8_t 
 // 316 and 253; 10^6 x 2000 Zipf: 552 and 546 (the table is past an XCD's L2).
 constexpr uint32_t kHopsMaxM = 1u << 19;
 
+// What the block family's kernels read beside the layout: the permutations' keys, and
+// the maps' elements before each (whole: no map has more than a chunk of them) or the
+// list of chunks.
+struct BlockInput {
+    uint4 h_keys[3 * kBlockKeysH];
+    bool whole = false;
+    std::vector<uint32_t> h_ebase;
+    std::vector<BucketChunk> h_chunks;
+    DevBuf<uint4> keys;
+    DevBuf<uint32_t> ebase;
+    DevBuf<BucketChunk> chunks;
+};
+
+// Fills the host side from the layout and allocates the device side.
+bm_status block_input(bm_index *idx, uint64_t seed, BlockInput &in)
+{
+    bm_context *ctx = idx->ctx;
+    const uint32_t n = idx->n, first = idx->first_built;
+    idx->bperm = make_block_perm(idx->m, 31u - (uint32_t)__builtin_clz(idx->r0), seed);
+    make_block_keys(idx->bperm, in.h_keys);
+    in.whole = idx->h_sizes_sorted[n - 1] <= kBucketChunk;  // the widest map
+    if (in.whole) {
+        in.h_ebase.assign(n, 0);
+        for (uint32_t p = first + 1; p < n; p++)
+            in.h_ebase[p] = in.h_ebase[p - 1] + idx->h_sizes_sorted[p - 1];
+    } else {
+        for (uint32_t p = first; p < n; p++)
+            for (uint64_t e0 = 0; e0 < idx->h_sizes_sorted[p]; e0 += kBucketChunk)
+                in.h_chunks.push_back({p, (uint32_t)e0});
+    }
+    HIPC(ctx, in.keys.alloc(3 * kBlockKeysH));
+    HIPC(ctx, in.ebase.alloc(std::max<size_t>(in.h_ebase.size(), 1)));
+    HIPC(ctx, in.chunks.alloc(std::max<size_t>(in.h_chunks.size(), 1)));
+    return BM_OK;
+}
+
 // The block family's construction.  done: the maps are built (else the chain
 // family builds them); corr_done: the corrections are made too (queued right
 // behind the build and read back with its counters, one wait for both).
 // early: the all-pairs plan being made on another thread, or null.
-bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t> &failed_bits, uint64_t fb_words,
-                          const uint8_t *has_map, std::future<Plan> *early, bool &done, bool &corr_done)
+bm_status block_construct(bm_index *idx, const bm_build_opts *o, const BlockInput &in, DevBuf<uint32_t> &failed_bits,
+                          uint64_t fb_words, uint8_t *has_map, std::future<Plan> *early, bool &done, bool &corr_done)
 {
     bm_context *ctx = idx->ctx;
     hipStream_t s = ctx->stream;
     const uint32_t n = idx->n, first = idx->first_built;
     done = false;
     corr_done = false;
-    const uint32_t l0 = 31u - (uint32_t)__builtin_clz(idx->r0);
-    idx->bperm = make_block_perm(idx->m, l0, o->seed);
     const uint32_t gb = idx->gb;
     const uint64_t n_blocks = idx->total_groups / gb;
-    std::vector<BucketChunk> h_chunks;
-    for (uint32_t p = first; p < n; p++) {
-        // r_i <= 2 * 2^ceil(log2 m) and m <= 127 r_0 give at most 256 blocks a
-        // map (the bucket passes' histogram); anything wider goes to the chain family
-        if (idx->h_r_sorted[p] / idx->r0 > 256)
-            return BM_OK;
-        const uint32_t sz = idx->h_sizes_sorted[p];
-        for (uint32_t e0 = 0; e0 < sz; e0 += kBucketChunk)
-            h_chunks.push_back({p, e0});
-    }
     Span span_construct(ctx, PH_CONSTRUCT);
-    DevBuf<BucketChunk> chunks;
-    DevBuf<uint4> keys;
     DevBuf<uint32_t> zeroed, bstart, bmap, bk;
+    DevBuf<uint16_t> hops;
     DevBuf<char> tmp;
-    HIPC(ctx, chunks.alloc(std::max<size_t>(h_chunks.size(), 1)));
-    // cleared by one fill: failures, the give-up flag, the corrections count
-    // (64-bit); elements per block (and the scan's last entry); elements placed per block
-    HIPC(ctx, zeroed.alloc(4 + 2 * (n_blocks + 1)));
+    // cleared: failures, the give-up flag, the corrections count (64-bit); then,
+    // unless the maps are whole chunks, elements per block (and the scan's last
+    // entry) and elements placed per block
+    const uint64_t zeroed_words = in.whole ? 4 : 4 + 2 * (n_blocks + 1);
+    HIPC(ctx, zeroed.alloc(zeroed_words));
     uint32_t *const counters = zeroed.p, *const count = zeroed.p + 4, *const cursor = count + n_blocks + 1;
     HIPC(ctx, bstart.alloc(n_blocks + 1));
     HIPC(ctx, bmap.alloc(n_blocks + 1));
@@ -1150,25 +1174,24 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
     const uint64_t corr_cap = corr_first_cap(std::max<uint64_t>(1u << 16, idx->nnz / 256));
     if (corr_here)
         HIPC(ctx, idx->corr.alloc(2 * corr_cap));
-    HIPC(ctx, tmp.alloc(scan_tmp_bytes(n_blocks + 1)));
-    HIPC(ctx, keys.alloc(3 * kBlockKeysH));
-    uint4 h_keys[3 * kBlockKeysH];
-    make_block_keys(idx->bperm, h_keys);
-    BMC(upload_many(ctx, {{keys.p, h_keys, sizeof h_keys},
-                          {chunks.p, h_chunks.data(), h_chunks.size() * sizeof(BucketChunk)}}));
-    DevBuf<uint16_t> hops;
-    if (idx->m <= kHopsMaxM) {
+    if (idx->m <= kHopsMaxM)
         HIPC(ctx, hops.alloc(block_hops_entries(idx->bperm)));
-        HIPC(ctx, launch_block_hops(idx->bperm, keys.p, hops.p, s));
+    HIPC(ctx, launch_block_prep({idx->sorted_items.p, n, first, idx->sorted_pos.p, has_map, failed_bits.p, zeroed.p,
+                                 fb_words + 1, zeroed_words, idx->goff.p, gb, in.whole ? nullptr : bmap.p, in.keys.p,
+                                 hops.p},
+                                idx->bperm, s));
+    if (in.whole) {
+        HIPC(ctx, launch_bucket_whole(in.ebase.p, first, n, idx->tids.p, idx->off.p, idx->sorted_items.p,
+                                      idx->r_sorted.p, idx->goff.p, gb, idx->bperm, bstart.p, bmap.p, bk.p, s));
+    } else {
+        const uint32_t n_chunks = (uint32_t)in.h_chunks.size();
+        HIPC(ctx, tmp.alloc(scan_tmp_bytes(n_blocks + 1)));
+        HIPC(ctx, launch_bucket_count(in.chunks.p, n_chunks, idx->tids.p, idx->off.p, idx->sorted_items.p,
+                                      idx->r_sorted.p, idx->goff.p, gb, idx->bperm, count, s));
+        HIPC(ctx, exclusive_scan_u32(count, bstart.p, n_blocks + 1, tmp.p, s));
+        HIPC(ctx, launch_bucket_scatter(in.chunks.p, n_chunks, idx->tids.p, idx->off.p, idx->sorted_items.p,
+                                        idx->r_sorted.p, idx->goff.p, gb, idx->bperm, bstart.p, cursor, bk.p, s));
     }
-    HIPC(ctx, fill_u32(zeroed.p, 4 + 2 * (n_blocks + 1), 0, s));
-    HIPC(ctx, launch_bucket_map(idx->goff.p, first, n, gb, bmap.p, s));
-    HIPC(ctx, launch_bucket_count(chunks.p, (uint32_t)h_chunks.size(), idx->tids.p, idx->off.p, idx->sorted_items.p,
-                                  idx->r_sorted.p, idx->goff.p, gb, idx->bperm, count, s));
-    HIPC(ctx, exclusive_scan_u32(count, bstart.p, n_blocks + 1, tmp.p, s));
-    HIPC(ctx, launch_bucket_scatter(chunks.p, (uint32_t)h_chunks.size(), idx->tids.p, idx->off.p,
-                                    idx->sorted_items.p, idx->r_sorted.p, idx->goff.p, gb, idx->bperm, bstart.p, cursor,
-                                    bk.p, s));
     uint64_t fail_cap = std::max<uint64_t>(1u << 16, idx->nnz / 64);
     for (int attempt = 0;; attempt++) {
         HIPC(ctx, idx->failed.alloc(2 * fail_cap));
@@ -1184,7 +1207,7 @@ bm_status block_construct(bm_index *idx, const bm_build_opts *o, DevBuf<uint32_t
             HIPC(ctx, hipEventRecord(ctx->fork, s));
         }
         HIPC(ctx, launch_block_build(bk.p, bstart.p, bmap.p, (uint32_t)n_blocks, idx->goff.p, idx->sorted_items.p,
-                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, keys.p, hops.p, idx->shift,
+                                     idx->r_sorted.p, idx->tids.p, idx->off.p, idx->bperm, in.keys.p, hops.p, idx->shift,
                                      o->max_loop, idx->arena.p, failed_bits.p, idx->failed.p, counters,
                                      (uint32_t)fail_cap, counters + 1, s));
         // the corrections of the failures the build lists (it stops listing
@@ -1379,7 +1402,8 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
     std::vector<uint64_t> &h_goff = idx->h_goff;
     h_goff.assign((size_t)n + 1, 0);
     bm_status st = BM_OK;
-    if (!order3 && n <= kSmallSortMax) {
+    const bool host_layout = !order3 && n <= kSmallSortMax;
+    if (host_layout) {
         // few maps: the order and the layout (r_i as in map_layout_kernel,
         // group offsets) from the sizes the host holds, sent without a wait
         host_size_order(idx->h_off, n, idx->h_sorted_items);
@@ -1396,11 +1420,6 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
             idx->h_r_sorted[p] = r;
             h_goff[p + 1] = h_goff[p] + 3ull * r / kSlotsPerGroup;
         }
-        st = upload_many(ctx, {{idx->sorted_items.p, idx->h_sorted_items.data(), (uint64_t)n * 4},
-                               {idx->r_sorted.p, idx->h_r_sorted.data(), (uint64_t)n * 4},
-                               {idx->goff.p, h_goff.data(), ((uint64_t)n + 1) * 8}});
-        if (st != BM_OK)
-            return st;
     } else {
         if (n <= kSmallSortMax) {
             HIPC(ctx, launch_size_order_small(idx->off.p, n, idx->sorted_items.p, s));
@@ -1433,12 +1452,6 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
         if (st != BM_OK)
             return st;
     }
-    // sorted_pos: item -> sorted index (or -1 when unbuilt); has_map for the
-    // corrections
-    DevBuf<uint8_t> has_map;
-    HIPC(ctx, idx->sorted_pos.alloc(n));
-    HIPC(ctx, has_map.alloc(std::max<uint32_t>(n, 1)));
-    HIPC(ctx, launch_sorted_pos(idx->sorted_items.p, n, first_built, idx->sorted_pos.p, has_map.p, s));
     idx->h_sizes_sorted.resize(n);
     for (uint32_t p = 0; p < n; p++) {
         const uint32_t it = idx->h_sorted_items[p];
@@ -1449,6 +1462,34 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
     if (idx->total_groups >= (1ull << 32))
         return fail(ctx, BM_EINVAL, "BatMaps of %llu groups (%llu bytes); at most 2^32 groups per index",
                     (unsigned long long)idx->total_groups, (unsigned long long)idx->total_groups * kSlotsPerGroup);
+    // The block family builds the paper's 8-bit maps of order two with
+    // generated permutations whenever a block of 3 r_0 code bytes fits the
+    // LDS; the chain family (staged and whole-map LDS builds below) builds the
+    // rest, and an index whose block build overflowed.  BM_BLOCK_BUILD=0
+    // turns the block family off.  r_i <= 2 * 2^ceil(log2 m) and m <= 127 r_0
+    // give at most 256 blocks a map (the bucket passes' histogram); anything
+    // wider goes to the chain family.
+    const char *bb_env = getenv("BM_BLOCK_BUILD");
+    const bool by_blocks = !(bb_env && atoi(bb_env) == 0) && !order3 && idx->planes == 8 && !o->perm[0] &&
+                           first_built < n && idx->r0 <= block_build_max_r0() &&
+                           idx->h_r_sorted[n - 1] / idx->r0 <= 256;
+    BlockInput block_in;
+    if (by_blocks)
+        BMC(block_input(idx, o->seed, block_in));
+    const uint64_t sent = host_layout ? n : 0;
+    BMC(upload_many(ctx, {{idx->sorted_items.p, idx->h_sorted_items.data(), sent * 4},
+                          {idx->r_sorted.p, idx->h_r_sorted.data(), sent * 4},
+                          {idx->goff.p, h_goff.data(), host_layout ? (sent + 1) * 8 : 0},
+                          {block_in.keys.p, block_in.h_keys, by_blocks ? sizeof block_in.h_keys : 0},
+                          {block_in.whole ? (void *)block_in.ebase.p : (void *)block_in.chunks.p,
+                           block_in.whole ? (const void *)block_in.h_ebase.data() : (const void *)block_in.h_chunks.data(),
+                           block_in.whole ? block_in.h_ebase.size() * 4
+                                          : block_in.h_chunks.size() * sizeof(BucketChunk)}}));
+    // sorted_pos: item -> sorted index (or -1 when unbuilt); has_map for the
+    // corrections
+    DevBuf<uint8_t> has_map;
+    HIPC(ctx, idx->sorted_pos.alloc(n));
+    HIPC(ctx, has_map.alloc(std::max<uint32_t>(n, 1)));
     idx->classes.clear();
     for (uint32_t p = first_built; p < n; p++) {
         uint32_t r = idx->h_r_sorted[p];
@@ -1473,22 +1514,13 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
     DevBuf<uint32_t> &failed_bits = idx->failed_bits;
     uint64_t fb_words = (idx->nnz + 31) / 32;
     HIPC(ctx, failed_bits.alloc(fb_words + 1));
-    HIPC(ctx, fill_u32(failed_bits.p, fb_words + 1, 0, s));
-    // The block family builds the paper's 8-bit maps of order two with
-    // generated permutations whenever a block of 3 r_0 code bytes fits the
-    // LDS; the chain family (staged and whole-map LDS builds below) builds the
-    // rest, and an index whose block build overflowed.  BM_BLOCK_BUILD=0
-    // turns the block family off.
     bool block_done = false, corr_done = false;
-    {
-        const char *bb_env = getenv("BM_BLOCK_BUILD");
-        if (!(bb_env && atoi(bb_env) == 0) && !order3 && idx->planes == 8 && !o->perm[0] && first_built < n &&
-            idx->r0 <= block_build_max_r0()) {
-            st = block_construct(idx, o, failed_bits, fb_words, has_map.p, plan_here ? &early_plan : nullptr, block_done,
-                                 corr_done);
-            if (st != BM_OK)
-                return st;
-        }
+    if (by_blocks) {
+        BMC(block_construct(idx, o, block_in, failed_bits, fb_words, has_map.p, plan_here ? &early_plan : nullptr,
+                            block_done, corr_done));
+    } else {
+        HIPC(ctx, launch_sorted_pos(idx->sorted_items.p, n, first_built, idx->sorted_pos.p, has_map.p, s));
+        HIPC(ctx, fill_u32(failed_bits.p, fb_words + 1, 0, s));
     }
     if (!block_done) {
         size_t free_b = 0, total_b = 0;
@@ -2447,7 +2479,6 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
     std::vector<uint64_t> roff;
     DevBuf<uint32_t> flags;  // bad offsets; items out of range
     HIPC(ctx, flags.alloc(2));
-    HIPC(ctx, fill_u32(flags.p, 2, 0, s));
     if (dev_off) {
         HIPC(ctx, launch_check_offsets(offsets, m_txn, flags.p, s));
         uint32_t hflag = 0;
@@ -2466,6 +2497,7 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
             if (roff[b + 1] < roff[b])
                 return fail(ctx, BM_EINVAL, "offsets decrease at transaction %u", b);
         nnz_in = roff[m_txn];
+        HIPC(ctx, fill_u32(flags.p, 2, 0, s));
     }
     if (nnz_in && !items)
         return fail(ctx, BM_EINVAL, "items is null");
@@ -2690,13 +2722,15 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
     HIPC(ctx, idx->scan_tmp.ensure(scan_tmp_bytes((uint64_t)nb + 1)));
     Span span_thr(ctx, PH_THRESHOLD);
     HIPC(ctx, launch_threshold_count(idx->pairbuf.p, np, min_support, idx->thr_counts.p, nb, s));
-    HIPC(ctx, exclusive_scan_u32_to_u64(idx->thr_counts.p, idx->thr_off.p, (uint64_t)nb + 1, idx->scan_tmp.p, s));
     // a device buffer is written before the total comes back (the kernel
     // writes nothing when the total exceeds capacity)
     const bool host = out && ptr_kind(out) == PTR_HOST;
+    const bool sums = out && !host && nb <= kThresholdSums;
+    if (!sums)
+        HIPC(ctx, exclusive_scan_u32_to_u64(idx->thr_counts.p, idx->thr_off.p, (uint64_t)nb + 1, idx->scan_tmp.p, s));
     if (out && !host)
-        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, n_eff, thr_ids, min_support, idx->thr_off.p, nb, capacity, out,
-                                         s));
+        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, n_eff, thr_ids, min_support,
+                                         sums ? idx->thr_counts.p : nullptr, idx->thr_off.p, nb, capacity, out, s));
     uint64_t total = 0;
     span_thr.end();
     BMC(read_back(ctx, &total, idx->thr_off.p + nb, 8));
@@ -2713,7 +2747,8 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
         HIPC(ctx, idx->pair_out.ensure(total));
         dst = idx->pair_out.p;
         Span sp(ctx, PH_THRESHOLD);
-        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, n_eff, thr_ids, min_support, idx->thr_off.p, nb, total, dst, s));
+        HIPC(ctx, launch_threshold_write(idx->pairbuf.p, np, n_eff, thr_ids, min_support, nullptr, idx->thr_off.p, nb,
+                                         total, dst, s));
     }
     if (host) {
         BMC(download(ctx, out, dst, total * sizeof(bm_pair)));
@@ -2809,9 +2844,12 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
         HIPC(ctx, launch_apply_corrections(idx->corr.p, idx->n_corr, counts, idx->n, s));
     }
     HIPC(ctx, launch_threshold_count(counts, np, min_support, thr_counts, nb, s));
-    HIPC(ctx, exclusive_scan_u32_to_u64(thr_counts, thr_off, (uint64_t)nb + 1, sc + o_tmp, s));
+    const bool sums = out && nb <= kThresholdSums;
+    if (!sums)
+        HIPC(ctx, exclusive_scan_u32_to_u64(thr_counts, thr_off, (uint64_t)nb + 1, sc + o_tmp, s));
     if (out)
-        HIPC(ctx, launch_threshold_write(counts, np, idx->n, nullptr, min_support, thr_off, nb, capacity, out, s));
+        HIPC(ctx, launch_threshold_write(counts, np, idx->n, nullptr, min_support, sums ? thr_counts : nullptr,
+                                         thr_off, nb, capacity, out, s));
     uint64_t total = 0;
     BMC(read_back(ctx, &total, thr_off + nb, 8));
     *n_out = total;

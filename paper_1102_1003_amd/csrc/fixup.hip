@@ -20,17 +20,25 @@ __device__ inline uint64_t packed_index(uint64_t n, uint64_t i, uint64_t j)
     return i * n - i * (i + 1) / 2 + (j - i - 1);
 }
 
+// Where x stands in a, or -1.  Three probes a step: a step is one load's latency
+// after another, and a correction does little else (30,011 x 613: the pass 23 us
+// with a probe a step).
 __device__ inline int64_t find_tid(const uint32_t *a, uint64_t n, uint32_t x)
 {
-    uint64_t lo = 0, hi = n;
-    while (lo < hi) {
-        uint64_t mid = (lo + hi) >> 1;
-        if (a[mid] < x)
-            lo = mid + 1;
-        else
-            hi = mid;
+    uint64_t lo = 0;
+    while (n > 3) {
+        const uint64_t q = n / 4;
+        const uint32_t v1 = a[lo + q], v2 = a[lo + 2 * q], v3 = a[lo + 3 * q];
+        const uint64_t quarter = (x >= v1) + (x >= v2) + (x >= v3);
+        lo += quarter * q;
+        n = quarter == 3 ? n - 3 * q : q;
     }
-    return (lo < n && a[lo] == x) ? (int64_t)lo : -1;
+    int64_t at = -1;
+#pragma unroll
+    for (uint32_t k = 0; k < 3; k++)
+        if (k < n && a[lo + k] == x)
+            at = (int64_t)(lo + k);
+    return at;
 }
 
 // Thread per (failure f, item c).  cap == 0 only counts.
@@ -183,13 +191,46 @@ __device__ inline uint64_t row_of_packed(uint64_t k, uint64_t n)
 // Writes nothing when the total (block_off[n_blocks]) exceeds capacity, so the
 // write can be queued before the host has read the total.
 // ids: the item of each of the n positions (null: position p is item p).
+// kSum: `block_off` holds the blocks' counts, not yet scanned: every block adds
+// those before it and all of them (the first one leaves the sum after them for the
+// caller), which for few blocks takes less than a scan's launch.
+template <bool kSum>
 __global__ void threshold_write_kernel(const uint32_t *sup, uint64_t n_pairs, uint64_t n, const uint32_t *ids,
-                                       uint32_t sigma,
-                                       const uint64_t *block_off, uint32_t n_blocks, uint64_t capacity,
-                                       bm_pair *out)
+                                       uint32_t sigma, const uint32_t *block_counts, uint64_t *block_off,
+                                       uint32_t n_blocks, uint64_t capacity, bm_pair *out)
 {
-    if (block_off[n_blocks] > capacity)
-        return;  // the same value for every thread of the grid
+    uint64_t first;
+    if constexpr (kSum) {
+        __shared__ uint32_t sums[2];
+        if (threadIdx.x < 2)
+            sums[threadIdx.x] = 0;
+        __syncthreads();
+        uint32_t all = 0, ahead = 0;
+        for (uint32_t b = threadIdx.x; b < n_blocks; b += kBlock) {
+            const uint32_t c = block_counts[b];
+            all += c;
+            ahead += b < blockIdx.x ? c : 0u;
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            all += __shfl_xor(all, d, 64);
+            ahead += __shfl_xor(ahead, d, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicAdd(&sums[0], all);
+            atomicAdd(&sums[1], ahead);
+        }
+        __syncthreads();
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            block_off[n_blocks] = sums[0];
+        if (sums[0] > capacity)
+            return;
+        first = sums[1];
+    } else {
+        if (block_off[n_blocks] > capacity)
+            return;  // the same value for every thread of the grid
+        first = block_off[blockIdx.x];
+    }
     uint64_t base = (uint64_t)blockIdx.x * kThrTile + (uint64_t)threadIdx.x * kThrItems;
     uint32_t v[kThrItems];
     uint32_t c = 0;
@@ -203,7 +244,7 @@ __global__ void threshold_write_kernel(const uint32_t *sup, uint64_t n_pairs, ui
     uint32_t before = block_excl_scan_u32(c, &total);
     if (c == 0)
         return;
-    uint64_t pos = block_off[blockIdx.x] + before;
+    uint64_t pos = first + before;
     uint64_t row = row_of_packed(base, n);
     uint64_t row_start = row * n - row * (row + 1) / 2;
     for (int i = 0; i < kThrItems; i++) {
@@ -363,12 +404,13 @@ hipError_t launch_threshold_count(const uint32_t *sup, uint64_t n_pairs, uint32_
 }
 
 hipError_t launch_threshold_write(const uint32_t *sup, uint64_t n_pairs, uint64_t n, const uint32_t *ids,
-                                  uint32_t sigma, const uint64_t *block_off, uint32_t n_blocks, uint64_t capacity,
-                                  bm_pair *out, hipStream_t s)
+                                  uint32_t sigma, const uint32_t *block_counts, uint64_t *block_off, uint32_t n_blocks,
+                                  uint64_t capacity, bm_pair *out, hipStream_t s)
 {
     if (n_blocks == 0)
         return hipSuccess;
-    threshold_write_kernel<<<n_blocks, kBlock, 0, s>>>(sup, n_pairs, n, ids, sigma, block_off, n_blocks, capacity, out);
+    auto *kernel = block_counts ? threshold_write_kernel<true> : threshold_write_kernel<false>;
+    kernel<<<n_blocks, kBlock, 0, s>>>(sup, n_pairs, n, ids, sigma, block_counts, block_off, n_blocks, capacity, out);
     return hipGetLastError();
 }
 

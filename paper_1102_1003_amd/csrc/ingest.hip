@@ -98,7 +98,20 @@ __global__ void check_items_kernel(const uint32_t *items, uint64_t nnz, uint32_t
 }
 
 // Row offsets of a transactions CSR: bit 1 when offsets[0] != 0, bit 2 when
-// they decrease somewhere.
+// they decrease somewhere.  The first form is one workgroup's and clears the
+// second word too, which saves a small build the launch that would.
+__global__ void __launch_bounds__(1024) check_offsets_small_kernel(const uint64_t *off, uint32_t m, uint32_t *flags)
+{
+    bool down = false;
+    for (uint32_t b = threadIdx.x; b < m; b += blockDim.x)
+        down |= off[b + 1] < off[b];
+    const int any = __syncthreads_or(down);
+    if (threadIdx.x == 0) {
+        flags[0] = (any ? 4u : 0u) | (off[0] != 0 ? 2u : 0u);
+        flags[1] = 0;
+    }
+}
+
 __global__ void check_offsets_kernel(const uint64_t *off, uint32_t m, uint32_t *flag)
 {
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -447,9 +460,16 @@ hipError_t launch_offsets_and_dups(const uint32_t *keys, const uint32_t *vals, u
     return hipGetLastError();
 }
 
-hipError_t launch_check_offsets(const uint64_t *off, uint32_t m, uint32_t *flag, hipStream_t s)
+hipError_t launch_check_offsets(const uint64_t *off, uint32_t m, uint32_t *flags, hipStream_t s)
 {
-    check_offsets_kernel<<<blocks_for(m, 4096), kBlock, 0, s>>>(off, m, flag);
+    if (m <= 16384) {
+        check_offsets_small_kernel<<<1, 1024, 0, s>>>(off, m, flags);
+        return hipGetLastError();
+    }
+    hipError_t e = fill_u32(flags, 2, 0, s);
+    if (e != hipSuccess)
+        return e;
+    check_offsets_kernel<<<blocks_for(m, 4096), kBlock, 0, s>>>(off, m, flags);
     return hipGetLastError();
 }
 
