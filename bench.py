@@ -82,7 +82,7 @@ def main():
                     choices=["step", "serving", "dense-sweep", "batch", "bipartite", "triples"],
                     help="step: the path on one instance (default); serving: subset-query stream against the "
                          "resident serving instance; dense-sweep: BatMap (slot width by density) vs MFMA "
-                         "bitmap across densities; batch: 64 uneven instances in one graph-captured launch vs one "
+                         "bitmap across densities; batch: 64 uneven instances in one graph vs one "
                          "call per instance; bipartite: |A_i cap B_j| of two families (boolean matrix product); "
                          "triples: supports of item triples on order-3 maps")
     ap.add_argument("--instances", type=int, default=64, help="batch: number of uneven instances")
@@ -377,7 +377,7 @@ def extras(args):
                 "frac_of_f4_peak": row["dense_tops"] / PEAK_F4_MFMA_TOPS}
 
     def batch_keep(r):
-        keys = ("batch_ms", "alone_sum_ms", "persistent_launch_ms", "speedup_vs_alone", "graph", "frac_of_valu_peak",
+        keys = ("batch_ms", "alone_sum_ms", "persistent_launch_ms", "speedup_vs_alone", "graph", "frac_of_f4_peak",
                 "exact")
         return {"workload": r["config"]["workload"], "pairs": r["config"]["pairs"], **{k: r[k] for k in keys}}
 
@@ -659,17 +659,21 @@ def bipartite_mode(args):
     cols_ok = bool(np.array_equal(got.astype(np.int64).sum(axis=0),
                                   np.add.reduceat(deg_a[tb], ob[:-1].astype(np.int64))))
     step_ms = float(np.median(ms))
-    tops = sp / 32 * OPS_PER_GROUP_PAIR / (cmp_ms * 1e-3) / 1e12
+    # slot compares on the VALU, or 2 m operations a pair on the matrix cores
+    ops, peak = ((sp / 32 * OPS_PER_GROUP_PAIR, PEAK_VALU_TOPS) if sp > 0 else
+                 (2.0 * m * na * nb, PEAK_F4_MFMA_TOPS))
+    tops = ops / (cmp_ms * 1e-3) / 1e12
     log(f"bipartite {na} x {nb}: {step_ms:.3f} ms per call ({na * nb / (step_ms * 1e-3):.3e} supports/s), compare "
-        f"{tops:.2f} TOP/s ({tops / PEAK_VALU_TOPS:.1%} of VALU peak); rows closed form {rows_ok}, columns "
-        f"{cols_ok}")
+        f"{tops:.2f} TOP/s ({tops / peak:.1%} of {'VALU' if sp > 0 else 'MFMA'} peak); rows closed form {rows_ok}, "
+        f"columns {cols_ok}")
     return {"metric": "bipartite intersection sizes |A_i cap B_j| per second (exact)",
         "value": na * nb / (step_ms * 1e-3), "unit": "pair supports/s", "n_gpus": 1,
         "ms_per_call": step_ms, "dtype": "u32", "data": "synthetic",
         "config": {"workload": f"A = {wa.name} ({na} sets), B = capped Zipf(1.0) at 1% ({nb} sets), "
                                f"m = {m}", "nnz_a": int(ta.size), "nnz_b": int(tb.size)},
-        "roofline": {"bound": "alu", "achieved": tops, "peak": PEAK_VALU_TOPS, "unit": "TOP/s",
-                     "frac": tops / PEAK_VALU_TOPS},
+        "route": "slots" if sp > 0 else "bits",
+        "roofline": {"bound": "alu" if sp > 0 else "mfma", "achieved": tops, "peak": peak, "unit": "TOP/s",
+                     "frac": tops / peak},
         "exact": {"row_closed_form": rows_ok, "column_closed_form": cols_ok}}
 
 
@@ -732,22 +736,29 @@ def triples_mode(args):
         np.add.at(got, (pos[:, a], pos[:, b]), v)
     iu = np.triu_indices(64, 1)
     pairs_ok = bool(np.array_equal(got[iu], want[iu]))
-    # r of every queried map: algorithmic bytes = the three maps once per triple (8 r bytes each)
-    r = np.maximum(idx.stats()["r0"], 1 << np.ceil(np.log2(2 * sizes[Q].astype(np.float64))).astype(np.int64))
-    r_of = dict(zip(Q.tolist(), r.tolist()))
-    alg_bytes = float(sum(8 * (r_of[a] + r_of[b] + r_of[c]) for a, b, c in T.tolist()))
-    gbs = alg_bytes / (cmp_ms * 1e-3) / 1e9
+    if slot_triples > 0:
+        # r of every queried map: algorithmic bytes = the three maps once per triple (8 r bytes each)
+        r = np.maximum(idx.stats()["r0"], 1 << np.ceil(np.log2(2 * sizes[Q].astype(np.float64))).astype(np.int64))
+        r_of = dict(zip(Q.tolist(), r.tolist()))
+        alg_bytes = float(sum(8 * (r_of[a] + r_of[b] + r_of[c]) for a, b, c in T.tolist()))
+        gbs = alg_bytes / (cmp_ms * 1e-3) / 1e9
+        roofline = {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
+                    "note": "algorithmic bytes: each of a triple's three maps once (8 r bytes)"}
+    else:
+        # bit rows: two ANDs, of which one is shared by the triples of a pair, and a count per 32 transactions
+        tops = 2.0 * w.m / 32 * T.shape[0] / (cmp_ms * 1e-3) / 1e12
+        roofline = {"bound": "alu", "achieved": tops, "peak": PEAK_VALU_TOPS, "unit": "TOP/s",
+                    "frac": tops / PEAK_VALU_TOPS, "note": "an AND and a count per triple and 32 transactions"}
     log(f"triples: {T.shape[0]} among the 64 largest sets, {call_ms:.3f} ms per call "
-        f"({T.shape[0] / (call_ms * 1e-3):.3e} triple supports/s, {slot_triples / (cmp_ms * 1e-3):.3e} slot triples/s,"
-        f" {gbs:.0f} GB/s of maps); order-3 build {build_ms:.2f} ms; closed form {closed}, per pair {pairs_ok}")
+        f"({T.shape[0] / (call_ms * 1e-3):.3e} triple supports/s, {roofline['achieved']:.1f} {roofline['unit']}); "
+        f"order-3 build {build_ms:.2f} ms; closed form {closed}, per pair {pairs_ok}")
     return {"metric": "item-triple supports per second (exact), order-3 BatMaps",
         "value": T.shape[0] / (call_ms * 1e-3), "unit": "triple supports/s", "n_gpus": 1,
         "ms_per_call": call_ms, "dtype": "u16 slots / u32 counts", "data": "synthetic",
         "config": {"workload": f"{w.name}: every triple among the 64 largest sets",
                    "triples": int(T.shape[0]), "order3_build_ms": build_ms},
-        "roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                     "frac": gbs / PEAK_HBM_GBS,
-                     "note": "algorithmic bytes: each of a triple's three maps once (8 r bytes)"},
+        "route": "slots" if slot_triples > 0 else "bits",
+        "roofline": roofline,
         "slot_triples_per_s": slot_triples / (cmp_ms * 1e-3),
         "exact": {"closed_form_sum": closed, "pair_closed_form": pairs_ok}}
 
@@ -755,8 +766,8 @@ def triples_mode(args):
 def batch_mode(args):
     """Uneven Bernoulli instances (m log-uniform in [1e4, 1e6], n uniform in [100, 4000], density uniform in
     [1%, 10%], per-instance seeds; tidlists drawn on the GPU) counted all-pairs, first with one call per
-    instance, then as one multi-instance batch (a launch per tile shape holding every instance's items)
-    replayed from a HIP graph.  Both are checked:
+    instance, then as one multi-instance batch (one launch for the instances counted from bit rows, one per
+    tile shape for the others) replayed from a HIP graph.  Both are checked:
     equal to each other and to the closed forms of every instance (its sum and each of its rows)."""
     import torch
 
@@ -784,14 +795,6 @@ def batch_mode(args):
     total_pairs = sum(pairs)
     outs_a = [torch.empty(max(p, 1), dtype=torch.int32, device=dev) for p in pairs]
     outs_b = [torch.empty(max(p, 1), dtype=torch.int32, device=dev) for p in pairs]
-
-    # algorithmic slot pairs of every instance (one profiled call each)
-    ctx.set_profiling(True)
-    slot_pairs = 0.0
-    for ix, o in zip(idxs, outs_a):
-        ix.all_pair_supports(o)
-        slot_pairs += ctx.timings()["compare_slot_pairs"]
-    ctx.set_profiling(False)
 
     def timed(fn, reps):
         ts = []
@@ -840,7 +843,7 @@ def batch_mode(args):
         want = cs[o[1:].long()] - cs[o[:-1].long()]
         rows_ok = rows_ok and bool(torch.equal(rows, want))
         del iu, v, rows, cs, want
-    ops = slot_pairs / SLOTS_PER_GROUP * OPS_PER_GROUP_PAIR
+    ops = sum(2.0 * w.m * p for w, p in zip(specs, pairs))   # of the bit rows' products
     log(f"one call per instance: {alone_s * 1e3:.2f} ms; one graph launch: {batch_s * 1e3:.2f} ms "
         f"(graph={batch.is_graph}); as one persistent launch: {persistent_s * 1e3:.2f} ms; "
         f"equal={equal and equal_p} closed={all(closed)} rows={rows_ok}")
@@ -853,13 +856,14 @@ def batch_mode(args):
                    "instances": len(specs), "nnz": nnz, "pairs": total_pairs},
         "index_build_s": build_s,
         "batch_ms": batch_s * 1e3, "alone_sum_ms": alone_s * 1e3, "speedup_vs_alone": alone_s / batch_s,
-        "launch_form": "one compare launch per tile shape over every instance's items, in one graph",
+        "launch_form": "one launch over all instances counted from bit rows, one per tile shape over the others' "
+                       "items, in one graph",
         "persistent_launch_ms": persistent_s * 1e3,
         "graph": batch.is_graph,
         "autotune_trial_ms": {"builtin_speeds": trial[0], "measured_speeds": trial[1],
                               "kept": "measured" if 0 < trial[1] < trial[0] else "builtin"},
         "batch_tops": ops / batch_s / 1e12, "alone_tops": ops / alone_s / 1e12,
-        "frac_of_valu_peak": ops / batch_s / 1e12 / PEAK_VALU_TOPS,
+        "frac_of_f4_peak": ops / batch_s / 1e12 / PEAK_F4_MFMA_TOPS,
         "exact": {"batch_equals_alone": equal, "persistent_equals_alone": equal_p,
                   "closed_form_sum_all": all(closed), "row_closed_form_all": rows_ok},
     }
