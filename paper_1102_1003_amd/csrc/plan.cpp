@@ -890,10 +890,14 @@ GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint3
 // One launch holds every family's tiles, of 64 or 128 counts whichever takes a
 // family less time: a small family alone is mostly the two launches' 10 us and a
 // chip that fills and drains, and several launches side by side share the
-// compute units unevenly (see bit_gram_jobs_kernel).  Every workgroup takes about the same
-// time, the total over three workgroups a CU; families that 256-wide tiles count
-// in over 1 ms go alone (2^20 x 4096: 2.46 ms against 2.73; 10^6 x 2000: 653 us
-// against 668, less than the launch and the larger parts cost).
+// compute units unevenly (see bit_gram_jobs_kernel).  Every workgroup takes
+// about the same time, the total over three workgroups a CU.  Families expected
+// to take over 200 us go alone, one after the other: they fill the chip by
+// themselves, and rows of several families at once are read at a lower rate.
+// Of 64 instances, in us, joint against one after the other: those of 300 to
+// 1,000 us 4640 and 4027, of 100 to 300 us 2463 and 2415, below 1806 and 2459;
+// all of them with the line at 120, 200 and 300: 12,276, 12,321 and 12,972
+// (12,860 alone), the eight of bit_gram_jobs_kernel 487, 450 and 447.
 GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, int pinned)
 {
     GramSetPlan set;
@@ -902,7 +906,7 @@ GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, i
     for (size_t q = 0; q < shapes.size(); q++) {
         const GramShape &f = shapes[q];
         GramPlan p = plan_gram(f.n, f.n, true, f.row_words, n_cu, pinned);
-        const bool alone = p.tile == 256 && (p.us > 1000 || pinned);
+        const bool alone = p.us > 200 || pinned == 256;
         if (!alone) {
             auto cost = [&](uint64_t t, double us) { return (f.n + t - 1) / t * ((f.n + t - 1) / t + 1) / 2 * us; };
             p.tile = pinned ? pinned : cost(128, 0.62) <= cost(64, 0.27) ? 128 : 64;

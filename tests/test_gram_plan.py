@@ -47,5 +47,6 @@ def test_set(check, pinned):
         joint, groups, msg = ctypes.c_uint32(), ctypes.c_uint32(), ctypes.create_string_buffer(256)
         assert check.lib.gram_set_check(n, m, len(fam), 256, pinned, ctypes.byref(joint), ctypes.byref(groups), msg,
                                         256) == 0, (fam[:4], msg.value.decode())
-        # a family alone needs the 256-wide tiles' better rate over a millisecond
-        assert joint.value == (0 if pinned == 256 else len(fam) - (pinned == 0 and (4096, 2**20) in fam))
+        # a family that fills the chip for over 200 us goes alone
+        alone = sum(f in fam for f in [(3000, 400_000), (4096, 2**20), (2, 2**32 - 1)])
+        assert joint.value == (0 if pinned == 256 else len(fam) - alone)
