@@ -161,9 +161,27 @@ __device__ inline ChunkView chunk_view(const BucketChunk &c, const uint32_t *tid
     return v;
 }
 
+// This thread's elements of the chunk (0 past its end), all on their way at once: a
+// whole chunk's without a test each, which would make one wait for the other.
+__device__ inline void load_chunk(const ChunkView &v, uint32_t (&x)[kBucketPer])
+{
+    const uint32_t *t = v.T + v.e0 + threadIdx.x;
+    if (v.e1 - v.e0 == kBucketChunk) {
+#pragma unroll
+        for (int k = 0; k < kBucketPer; k++)
+            x[k] = t[k * kBucketThreads];
+    } else {
+#pragma unroll
+        for (int k = 0; k < kBucketPer; k++)
+            x[k] = v.e0 + k * kBucketThreads + threadIdx.x < v.e1 ? t[k * kBucketThreads] : 0u;
+    }
+}
+
 // Counts per block: a histogram of the chunk in LDS (a map has at most 256
-// blocks, since r_i <= 2 * 2^ceil(log2 m) and m <= 127 r_0), then one atomic
-// per nonempty block.
+// blocks, since r_i <= 2 * 2^ceil(log2 m) and m <= 127 r_0; one of R blocks counts
+// each in 256 / R words, a lane to each, since 64 lanes that add to a few words
+// wait for one another), then an atomic per nonempty block.  4 * 10^7 elements,
+// Zipf: 51 us, 3.1 TB/s (76 with one word a block and a load a step).
 template <bool K24>
 __global__ void __launch_bounds__(kBucketThreads)
     bucket_count_kernel(const BucketChunk *chunks, const uint32_t *__restrict__ tids, const uint64_t *off,
@@ -172,24 +190,30 @@ __global__ void __launch_bounds__(kBucketThreads)
 {
     __shared__ uint32_t hist[256];
     const ChunkView v = chunk_view(chunks[blockIdx.x], tids, off, sorted_items, r_sorted, goff, gb, B.l0);
-    for (uint32_t j = threadIdx.x; j < v.R; j += blockDim.x)
-        hist[j] = 0;
+    hist[threadIdx.x] = 0;
     __syncthreads();
-    for (uint32_t e = v.e0 + threadIdx.x; e < v.e1; e += blockDim.x) {
-        const uint32_t y = perm_eval_k<K24>(B.sig, 0, v.T[e]);
-        atomicAdd(&hist[(y >> B.l0) & (v.R - 1u)], 1u);
-    }
+    const uint32_t rep = 256u / v.R, own = threadIdx.x & (rep - 1u);
+    uint32_t xs[kBucketPer];
+    load_chunk(v, xs);
+#pragma unroll
+    for (int k = 0; k < kBucketPer; k++)
+        if (v.e0 + k * kBucketThreads + threadIdx.x < v.e1)
+            atomicAdd(&hist[((perm_eval_k<K24>(B.sig, 0, xs[k]) >> B.l0) & (v.R - 1u)) * rep + own], 1u);
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < v.R; j += blockDim.x)
-        if (hist[j])
-            atomicAdd(&count[v.b0 + j], hist[j]);
+    const uint32_t fold = min(rep, 64u);
+    uint32_t sum = hist[threadIdx.x];
+    for (uint32_t o = 1; o < fold; o <<= 1)
+        sum += __shfl_xor(sum, o, 64);
+    if (threadIdx.x % fold == 0 && sum)
+        atomicAdd(&count[v.b0 + threadIdx.x / rep], sum);
 }
 
 // The chunk's y values into their blocks' runs: ranked per block and put in
 // block order in LDS, the chunk reserves its part of each run with one atomic,
 // and the values leave in that order, neighbouring lanes to neighbouring words
-// (large Zipf 100 us; written straight from the tidlist's order, a wavefront's 64
-// stores went to as many lines: 160).
+// (4 * 10^7 elements, Zipf: 70 us, 4.5 TB/s, as fast as a copy; 100 with one counter
+// a block; written straight from the tidlist's order, a wavefront's 64 stores went
+// to as many lines: 160).
 //
 // kWhole: every map is one chunk (its elements from ebase[p] on), so the chunk's own
 // counts are the runs: nothing is counted or scanned before, and the blocks' starts
@@ -208,20 +232,22 @@ __global__ void __launch_bounds__(kBucketThreads)
     const BucketChunk c = kWhole ? BucketChunk{p_first + blockIdx.x, 0} : chunks[blockIdx.x];
     const ChunkView v = chunk_view(c, tids, off, sorted_items, r_sorted, goff, gb, B.l0);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x / 64u;
+    const uint32_t rep = 256u / v.R, own = threadIdx.x & (rep - 1u);
     hist[threadIdx.x] = 0;
     __syncthreads();
     uint32_t ys[kBucketPer], rank[kBucketPer];
+    load_chunk(v, ys);
 #pragma unroll
     for (int k = 0; k < kBucketPer; k++) {
         const uint32_t e = v.e0 + k * kBucketThreads + threadIdx.x;
         if (e < v.e1) {
-            ys[k] = perm_eval_k<K24>(B.sig, 0, v.T[e]);
-            rank[k] = atomicAdd(&hist[(ys[k] >> B.l0) & (v.R - 1u)], 1u);
+            ys[k] = perm_eval_k<K24>(B.sig, 0, ys[k]);
+            rank[k] = atomicAdd(&hist[((ys[k] >> B.l0) & (v.R - 1u)) * rep + own], 1u);
         }
     }
     __syncthreads();
-    const uint32_t mine = hist[threadIdx.x];
-    uint32_t incl = mine;
+    const uint32_t part = hist[threadIdx.x];
+    uint32_t incl = part;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const uint32_t up = __shfl_up(incl, o, 64);
@@ -230,30 +256,31 @@ __global__ void __launch_bounds__(kBucketThreads)
     if (lane == 63)
         wsum[wave] = incl;
     __syncthreads();
-    uint32_t first = incl - mine;
+    uint32_t before = incl - part;
 #pragma unroll
     for (uint32_t w = 0; w < kBucketThreads / 64; w++)
-        first += w < wave ? wsum[w] : 0u;
+        before += w < wave ? wsum[w] : 0u;
+    hist[threadIdx.x] = before;
+    __syncthreads();
+    const uint32_t j = threadIdx.x, first = j < v.R ? hist[j * rep] : 0u;  // block j's place in `vals`
     if constexpr (kWhole) {
         const uint32_t e0 = ebase[c.p];
-        if (threadIdx.x < v.R) {
-            bstart[v.b0 + threadIdx.x] = e0 + first;
-            bucket_map[v.b0 + threadIdx.x] = c.p;
+        if (j < v.R) {
+            bstart[v.b0 + j] = e0 + first;
+            bucket_map[v.b0 + j] = c.p;
         }
-        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        if (blockIdx.x == gridDim.x - 1 && j == 0)
             bstart[v.b0 + v.R] = e0 + v.e1;
-        shift[threadIdx.x] = e0;
-    } else {
-        shift[threadIdx.x] =
-            (mine ? bstart[v.b0 + threadIdx.x] + atomicAdd(&cursor[v.b0 + threadIdx.x], mine) : 0u) - first;
+        shift[j] = e0;
+    } else if (j < v.R) {
+        const uint32_t mine = (j + 1 < v.R ? hist[(j + 1) * rep] : v.e1 - v.e0) - first;
+        shift[j] = (mine ? bstart[v.b0 + j] + atomicAdd(&cursor[v.b0 + j], mine) : 0u) - first;
     }
-    hist[threadIdx.x] = first;
-    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kBucketPer; k++) {
         const uint32_t e = v.e0 + k * kBucketThreads + threadIdx.x;
         if (e < v.e1)
-            vals[hist[(ys[k] >> B.l0) & (v.R - 1u)] + rank[k]] = ys[k];
+            vals[hist[((ys[k] >> B.l0) & (v.R - 1u)) * rep + own] + rank[k]] = ys[k];
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < v.e1 - v.e0; i += kBucketThreads) {
