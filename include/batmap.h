@@ -339,7 +339,8 @@ typedef struct {
     uint32_t max_queue;      /* submits beyond this many waiting queries get BM_EBUSY (default 1 << 16) */
     uint32_t max_batch;      /* queries admitted into one launch at most (default 64, at most 65535) */
     uint32_t flags;          /* reserved, 0 */
-    uint64_t memory_budget;  /* device bytes for in-flight queries (default 1 GiB) */
+    uint64_t memory_budget;  /* device bytes for in-flight queries (default 1 GiB); with bit rows
+                              * a stream also keeps about 100 MB of scratch */
 } bm_server_opts;
 typedef struct {
     double queued_s;   /* submit -> admitted */
