@@ -954,4 +954,18 @@ GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, i
     return set;
 }
 
+// Segments of at most 32 KB (64 rows of one are half an L2), more of them
+// while there are fewer than 32 wavefronts a CU, down to four steps each.
+TripleBitsPlan plan_triple_bits(uint64_t count, uint64_t row_words, uint32_t n_cu)
+{
+    TripleBitsPlan p;
+    p.n_runs = (count + kTripleRun - 1) / kTripleRun;
+    const uint64_t want = std::max<uint64_t>((row_words + 8191) / 8192, (n_cu * 32ull + p.n_runs - 1) / p.n_runs);
+    p.seg = (uint32_t)std::max<uint64_t>((row_words / want + 255) / 256 * 256, 1024);
+    p.n_work = p.n_runs * ((row_words + p.seg - 1) / p.seg);
+    const uint64_t waves = kTripleThreads / 64;
+    p.blocks = (uint32_t)std::min<uint64_t>((p.n_work + waves - 1) / waves, 1u << 20);
+    return p;
+}
+
 }  // namespace bm

@@ -217,4 +217,16 @@ struct GramSetPlan {
 };
 GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, int pinned = 0);
 
+// The count of triples from bit rows: runs of kTripleRun consecutive triples over
+// segments of seg words of the rows, a wavefront each, n_work in all; `blocks`
+// workgroups of kTripleThreads walk them, however many there are (a launch holds
+// fewer than 2^32 work-items).
+constexpr uint32_t kTripleRun = 8;
+constexpr uint32_t kTripleThreads = 256;
+struct TripleBitsPlan {
+    uint32_t seg = 0, blocks = 0;
+    uint64_t n_runs = 0, n_work = 0;
+};
+TripleBitsPlan plan_triple_bits(uint64_t count, uint64_t row_words, uint32_t n_cu);
+
 }  // namespace bm

@@ -11,8 +11,6 @@
 // one of the tables the three copies share, so each shared element counts
 // exactly once.  Elements whose insertion failed are added back per triple
 // (Sec. III-C).
-#include <algorithm>
-
 #include "bm_internal.h"
 
 namespace bm {
@@ -293,11 +291,10 @@ __global__ __launch_bounds__(256) void triple_compare_kernel(const uint32_t *tri
 // triples of 64 items over 10^6 transactions; the slot compare reads 8 r bytes
 // a map there at 14 VALU operations a slot, and adds the failed
 // insertions of each triple back after it (94 against 0.27 ms for the call).
-constexpr uint32_t kTripleRun = 8;
-
-__global__ __launch_bounds__(256) void triple_bits_kernel(const uint32_t *triples, uint64_t count,
-                                                          const uint32_t *bits, uint64_t ld, uint32_t seg_words,
-                                                          uint64_t n_runs, uint64_t n_work, uint32_t *out)
+__global__ __launch_bounds__(kTripleThreads) void triple_bits_kernel(const uint32_t *triples, uint64_t count,
+                                                                     const uint32_t *bits, uint64_t ld,
+                                                                     uint32_t seg_words, uint64_t n_runs,
+                                                                     uint64_t n_work, uint32_t *out)
 {
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / 64u);
@@ -465,14 +462,8 @@ hipError_t launch_triple_bits(const uint32_t *triples, uint64_t count, const uin
     hipError_t e = fill_u32(out, count, 0, s);
     if (e != hipSuccess)
         return e;
-    const uint64_t n_runs = (count + kTripleRun - 1) / kTripleRun;
-    // segments of at most 32 KB (64 rows of one are half an L2), more of them
-    // while there are fewer than 32 wavefronts a CU, down to four steps each
-    const uint64_t want = std::max<uint64_t>((ld + 8191) / 8192, (n_cu * 32ull + n_runs - 1) / n_runs);
-    const uint64_t seg = std::max<uint64_t>((ld / want + 255) / 256 * 256, 1024);
-    const uint64_t n_work = n_runs * ((ld + seg - 1) / seg);
-    const uint64_t blocks = std::min<uint64_t>((n_work + 3) / 4, 1u << 24);
-    triple_bits_kernel<<<(uint32_t)blocks, 256, 0, s>>>(triples, count, bits, ld, (uint32_t)seg, n_runs, n_work, out);
+    const TripleBitsPlan p = plan_triple_bits(count, ld, n_cu);
+    triple_bits_kernel<<<p.blocks, kTripleThreads, 0, s>>>(triples, count, bits, ld, p.seg, p.n_runs, p.n_work, out);
     return hipGetLastError();
 }
 

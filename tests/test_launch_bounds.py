@@ -1,0 +1,31 @@
+"""Launch sizes at the far end of what the calls take: a launch of 2^32 work-items or more is refused
+by the runtime, so every grid has to stay below that, whatever the sizes."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIMIT = 2**32
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("launch") / "liblaunchcheck.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC",
+                    os.path.join(ROOT, "paper_1102_1003_amd", "csrc", "plan.cpp"),
+                    os.path.join(ROOT, "tests", "launch_check.cpp"), "-o", out], check=True)
+    L = ctypes.CDLL(out)
+    L.triple_bits_items.restype = ctypes.c_uint64
+    return L
+
+
+@pytest.mark.parametrize("m,count", [
+    (1, 1), (512, 7), (10**6, 41_664), (10**6, 134_300_000), (10**7, 436 * 435 * 434 // 6),
+    (10**7, 437 * 436 * 435 // 6), (2**32 - 1, 2**31), (1, 2**40),
+])
+def test_triples_from_bits(lib, m, count):
+    covered = ctypes.c_int()
+    items = lib.triple_bits_items(ctypes.c_uint64(count), ctypes.c_uint32(m), 256, ctypes.byref(covered))
+    assert covered.value and 0 < items < LIMIT
