@@ -377,10 +377,10 @@ __device__ __forceinline__ void gram_reduce(const GramArgs &g, uint32_t block, u
 }
 
 template <int BR, int BC, int WR, int WC, int Y>
-__global__ void __launch_bounds__(256) gram_reduce_kernel(const GramArgs g)
+__global__ void __launch_bounds__(kReduceThreads) gram_reduce_kernel(const GramArgs g, uint32_t first)
 {
-    __shared__ uint4 lds[256];
-    gram_reduce<BR, BC, WR, WC, Y>(g, blockIdx.x, lds);
+    __shared__ uint4 lds[kReduceThreads];
+    gram_reduce<BR, BC, WR, WC, Y>(g, first + blockIdx.x, lds);
 }
 
 __global__ void __launch_bounds__(256) gram_reduce_jobs_kernel(const GramJob *jobs, uint32_t n)
@@ -407,23 +407,23 @@ __global__ void __launch_bounds__(256) gram_reduce_jobs_kernel(const GramJob *jo
 }
 
 template <int BR, int BC, int WR, int WC>
-hipError_t run_gram(const GramArgs &g, uint32_t tiles, bool split, hipStream_t s)
+hipError_t run_gram(const GramArgs &g, const GramPlan &p, hipStream_t s)
 {
-    constexpr uint32_t R = 32 * BR * WR, C = 32 * BC * WC;
     bit_gram_kernel<BR, BC, WR, WC><<<g.W, 64 * WR * WC, 0, s>>>(g);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !split)
+    if (p.ws_floats == 0)
         return e;
-    const uint32_t per_tile = g.W / tiles;  // parts of a tile, about
-    if (per_tile >= 128)
-        gram_reduce_kernel<BR, BC, WR, WC, 64><<<tiles * (R * C / 16), 256, 0, s>>>(g);
-    else if (per_tile >= 32)
-        gram_reduce_kernel<BR, BC, WR, WC, 16><<<tiles * (R * C / 64), 256, 0, s>>>(g);
-    else if (per_tile >= 8)
-        gram_reduce_kernel<BR, BC, WR, WC, 4><<<tiles * (R * C / 256), 256, 0, s>>>(g);
-    else
-        gram_reduce_kernel<BR, BC, WR, WC, 1><<<tiles * (R * C / 1024), 256, 0, s>>>(g);
-    return hipGetLastError();
+    const uint32_t fold = gram_reduce_fold(p, 64);
+    auto *kernel = fold == 64   ? gram_reduce_kernel<BR, BC, WR, WC, 64>
+                   : fold == 16 ? gram_reduce_kernel<BR, BC, WR, WC, 16>
+                   : fold == 4  ? gram_reduce_kernel<BR, BC, WR, WC, 4>
+                                : gram_reduce_kernel<BR, BC, WR, WC, 1>;
+    const uint64_t blocks = gram_reduce_blocks(p, fold);
+    for (uint64_t first = 0; first < blocks && e == hipSuccess; first += kReduceGrid) {
+        kernel<<<gram_reduce_launch(blocks, first), kReduceThreads, 0, s>>>(g, (uint32_t)first);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 GramArgs gram_args(const GramPlan &p, const BitMat &a, const BitMat &b, uint32_t *out, uint64_t n_out, float *ws)
@@ -465,11 +465,10 @@ hipError_t launch_gram(const GramPlan &p, const BitMat &a, const BitMat &b, uint
     if (a.ld != b.ld || a.ld != (uint64_t)p.stages * (kGramStage / 32) || (p.ws_floats && !ws))
         return hipErrorInvalidValue;
     const GramArgs g = gram_args(p, a, b, out, n_out, ws);
-    const bool split = p.ws_floats != 0;
     switch (p.tile) {
-    case 256: return run_gram<4, 2, 2, 4>(g, p.tiles, split, s);
-    case 128: return run_gram<2, 2, 2, 2>(g, p.tiles, split, s);
-    default: return run_gram<1, 1, 2, 2>(g, p.tiles, split, s);
+    case 256: return run_gram<4, 2, 2, 4>(g, p, s);
+    case 128: return run_gram<2, 2, 2, 2>(g, p, s);
+    default: return run_gram<1, 1, 2, 2>(g, p, s);
     }
 }
 
@@ -483,13 +482,12 @@ GramJobs gram_jobs(const GramSetPlan &set, const BitMat *a, uint32_t *const *out
         GramJob &o = jobs[j.n++];
         o.g = gram_args(p, a[q], a[q], out[q], a[q].n, ws);
         o.tile = (uint32_t)p.tile;
-        const uint32_t per_tile = p.tiles ? p.groups / p.tiles : 0;
-        o.fold = per_tile >= 32 ? 16 : per_tile >= 8 ? 4 : 1;
+        o.fold = gram_reduce_fold(p, 16);
         o.w0 = j.groups;
         o.r0 = j.reduce_blocks;
         j.groups += p.groups;
         if (p.ws_floats)
-            j.reduce_blocks += p.tiles * (o.tile * o.tile * o.fold / 1024);
+            j.reduce_blocks += (uint32_t)gram_reduce_blocks(p, o.fold);
         ws += p.ws_floats;
     }
     return j;

@@ -204,6 +204,28 @@ struct GramPlan {
 GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0,
                    uint64_t max_ws = UINT64_MAX);
 
+// The addition of a plan's parts: `fold` threads share the parts of the same four
+// counts, and workgroups of kReduceThreads take 1024 / fold counts each, all of
+// them in launches of at most kReduceGrid (a launch holds fewer than 2^32
+// work-items; the pairs of 185,089 items are past that).
+constexpr uint32_t kReduceThreads = 256;
+constexpr uint32_t kReduceGrid = 1u << 23;
+inline uint32_t gram_reduce_fold(const GramPlan &p, uint32_t most)
+{
+    const uint32_t per_tile = p.tiles ? p.groups / p.tiles : 0;  // parts of a tile, about
+    const uint32_t fold = per_tile >= 128 ? 64 : per_tile >= 32 ? 16 : per_tile >= 8 ? 4 : 1;
+    return fold < most ? fold : most;
+}
+inline uint64_t gram_reduce_blocks(const GramPlan &p, uint32_t fold)
+{
+    return (uint64_t)p.tiles * ((uint32_t)p.tile * p.tile * fold / 1024);
+}
+// Workgroups of the launch that starts with workgroup `first` of `blocks`.
+inline uint32_t gram_reduce_launch(uint64_t blocks, uint64_t first)
+{
+    return (uint32_t)(blocks - first < kReduceGrid ? blocks - first : kReduceGrid);
+}
+
 // The pairs of several families, counted by one launch where that pays.
 struct GramShape {
     uint32_t n;

@@ -13,3 +13,24 @@ extern "C" uint64_t triple_bits_items(uint64_t count, uint32_t m, uint32_t n_cu,
                p.n_work / p.n_runs * p.seg >= words && p.seg % 256 == 0 && p.blocks > 0;
     return (uint64_t)p.blocks * bm::kTripleThreads;
 }
+
+// Work-items of the largest launch that adds the parts of na x nb counts; *covered:
+// whether the launches follow one another over all of them.
+extern "C" uint64_t gram_reduce_items(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned,
+                                      int *covered)
+{
+    const bm::GramPlan p = bm::plan_gram(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned);
+    const uint32_t fold = bm::gram_reduce_fold(p, 64);
+    const uint64_t blocks = bm::gram_reduce_blocks(p, fold);
+    uint64_t most = 0, first = 0;
+    while (first < blocks) {
+        const uint64_t n = bm::gram_reduce_launch(blocks, first);
+        most = n > most ? n : most;
+        first += bm::kReduceGrid;
+        if (n != bm::kReduceGrid)
+            break;
+    }
+    *covered = first >= blocks && blocks * 1024 == (uint64_t)p.tiles * p.tile * p.tile * fold && blocks < (1ull << 32) &&
+               (uint64_t)p.groups * (p.tile == 256 ? 512 : 256) < (1ull << 32);
+    return most * bm::kReduceThreads;
+}

@@ -17,7 +17,7 @@ def lib(tmp_path_factory):
                     os.path.join(ROOT, "paper_1102_1003_amd", "csrc", "plan.cpp"),
                     os.path.join(ROOT, "tests", "launch_check.cpp"), "-o", out], check=True)
     L = ctypes.CDLL(out)
-    L.triple_bits_items.restype = ctypes.c_uint64
+    L.triple_bits_items.restype = L.gram_reduce_items.restype = ctypes.c_uint64
     return L
 
 
@@ -29,3 +29,15 @@ def test_triples_from_bits(lib, m, count):
     covered = ctypes.c_int()
     items = lib.triple_bits_items(ctypes.c_uint64(count), ctypes.c_uint32(m), 256, ctypes.byref(covered))
     assert covered.value and 0 < items < LIMIT
+
+
+@pytest.mark.parametrize("pinned", [0, 64, 128, 256])
+@pytest.mark.parametrize("na,nb,m", [
+    (2, 2, 1), (4096, 4096, 2**20), (185_088, 185_088, 100_000), (185_089, 185_089, 100_000),
+    (370_000, 370_000, 300_000),                             # 2.7 * 10^11 bytes of counts
+    (185_000, 360_000, 50_000), (16, 16_000_000, 512),       # rectangles
+])
+def test_parts_of_the_product(lib, na, nb, m, pinned):
+    covered = ctypes.c_int()
+    items = lib.gram_reduce_items(na, nb, int(na == nb), ctypes.c_uint32(m), 256, pinned, ctypes.byref(covered))
+    assert covered.value and items < LIMIT
