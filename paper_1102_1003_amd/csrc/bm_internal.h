@@ -359,13 +359,11 @@ hipError_t radix_sort_pairs_from(const uint32_t *keys_in, uint32_t *keys, uint32
 
 // Ingest.
 hipError_t launch_expand_rows(const uint64_t *row_off, uint32_t m, uint32_t *row_of, hipStream_t s);
-// Ingest by bit rows: whether the kernel's LDS block for n items fits `lds`
-// bytes; the rows (and the zero row) of a transactions CSR, bit 0 of *flag set
-// when an item id is >= n; the ones of every (item, segment), of which there
-// are bit_ingest_segments(); and, with those scanned into start (one more entry:
-// the total), every item's tids and their offsets off[0 .. n].
-bool bit_ingest_fits(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu);
-uint64_t bit_ingest_segments(uint32_t m, uint32_t n);
+// Ingest by bit rows, where bit_ingest_fits(): the rows (and the zero row) of a
+// transactions CSR, bit 0 of *flag set when an item id is >= n; the ones of every
+// (item, segment), of which there are bit_ingest_segments(); and, with those
+// scanned into start (one more entry: the total), every item's tids and their
+// offsets off[0 .. n].
 hipError_t launch_txn_bits(const uint64_t *row_off, const uint32_t *items, uint32_t m, uint32_t n, uint32_t lds,
                            uint32_t n_cu, uint32_t *bits, uint32_t *flag, hipStream_t s);
 hipError_t launch_bit_count(const uint32_t *bits, uint32_t m, uint32_t n, uint32_t *count, hipStream_t s);

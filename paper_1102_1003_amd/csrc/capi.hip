@@ -565,10 +565,11 @@ double compare_us(double slot_pairs, uint32_t planes, double r_max, double fixed
 // Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
 double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (rows * row_words + tids) * 4 / 2.5e6; }
 
-// Whether `rows` bit rows may be made: at most a sixteenth of the device's memory.
+// Whether `rows` bit rows may be made: at most a sixteenth of the device's memory,
+// and by one launch.
 bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
 {
-    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16;
+    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16 && grid_fits(bit_row_blocks(rows, row_words), kBitRowThreads);
 }
 
 // A stream being captured takes the slot compare, as ever (the bitmap route's

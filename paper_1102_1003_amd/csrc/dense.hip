@@ -50,9 +50,8 @@ __device__ inline uint64_t wave_lower_bound(const uint32_t *a, uint64_t lo, uint
 // Four consecutive tids a thread: the bits of one word are merged before the
 // LDS atomic (in a dense row all four share a word).  Row n_rows is all zero:
 // the rows that pad a tile read it.
-constexpr uint32_t kBitSeg = 1u << 17;  // transactions: 16 KB of LDS, eight workgroups a CU
-
-__global__ void __launch_bounds__(256) bit_rows_kernel(const uint64_t *__restrict__ off,
+// A segment of 2^17 transactions takes 16 KB of LDS: eight workgroups a CU.
+__global__ void __launch_bounds__(kBitRowThreads) bit_rows_kernel(const uint64_t *__restrict__ off,
                                                        const uint32_t *__restrict__ tids,
                                                        const uint32_t *__restrict__ items, uint32_t n_rows,
                                                        uint64_t ld, uint32_t n_seg, uint32_t *__restrict__ bits)
@@ -450,10 +449,10 @@ hipError_t launch_bit_rows(const uint64_t *off, const uint32_t *tids, const uint
 {
     const uint64_t ld = bit_row_words(m);
     const uint64_t n_seg = (ld + kBitSeg / 32 - 1) / (kBitSeg / 32);
-    if (((uint64_t)n_rows + 1) * n_seg > 0x7FFFFFFFull)
+    const uint64_t blocks = bit_row_blocks(n_rows, ld);
+    if (!grid_fits(blocks, kBitRowThreads))
         return hipErrorInvalidValue;
-    bit_rows_kernel<<<(uint32_t)((n_rows + 1) * n_seg), 256, 0, s>>>(off, tids, items, n_rows, ld, (uint32_t)n_seg,
-                                                                     bits);
+    bit_rows_kernel<<<(uint32_t)blocks, kBitRowThreads, 0, s>>>(off, tids, items, n_rows, ld, (uint32_t)n_seg, bits);
     return hipGetLastError();
 }
 

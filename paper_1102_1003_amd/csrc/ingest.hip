@@ -239,8 +239,6 @@ __global__ void offsets_and_dups_kernel(const uint32_t *keys, const uint32_t *va
 // chunks run on one XCD, whose L2 puts the pieces of a line together.  Bound by
 // memory: m = 10^6, n = 2000, 4 * 10^7 incidences (160 MB in, 250 MB out) 125 us,
 // and 39 us to count them.
-constexpr int kTxnBitsThreads = 1024;
-
 template <int TW>
 __global__ void __launch_bounds__(kTxnBitsThreads)
     txn_bits_kernel(const uint64_t *__restrict__ row_off, const uint32_t *__restrict__ items, uint32_t m, uint32_t n,
@@ -306,8 +304,6 @@ __global__ void __launch_bounds__(kTxnBitsThreads)
 }
 
 // Ones of every (row, segment of kSegWords words), and a 0 behind them.
-constexpr uint32_t kSegWords = 1024;
-
 __global__ void __launch_bounds__(256) bit_count_kernel(const uint32_t *__restrict__ bits, uint64_t ld,
                                                         uint32_t n_seg, uint32_t *count)
 {
@@ -514,37 +510,12 @@ hipError_t launch_validate_sets(const uint64_t *off, const uint32_t *tids, uint3
     return hipGetLastError();
 }
 
-// Words of a row that one workgroup of txn_bits_kernel covers, for n items: the
-// most (whole 128-byte lines, at best) whose block fits lds bytes, but enough
-// workgroups for the chip; 0: too many items.
-static uint32_t txn_bits_words(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
-{
-    uint32_t best = 0;
-    for (uint32_t tw : {8u, 16u, 32u}) {
-        const uint64_t need = ((uint64_t)n + 1) * (tw + 1) * 4 + (32 * tw + 1) * 4;
-        if (need <= lds && (best == 0 || (uint64_t)m / (32 * tw) >= n_cu))
-            best = tw;
-    }
-    return best;
-}
-
-bool bit_ingest_fits(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
-{
-    const uint64_t n_seg = (bit_row_words(m) + kSegWords - 1) / kSegWords;
-    return txn_bits_words(m, n, lds, n_cu) != 0 && n * n_seg <= 0x7FFFFFFFull;
-}
-
-uint64_t bit_ingest_segments(uint32_t m, uint32_t n)
-{
-    return n * ((bit_row_words(m) + kSegWords - 1) / kSegWords);
-}
-
 hipError_t launch_txn_bits(const uint64_t *row_off, const uint32_t *items, uint32_t m, uint32_t n, uint32_t lds,
                            uint32_t n_cu, uint32_t *bits, uint32_t *flag, hipStream_t s)
 {
     const uint64_t ld = bit_row_words(m);
     const uint32_t tw = txn_bits_words(m, n, lds, n_cu);
-    if (tw == 0)
+    if (!bit_ingest_fits(m, n, lds, n_cu))
         return hipErrorInvalidValue;
     const uint32_t n_chunks = (uint32_t)((ld + tw - 1) / tw), per_xcd = (n_chunks + kXcds - 1) / kXcds;
     const uint32_t bytes = (n + 1) * (tw + 1) * 4;
@@ -556,7 +527,7 @@ hipError_t launch_txn_bits(const uint64_t *row_off, const uint32_t *items, uint3
         if (e != hipSuccess)
             return e;
     }
-    const uint32_t grid = per_xcd * kXcds;
+    const uint32_t grid = (uint32_t)txn_bits_blocks(m, tw);
     if (tw == 8)
         txn_bits_kernel<8><<<grid, kTxnBitsThreads, bytes, s>>>(row_off, items, m, n, ld, n_chunks, per_xcd, bits, flag);
     else if (tw == 16)

@@ -954,6 +954,23 @@ GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, i
     return set;
 }
 
+uint32_t txn_bits_words(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
+{
+    uint32_t best = 0;
+    for (uint32_t tw : {8u, 16u, 32u}) {
+        const uint64_t need = ((uint64_t)n + 1) * (tw + 1) * 4 + (32 * tw + 1) * 4;
+        if (need <= lds && (best == 0 || (uint64_t)m / (32 * tw) >= n_cu))
+            best = tw;
+    }
+    return best;
+}
+
+bool bit_ingest_fits(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
+{
+    const uint32_t tw = txn_bits_words(m, n, lds, n_cu);
+    return tw != 0 && grid_fits(txn_bits_blocks(m, tw), kTxnBitsThreads) && grid_fits(bit_ingest_segments(m, n), 256);
+}
+
 // Segments of at most 32 KB (64 rows of one are half an L2), more of them
 // while there are fewer than 32 wavefronts a CU, down to four steps each.
 TripleBitsPlan plan_triple_bits(uint64_t count, uint64_t row_words, uint32_t n_cu)

@@ -183,6 +183,39 @@ inline uint64_t bit_row_words(uint32_t m)
 // transactions: counts stay exact whole numbers).
 constexpr uint64_t kGramMaxStages = (1u << 24) / kGramStage;
 
+// A launch holds fewer than 2^32 work-items.
+inline bool grid_fits(uint64_t blocks, uint64_t threads) { return blocks < (1ull << 32) / threads; }
+
+// Workgroups that write n_rows bit rows and the zero row behind them: one per row
+// and segment of kBitSeg transactions.
+constexpr uint32_t kBitSeg = 1u << 17;
+constexpr uint32_t kBitRowThreads = 256;
+inline uint64_t bit_row_blocks(uint64_t n_rows, uint64_t row_words)
+{
+    return (n_rows + 1) * ((row_words + kBitSeg / 32 - 1) / (kBitSeg / 32));
+}
+
+// Words of a row that one workgroup of the transactions' bit rows covers, for n
+// items: the most (whole 128-byte lines, at best) whose block fits lds bytes, but
+// enough workgroups for the chip; 0: too many items.
+uint32_t txn_bits_words(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu);
+// Workgroups (of kTxnBitsThreads) for tw words each.
+constexpr uint32_t kTxnBitsThreads = 1024;
+inline uint64_t txn_bits_blocks(uint32_t m, uint32_t tw)
+{
+    return ((bit_row_words(m) + tw - 1) / tw + kXcds - 1) / kXcds * kXcds;
+}
+// Segments of kSegWords words that an item's rows are counted and expanded in.
+constexpr uint32_t kSegWords = 1024;
+inline uint64_t bit_ingest_segments(uint32_t m, uint32_t n)
+{
+    return n * ((bit_row_words(m) + kSegWords - 1) / kSegWords);
+}
+// Whether transactions can go through bit rows: the block for n items fits `lds`
+// bytes and every launch holds its workgroups (which keeps chunks' first
+// transactions below 2^32).
+bool bit_ingest_fits(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu);
+
 // How a Gram matrix is cut: tiles of tile x tile counts (tri: those on and
 // above the diagonal), each over `stages` stages.  The (tile, stage) list in
 // tile order is cut into `groups` equal runs, run w = [U w / W, U (w + 1) / W)

@@ -34,3 +34,24 @@ extern "C" uint64_t gram_reduce_items(uint32_t na, uint32_t nb, int tri, uint32_
                (uint64_t)p.groups * (p.tile == 256 ? 512 : 256) < (1ull << 32);
     return most * bm::kReduceThreads;
 }
+
+// Work-items of the launches that make bit rows from tidlists (rows), and from
+// transactions and tidlists from them (ingest; 0: not done that way).
+extern "C" uint64_t bit_rows_items(uint64_t rows, uint32_t m, int *fits)
+{
+    const uint64_t blocks = bm::bit_row_blocks(rows, bm::bit_row_words(m));
+    *fits = bm::grid_fits(blocks, bm::kBitRowThreads);
+    return blocks * bm::kBitRowThreads;
+}
+extern "C" uint64_t bit_ingest_items(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu, int *whole)
+{
+    *whole = 1;
+    if (!bm::bit_ingest_fits(m, n, lds, n_cu))
+        return 0;
+    const uint32_t tw = bm::txn_bits_words(m, n, lds, n_cu);
+    const uint64_t blocks = bm::txn_bits_blocks(m, tw), last = (bm::bit_row_words(m) - 1) / tw;
+    // every word of a row has a workgroup, and its first transaction 32 bits
+    *whole = blocks > last && last * (32ull * tw) < (1ull << 32);
+    const uint64_t rows = blocks * bm::kTxnBitsThreads, segs = bm::bit_ingest_segments(m, n) * 256;
+    return rows > segs ? rows : segs;
+}

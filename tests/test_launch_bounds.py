@@ -17,7 +17,8 @@ def lib(tmp_path_factory):
                     os.path.join(ROOT, "paper_1102_1003_amd", "csrc", "plan.cpp"),
                     os.path.join(ROOT, "tests", "launch_check.cpp"), "-o", out], check=True)
     L = ctypes.CDLL(out)
-    L.triple_bits_items.restype = L.gram_reduce_items.restype = ctypes.c_uint64
+    for f in ("triple_bits_items", "gram_reduce_items", "bit_rows_items", "bit_ingest_items"):
+        getattr(L, f).restype = ctypes.c_uint64
     return L
 
 
@@ -41,3 +42,21 @@ def test_parts_of_the_product(lib, na, nb, m, pinned):
     covered = ctypes.c_int()
     items = lib.gram_reduce_items(na, nb, int(na == nb), ctypes.c_uint32(m), 256, pinned, ctypes.byref(covered))
     assert covered.value and items < LIMIT
+
+
+@pytest.mark.parametrize("rows,m", [(1, 1), (2**24 - 2, 512), (2**24 - 1, 512), (2**24, 512), (511, 2**32 - 1),
+                                    (512, 2**32 - 1), (280_000_000, 512)])
+def test_bit_rows(lib, rows, m):
+    fits = ctypes.c_int()
+    items = lib.bit_rows_items(ctypes.c_uint64(rows), ctypes.c_uint32(m), ctypes.byref(fits))
+    assert bool(fits.value) == (items < LIMIT)
+
+
+@pytest.mark.parametrize("m", [1, 10**6, 2**31, 2**32 - 8193, 2**32 - 8192, 2**32 - 512, 2**32 - 1])
+@pytest.mark.parametrize("n", [1, 34, 1200, 2400, 4500, 10**6])
+def test_transactions_through_bit_rows(lib, m, n):
+    whole = ctypes.c_int()
+    items = lib.bit_ingest_items(ctypes.c_uint32(m), n, 163_840, 256, ctypes.byref(whole))
+    assert whole.value and items < LIMIT
+    if m <= 10**6 and n <= 4500:
+        assert items
