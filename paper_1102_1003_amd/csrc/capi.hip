@@ -572,9 +572,9 @@ bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
     return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16 && grid_fits(bit_row_blocks(rows, row_words), kBitRowThreads);
 }
 
-// A stream being captured takes the slot compare, as ever (the bitmap route's
-// rows and scratch would become part of the graph), unless the index was built
-// without a plan because its rows are there: then each tile is one workgroup's.
+// Whether a stream is being captured.  What is made then (a plan and its upload,
+// bit rows, scratch) would belong to the graph and hold nothing until it runs, so
+// a captured call only launches over what earlier calls have left in the index.
 bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -724,6 +724,8 @@ bm_status ensure_plan(bm_index *idx, uint32_t first, hipStream_t st = nullptr, s
     bm_context *ctx = idx->ctx;
     if (idx->planned_first == first && idx->planned_gen == ctx->tune_gen)
         return BM_OK;
+    if (capturing(st ? st : ctx->stream))
+        return fail(ctx, BM_EINVAL, "no plan of the compare to capture: make the call once before the capture");
     Plan plan;
     const bool single = single_launch(ctx, idx->planes);
     if (early && early->valid()) {
@@ -1853,18 +1855,8 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
     }
     if (!go)
         return BM_OK;
-    if (capturing(s)) {
-        if (list || !idx->bits.p || idx->planned_first != UINT32_MAX)
-            return BM_OK;
-        const GramPlan one = plan_gram(k, k, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile(), 0);
-        if (one.ws_floats)
-            return BM_OK;
-        Span sp(ctx, PH_COMPARE);
-        const BitMat a = whole_bits(idx);
-        HIPC(ctx, launch_gram(one, a, a, out, k, nullptr, s));
-        taken = true;
+    if (capturing(s))
         return BM_OK;
-    }
     DevBuf<float> ws;
     DevBuf<uint32_t> own;
     if (ws.alloc(p.ws_floats) != hipSuccess || (list && ids.alloc(k) != hipSuccess))
@@ -1964,7 +1956,7 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
         idx->txn_start.swap(start);
         idx->txn_items.swap(items);
         idx->txn_pairs = pairs;
-    } else if ((!forced && txn_us(idx, (double)idx->txn_pairs) >= other_us) || capturing(s)) {
+    } else if (!forced && txn_us(idx, (double)idx->txn_pairs) >= other_us) {
         return BM_OK;
     }
     Span sp(ctx, PH_COMPARE);
@@ -1973,18 +1965,13 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
     return BM_OK;
 }
 
-// Counts of all pairs among sorted indices >= first into the packed buffer `out` (device, zeroed here).
-bm_status count_pairs(bm_index *idx, uint32_t first, uint32_t *out)
+// Counts of all pairs of the resident plan into the packed buffer `out` (device, zeroed here).
+bm_status compare_pairs(bm_index *idx, uint32_t *out)
 {
     bm_context *ctx = idx->ctx;
     {
         Span sp(ctx, PH_FILL);
         HIPC(ctx, fill_u32(out, n_pairs(idx->n), 0, ctx->stream));
-    }
-    {
-        bm_status st = ensure_plan(idx, first);
-        if (st != BM_OK)
-            return st;
     }
     ctx->slot_pairs = idx->planned_slot_pairs;
     {
@@ -1996,6 +1983,37 @@ bm_status count_pairs(bm_index *idx, uint32_t first, uint32_t *out)
     Span sp(ctx, PH_APPLY);
     HIPC(ctx, launch_apply_corrections(idx->corr.p, idx->n_corr, out, idx->n, ctx->stream));
     return BM_OK;
+}
+
+// The same among sorted indices >= first, planned here where the index's plan is another.
+bm_status count_pairs(bm_index *idx, uint32_t first, uint32_t *out)
+{
+    BMC(ensure_plan(idx, first));
+    return compare_pairs(idx, out);
+}
+
+// All pair counts while the stream is captured, from what the index holds: slots
+// by a resident plan (one of either launch form: each is complete), else the
+// grouped incidences, else the bit rows, each tile one workgroup's (no scratch).
+bm_status captured_pairs(bm_index *idx, uint32_t *out)
+{
+    bm_context *ctx = idx->ctx;
+    if (idx->planned_first == 0)
+        return compare_pairs(idx, out);
+    Span sp(ctx, PH_COMPARE);
+    if (idx->txn_items.p) {
+        HIPC(ctx, launch_txn_rows(idx->off.p, idx->tids.p, idx->txn_start.p, idx->txn_items.p, idx->n, out, ctx->stream));
+        return BM_OK;
+    }
+    if (idx->bits.p) {
+        const BitMat a = whole_bits(idx);
+        const GramPlan p = plan_gram(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile(), 0);
+        if (p.ws_floats == 0) {
+            HIPC(ctx, launch_gram(p, a, a, out, idx->n, nullptr, ctx->stream));
+            return BM_OK;
+        }
+    }
+    return fail(ctx, BM_EINVAL, "nothing to count the pairs from under capture: make the call once before the capture");
 }
 
 }  // namespace
@@ -2646,6 +2664,8 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
         return fail(ctx, BM_EINVAL, "index built with min_support > 0 has no BatMap for some items");
     HIPC(ctx, hipSetDevice(ctx->device));
     bool host = ptr_kind(out) == PTR_HOST;
+    if (!host && capturing(ctx->stream))
+        return captured_pairs(idx, out);
     uint32_t *dst = out;
     if (host) {
         HIPC(ctx, idx->pairbuf.ensure(np));

@@ -1,0 +1,103 @@
+"""Captured calls count from what the index holds, and make nothing inside the capture; every replay against
+the oracle's merge, with eager work and other builds on the context in between."""
+import numpy as np
+import pytest
+
+import datagen
+import oracle
+
+torch = pytest.importorskip("torch")
+bm = pytest.importorskip("paper_1102_1003_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def stream_ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    stream = torch.cuda.Stream()
+    c = bm.Context(0, stream)
+    yield stream, c
+    c.close()
+
+
+def replays(stream, c, call, out, want, between):
+    """Captures call(out) and replays it, with between() before each replay."""
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        call(out)
+    for rep in range(3):
+        between()
+        out.fill_(-1)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+    del g
+
+
+@pytest.mark.parametrize("route", [None, "0", "1", "2"])
+def test_after_an_eager_call(stream_ctx, monkeypatch, route):
+    """More items than a build plans for: the eager call leaves a plan, rows or grouped incidences."""
+    stream, c = stream_ctx
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    m, n = 200_000, 5_000
+    off, tids = datagen.bernoulli_sets(m, n, 0.0005, seed=5)
+    want = oracle.all_pairs(off, tids)
+    idx = bm.Index.from_sets(c, m, off, tids)
+    out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    c.set_profiling(True)
+    idx.all_pair_supports(out)
+    assert (c.timings()["compare_slot_pairs"] > 0) == (route == "0")     # by time: the incidences
+    c.set_profiling(False)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+
+    def between():
+        o, t = datagen.bernoulli_sets(9_000, 4_500, 0.01, seed=6)
+        other = bm.Index.from_sets(c, 9_000, o, t)
+        other.all_pair_supports()
+        other.close()
+    replays(stream, c, idx.all_pair_supports, out, want, between)
+    assert np.array_equal(idx.all_pair_supports(), want)
+
+
+@pytest.mark.parametrize("route", [None, "0"])
+def test_nothing_made_inside(stream_ctx, monkeypatch, route):
+    """A capture before any eager call is refused where there is nothing to count from, and leaves no plan behind."""
+    stream, c = stream_ctx
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    m, n = 30_000, 4_200
+    off, tids = datagen.bernoulli_sets(m, n, 0.001, seed=7)
+    want = oracle.all_pairs(off, tids)
+    idx = bm.Index.from_sets(c, m, off, tids)
+    out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        with pytest.raises(bm.BatmapError) as e:
+            idx.all_pair_supports(out)
+        out.zero_()
+    assert e.value.status == bm.BM_EINVAL
+    del g
+    for rep in range(2):
+        assert np.array_equal(idx.all_pair_supports(), want)
+    replays(stream, c, idx.all_pair_supports, out, want, lambda: None)
+
+
+def test_plan_of_the_other_launch_form(stream_ctx, monkeypatch):
+    """A plan made for one launch form still serves a capture after the form has changed."""
+    stream, c = stream_ctx
+    monkeypatch.setenv("BM_BITMAP_ROUTE", "0")
+    m, n = 20_000, 400
+    off, tids = datagen.bernoulli_sets(m, n, 0.02, seed=8)
+    want = oracle.all_pairs(off, tids)
+    idx = bm.Index.from_sets(c, m, off, tids)
+    out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    c.set_launch_mode(True)
+    replays(stream, c, idx.all_pair_supports, out, want, lambda: None)
+    c.set_launch_mode(False)
