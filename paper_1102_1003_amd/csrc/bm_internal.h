@@ -502,13 +502,13 @@ hipError_t launch_subset_prepare(const uint32_t *items, uint32_t k, uint32_t n, 
                                  uint32_t *pos_of_item, uint32_t *flag, hipStream_t s);
 
 // Counting by transactions (sparse.hip): count[t] += 1 per incidence (zeroed
-// by the caller) and *pairs += sum of count (count - 1) / 2; then, with the
+// by the caller) and *walk filled (zeroed too); then, with the
 // counts scanned into starts, items grouped by transaction (cursor: a copy of
 // the starts, used up); then the packed triangle, a workgroup per row, the
 // counters of a row in LDS (at most kTxnMaxItems items).
 constexpr uint32_t kTxnMaxItems = 16384;
-hipError_t launch_txn_count(const uint32_t *tids, uint64_t nnz, uint32_t m, uint32_t *count,
-                            unsigned long long *pairs, hipStream_t s);
+hipError_t launch_txn_count(const uint32_t *tids, uint64_t nnz, uint32_t m, uint32_t *count, TxnWalk *walk,
+                            hipStream_t s);
 hipError_t launch_txn_scatter(const uint64_t *off, const uint32_t *tids, uint32_t n, uint32_t *cursor,
                               uint32_t *items, hipStream_t s);
 hipError_t launch_txn_rows(const uint64_t *off, const uint32_t *tids, const uint32_t *start, const uint32_t *items,

@@ -414,8 +414,8 @@ struct bm_index {
     DevBuf<float> gram_ws;       // bm_all_pair_supports_dense
     // counting by transactions: items grouped by transaction, made at first use
     DevBuf<uint32_t> txn_start, txn_items;
-    uint64_t txn_pairs = 0;   // sum over transactions of their pairs
-    bool txn_dense = false;   // more pairs than independent sets would have: made for nothing
+    TxnWalk txn_walk;
+    bool txn_dense = false;   // longer to walk than independent sets would be: made for nothing
 };
 
 struct bm_batch {
@@ -1885,26 +1885,16 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double oth
     return BM_OK;
 }
 
-// Expected time of counting by transactions (us) with `pairs` pairs in all
-// transactions: the triangle written at 3 TB/s, 9 ps an incidence and 4.6 ps for
-// each item of its transaction; or the largest set, walked by one workgroup, 1 us
-// a round of its lanes and 0.25 us for each item of a transaction.  Measured
-// (MI355X, us, transactions / bits / slots): 2^20 x 8192 at 0.01 %: 53 / 9396 /
-// 802; 0.05 %: 189 / 9357 / 4718; 0.2 %: 1506 / 9400 / 12,888; 0.4 %: 5549 /
-// 9397 / 13,347; 10^6 x 4000 Zipf(1.0) at 0.05 % (largest set 225,199): 1741 /
-// 2530 / 3516; 10^6 x 8000 Zipf(1.0) at 0.1 % (836,079): 10,404 / 8914 / 12,818.
-double txn_us(const bm_index *idx, double pairs)
+double txn_us(const bm_index *idx, const TxnWalk &w)
 {
-    const double nnz = std::max<double>((double)idx->nnz, 1), walked = 2 * pairs + nnz;
-    const double lanes = idx->n > 8192 ? 600 : 256;
-    return 10 + 4.0 * (double)n_pairs(idx->n) / 3e6 +
-           std::max(4.6e-6 * walked + 9e-6 * nnz, idx->h_sizes_sorted.back() / lanes * (1 + 0.25 * walked / nnz));
+    return txn_us(idx->n, idx->nnz, idx->h_sizes_sorted.back(), w, (uint32_t)idx->ctx->n_cu);
 }
 
 // All pair counts of the index into the packed triangle `out` (device, every
 // entry written) by transactions, when that is expected to take less than
 // other_us.  The grouped incidences are made at first use and kept; sets that
-// turn out to share far more than independent ones would are left to the others.
+// turn out to share far more than independent ones would, or that long transactions
+// run through, are left to the others.
 bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
 {
     taken = false;
@@ -1917,13 +1907,14 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
         // counted, scanned and grouped: a device atomic an incidence in two
         // passes (4.3 * 10^6 incidences: 160 and 370 us)
         const double nnz = (double)idx->nnz, make_us = 60 + nnz * 1.25e-4 + idx->m / 1e5;
-        if (!forced && txn_us(idx, 0) >= other_us)
+        TxnWalk w;
+        if (!forced && txn_us(idx, w) >= other_us)
             return BM_OK;
         double squares = 0;
         for (uint32_t sz : idx->h_sizes_sorted)
             squares += (double)sz * sz;
-        const double guess = std::max(0.0, (nnz * nnz - squares) / (2.0 * idx->m));  // independent sets
-        const double us = txn_us(idx, guess);
+        w.pairs = (uint64_t)std::max(0.0, (nnz * nnz - squares) / (2.0 * idx->m));  // independent sets
+        const double us = txn_us(idx, w);
         if (!forced && us + make_us >= other_us) {
             if (us < other_us)
                 idx->txn_saved_us += other_us - us;
@@ -1936,17 +1927,15 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
         DevBuf<uint32_t> count, start, items;
         DevBuf<char> tmp;
         const uint64_t mm = (uint64_t)idx->m + 1;
-        // [m + 1 counts | the pair total, 64-bit]
-        const uint64_t at = (mm + 1) / 2 * 2;
-        if (count.alloc(at + 2) != hipSuccess || start.alloc(mm) != hipSuccess ||
+        // [m + 1 counts | a TxnWalk]
+        const uint64_t at = (mm + 1) / 2 * 2, walk_words = sizeof(TxnWalk) / 4;
+        if (count.alloc(at + walk_words) != hipSuccess || start.alloc(mm) != hipSuccess ||
             items.alloc(idx->nnz) != hipSuccess || tmp.alloc(scan_tmp_bytes(mm)) != hipSuccess)
             return BM_OK;
-        HIPC(ctx, fill_u32(count.p, at + 2, 0, s));
-        HIPC(ctx, launch_txn_count(idx->tids.p, idx->nnz, idx->m, count.p,
-                                   reinterpret_cast<unsigned long long *>(count.p + at), s));
-        uint64_t pairs = 0;
-        BMC(read_back(ctx, &pairs, count.p + at, 8));
-        if (!forced && txn_us(idx, (double)pairs) >= other_us) {
+        HIPC(ctx, fill_u32(count.p, at + walk_words, 0, s));
+        HIPC(ctx, launch_txn_count(idx->tids.p, idx->nnz, idx->m, count.p, reinterpret_cast<TxnWalk *>(count.p + at), s));
+        BMC(read_back(ctx, &w, count.p + at, sizeof w));
+        if (!forced && txn_us(idx, w) >= other_us) {
             idx->txn_dense = true;
             return BM_OK;
         }
@@ -1955,8 +1944,8 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
         HIPC(ctx, launch_txn_scatter(idx->off.p, idx->tids.p, idx->n, count.p, items.p, s));
         idx->txn_start.swap(start);
         idx->txn_items.swap(items);
-        idx->txn_pairs = pairs;
-    } else if (!forced && txn_us(idx, (double)idx->txn_pairs) >= other_us) {
+        idx->txn_walk = w;
+    } else if (!forced && txn_us(idx, idx->txn_walk) >= other_us) {
         return BM_OK;
     }
     Span sp(ctx, PH_COMPARE);

@@ -954,6 +954,38 @@ GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, i
     return set;
 }
 
+// The triangle written at 3 TB/s, 9 ps an incidence and 4.6 ps for each item of its
+// transaction; or the largest set, walked by one workgroup, 1 us a round of its lanes
+// and 0.25 us for each item of a transaction.  Measured (MI355X, us, transactions /
+// bits / slots): 2^20 x 8192 at 0.01 %: 53 / 9396 / 802; 0.05 %: 189 / 9357 / 4718;
+// 0.2 %: 1506 / 9400 / 12,888; 0.4 %: 5549 / 9397 / 13,347; 10^6 x 4000 Zipf(1.0) at
+// 0.05 % (largest set 225,199): 1741 / 2530 / 3516; 10^6 x 8000 Zipf(1.0) at 0.1 %
+// (836,079): 10,404 / 8914 / 12,818.
+//
+// A long transaction holds the lane that walks it, and with it a wavefront, in the row
+// of each of its items.  Few of them: 0.14 us an item (0.11 to 0.19), as many rows at a
+// time as workgroups fit the CUs (their counters fill the LDS).  Many: 22 * 10^9 such
+// steps a second, a step for each wavefront of the walk that has one.  With one
+// transaction of d items more (us, transactions / slots / this): 2^20 x 8192 at
+// 0.05 %, d = 256: 214 / 4700 / 230; 1024: 382 / 4722 / 342; 4096: 2299 / 4811 / 2106;
+// 8192: 7198 / 4924 / 7843; with 16 of 8192: 22,073 / 5429 / 33,936; 200 of 1024: 3525
+// / 5863 / 4814; 2^20 x 4000, d = 4000: 949 / 1378 / 1236; 2^20 x 16,000 at 0.02 %, d =
+// 16,000: 53,718 / 8045 / 71,453.
+double txn_us(uint32_t n, uint64_t nnz, uint32_t largest_set, const TxnWalk &w, uint32_t n_cu)
+{
+    const double inc = (double)std::max<uint64_t>(nnz, 1), walked = 2.0 * w.pairs + inc;
+    const double lanes = n > 8192 ? 600 : 256;
+    double us = 10 + 2.0 * n * (n - 1.0) / 3e6 +
+                std::max(4.6e-6 * walked + 9e-6 * inc, largest_set / lanes * (1 + 0.25 * walked / inc));
+    if (w.long_items) {
+        const double per_cu = std::min(163840 / (4.0 * n), n > 8192 ? 2.0 : 8.0);  // 1024 threads a row past 8192 items
+        const double rounds = std::max(1.0, std::min<double>(w.long_items, n) / (per_cu * n_cu));
+        const double waves = std::min<double>(w.long_items, inc / 64 + n);  // with a long transaction
+        us += std::max(rounds * w.longest * 0.14, waves * ((double)w.long_squares / w.long_items) / 22e3);
+    }
+    return us;
+}
+
 uint32_t txn_bits_words(uint32_t m, uint32_t n, uint32_t lds, uint32_t n_cu)
 {
     uint32_t best = 0;

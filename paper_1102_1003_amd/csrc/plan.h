@@ -272,6 +272,17 @@ struct GramSetPlan {
 };
 GramSetPlan plan_gram_set(const std::vector<GramShape> &shapes, uint32_t n_cu, int pinned = 0);
 
+// What the count by transactions walks: pairs in all transactions; and, of those
+// longer than kTxnLong items, which one lane walks alone, the items in all and
+// their squares, and the longest.
+constexpr uint32_t kTxnLong = 64;
+struct TxnWalk {
+    uint64_t pairs = 0, long_items = 0, long_squares = 0, longest = 0;
+};
+// Expected time (us) of the triangle of n items with nnz incidences, the largest
+// set of largest_set transactions.
+double txn_us(uint32_t n, uint64_t nnz, uint32_t largest_set, const TxnWalk &w, uint32_t n_cu);
+
 // The count of triples from bit rows: runs of kTripleRun consecutive triples over
 // segments of seg words of the rows, a wavefront each, n_work in all; `blocks`
 // workgroups of kTripleThreads walk them, however many there are (a launch holds

@@ -18,20 +18,33 @@ __global__ void txn_count_kernel(const uint32_t *__restrict__ tids, uint64_t nnz
         atomicAdd(&count[tids[k]], 1u);
 }
 
-// sum += d (d - 1) / 2 over the m transaction sizes d.
-__global__ void __launch_bounds__(256) txn_pairs_kernel(const uint32_t *__restrict__ count, uint32_t m,
-                                                        unsigned long long *sum)
+// The m transaction sizes d: their pairs, the longest, and the sums over those of more
+// than kTxnLong items.
+__global__ void __launch_bounds__(256) txn_walk_kernel(const uint32_t *__restrict__ count, uint32_t m, TxnWalk *walk)
 {
-    unsigned long long s = 0;
+    unsigned long long pairs = 0, items = 0, squares = 0, longest = 0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < m; t += stride) {
         const unsigned long long d = count[t];
-        s += d ? d * (d - 1) / 2 : 0;
+        pairs += d ? d * (d - 1) / 2 : 0;
+        items += d > kTxnLong ? d : 0;
+        squares += d > kTxnLong ? d * d : 0;
+        longest = max(longest, d);
     }
-    for (int o = 32; o > 0; o >>= 1)
-        s += __shfl_xor(s, o, 64);
-    if ((threadIdx.x & 63) == 0 && s)
-        atomicAdd(sum, s);
+    for (int o = 32; o > 0; o >>= 1) {
+        pairs += __shfl_xor(pairs, o, 64);
+        items += __shfl_xor(items, o, 64);
+        squares += __shfl_xor(squares, o, 64);
+        longest = max(longest, __shfl_xor(longest, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0 && longest) {
+        atomicAdd(reinterpret_cast<unsigned long long *>(&walk->pairs), pairs);
+        atomicMax(reinterpret_cast<unsigned long long *>(&walk->longest), longest);
+        if (items) {
+            atomicAdd(reinterpret_cast<unsigned long long *>(&walk->long_items), items);
+            atomicAdd(reinterpret_cast<unsigned long long *>(&walk->long_squares), squares);
+        }
+    }
 }
 
 // items[cursor[t]++] = item of every incidence, a workgroup per item (the order
@@ -79,8 +92,8 @@ __global__ void txn_rows_kernel(const uint64_t *__restrict__ off, const uint32_t
 
 }  // namespace
 
-hipError_t launch_txn_count(const uint32_t *tids, uint64_t nnz, uint32_t m, uint32_t *count,
-                            unsigned long long *pairs, hipStream_t s)
+hipError_t launch_txn_count(const uint32_t *tids, uint64_t nnz, uint32_t m, uint32_t *count, TxnWalk *walk,
+                            hipStream_t s)
 {
     if (nnz) {
         const uint64_t blocks = (nnz + 255) / 256;
@@ -90,7 +103,7 @@ hipError_t launch_txn_count(const uint32_t *tids, uint64_t nnz, uint32_t m, uint
             return e;
     }
     const uint32_t blocks = (m + 255) / 256;
-    txn_pairs_kernel<<<blocks < 256 ? blocks : 256, 256, 0, s>>>(count, m, pairs);
+    txn_walk_kernel<<<blocks < 256 ? blocks : 256, 256, 0, s>>>(count, m, walk);
     return hipGetLastError();
 }
 

@@ -55,3 +55,18 @@ extern "C" uint64_t bit_ingest_items(uint32_t m, uint32_t n, uint32_t lds, uint3
     const uint64_t rows = blocks * bm::kTxnBitsThreads, segs = bm::bit_ingest_segments(m, n) * 256;
     return rows > segs ? rows : segs;
 }
+
+// Expected time of the count by transactions: nnz incidences of independent sets of
+// equal size, and `longs` transactions of d items.
+extern "C" double txn_price(uint32_t n, uint32_t m, double p, uint32_t longs, uint32_t d)
+{
+    const double nnz = (double)n * m * p;
+    bm::TxnWalk w;
+    w.pairs = (uint64_t)(nnz * nnz / (2.0 * m) + longs * 0.5 * d * (d - 1.0));
+    if (d > bm::kTxnLong && longs) {
+        w.long_items = (uint64_t)longs * d;
+        w.long_squares = w.long_items * d;
+        w.longest = d;
+    }
+    return bm::txn_us(n, (uint64_t)nnz + (uint64_t)longs * d, (uint32_t)(m * p) + longs, w, 256);
+}

@@ -1,0 +1,37 @@
+"""Very sparse sets with a transaction that holds every item: exact by every route, and left to the slot
+compare where one lane's walk of that transaction would take longer."""
+import numpy as np
+import pytest
+
+import datagen
+import oracle
+
+torch = pytest.importorskip("torch")
+bm = pytest.importorskip("paper_1102_1003_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("route", [None, "2"])
+@pytest.mark.parametrize("long", [False, True])
+def test_one_transaction_of_all_items(monkeypatch, long, route):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    m, n = 400_000, 3_000
+    off, tids = datagen.bernoulli_sets(m, n, 0.0004, seed=9)
+    lists = [tids[off[i]:off[i + 1]] for i in range(n)]
+    if long:
+        lists = [np.union1d(s, [m // 3]).astype(np.uint32) for s in lists]
+    off = np.concatenate([[0], np.cumsum([s.size for s in lists])]).astype(np.uint64)
+    tids = np.concatenate(lists)
+    want = oracle.all_pairs(off, tids)
+    ctx = bm.Context(0)
+    idx = bm.Index.from_sets(ctx, m, off, tids, slot_bits=0)
+    for rep in range(2):
+        ctx.set_profiling(True)
+        assert np.array_equal(idx.all_pair_supports(), want)
+        assert (ctx.timings()["compare_slot_pairs"] > 0) == (long and route is None)
+        assert np.array_equal(idx.frequent_pairs(2), oracle.frequent_pairs(off, tids, 2))
+    ctx.close()

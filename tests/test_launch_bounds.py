@@ -1,5 +1,6 @@
-"""Launch sizes at the far end of what the calls take: a launch of 2^32 work-items or more is refused
-by the runtime, so every grid has to stay below that, whatever the sizes."""
+"""What the host computes before a launch, checked on the CPU.  Launch sizes at the far end of what the
+calls take: a launch of 2^32 work-items or more is refused by the runtime, so every grid has to stay below
+that, whatever the sizes.  And the expected time that chooses the count by transactions."""
 import ctypes
 import os
 import subprocess
@@ -19,6 +20,7 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(out)
     for f in ("triple_bits_items", "gram_reduce_items", "bit_rows_items", "bit_ingest_items"):
         getattr(L, f).restype = ctypes.c_uint64
+    L.txn_price.restype = ctypes.c_double
     return L
 
 
@@ -60,3 +62,24 @@ def test_transactions_through_bit_rows(lib, m, n):
     assert whole.value and items < LIMIT
     if m <= 10**6 and n <= 4500:
         assert items
+
+
+# (n, m, density, long transactions, their items): measured by transactions and by slots (MI355X, us)
+TXN_MEASURED = [
+    ((8192, 2**20, 0.0005, 0, 0), 186, 4742), ((8192, 2**20, 0.0005, 1, 256), 214, 4700),
+    ((8192, 2**20, 0.0005, 1, 1024), 382, 4722), ((8192, 2**20, 0.0005, 1, 4096), 2299, 4811),
+    ((8192, 2**20, 0.0005, 1, 8192), 7198, 4924), ((8192, 2**20, 0.0005, 16, 1024), 1495, 4774),
+    ((8192, 2**20, 0.0005, 16, 8192), 22_073, 5429), ((8192, 2**20, 0.0005, 200, 1024), 3525, 5863),
+    ((4000, 2**20, 0.0005, 0, 0), 63, 1277), ((4000, 2**20, 0.0005, 1, 500), 116, 1317),
+    ((4000, 2**20, 0.0005, 1, 4000), 949, 1378), ((16_000, 2**20, 0.0002, 0, 0), 245, 5976),
+    ((16_000, 2**20, 0.0002, 1, 2000), 1469, 6012), ((16_000, 2**20, 0.0002, 1, 16_000), 53_718, 8045),
+]
+
+
+@pytest.mark.parametrize("shape,txn,slots", TXN_MEASURED)
+def test_long_transactions_are_priced(lib, shape, txn, slots):
+    """The faster of the two ways is the one that the expected time names, and it is within a factor of two."""
+    n, m, p, longs, d = shape
+    us = lib.txn_price(n, m, ctypes.c_double(p), longs, d)
+    assert txn / 2 < us < txn * 2
+    assert (us < slots) == (txn < slots)
