@@ -529,7 +529,8 @@ struct BitMat {
     uint32_t zero = 0;  // the all-zero row
 };
 // Counts |a_i cap b_j|: tri (a == b): the packed upper triangle over n_out
-// positions; else rows of n_out.  Every count is written (none is read).
+// positions; else rows of n_out.  Every count is written (none is read), unless
+// p.add: then the counts, zeroed by the caller, are added to.
 hipError_t launch_gram(const GramPlan &p, const BitMat &a, const BitMat &b, uint32_t *out, uint64_t n_out, float *ws,
                        hipStream_t s);
 

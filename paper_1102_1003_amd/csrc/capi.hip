@@ -586,7 +586,7 @@ bool capturing(hipStream_t s)
 }
 
 // Whether all pairs of an index that holds its bit rows will be counted from
-// them (with no scratch too, should a stream be captured).
+// them, now and at every later call.
 bool pairs_by_kept_bits(const bm_index *idx)
 {
     const bm_context *ctx = idx->ctx;
@@ -1770,6 +1770,8 @@ bm_status ensure_bits(bm_index *idx)
     bm_context *ctx = idx->ctx;
     if (idx->bits.p)
         return BM_OK;
+    if (capturing(ctx->stream))
+        return fail(ctx, BM_EINVAL, "no bit rows to capture a product of: make the call once before the capture");
     Span sp(ctx, PH_ENCODE);
     DevBuf<uint32_t> bits;
     HIPC(ctx, bits.alloc(((uint64_t)idx->n + 1) * bit_row_words(idx->m)));
@@ -1981,27 +1983,36 @@ bm_status count_pairs(bm_index *idx, uint32_t first, uint32_t *out)
     return compare_pairs(idx, out);
 }
 
+// All pair counts from the index's bit rows without scratch of any call's or graph's.
+bm_status gram_no_scratch(bm_index *idx, uint32_t *out)
+{
+    bm_context *ctx = idx->ctx;
+    const BitMat a = whole_bits(idx);
+    const GramPlan p = plan_gram_add(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
+    if (p.add) {
+        Span sp(ctx, PH_FILL);
+        HIPC(ctx, fill_u32(out, n_pairs(idx->n), 0, ctx->stream));
+    }
+    Span sp(ctx, PH_COMPARE);
+    HIPC(ctx, launch_gram(p, a, a, out, idx->n, nullptr, ctx->stream));
+    return BM_OK;
+}
+
 // All pair counts while the stream is captured, from what the index holds: slots
 // by a resident plan (one of either launch form: each is complete), else the
-// grouped incidences, else the bit rows, each tile one workgroup's (no scratch).
+// grouped incidences, else the bit rows.
 bm_status captured_pairs(bm_index *idx, uint32_t *out)
 {
     bm_context *ctx = idx->ctx;
     if (idx->planned_first == 0)
         return compare_pairs(idx, out);
-    Span sp(ctx, PH_COMPARE);
     if (idx->txn_items.p) {
+        Span sp(ctx, PH_COMPARE);
         HIPC(ctx, launch_txn_rows(idx->off.p, idx->tids.p, idx->txn_start.p, idx->txn_items.p, idx->n, out, ctx->stream));
         return BM_OK;
     }
-    if (idx->bits.p) {
-        const BitMat a = whole_bits(idx);
-        const GramPlan p = plan_gram(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile(), 0);
-        if (p.ws_floats == 0) {
-            HIPC(ctx, launch_gram(p, a, a, out, idx->n, nullptr, ctx->stream));
-            return BM_OK;
-        }
-    }
+    if (idx->bits.p)
+        return gram_no_scratch(idx, out);
     return fail(ctx, BM_EINVAL, "nothing to count the pairs from under capture: make the call once before the capture");
 }
 
@@ -3430,6 +3441,8 @@ bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_
     HIPC(ctx, hipSetDevice(ctx->device));
     BMC(ensure_bits(idx));
     bool host = ptr_kind(out) == PTR_HOST;
+    if (!host && capturing(ctx->stream))
+        return gram_no_scratch(idx, out);
     uint32_t *dst = out;
     if (host) {
         HIPC(ctx, idx->pairbuf.ensure(np));

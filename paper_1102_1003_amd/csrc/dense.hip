@@ -137,6 +137,18 @@ __device__ inline void put_count(const GramArgs &g, uint32_t i, uint32_t j, uint
     }
 }
 
+__device__ inline void add_count(const GramArgs &g, uint32_t i, uint32_t j, uint32_t v)
+{
+    if (v == 0)
+        return;
+    if (g.tri) {
+        if (i < j && j < g.b.n)
+            atomicAdd(&g.out[(uint64_t)i * g.n_out - (uint64_t)i * (i + 1) / 2 + (j - i - 1)], v);
+    } else if (i < g.a.n && j < g.b.n) {
+        atomicAdd(&g.out[(uint64_t)i * g.n_out + j], v);
+    }
+}
+
 // A workgroup is WR x WC wavefronts, each owning BR x BC blocks of 32 x 32
 // counts.  Lane l holds row (or column) l mod 32 of a block and the 16 bytes
 // l / 32 of the current 32: rows and columns read their bits in the same order,
@@ -149,7 +161,8 @@ __device__ inline void put_count(const GramArgs &g, uint32_t i, uint32_t j, uint
 // workgroup's own place in ws (its first run part in place 2 w, its last in
 // 2 w + 1), and gram_reduce_kernel adds the parts.  (Device atomics run at about
 // 27 * 10^9 a second here: 0.6 ms for 256 parts of 256 x 256, against 0.03 ms
-// for writing them out and reading them back.)
+// for writing them out and reading them back.)  kAdd: those atomics all the same,
+// where there is no scratch (plan_gram_add).
 //
 // Bound by the matrix cores: 32 MFMAs of 32 cycles a wavefront against 6 LDS
 // reads and 120 VALU operations per 256 transactions (128 x 64 counts).  Bits
@@ -159,7 +172,7 @@ __device__ inline void put_count(const GramArgs &g, uint32_t i, uint32_t j, uint
 // needed.  m = 2^20, n = 4096: 2.5 ms, 7.0 * 10^15 operations (2 m per pair) a
 // second; the int8 kernel before it (0/1 bytes, v_mfma_i32_16x16x64_i8, bound by
 // its LDS reads) took 9.8 ms.
-template <int BR, int BC, int WR, int WC>
+template <int BR, int BC, int WR, int WC, bool kAdd = false>
 __device__ __forceinline__ void gram_run(const GramArgs &g, uint32_t wg, uint8_t (*lds)[32 * (BR * WR + BC * WC)][kLdsRow])
 {
     constexpr int R = 32 * BR * WR, C = 32 * BC * WC, NT = 64 * WR * WC;
@@ -257,6 +270,15 @@ __device__ __forceinline__ void gram_run(const GramArgs &g, uint32_t wg, uint8_t
                     for (int e = 0; e < 16; e++)
                         put_count(g, ti * R + (wr * BR + a) * 32 + 8 * (e / 4) + 4 * (lane >> 5) + e % 4,
                                   tj * C + (wc * BC + b) * 32 + (lane & 31), (uint32_t)acc[a][b][e]);
+        } else if constexpr (kAdd) {
+#pragma unroll
+            for (int a = 0; a < BR; a++)
+#pragma unroll
+                for (int b = 0; b < BC; b++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++)
+                        add_count(g, ti * R + (wr * BR + a) * 32 + 8 * (e / 4) + 4 * (lane >> 5) + e % 4,
+                                  tj * C + (wc * BC + b) * 32 + (lane & 31), (uint32_t)acc[a][b][e]);
         } else {
             float *part = g.ws + (uint64_t)(2 * wg + (u != u0)) * ((uint64_t)R * C) + wv * (BR * BC * 1024) + lane;
 #pragma unroll
@@ -271,11 +293,11 @@ __device__ __forceinline__ void gram_run(const GramArgs &g, uint32_t wg, uint8_t
     }
 }
 
-template <int BR, int BC, int WR, int WC>
+template <int BR, int BC, int WR, int WC, bool kAdd>
 __global__ void __launch_bounds__(64 * WR * WC, BR * BC >= 8 ? 2 : BR * BC >= 4 ? 3 : 4) bit_gram_kernel(const GramArgs g)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][32 * (BR * WR + BC * WC)][kLdsRow];
-    gram_run<BR, BC, WR, WC>(g, blockIdx.x, lds);
+    gram_run<BR, BC, WR, WC, kAdd>(g, blockIdx.x, lds);
 }
 
 // The job that owns workgroup w.
@@ -408,7 +430,8 @@ __global__ void __launch_bounds__(256) gram_reduce_jobs_kernel(const GramJob *jo
 template <int BR, int BC, int WR, int WC>
 hipError_t run_gram(const GramArgs &g, const GramPlan &p, hipStream_t s)
 {
-    bit_gram_kernel<BR, BC, WR, WC><<<g.W, 64 * WR * WC, 0, s>>>(g);
+    auto *product = p.add ? bit_gram_kernel<BR, BC, WR, WC, true> : bit_gram_kernel<BR, BC, WR, WC, false>;
+    product<<<g.W, 64 * WR * WC, 0, s>>>(g);
     hipError_t e = hipGetLastError();
     if (p.ws_floats == 0)
         return e;

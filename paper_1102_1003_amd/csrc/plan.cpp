@@ -887,6 +887,36 @@ GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint3
     return best;
 }
 
+// As plan_gram, with 27 * 10^9 adds a second for the parts: fewer groups share the
+// tiles the more counts a part has.  (What a call under capture takes: scratch would be
+// the graph's, or shared with other graphs and calls.)
+GramPlan plan_gram_add(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned)
+{
+    GramPlan best;
+    for (int tile : {256, 128, 64}) {
+        if (pinned && tile != pinned)
+            continue;
+        GramPlan p = plan_gram(na, nb, tri, row_words, n_cu, tile);
+        const uint64_t U = (uint64_t)p.tiles * p.stages;
+        const uint64_t least = std::max<uint64_t>((U + kGramMaxStages - 1) / kGramMaxStages, 1);
+        const uint64_t full = std::max<uint64_t>(p.groups, least);
+        const double stage_us = tile == 256 ? 2.3 : (tile == 128 ? 0.62 : 0.27);
+        p.ws_floats = 0;
+        for (uint64_t w = std::max<uint64_t>(p.tiles, least);; w = std::min(2 * w, full)) {
+            p.groups = (uint32_t)w;
+            p.add = U % w != 0 || (U / w) % p.stages != 0;
+            const double idle = w < full ? 1.3 * std::max(1.0, (double)std::min<uint64_t>(U, n_cu) / w) : 1;
+            const double parts = p.add ? (double)std::min<uint64_t>(2 * w, w + p.tiles) : 0;
+            p.us = 10 + (double)U * stage_us / n_cu * idle + parts * tile * tile / 27e3;
+            if (!best.groups || p.us < best.us)
+                best = p;
+            if (w >= full)
+                break;
+        }
+    }
+    return best;
+}
+
 // One launch holds every family's tiles, of 64 or 128 counts whichever takes a
 // family less time: a small family alone is mostly the two launches' 10 us and a
 // chip that fills and drains, and several launches side by side share the

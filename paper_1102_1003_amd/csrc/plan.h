@@ -225,6 +225,7 @@ struct GramPlan {
     int tile = 256;
     uint32_t tile_rows = 0, tile_cols = 0, tiles = 0, stages = 0, groups = 0;
     bool tri = true;
+    bool add = false;  // parts are added into the counts (plan_gram_add)
     uint64_t ws_floats = 0;
     double us = 0;  // expected time
 };
@@ -236,6 +237,10 @@ struct GramPlan {
 // longer than kGramMaxStages, where ws_floats says what it takes all the same).
 GramPlan plan_gram(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0,
                    uint64_t max_ws = UINT64_MAX);
+
+// The same without scratch: groups add the parts of tiles that they share into the
+// counts themselves (zeroed before), by device atomics; add says whether any is shared.
+GramPlan plan_gram_add(uint32_t na, uint32_t nb, bool tri, uint64_t row_words, uint32_t n_cu, int pinned = 0);
 
 // The addition of a plan's parts: `fold` threads share the parts of the same four
 // counts, and workgroups of kReduceThreads take 1024 / fold counts each, all of

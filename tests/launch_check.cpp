@@ -70,3 +70,21 @@ extern "C" double txn_price(uint32_t n, uint32_t m, double p, uint32_t longs, ui
     }
     return bm::txn_us(n, (uint64_t)nnz + (uint64_t)longs * d, (uint32_t)(m * p) + longs, w, 256);
 }
+
+// The cut without scratch: 0, or what is wrong with it.
+extern "C" int gram_add_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uint32_t n_cu, int pinned)
+{
+    const bm::GramPlan p = bm::plan_gram_add(na, nb, tri != 0, bm::bit_row_words(m), n_cu, pinned);
+    const uint64_t U = (uint64_t)p.tiles * p.stages, W = p.groups;
+    if (W == 0 || W > U || p.ws_floats || (pinned && p.tile != pinned))
+        return 1;
+    bool shared = false;
+    for (uint64_t w = 0; w < W; w++) {
+        const uint64_t u0 = U * w / W, u1 = U * (w + 1) / W;
+        shared = shared || u0 % p.stages != 0 || u1 % p.stages != 0;
+        // the longest part of a tile in the run
+        if (u1 - u0 > bm::kGramMaxStages && p.stages > bm::kGramMaxStages)
+            return 2;
+    }
+    return shared && !p.add ? 3 : 0;
+}

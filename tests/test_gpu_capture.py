@@ -101,3 +101,32 @@ def test_plan_of_the_other_launch_form(stream_ctx, monkeypatch):
     c.set_launch_mode(True)
     replays(stream, c, idx.all_pair_supports, out, want, lambda: None)
     c.set_launch_mode(False)
+
+
+@pytest.mark.parametrize("tile", [0, 64, 128, 256])
+@pytest.mark.parametrize("m,n,p", [(500, 2, 0.5), (1_000_000, 70, 0.002), (20_000, 300, 0.05), (3_000, 1_100, 0.02),
+                                   (2**24 + 600_000, 3, None)])
+def test_product_without_scratch(stream_ctx, monkeypatch, tile, m, n, p):
+    """The bitmap product captured: its graph shares no scratch with eager calls or other graphs."""
+    stream, c = stream_ctx
+    if tile:
+        monkeypatch.setenv("BM_GRAM_TILE", str(tile))
+    if p is None:                                        # full sets: a count that fp32 cannot hold
+        off = np.arange(n + 1, dtype=np.uint64) * m
+        tids, want = np.tile(np.arange(m, dtype=np.uint32), n), np.full(3, m, np.uint32)
+    else:
+        off, tids = datagen.bernoulli_sets(m, n, p, seed=n)
+        want = oracle.all_pairs(off, tids)
+    idx = bm.Index.from_sets(c, m, off, tids)
+    out = torch.full((want.size,), -1, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        with pytest.raises(bm.BatmapError) as e:         # no rows yet: none are made inside a capture
+            idx.all_pair_supports_dense(out)
+        out.zero_()
+    assert e.value.status == bm.BM_EINVAL
+    del g
+    assert np.array_equal(idx.all_pair_supports_dense(), want)
+    replays(stream, c, idx.all_pair_supports_dense, out, want,
+            lambda: np.testing.assert_array_equal(idx.all_pair_supports_dense(), want))

@@ -83,3 +83,13 @@ def test_long_transactions_are_priced(lib, shape, txn, slots):
     us = lib.txn_price(n, m, ctypes.c_double(p), longs, d)
     assert txn / 2 < us < txn * 2
     assert (us < slots) == (txn < slots)
+
+
+@pytest.mark.parametrize("pinned", [0, 64, 128, 256])
+@pytest.mark.parametrize("m", [1, 512, 513, 10_000, 1_000_003, 2**24 + 1, 2**32 - 1])
+def test_product_without_scratch(lib, m, pinned):
+    """Parts within fp32's whole numbers, and added wherever a tile is shared."""
+    for n in (2, 64, 65, 257, 3000):
+        if n < 300 or m < 2**24:
+            assert lib.gram_add_check(n, n, 1, ctypes.c_uint32(m), 256, pinned) == 0
+    assert lib.gram_add_check(300, 1, 0, ctypes.c_uint32(m), 8, pinned) == 0
