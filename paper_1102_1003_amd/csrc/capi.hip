@@ -2810,18 +2810,23 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     const uint64_t o_off = o_cnt + align_up(((uint64_t)nb + 1) * 4, 256);
     const uint64_t o_tmp = o_off + align_up(((uint64_t)nb + 1) * 8, 256);
     const uint64_t o_work = o_tmp + align_up(scan_tmp_bytes((uint64_t)nb + 1), 256);
-    // From the index's bit rows, when it holds them and their product (with
-    // the scratch that is left) is expected to be faster.
+    // From the index's grouped incidences, or its bit rows, when it holds them and
+    // that (with the scratch that is left) is expected to be faster.  An index that
+    // has counted by them may hold no plan, and one made here costs more than it.
     const uint64_t room = o_work < kNoAllocScratchBytes ? (kNoAllocScratchBytes - o_work) / 4 : 0;
     GramPlan gram;
-    bool by_bits = false;
-    if (idx->bits.p && o_work <= kNoAllocScratchBytes && bitmap_route_on(ctx) && bitmap_route_env() != 2 &&
-        !capturing(s)) {
-        gram = plan_gram(idx->n, idx->n, true, bit_row_words(idx->m), (uint32_t)ctx->n_cu, pinned_gram_tile(), room);
-        by_bits = gram.ws_floats <= room &&
-                  (bitmap_route_env() == 1 ||
-                   gram.us < compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes),
-                                        idx->planes, idx->h_r_sorted.back(), 20));
+    double us = compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes,
+                           idx->h_r_sorted.back(), 20);
+    bool by_bits = false, by_txn = false;
+    if (o_work <= kNoAllocScratchBytes && bitmap_route_on(ctx)) {
+        if (idx->bits.p && bitmap_route_env() != 2) {
+            gram = plan_gram(idx->n, idx->n, true, bit_row_words(idx->m), (uint32_t)ctx->n_cu, pinned_gram_tile(), room);
+            by_bits = gram.ws_floats <= room && (bitmap_route_env() == 1 || gram.us < us);
+            us = by_bits ? gram.us : us;
+        }
+        by_txn = idx->txn_items.p && bitmap_route_env() != 1 &&
+                 (bitmap_route_env() == 2 || txn_us(idx, idx->txn_walk) < us);
+        by_bits = by_bits && !by_txn;
     }
     // The index's resident plan serves when it covers every pair among sorted
     // indices >= first (it was made for a prefix no longer than that; tile
@@ -2832,7 +2837,7 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     std::vector<WorkItem> flat;
     std::vector<std::pair<int, uint32_t>> ranges;
     double slot_pairs = idx->planned_slot_pairs;
-    if (!own && !by_bits) {
+    if (!own && !by_bits && !by_txn) {
         Plan plan;
         plan_classes(classes_from(idx->classes, first), 0, target_items(ctx), plan, nullptr,
                      single_launch(ctx, idx->planes) ? 1 : 0, forced_variant(), false, idx->planes, packed_rows());
@@ -2853,9 +2858,11 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     if (!flat.empty())
         BMC(upload(ctx, work, flat.data(), flat.size() * sizeof(WorkItem), /*grow=*/false));
     // the scratch keeps the last call's contents: counts and the block-count
-    // tail start from zero here (fill kernels, no memset nodes; the product
-    // writes every count)
-    if (by_bits) {
+    // tail start from zero here (fill kernels, no memset nodes; the other two
+    // write every count)
+    if (by_txn) {
+        HIPC(ctx, launch_txn_rows(idx->off.p, idx->tids.p, idx->txn_start.p, idx->txn_items.p, idx->n, counts, s));
+    } else if (by_bits) {
         const BitMat a = whole_bits(idx);
         HIPC(ctx, launch_gram(gram, a, a, counts, idx->n, reinterpret_cast<float *>(sc + o_work), s));
     } else {

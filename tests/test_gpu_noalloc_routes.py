@@ -1,0 +1,37 @@
+"""bm_frequent_pairs_noalloc after calls that counted by transactions, and so left no plan of the compare."""
+import numpy as np
+import pytest
+
+import datagen
+import oracle
+
+torch = pytest.importorskip("torch")
+bm = pytest.importorskip("paper_1102_1003_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,p", [
+    (200_000, 5_000, 0.0005),      # the counts fill the scratch: no room for a plan beside them
+    (60_000, 4_200, 0.001),
+])
+def test_after_counting_by_transactions(m, n, p):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    off, tids = datagen.bernoulli_sets(m, n, p, seed=n)
+    ctx = bm.Context(0)
+    idx = bm.Index.from_sets(ctx, m, off, tids)
+    for rep in range(2):
+        ctx.set_profiling(True)
+        idx.all_pair_supports()
+        assert ctx.timings()["compare_slot_pairs"] == 0
+        ctx.set_profiling(False)
+    for sigma in (1, 2, 3):
+        want = oracle.frequent_pairs(off, tids, sigma)
+        out = torch.zeros(3 * max(len(want), 1), dtype=torch.int32, device="cuda:0")
+        torch.cuda.synchronize()
+        assert idx.frequent_pairs_noalloc(sigma) == len(want)
+        assert idx.frequent_pairs_noalloc(sigma, out) == len(want)
+        ctx.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32)[:3 * len(want)].reshape(-1, 3), want)
+    ctx.close()
