@@ -19,6 +19,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -45,6 +46,9 @@ struct AllocStream {
     std::mutex mu;
     std::multimap<uint64_t, void *> spare;  // bytes -> block
     uint64_t spare_bytes = 0;
+    // bytes of the blocks in use, refused past `limit` as when the device is full
+    // (BM_MEM_LIMIT_MB; exercises what calls do then)
+    uint64_t used = 0, limit = ~0ull;
 
     // A spare block of at least `bytes` and at most 1.25x that, or null.
     void *take(uint64_t bytes, uint64_t *got)
@@ -110,6 +114,7 @@ struct DevBuf {
     {
         if (p) {
             if (as) {
+                as->used -= bytes;
                 if (!as->give(p, bytes))
                     (void)hipFreeAsync(p, as->s);
             } else {
@@ -131,16 +136,20 @@ struct DevBuf {
         bytes = want;
         if (t_alloc_scope && *t_alloc_scope) {
             const std::shared_ptr<AllocStream> &a = *t_alloc_scope;
-            void *q = a->take(want, &bytes);
+            void *q = a->used + want > a->limit ? nullptr : a->take(want, &bytes);
             if (q) {
                 p = reinterpret_cast<T *>(q);
                 e = hipSuccess;
+            } else if (a->used + want > a->limit) {
+                e = hipErrorOutOfMemory;
             } else {
                 bytes = want;
                 e = hipMallocAsync(reinterpret_cast<void **>(&p), want, a->s);
             }
-            if (e == hipSuccess)
+            if (e == hipSuccess) {
                 as = a;
+                a->used += bytes;
+            }
         } else {
             e = hipMalloc(reinterpret_cast<void **>(&p), count * sizeof(T));
         }
@@ -235,6 +244,12 @@ uint8_t *scratch_address(int device)
 }  // namespace
 
 
+// A context's indexes; shared with them, since they may outlive it.
+struct IndexList {
+    std::mutex mu;
+    std::set<bm_index *> all;
+};
+
 enum Phase { PH_INGEST, PH_LAYOUT, PH_CONSTRUCT, PH_ENCODE, PH_CORRECT, PH_FILL, PH_COMPARE, PH_APPLY,
              PH_THRESHOLD, PH_COUNT };
 
@@ -276,6 +291,9 @@ struct bm_context {
     hipEvent_t fork = nullptr, join[kSide] = {};
     // device address of this GPU's allocation-free scratch (see scratch below)
     uint8_t *scratch = nullptr;
+    // the context's indexes, whose rows are given back when memory runs out (with_room)
+    std::shared_ptr<IndexList> indexes = std::make_shared<IndexList>();
+    bool in_room = false, no_rows = false;
 };
 
 namespace {
@@ -416,6 +434,22 @@ struct bm_index {
     DevBuf<uint32_t> txn_start, txn_items;
     TxnWalk txn_walk;
     bool txn_dense = false;   // longer to walk than independent sets would be: made for nothing
+    // Who else launches over the rows or the incidences: batches and servers hold a
+    // copy of rows_use, captured graphs set rows_captured.
+    std::shared_ptr<char> rows_use = std::make_shared<char>();
+    bool rows_captured = false;
+    std::shared_ptr<IndexList> list;
+
+    explicit bm_index(bm_context *c) : ctx(c), device(c->device), list(c->indexes)
+    {
+        std::lock_guard<std::mutex> lk(list->mu);
+        list->all.insert(this);
+    }
+    ~bm_index()
+    {
+        std::lock_guard<std::mutex> lk(list->mu);
+        list->all.erase(this);
+    }
 };
 
 struct bm_batch {
@@ -437,6 +471,7 @@ struct bm_batch {
     GramJobs joint;
     DevBuf<float> gram_ws;
     std::vector<char> by_bits;  // per instance
+    std::vector<std::shared_ptr<char>> rows_use;  // of the indexes whose rows the graph reads
     double slot_pairs = 0;
     float tuned_ms[2] = {0, 0};  // batch time with catalogue / measured tile speeds (0: not tried)
     hipGraph_t graph = nullptr;
@@ -475,6 +510,74 @@ bm_status fail(bm_context *ctx, bm_status code, const char *fmt, ...)
         const bm_status st_ = (expr);  \
         if (st_ != BM_OK)              \
             return st_;                \
+    } while (0)
+
+// Whether a stream is being captured.  What is made then (a plan and its upload,
+// bit rows, scratch) would belong to the graph and hold nothing until it runs, so
+// a captured call only launches over what earlier calls have left in the index.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Gives back the bit rows and grouped incidences of the context's indexes that no
+// batch, server or graph reads, and the spare blocks; false when there are none.
+bool give_back_rows(bm_context *ctx)
+{
+    if (capturing(ctx->stream))
+        return false;
+    bool any = false;
+    {
+        std::lock_guard<std::mutex> lk(ctx->indexes->mu);
+        for (bm_index *ix : ctx->indexes->all) {
+            if (ix->rows_captured || ix->rows_use.use_count() > 1 || !(ix->bits.p || ix->txn_items.p))
+                continue;
+            any = true;
+            ix->bits.reset();
+            ix->txn_start.reset();
+            ix->txn_items.reset();
+        }
+    }
+    if (!any)
+        return false;
+    if (ctx->as)
+        ctx->as->release();
+    hipMemPool_t pool = nullptr;
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess || hipDeviceGetDefaultMemPool(&pool, ctx->device) != hipSuccess ||
+        hipMemPoolTrimTo(pool, 0) != hipSuccess)
+        (void)hipGetLastError();
+    return true;
+}
+
+// Bit rows and grouped incidences only save time, so they must not cost a call its
+// memory: one that finds none is made again after they are given back, comparing
+// slots (and sorting transactions) as if there were no such routes.
+template <typename F>
+bm_status with_room(bm_context *ctx, F call)
+{
+    struct Scope {
+        bm_context *c;
+        ~Scope() { c->in_room = c->no_rows = false; }
+    } scope{ctx};
+    ctx->in_room = true;
+    bm_status st = call();
+    if (st == BM_ENOMEM && give_back_rows(ctx)) {
+        ctx->no_rows = true;
+        st = call();
+    }
+    return st;
+}
+
+// At the head of a call that allocates: `again` is the call itself.
+#define BM_WITH_ROOM(ctx, again)                                      \
+    do {                                                              \
+        if (!(ctx)->in_room)                                          \
+            return with_room((ctx), [&]() { return (again); });       \
     } while (0)
 
 // ------------------------------------------------------------------ planner
@@ -543,7 +646,7 @@ int bitmap_route_env()
 // compare).
 bool bitmap_route_on(const bm_context *ctx)
 {
-    return bitmap_route_env() != 0 && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
+    return bitmap_route_env() != 0 && !ctx->no_rows && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
 }
 
 // Expected time of a slot compare (us): W + 1 VALU operations per 32 slot
@@ -570,19 +673,6 @@ double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (
 bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
 {
     return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16 && grid_fits(bit_row_blocks(rows, row_words), kBitRowThreads);
-}
-
-// Whether a stream is being captured.  What is made then (a plan and its upload,
-// bit rows, scratch) would belong to the graph and hold nothing until it runs, so
-// a captured call only launches over what earlier calls have left in the index.
-bool capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return st != hipStreamCaptureStatusNone;
 }
 
 // Whether all pairs of an index that holds its bit rows will be counted from
@@ -1265,7 +1355,7 @@ bm_status ingest_by_bits(bm_index *idx, const uint64_t *row_off, const uint32_t 
     // incidences of 2000 items in 10^6 transactions 0.70 ms by two passes)
     const double bits_us = 30 + (3.0 * words * 4 + 8.0 * nnz) / 4e6;
     const double sort_us = 45 + nnz * 8.7e-6 * ((bits_for(n - 1) + 7) / 8);
-    if (nnz == 0 || (env && env[0] == '0') || (bits_us >= sort_us && !(env && env[0] == '1')) ||
+    if (nnz == 0 || ctx->no_rows || (env && env[0] == '0') || (bits_us >= sort_us && !(env && env[0] == '1')) ||
         words * 4 > ctx->mem_bytes / 16 || !bit_ingest_fits(m, n, ctx->lds_bytes, (uint32_t)ctx->n_cu))
         return BM_OK;
     const uint64_t segs = bit_ingest_segments(m, n);
@@ -1983,10 +2073,11 @@ bm_status count_pairs(bm_index *idx, uint32_t first, uint32_t *out)
     return compare_pairs(idx, out);
 }
 
-// All pair counts from the index's bit rows without scratch of any call's or graph's.
+// All pair counts from the index's bit rows into a graph, without scratch of any call's or graph's.
 bm_status gram_no_scratch(bm_index *idx, uint32_t *out)
 {
     bm_context *ctx = idx->ctx;
+    idx->rows_captured = true;
     const BitMat a = whole_bits(idx);
     const GramPlan p = plan_gram_add(idx->n, idx->n, true, a.ld, (uint32_t)ctx->n_cu, pinned_gram_tile());
     if (p.add) {
@@ -2007,6 +2098,7 @@ bm_status captured_pairs(bm_index *idx, uint32_t *out)
     if (idx->planned_first == 0)
         return compare_pairs(idx, out);
     if (idx->txn_items.p) {
+        idx->rows_captured = true;
         Span sp(ctx, PH_COMPARE);
         HIPC(ctx, launch_txn_rows(idx->off.p, idx->tids.p, idx->txn_start.p, idx->txn_items.p, idx->n, out, ctx->stream));
         return BM_OK;
@@ -2208,6 +2300,9 @@ bm_status bm_context_create(int device, void *hip_stream, bm_context **out)
             hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess) {
             ctx->as = std::make_shared<AllocStream>();
             ctx->as->s = ctx->stream;
+            if (const char *e = getenv("BM_MEM_LIMIT_MB"))
+                if (atoll(e) > 0)
+                    ctx->as->limit = (uint64_t)atoll(e) << 20;
         } else {
             (void)hipGetLastError();
         }
@@ -2334,6 +2429,7 @@ bm_status bm_context_autotune(bm_context *ctx, uint32_t reps)
 {
     if (!ctx)
         return BM_EINVAL;
+    BM_WITH_ROOM(ctx, bm_context_autotune(ctx, reps));
     ctx->err.clear();
     AllocScope scope(ctx->as);
     HIPC(ctx, hipSetDevice(ctx->device));
@@ -2388,6 +2484,7 @@ bm_status bm_index_build_sets(bm_context *ctx, uint32_t m, uint32_t n_sets, cons
 {
     if (!ctx)
         return BM_EINVAL;
+    BM_WITH_ROOM(ctx, bm_index_build_sets(ctx, m, n_sets, offsets, tids, opts, out));
     ctx->err.clear();
     AllocScope scope(ctx->as);
     begin_build(ctx);
@@ -2402,11 +2499,9 @@ bm_status bm_index_build_sets(bm_context *ctx, uint32_t m, uint32_t n_sets, cons
     if (st != BM_OK)
         return st;
     HIPC(ctx, hipSetDevice(ctx->device));
-    std::unique_ptr<bm_index> idx(new (std::nothrow) bm_index());
+    std::unique_ptr<bm_index> idx(new (std::nothrow) bm_index(ctx));
     if (!idx)
         return fail(ctx, BM_ENOMEM, "host allocation");
-    idx->ctx = ctx;
-    idx->device = ctx->device;
     idx->m = m;
     idx->n = n_sets;
     hipStream_t s = ctx->stream;
@@ -2467,6 +2562,7 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
 {
     if (!ctx)
         return BM_EINVAL;
+    BM_WITH_ROOM(ctx, bm_index_build_transactions(ctx, n_items, m_txn, offsets, items, opts, out));
     ctx->err.clear();
     AllocScope scope(ctx->as);
     begin_build(ctx);
@@ -2481,11 +2577,9 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
     if (st != BM_OK)
         return st;
     HIPC(ctx, hipSetDevice(ctx->device));
-    std::unique_ptr<bm_index> idx(new (std::nothrow) bm_index());
+    std::unique_ptr<bm_index> idx(new (std::nothrow) bm_index(ctx));
     if (!idx)
         return fail(ctx, BM_ENOMEM, "host allocation");
-    idx->ctx = ctx;
-    idx->device = ctx->device;
     idx->m = m_txn;
     idx->n = n_items;
     hipStream_t s = ctx->stream;
@@ -2647,6 +2741,7 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
 {
     if (!idx)
         return BM_EINVAL;
+    BM_WITH_ROOM(idx->ctx, bm_all_pair_supports(idx, out, out_len));
     bm_context *ctx = idx->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -2690,6 +2785,7 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
 {
     if (!idx)
         return BM_EINVAL;
+    BM_WITH_ROOM(idx->ctx, bm_frequent_pairs(idx, min_support, out, capacity, n_out));
     bm_context *ctx = idx->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -2891,6 +2987,7 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
 {
     if (!idx)
         return BM_EINVAL;
+    BM_WITH_ROOM(idx->ctx, bm_triple_supports(idx, triples, count, out));
     bm_context *ctx = idx->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -2975,6 +3072,7 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
 {
     if (!idx)
         return BM_EINVAL;
+    BM_WITH_ROOM(idx->ctx, bm_subset_pair_supports(idx, items, k, out));
     bm_context *ctx = idx->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -3183,8 +3281,10 @@ bm_status batch_by_bits(bm_batch *b, const std::vector<double> &inst_work, bool 
     b->joint = gram_jobs(b->set, mats.data(), outs.data(), b->gram_ws.p, jobs.data());
     if (b->joint.n)
         BMC(upload(ctx, b->jobs.p, jobs.data(), b->joint.n * sizeof(GramJob)));
-    for (uint32_t q : b->gram_q)
+    for (uint32_t q : b->gram_q) {
         b->by_bits[q] = 1;
+        b->rows_use.push_back(b->idx[q]->rows_use);
+    }
     return BM_OK;
 }
 
@@ -3193,6 +3293,7 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
 {
     if (!ctx)
         return BM_EINVAL;
+    BM_WITH_ROOM(ctx, batch_create(ctx, idxs, count, outs, out, trial));
     ctx->err.clear();
     if (!out || !idxs || !outs || count == 0)
         return fail(ctx, BM_EINVAL, "null pointer or empty batch");
@@ -3433,6 +3534,7 @@ bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_
 {
     if (!idx)
         return BM_EINVAL;
+    BM_WITH_ROOM(idx->ctx, bm_all_pair_supports_dense(idx, out, out_len));
     bm_context *ctx = idx->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -3628,6 +3730,7 @@ bm_status bm_cross_pair_supports(bm_index *a, bm_index *b, uint32_t *out, uint64
 {
     if (!a || !b)
         return BM_EINVAL;
+    BM_WITH_ROOM(a->ctx, bm_cross_pair_supports(a, b, out, out_len));
     bm_context *ctx = a->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -3659,6 +3762,7 @@ bm_status bm_cross_pairs(bm_index *a, bm_index *b, uint32_t min_support, bm_pair
 {
     if (!a || !b)
         return BM_EINVAL;
+    BM_WITH_ROOM(a->ctx, bm_cross_pairs(a, b, min_support, out, capacity, n_out));
     bm_context *ctx = a->ctx;
     ctx->err.clear();
     AllocScope scope(ctx->as);
@@ -3711,6 +3815,7 @@ bm_status bm_index_export(const bm_index *cidx, uint32_t *sorted_items, uint32_t
 {
     if (!cidx)
         return BM_EINVAL;
+    BM_WITH_ROOM(cidx->ctx, bm_index_export(cidx, sorted_items, r, bytes, failed, perms));
     bm_index *idx = const_cast<bm_index *>(cidx);
     bm_context *ctx = idx->ctx;
     HIPC(ctx, hipSetDevice(ctx->device));
@@ -3844,6 +3949,7 @@ struct bm_server {
     std::vector<std::unique_ptr<SrvLaunch>> launches;
     std::vector<int32_t> sorted_pos;  // item -> sorted index (host copy)
     BitMat bits;                      // the index's bit rows; bits.bits null: queries compare slots
+    std::shared_ptr<char> rows_use;   // of the index, with them
     std::mutex mu;
     std::condition_variable cv_pump, cv_done;
     std::thread pump;
@@ -4252,6 +4358,7 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
 {
     if (!idx || !out)
         return BM_EINVAL;
+    BM_WITH_ROOM(idx->ctx, bm_server_create(idx, opts, out));
     *out = nullptr;
     bm_context *ctx = idx->ctx;
     bm_server_opts o;
@@ -4284,8 +4391,10 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
     if (!srv)
         return fail(ctx, BM_ENOMEM, "host allocation");
     srv->idx = idx;
-    if (by_bits)
+    if (by_bits) {
         srv->bits = whole_bits(idx);
+        srv->rows_use = idx->rows_use;
+    }
     srv->opts = o;
     srv->pool_bytes = align256(o.memory_budget);
     HIPC(ctx, hipMalloc(reinterpret_cast<void **>(&srv->dpool), srv->pool_bytes));
