@@ -397,6 +397,9 @@ struct bm_index {
     std::vector<uint32_t> h_sorted_items, h_r_sorted, h_sizes_sorted;
     std::vector<Cls> classes;
 
+    uint32_t load_first = UINT32_MAX;  // what `load` is of (see index_load)
+    CompareLoad load;
+
     // query scratch
     DevBuf<uint32_t> pairbuf;
     DevBuf<WorkItem> work;
@@ -649,21 +652,28 @@ bool bitmap_route_on(const bm_context *ctx)
     return bitmap_route_env() != 0 && !ctx->no_rows && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
 }
 
-// Expected time of a slot compare (us): W + 1 VALU operations per 32 slot
-// pairs, 30 * 10^12 a second with 8-bit slots and 20 with wider ones; a work
-// item's walk over up to 256 groups of the widest map (r_max slots a table),
-// about 1 us a group (2 with wider slots), which is what a compare takes that
-// does not fill the chip; fixed_us for launches, zero fill, corrections and
-// planning.  Slots and bits measured (MI355X, us, rows kept): 10^4 x 100 at 0.5 %:
-// 111 and 14; 200,000 x 300 at 0.5 %: 261 and 20; 50,000 x 1500 at 0.05 %
-// (16-bit slots, r = 128): 31 and 44; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x
-// 2000 Zipf at 2 %: 4700 and 670; 10^6 x 1500 at 0.05 % (16-bit): 332 and 390.
-double compare_us(double slot_pairs, uint32_t planes, double r_max, double fixed_us)
+// Expected time of a slot compare (us): fixed_us for launches, zero fill and planning,
+// 5 more where there are corrections, and its load.  Slots and bits measured (MI355X,
+// us, rows kept): 100,000 x 64 of 16,384 slots: 187 and 20; 5 * 10^6 x 32 of 65,536: 25
+// and 35; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x 2000 Zipf at 2 %: 4700 and 670; 10^6
+// x 1500 at 0.05 % (16-bit): 332 and 390.
+double compare_us(const CompareLoad &l, uint64_t n_corr, double fixed_us)
 {
-    const bool wide = planes != 8;
-    return fixed_us + std::min(256.0, 3 * r_max / 32) * (wide ? 2 : 1) +
-           slot_pairs / 32 * (planes + 1) / (wide ? 20e6 : 30e6);
+    return fixed_us + (n_corr ? 5 : 0) + l.wait_us + l.work_us;
 }
+
+// The load of the index's maps from sorted index `first` on.
+const CompareLoad &index_load(bm_index *idx, uint32_t first)
+{
+    if (idx->load_first != first) {
+        idx->load = compare_load(first > idx->first_built ? classes_from(idx->classes, first) : idx->classes, idx->planes);
+        idx->load_first = first;
+    }
+    return idx->load;
+}
+
+// Expected time of counting its pairs by slots in a call that only launches.
+double slots_us(bm_index *idx, uint32_t first) { return compare_us(index_load(idx, first), idx->n_corr, 10); }
 
 // Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
 double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (rows * row_words + tids) * 4 / 2.5e6; }
@@ -677,7 +687,7 @@ bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
 
 // Whether all pairs of an index that holds its bit rows will be counted from
 // them, now and at every later call.
-bool pairs_by_kept_bits(const bm_index *idx)
+bool pairs_by_kept_bits(bm_index *idx)
 {
     const bm_context *ctx = idx->ctx;
     if (!idx->bits.p || !bitmap_route_on(ctx) || bitmap_route_env() == 2 || idx->classes.empty() ||
@@ -685,7 +695,7 @@ bool pairs_by_kept_bits(const bm_index *idx)
         return false;
     return bitmap_route_env() == 1 ||
            plan_gram(idx->n, idx->n, true, bit_row_words(idx->m), (uint32_t)ctx->n_cu, pinned_gram_tile()).us <
-               compare_us(class_work(idx->classes), idx->planes, idx->h_r_sorted.back(), 20);
+               slots_us(idx, idx->first_built);
 }
 
 // Persistent plans run as one single-launch list: range (-1, all items),
@@ -1870,19 +1880,20 @@ bm_status ensure_bits(bm_index *idx)
     return BM_OK;
 }
 
-// Slot pairs of all pairs among k maps of widths r(0) .. r(k - 1) (powers of two).
+// The width classes of k maps of widths r(0) .. r(k - 1) (powers of two), narrowest first.
 template <typename F>
-double slot_work(uint32_t k, F r)
+std::vector<Cls> list_classes(uint32_t k, F r)
 {
-    uint32_t of_width[64] = {};
+    uint32_t of_width[32] = {}, start = 0;
     for (uint32_t p = 0; p < k; p++)
-        of_width[__builtin_ctzll(r(p))]++;
-    double work = 0, narrower = 0;
-    for (uint32_t l = 0; l < 64; l++) {
-        work += 3.0 * (double)(1ull << l) * of_width[l] * (narrower + 0.5 * (of_width[l] - 1.0));
-        narrower += of_width[l];
-    }
-    return work;
+        of_width[__builtin_ctz(r(p))]++;
+    std::vector<Cls> cls;
+    for (uint32_t l = 0; l < 32; l++)
+        if (of_width[l]) {
+            cls.push_back({1u << l, start, of_width[l]});
+            start += of_width[l];
+        }
+    return cls;
 }
 
 BitMat whole_bits(const bm_index *idx)
@@ -1929,14 +1940,13 @@ GramChoice choose_gram(const bm_index *idx, bool listed, uint32_t k)
 // items (or all) makes every item's row, which the index keeps; a shorter one
 // makes its own rows, until such lists have made as many rows as the index has
 // items: then the index's are made (their cost is what was spent already).
-// ids: receives the list on the device.
-bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, double other_us, uint32_t *out,
+// ids: receives the list on the device.  c: choose_gram of this list.
+bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, const GramChoice &c, double other_us, uint32_t *out,
                      DevBuf<uint32_t> &ids, bool &taken)
 {
     taken = false;
     bm_context *ctx = idx->ctx;
     hipStream_t s = ctx->stream;
-    const GramChoice c = choose_gram(idx, list != nullptr, k);
     const GramPlan &p = c.plan;
     const uint64_t ld = bit_row_words(idx->m);
     const bool whole = c.whole;
@@ -2768,10 +2778,11 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
     }
     bool taken = false;
     DevBuf<uint32_t> ids;
-    const double slots_us = compare_us(class_work(idx->classes), idx->planes, idx->h_r_sorted.back(), 20);
-    BMC(txn_pairs(idx, std::min(slots_us, choose_gram(idx, false, idx->n).us), dst, taken));
+    const double by_slots = slots_us(idx, 0);
+    const GramChoice c = choose_gram(idx, false, idx->n);
+    BMC(txn_pairs(idx, std::min(by_slots, c.us), dst, taken));
     if (!taken)
-        BMC(gram_pairs(idx, nullptr, idx->n, slots_us, dst, ids, taken));
+        BMC(gram_pairs(idx, nullptr, idx->n, c, by_slots, dst, ids, taken));
     if (!taken)
         BMC(count_pairs(idx, 0, dst));
     if (host) {
@@ -2816,15 +2827,14 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
         ids.assign(idx->h_sorted_items.begin() + first, idx->h_sorted_items.end());
         std::sort(ids.begin(), ids.end());
     }
-    const double slots_us =
-        compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes,
-                   idx->h_r_sorted.back(), 20);
+    const double by_slots = slots_us(idx, first);
     DevBuf<uint32_t> d_ids;
     bool by_txn = false, by_bits = false;
     HIPC(ctx, idx->pairbuf.ensure(np));
-    BMC(txn_pairs(idx, std::min(slots_us, choose_gram(idx, first > 0, live).us), idx->pairbuf.p, by_txn));
+    const GramChoice c = choose_gram(idx, first > 0, live);
+    BMC(txn_pairs(idx, std::min(by_slots, c.us), idx->pairbuf.p, by_txn));
     if (!by_txn)
-        BMC(gram_pairs(idx, first ? ids.data() : nullptr, live, slots_us, idx->pairbuf.p, d_ids, by_bits));
+        BMC(gram_pairs(idx, first ? ids.data() : nullptr, live, c, by_slots, idx->pairbuf.p, d_ids, by_bits));
     uint32_t n_eff = idx->n;
     if (by_bits && first) {
         n_eff = live;
@@ -2907,12 +2917,12 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     const uint64_t o_tmp = o_off + align_up(((uint64_t)nb + 1) * 8, 256);
     const uint64_t o_work = o_tmp + align_up(scan_tmp_bytes((uint64_t)nb + 1), 256);
     // From the index's grouped incidences, or its bit rows, when it holds them and
-    // that (with the scratch that is left) is expected to be faster.  An index that
-    // has counted by them may hold no plan, and one made here costs more than it.
+    // that (with the scratch that is left) is expected to be faster than slots, by
+    // the resident plan (see below) or one made here.
     const uint64_t room = o_work < kNoAllocScratchBytes ? (kNoAllocScratchBytes - o_work) / 4 : 0;
     GramPlan gram;
-    double us = compare_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes,
-                           idx->h_r_sorted.back(), 20);
+    const bool own = idx->planned_first != UINT32_MAX && idx->planned_first <= first;
+    double us = slots_us(idx, own ? idx->planned_first : first) + (own ? 0 : 50);  // planned and uploaded
     bool by_bits = false, by_txn = false;
     if (o_work <= kNoAllocScratchBytes && bitmap_route_on(ctx)) {
         if (idx->bits.p && bitmap_route_env() != 2) {
@@ -2929,7 +2939,6 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     // speeds only weigh shapes, every plan is complete).  Pairs it adds among
     // items below the support bound cannot reach the bound.  Otherwise a plan
     // is made here and placed in the scratch.
-    const bool own = idx->planned_first != UINT32_MAX && idx->planned_first <= first;
     std::vector<WorkItem> flat;
     std::vector<std::pair<int, uint32_t>> ranges;
     double slot_pairs = idx->planned_slot_pairs;
@@ -3027,12 +3036,14 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
         HIPC(ctx, res.alloc(count));
         dst = res.p;
     }
-    // slots: 1.3 * 10^7 slot triples a microsecond; bits: the rows at 12 TB/s,
-    // mostly one row a triple (41,664 triples of 64 items, 10^6 transactions, 500
-    // items at 2 %: 94 ms and 0.25 ms).  Rows not yet made are paid by the call or,
+    // slots: 1.3 * 10^7 slot triples a microsecond, a triple's walk 10 ns a slot; bits: the
+    // rows at 12 TB/s, mostly one row a triple.  Measured (us, slots and bits): 41,664
+    // triples of 64 items, 10^6 transactions, 500 items at 2 %: 94,000 and 250; 100 triples
+    // of maps of 512 slots (300 x 2000): 34.3 and 37.7; one of 8192 slots: 117 and 37.  Rows not yet made are paid by the call or,
     // item by item named, by the calls before it.
     const uint64_t ld = bit_row_words(idx->m);
-    const double slots_us = 30 + slot_triples / 1.3e7, bits_us = 12 + (double)count * ld * 4 * 1.3 / 12e6;
+    const double slots_us = 22 + 0.01 * slot_triples / (double)count + slot_triples / 1.3e7;
+    const double bits_us = 28 + (double)count * ld * 4 * 1.3 / 12e6;
     const bool have = idx->bits.p != nullptr;
     const uint64_t named = std::min<uint64_t>(idx->n, 3 * count);
     bool by_bits = false;
@@ -3112,20 +3123,24 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
             good = !seen[q[p]] && idx->h_off[q[p] + 1] - idx->h_off[q[p]] >= idx->min_support;
             seen[q[p]] = true;
         }
-        uint64_t r_max = 0;
-        const double slots = slot_work(k, [&](uint32_t p) {
-            const uint64_t sz = idx->h_off[q[p] + 1] - idx->h_off[q[p]];
-            uint64_t r = idx->r0;
-            while (r < 2 * sz)
-                r <<= 1;
-            r_max = std::max(r_max, r);
-            return r;
-        });
         bool taken = false;
         DevBuf<uint32_t> ids;
-        // the slot compare plans its tiles on the host and uploads five lists: about 60 us
-        if (good)
-            BMC(gram_pairs(idx, q.data(), k, compare_us(slots, idx->planes, (double)r_max, 60), dst, ids, taken));
+        if (good) {
+            const std::vector<Cls> cls = list_classes(k, [&](uint32_t p) {
+                const uint64_t sz = idx->h_off[q[p] + 1] - idx->h_off[q[p]];
+                uint64_t r = idx->r0;
+                while (r < 2 * sz && r < 1ull << 31)
+                    r <<= 1;
+                return (uint32_t)r;
+            });
+            // the slot compare plans its tiles on the host and uploads five lists: about 60
+            // us; how it would run is only looked at where the work alone leaves it open
+            double by_slots = 60 + slot_pairs_us(class_work(cls), idx->planes);
+            const GramChoice c = choose_gram(idx, true, k);
+            if (c.us >= by_slots)
+                by_slots = compare_us(compare_load(cls, idx->planes), idx->n_corr, 60);
+            BMC(gram_pairs(idx, q.data(), k, c, by_slots, dst, ids, taken));
+        }
         if (taken) {
             if (host)
                 BMC(download(ctx, out, dst, np * 4));
@@ -3255,7 +3270,11 @@ bm_status batch_by_bits(bm_batch *b, const std::vector<double> &inst_work, bool 
             double us = plan_gram(ix->n, ix->n, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile()).us;
             if (once && !ix->bits.p)  // a batch to be replayed keeps its rows
                 us += bit_rows_us(ix->n, ld, (double)ix->nnz);
-            if ((us >= compare_us(inst_work[q], ix->planes, ix->h_r_sorted.back(), 10) && bitmap_route_env() != 1) ||
+            // several instances' items wait for one another's
+            CompareLoad load = index_load(ix, 0);
+            if (b->idx.size() > 1)
+                load.wait_us = std::max(0.0, load.wait_us / b->idx.size() - load.work_us);
+            if ((us >= compare_us(load, ix->n_corr, 10) && bitmap_route_env() != 1) ||
                 (!ix->bits.p && !bit_rows_fit(ctx, ix->n, ld)))
                 continue;
             const uint64_t bytes = ix->bits.p ? 0 : ((uint64_t)ix->n + 1) * ld * 4;
@@ -3649,9 +3668,12 @@ bm_status cross_gram(bm_index *a, bm_index *b, uint32_t *out, bool &taken)
     for (const Cls &x : a->classes)
         for (const Cls &y : b->classes)
             slots += 3.0 * std::max(x.r, y.r) * x.count * y.count;
-    // planning, the uploads and the launches of the slot compare: about 130 us
-    const double r_max = std::max(a->h_r_sorted.back(), b->h_r_sorted.back());
-    if ((us >= compare_us(slots, a->planes, r_max, 130) && bitmap_route_env() != 1) || capturing(ctx->stream))
+    // planning, the uploads and the launches of the slot compare: about 130 us; the
+    // load's wait as among all of a family's maps, the one that waits longer
+    CompareLoad load;
+    load.work_us = slot_pairs_us(slots, a->planes);
+    load.wait_us = std::max(index_load(a, 0).wait_us, index_load(b, 0).wait_us);
+    if ((us >= compare_us(load, a->n_failed + b->n_failed, 130) && bitmap_route_env() != 1) || capturing(ctx->stream))
         return BM_OK;
     DevBuf<float> ws;
     if (ws.alloc(p.ws_floats) != hipSuccess)
@@ -4034,8 +4056,9 @@ hipError_t bm_server::launch_group(SrvLaunch &L, const std::vector<SrvRequest *>
         if (!bits.bits)
             continue;
         const double us = plan_gram(r.k, r.k, true, bits.ld, (uint32_t)ix->ctx->n_cu, pinned_gram_tile()).us;
-        const double slots = slot_work(r.k, [&](uint32_t p) { return ix->h_r_sorted[sorted_pos[r.items[p]]]; });
-        if (us < compare_us(slots, 8, 0, 50) || bitmap_route_env() == 1) {
+        const std::vector<Cls> cls =
+            list_classes(r.k, [&](uint32_t p) { return ix->h_r_sorted[sorted_pos[r.items[p]]]; });
+        if (us < 50 + slot_pairs_us(class_work(cls), 8) || bitmap_route_env() == 1) {
             by_bits[j] = 1;
             shapes.push_back({r.k, bits.ld});
             n_ids += r.k;
@@ -4380,7 +4403,7 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
         AllocScope scope(ctx->as);
         const uint64_t ld = bit_row_words(idx->m);
         const double us = plan_gram(idx->n, idx->n, true, ld, (uint32_t)ctx->n_cu).us;
-        by_bits = idx->bits.p || ((us < compare_us(class_work(idx->classes), 8, 0, 0) || bitmap_route_env() == 1) &&
+        by_bits = idx->bits.p || ((us < slot_pairs_us(class_work(idx->classes), 8) || bitmap_route_env() == 1) &&
                                   bit_rows_fit(ctx, idx->n, ld) && ensure_bits(idx) == BM_OK);
         ctx->err.clear();
     }

@@ -834,6 +834,60 @@ std::vector<Cls> classes_from(const std::vector<Cls> &cls, uint32_t first)
     return out;
 }
 
+// W + 1 VALU operations per 32 slot pairs, 30 * 10^12 a second with 8-bit slots and 20
+// with wider ones.
+double slot_pairs_us(double slot_pairs, uint32_t planes)
+{
+    return slot_pairs / 32 * (planes + 1) / (planes == 8 ? 30e6 : 20e6);
+}
+
+// A row-resident item walks up to 256 groups of the widest map, 0.66 us a group (1.05
+// with wider slots).  Where every pair of classes goes by group-parallel tiles (up to
+// about 60 maps a class with 8-bit slots, 76 with wider ones), lanes share the groups:
+// a few microseconds, more when widths differ (a narrow map meets a wide one's groups
+// one wrap after the other), and about three times the work at a time when the chip
+// has little of it.  1,149 instances of 3 to 3,000 maps of 128 to 2^24 slots over 10^4 to
+// 10^7 transactions (MI355X): choosing between slots and bits by this and plan_gram
+// takes 1.0 % (8 bits), 1.3 % (16) and 0.7 % (32) longer in the mean than the faster
+// of the two each time, and 35 go by bits that slots count over 5 % faster (31 us
+// against 42 at most).  With the walk at 1 us (2) and on every call: 7.0, 3.7 and
+// 0.6 %, and 151, of which the worst by 2.3 (34 us against 79).
+CompareLoad compare_load(const std::vector<Cls> &cls, uint32_t planes)
+{
+    CompareLoad l;
+    if (cls.empty())
+        return l;
+    l.work_us = slot_pairs_us(class_work(cls), planes);
+    const double G = 3.0 * cls.back().r / kSlotsPerGroup;
+    uint64_t maps = 0, most = 0;
+    for (const Cls &c : cls) {
+        maps += c.count;
+        most = std::max<uint64_t>(most, c.count);
+    }
+    bool small_tiles = most < 80 && maps <= 256;
+    for (size_t a = 0; a < cls.size() && small_tiles; a++)
+        for (size_t b = a; b < cls.size() && small_tiles; b++) {
+            double cost = 0, speed = 0;
+            if (a == b && cls[a].count < 2)
+                continue;
+            const int v = best_shape({cls[a], cls[b], a == b, 0}, nullptr, 0, -1, planes, &cost, &speed);
+            small_tiles = v >= 0 && kInfo[v].step == 64;
+        }
+    const bool near = cls.back().r <= 4 * cls.front().r;
+    if (!small_tiles || (!near && planes == 32)) {
+        l.wait_us = std::min(256.0, G) * (planes == 8 ? 0.66 : 1.05);
+        return l;
+    }
+    l.work_us *= 3;
+    if (!near)
+        l.wait_us = 0.2 * std::min(256.0, G);
+    else if (cls.size() > 1)
+        l.wait_us = (planes == 8 ? 12 : planes == 16 ? 30 : 60) * std::min(1.0, G / 512);
+    else
+        l.wait_us = (planes == 8 ? 4 : planes == 16 ? 14 : 30) * std::min(1.0, G / 512);
+    return l;
+}
+
 // Time of a plan = launches (10 us for the pair) + stages over the chip + parts
 // written and read back (4 TB/s).  A stage of a 256-, 128- or 64-wide tile takes
 // a CU 2.3, 0.62 or 0.27 us (MI355X, m = 2^20, n = 4096); one, three and up to

@@ -183,6 +183,15 @@ inline uint64_t bit_row_words(uint32_t m)
 // transactions: counts stay exact whole numbers).
 constexpr uint64_t kGramMaxStages = (1u << 24) / kGramStage;
 
+// What a slot compare of all pairs among maps of these classes takes beyond its
+// launches (us): its slot pairs at the rate of their width, and the wait for its
+// longest work item.
+struct CompareLoad {
+    double work_us = 0, wait_us = 0;
+};
+double slot_pairs_us(double slot_pairs, uint32_t planes);
+CompareLoad compare_load(const std::vector<Cls> &cls, uint32_t planes);
+
 // A launch holds fewer than 2^32 work-items.
 inline bool grid_fits(uint64_t blocks, uint64_t threads) { return blocks < (1ull << 32) / threads; }
 

@@ -216,10 +216,19 @@ __global__ void check_triples_kernel(const uint32_t *triples, uint64_t count, ui
         else  // sorted by size, so the last position is the widest map
             sum += (unsigned long long)kTables3 * r_sorted[max(pa, max(pb, pc))];
     }
+    // one atomic a workgroup: they all meet on one word (20,000 triples, one a wavefront: 4 us more)
+    __shared__ unsigned long long part[kBlock / 64];
     for (int o = 32; o > 0; o >>= 1)
         sum += __shfl_xor(sum, o, 64);
-    if ((threadIdx.x & 63) == 0 && sum)
-        atomicAdd(slots, sum);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x / 64] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; w++)
+            sum += part[w];
+        if (sum)
+            atomicAdd(slots, sum);
+    }
 }
 
 // Counts of the triple rule for 8 consecutive slots of table t (16-bit slots
@@ -438,7 +447,8 @@ hipError_t launch_check_triples(const uint32_t *triples, uint64_t count, uint32_
 {
     if (count == 0)
         return hipSuccess;
-    check_triples_kernel<<<blocks_for(count, 65536), kBlock, 0, s>>>(triples, count, n, sorted_pos, r_sorted, flag, slots);
+    check_triples_kernel<<<blocks_for(count, 1024), kBlock, 0, s>>>(triples, count, n, sorted_pos, r_sorted, flag,
+                                                                    slots);
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 // The sizes of launches as the host computes them, built with plan.cpp (no GPU).
 #include <cstdint>
+#include <vector>
 
 #include "../paper_1102_1003_amd/csrc/plan.h"
 
@@ -87,4 +88,20 @@ extern "C" int gram_add_check(uint32_t na, uint32_t nb, int tri, uint32_t m, uin
             return 2;
     }
     return shared && !p.add ? 3 : 0;
+}
+
+// Expected times of counting all pairs among maps of these classes (widths and counts,
+// narrowest first) by slots and from bit rows of m transactions.
+extern "C" void route_prices(const uint32_t *r, const uint32_t *count, uint32_t n_cls, uint32_t planes, uint32_t m,
+                             int corrections, double *slots, double *bits)
+{
+    std::vector<bm::Cls> cls;
+    uint32_t maps = 0;
+    for (uint32_t c = 0; c < n_cls; c++) {
+        cls.push_back({r[c], maps, count[c]});
+        maps += count[c];
+    }
+    const bm::CompareLoad l = bm::compare_load(cls, planes);
+    *slots = 10 + (corrections ? 5 : 0) + l.wait_us + l.work_us;
+    *bits = bm::plan_gram(maps, maps, true, bm::bit_row_words(m), 256).us;
 }

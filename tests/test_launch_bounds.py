@@ -1,6 +1,6 @@
 """What the host computes before a launch, checked on the CPU.  Launch sizes at the far end of what the
 calls take: a launch of 2^32 work-items or more is refused by the runtime, so every grid has to stay below
-that, whatever the sizes.  And the expected time that chooses the count by transactions."""
+that, whatever the sizes.  And the expected times that choose how pairs are counted."""
 import ctypes
 import os
 import subprocess
@@ -93,3 +93,31 @@ def test_product_without_scratch(lib, m, pinned):
         if n < 300 or m < 2**24:
             assert lib.gram_add_check(n, n, 1, ctypes.c_uint32(m), 256, pinned) == 0
     assert lib.gram_add_check(300, 1, 0, ctypes.c_uint32(m), 8, pinned) == 0
+
+
+# (slot bits, m, corrections, width classes, measured by slots, from bit rows): MI355X, us, a call and a wait
+ROUTES_MEASURED = [
+    (8, 10**7, 0, [(131072, 3)], 23, 42), (8, 10**7, 0, [(131072, 12)], 22, 42), (8, 10**7, 0, [(1048576, 3)], 21, 41),
+    (8, 5 * 10**6, 0, [(65536, 32)], 25, 35), (8, 5 * 10**6, 0, [(65536, 64)], 188, 33),
+    (8, 10**6, 0, [(8192, 10), (16384, 8), (32768, 18), (65536, 4)], 61, 25),
+    (8, 10**4, 2, [(128, 38), (256, 9), (512, 5), (1024, 2), (2048, 1), (4096, 1)], 76, 19),
+    (8, 10**5, 1, [(1024, 1), (2048, 2), (4096, 3), (8192, 8), (16384, 22), (32768, 4)], 69, 20),
+    (8, 10**4, 0, [(128, 1600)], 28, 37), (8, 10**4, 0, [(128, 3000)], 39, 58), (8, 10**6, 0, [(8192, 3000)], 1010, 1359),
+    (8, 10**6, 0, [(32768, 1600)], 1223, 461), (8, 10**5, 0, [(1024, 200)], 78, 24), (8, 10**6, 0, [(8192, 400)], 331, 76),
+    (8, 10**5, 31640, [(2048, 3000)], 329, 183), (16, 10**7, 8, [(2048, 800)], 356, 1515),
+    (16, 10**7, 0, [(512, 17), (1024, 9), (2048, 27), (4096, 47)], 34, 79),
+    (16, 10**6, 1, [(128, 255), (256, 275), (512, 270)], 74, 172), (16, 10**5, 85, [(256, 1600)], 59, 84),
+    (16, 10**6, 0, [(1024, 1), (16384, 2), (32768, 6), (65536, 3)], 216, 24),
+    (16, 10**6, 0, [(1024, 5), (2048, 4), (4096, 2), (8192, 1)], 41, 23), (32, 10**7, 0, [(2048, 12)], 31, 42),
+    (16, 10**6, 0, [(32768, 20), (65536, 36)], 1060, 24), (32, 10**5, 63, [(2048, 104), (4096, 148), (8192, 131)], 1260, 28),
+]
+
+
+@pytest.mark.parametrize("planes,m,corr,classes,slots,bits", ROUTES_MEASURED)
+def test_slots_or_bits(lib, planes, m, corr, classes, slots, bits):
+    """The way that the expected times name is the faster one, where the two are a fifth apart."""
+    r = (ctypes.c_uint32 * len(classes))(*[c[0] for c in classes])
+    n = (ctypes.c_uint32 * len(classes))(*[c[1] for c in classes])
+    by_slots, by_bits = ctypes.c_double(), ctypes.c_double()
+    lib.route_prices(r, n, len(classes), planes, ctypes.c_uint32(m), corr, ctypes.byref(by_slots), ctypes.byref(by_bits))
+    assert (by_slots.value <= by_bits.value) == (slots < bits), (by_slots.value, by_bits.value)
