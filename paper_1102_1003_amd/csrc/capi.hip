@@ -1565,24 +1565,6 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
     if (idx->total_groups >= (1ull << 32))
         return fail(ctx, BM_EINVAL, "BatMaps of %llu groups (%llu bytes); at most 2^32 groups per index",
                     (unsigned long long)idx->total_groups, (unsigned long long)idx->total_groups * kSlotsPerGroup);
-    idx->classes.clear();
-    for (uint32_t p = first_built; p < n; p++) {
-        uint32_t r = idx->h_r_sorted[p];
-        if (idx->classes.empty() || idx->classes.back().r != r)
-            idx->classes.push_back({r, p, 0});
-        idx->classes.back().count++;
-    }
-    // the all-pairs plan depends only on the width classes: a host thread
-    // makes it from here on while the construction's kernels run (indexes of
-    // up to kPlanAtBuild maps; larger ones are mostly queried by subsets, and
-    // planning all their pairs takes longer than building them)
-    // Not where the pairs will be counted from the bit rows that the ingest
-    // left: the build waited for its plan (large Zipf: 0.3 ms past its kernels).
-    const bool plan_here = !order3 && n - first_built <= kPlanAtBuild && !pairs_by_kept_bits(idx);
-    std::future<Plan> early_plan;
-    if (plan_here)
-        early_plan = start_plan(idx, first_built);
-
     // The block family builds the paper's 8-bit maps of order two with
     // generated permutations whenever a block of 3 r_0 code bytes fits the
     // LDS; the chain family (staged and whole-map LDS builds below) builds the
@@ -1611,6 +1593,24 @@ bm_status build_common(bm_index *idx, const bm_build_opts *o)
     DevBuf<uint8_t> has_map;
     HIPC(ctx, idx->sorted_pos.alloc(n));
     HIPC(ctx, has_map.alloc(std::max<uint32_t>(n, 1)));
+    idx->classes.clear();
+    for (uint32_t p = first_built; p < n; p++) {
+        uint32_t r = idx->h_r_sorted[p];
+        if (idx->classes.empty() || idx->classes.back().r != r)
+            idx->classes.push_back({r, p, 0});
+        idx->classes.back().count++;
+    }
+    // the all-pairs plan depends only on the width classes: a host thread
+    // makes it from here on while the construction's kernels run (indexes of
+    // up to kPlanAtBuild maps; larger ones are mostly queried by subsets, and
+    // planning all their pairs takes longer than building them)
+    // Not where the pairs will be counted from the bit rows that the ingest
+    // left: the build waited for its plan (large Zipf: 0.3 ms past its kernels).
+    const bool plan_here = !order3 && n - first_built <= kPlanAtBuild && !pairs_by_kept_bits(idx);
+    std::future<Plan> early_plan;
+    if (plan_here)
+        early_plan = start_plan(idx, first_built);
+
     // construction, in batches of maps whose staging fits the budget
     span_layout.end();
     HIPC(ctx, idx->arena.alloc(std::max<uint64_t>(idx->total_groups, 1) * idx->planes));
