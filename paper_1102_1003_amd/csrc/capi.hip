@@ -2942,7 +2942,8 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     std::vector<WorkItem> flat;
     std::vector<std::pair<int, uint32_t>> ranges;
     double slot_pairs = idx->planned_slot_pairs;
-    if (!own && !by_bits && !by_txn) {
+    const bool none = idx->n - first < 2;  // no pair of items that reach the bound
+    if (!own && !by_bits && !by_txn && !none) {
         Plan plan;
         plan_classes(classes_from(idx->classes, first), 0, target_items(ctx), plan, nullptr,
                      single_launch(ctx, idx->planes) ? 1 : 0, forced_variant(), false, idx->planes, packed_rows());
@@ -2955,6 +2956,8 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     if (end > kNoAllocScratchBytes)
         return fail(ctx, BM_EINVAL, "%u items need %llu bytes of scratch; the allocation-free call has %llu", idx->n,
                     (unsigned long long)end, (unsigned long long)kNoAllocScratchBytes);
+    if (none)
+        return BM_OK;
     uint8_t *sc = ctx->scratch;
     uint32_t *counts = reinterpret_cast<uint32_t *>(sc);
     uint32_t *thr_counts = reinterpret_cast<uint32_t *>(sc + o_cnt);

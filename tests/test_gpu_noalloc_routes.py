@@ -35,3 +35,30 @@ def test_after_counting_by_transactions(m, n, p):
         ctx.synchronize()
         assert np.array_equal(out.cpu().numpy().view(np.uint32)[:3 * len(want)].reshape(-1, 3), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("route", [None, "0"])
+def test_bound_above_every_set(monkeypatch, route):
+    """No item, or one, reaches the bound: no pair; an index past the scratch is refused all the same."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if route is not None:
+        monkeypatch.setenv("BM_BITMAP_ROUTE", route)
+    off, tids = datagen.bernoulli_sets(20_000, 300, 0.02, seed=3)
+    sizes = np.sort(np.diff(off))
+    ctx = bm.Context(0)
+    idx = bm.Index.from_sets(ctx, 20_000, off, tids)
+    out = torch.full((300,), -1, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    for rep in range(2):
+        for sigma in (int(sizes[-1]) + 1, int(sizes[-2]) + 1, 1 << 31):
+            assert idx.frequent_pairs_noalloc(sigma, out) == 0 == idx.frequent_pairs_noalloc(sigma)
+            assert len(idx.frequent_pairs(sigma)) == 0
+        idx.all_pair_supports()
+    assert (out == -1).all()
+    big_off, big_tids = datagen.bernoulli_sets(1_000, 5_200, 0.01, seed=4)
+    big = bm.Index.from_sets(ctx, 1_000, big_off, big_tids)
+    with pytest.raises(bm.BatmapError) as e:
+        big.frequent_pairs_noalloc(1 << 20)
+    assert e.value.status == bm.BM_EINVAL
+    ctx.close()
