@@ -37,7 +37,25 @@ __global__ void __launch_bounds__(256) txn_walk_kernel(const uint32_t *__restric
         squares += __shfl_xor(squares, o, 64);
         longest = max(longest, __shfl_xor(longest, o, 64));
     }
-    if ((threadIdx.x & 63) == 0 && longest) {
+    // one workgroup's atomics: they all meet on one line
+    __shared__ unsigned long long part[4][4];
+    if ((threadIdx.x & 63) == 0) {
+        const uint32_t w = threadIdx.x / 64;
+        part[w][0] = pairs;
+        part[w][1] = items;
+        part[w][2] = squares;
+        part[w][3] = longest;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; w++) {
+            pairs += part[w][0];
+            items += part[w][1];
+            squares += part[w][2];
+            longest = max(longest, part[w][3]);
+        }
+        if (longest == 0)
+            return;
         atomicAdd(reinterpret_cast<unsigned long long *>(&walk->pairs), pairs);
         atomicMax(reinterpret_cast<unsigned long long *>(&walk->longest), longest);
         if (items) {
@@ -62,9 +80,10 @@ __global__ void __launch_bounds__(256) txn_scatter_kernel(const uint64_t *__rest
 // after i live in LDS, the lanes walk the transactions of S_i, and the row leaves
 // once, in order (no zero fill, no device atomics: added into device memory
 // the counts would run at 27 * 10^9 a second, and slower where pairs are hot).
-// Bound by the dependent loads tid -> transaction -> items; 2^20 x 8192 at 0.05 %
-// (4.3 * 10^6 incidences, 4 items a transaction, 134 MB of counts): 0.18 ms,
-// the slot compare 4.8 ms.
+// Bound by the random loads tid -> transaction -> items: at 2^20 x 8192 and 0.05 % (4.3
+// * 10^6 incidences, 4 items a transaction, 134 MB of counts) they read 870 MB past
+// the L2s, and the waves wait for them nine tenths of their time: 0.18 ms, the slot
+// compare 4.8 ms.
 __global__ void txn_rows_kernel(const uint64_t *__restrict__ off, const uint32_t *__restrict__ tids,
                                 const uint32_t *__restrict__ start, const uint32_t *__restrict__ items, uint32_t n,
                                 uint32_t *__restrict__ out)
