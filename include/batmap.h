@@ -214,7 +214,14 @@ void bm_index_destroy(bm_index *idx);
  * sparse sets, up to 16,384 of them) by walking the transactions of each set;
  * the counts are exact whichever way.  Bit rows take n m / 8 bytes, at most a
  * sixteenth of the device's memory; the index keeps them, and the incidences
- * grouped by transaction, until it is destroyed. */
+ * grouped by transaction, until it is destroyed or a call on its context finds
+ * no memory: that call gives back what no batch, server or captured graph
+ * reads, and compares slots.
+ * Under stream capture (out: device) the call launches over what earlier calls
+ * and the build have left in the index, with no scratch that another call or
+ * graph uses: a slot plan, else the grouped incidences, else the bit rows.
+ * BM_EINVAL where it holds none of them (an index of more than 4096 items before
+ * its first all-pairs call); nothing is made inside a capture. */
 bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len);
 
 /* Frequent pair mining (Sec. I: pairs with support at least sigma): every
@@ -227,7 +234,8 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * result as bm_frequent_pairs, computed without any hipMalloc, hipFree or
- * other allocating call.  Its intermediate counts, per-block counts, scan
+ * other allocating call, from the index's bit rows or grouped incidences where
+ * it holds them and that is expected to be faster.  Its intermediate counts, per-block counts, scan
  * workspace and (when the index holds no plan covering these items) work
  * list live in one scratch array of 48 MiB per GPU, part of the library and
  * held until the process ends; the context and the index bring everything
@@ -325,8 +333,9 @@ bm_status bm_batch_all_pair_supports(bm_context *ctx, bm_index *const *idx, uint
  * its memory.  Results are identical to bm_subset_pair_supports.
  * bm_server_create makes the index's bit rows when the bitmap route is
  * expected to count all its pairs faster (see bm_all_pair_supports); queries
- * that it counts faster are then multiplied instead of compared, with up to
- * 134 MB of scratch a launch slot.
+ * that it counts faster are then multiplied instead of compared.  Each launch
+ * slot then holds scratch outside memory_budget: 101 MB from creation on, at
+ * most 134 MB.
  * The index must stay alive and must not be destroyed while the server
  * runs; other calls on the index may run from the thread that owns the
  * context.  A server's calls are thread-safe among themselves.
@@ -340,7 +349,7 @@ typedef struct {
     uint32_t max_batch;      /* queries admitted into one launch at most (default 64, at most 65535) */
     uint32_t flags;          /* reserved, 0 */
     uint64_t memory_budget;  /* device bytes for in-flight queries (default 1 GiB); with bit rows
-                              * a stream also keeps about 100 MB of scratch */
+                              * each slot holds scratch beside it (see above) */
 } bm_server_opts;
 typedef struct {
     double queued_s;   /* submit -> admitted */
@@ -371,7 +380,8 @@ void bm_server_destroy(bm_server *srv);
 /* Same result as bm_all_pair_supports by the plain bitmap route (Sec. I-A,
  * bitmaps: AND and count): a bit row per item (one bit per transaction, kept
  * in the index from the first such call) and the product A A^T on the matrix
- * cores, 0 and 1 as 4-bit floats, counts exact. */
+ * cores, 0 and 1 as 4-bit floats, counts exact.  Under stream capture BM_EINVAL
+ * before the index has rows. */
 bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_len);
 
 /* Inspection (tests, tools).  Copies to host buffers:

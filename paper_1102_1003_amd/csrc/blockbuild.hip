@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(kBucketThreads)
 // element is recovered by inverting beta, with no staging of tids.
 //
 // kHops: `hops` holds, for a copy at position pos of table t in a block of H's,
-// its position in the next table (launch_block_hops); one load then takes the
+// its position in the next table (block_prep_kernel); one load then takes the
 // place of two keys, beta's inverse and beta.  A chain's moves wait for one
 // another, so in small builds, where the longest chains (failures: 3 MaxLoop moves)
 // are what the launch takes, a move's latency is all that counts.

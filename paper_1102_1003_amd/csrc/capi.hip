@@ -943,7 +943,8 @@ struct ReadBack {
 // Up to here small pieces go to and from pinned memory by one kernel.
 constexpr uint64_t kPieceBytes = 256u << 10;
 
-// callers: a source is the caller's memory, which only copy commands touch.
+// callers: a source is the caller's memory that no kernel has read yet, which is
+// left to copy commands (the runtime checks their addresses).
 bm_status read_back_many(bm_context *ctx, std::initializer_list<ReadBack> reads, bool callers = false)
 {
     uint64_t total = 0;

@@ -45,7 +45,7 @@ def test_after_an_eager_call(stream_ctx, monkeypatch, route):
         monkeypatch.setenv("BM_BITMAP_ROUTE", route)
     m, n = 200_000, 5_000
     off, tids = datagen.bernoulli_sets(m, n, 0.0005, seed=5)
-    want = oracle.all_pairs(off, tids)
+    want = oracle.all_pairs(off, tids, threads=0)
     idx = bm.Index.from_sets(c, m, off, tids)
     out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
     torch.cuda.synchronize()
@@ -72,7 +72,7 @@ def test_nothing_made_inside(stream_ctx, monkeypatch, route):
         monkeypatch.setenv("BM_BITMAP_ROUTE", route)
     m, n = 30_000, 4_200
     off, tids = datagen.bernoulli_sets(m, n, 0.001, seed=7)
-    want = oracle.all_pairs(off, tids)
+    want = oracle.all_pairs(off, tids, threads=0)
     idx = bm.Index.from_sets(c, m, off, tids)
     out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
     torch.cuda.synchronize()

@@ -26,8 +26,11 @@ def test_after_counting_by_transactions(m, n, p):
         idx.all_pair_supports()
         assert ctx.timings()["compare_slot_pairs"] == 0
         ctx.set_profiling(False)
+    every = oracle.all_pairs(off, tids, threads=0)
+    i, j = np.triu_indices(n, 1)
     for sigma in (1, 2, 3):
-        want = oracle.frequent_pairs(off, tids, sigma)
+        keep = every >= sigma
+        want = np.stack([i[keep], j[keep], every[keep]], 1).astype(np.uint32)
         out = torch.zeros(3 * max(len(want), 1), dtype=torch.int32, device="cuda:0")
         torch.cuda.synchronize()
         assert idx.frequent_pairs_noalloc(sigma) == len(want)
