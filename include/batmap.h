@@ -22,6 +22,9 @@
  *    device memory are complete after bm_synchronize() (or any later work
  *    on that stream); results written to host memory are complete when the
  *    call returns.
+ *  - While the context's stream is being captured, the two all-pairs calls of
+ *    one index record their work (device output); calls that wait for the
+ *    device return BM_EINVAL before they queue or allocate anything.
  *  - A context and the indexes built on it must not be used from two host
  *    threads at the same time.
  *  - Item ids are 0..n-1 in the caller's numbering; transaction ids (tids)

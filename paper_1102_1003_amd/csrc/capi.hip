@@ -522,10 +522,19 @@ bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
+        (void)hipGetLastError();  // a stream that cannot be asked: the work queued on it reports why
+        return false;
     }
     return st != hipStreamCaptureStatusNone;
+}
+
+// For calls that wait for the device: refused under capture before they allocate
+// or queue anything (a buffer grown there would be the graph's).
+bm_status not_captured(bm_context *ctx)
+{
+    if (capturing(ctx->stream))
+        return fail(ctx, BM_EINVAL, "the call waits for the device and cannot be captured");
+    return BM_OK;
 }
 
 // Gives back the bit rows and grouped incidences of the context's indexes that no
@@ -649,7 +658,8 @@ int bitmap_route_env()
 // compare).
 bool bitmap_route_on(const bm_context *ctx)
 {
-    return bitmap_route_env() != 0 && !ctx->no_rows && !ctx->persistent && forced_variant() < 0 && !getenv("BM_PACKED_ROWS");
+    return bitmap_route_env() != 0 && !ctx->no_rows && !ctx->persistent && forced_variant() < 0 &&
+           !getenv("BM_PACKED_ROWS");
 }
 
 // Expected time of a slot compare (us): fixed_us for launches, zero fill and planning,
@@ -682,7 +692,8 @@ double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (
 // and by one launch.
 bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
 {
-    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16 && grid_fits(bit_row_blocks(rows, row_words), kBitRowThreads);
+    return (rows + 1) * row_words * 4 <= ctx->mem_bytes / 16 &&
+           grid_fits(bit_row_blocks(rows, row_words), kBitRowThreads);
 }
 
 // Whether all pairs of an index that holds its bit rows will be counted from
@@ -824,8 +835,6 @@ bm_status ensure_plan(bm_index *idx, uint32_t first, hipStream_t st = nullptr, s
     bm_context *ctx = idx->ctx;
     if (idx->planned_first == first && idx->planned_gen == ctx->tune_gen)
         return BM_OK;
-    if (capturing(st ? st : ctx->stream))
-        return fail(ctx, BM_EINVAL, "no plan of the compare to capture: make the call once before the capture");
     Plan plan;
     const bool single = single_launch(ctx, idx->planes);
     if (early && early->valid()) {
@@ -1958,8 +1967,6 @@ bm_status gram_pairs(bm_index *idx, const uint32_t *list, uint32_t k, const Gram
     }
     if (!go)
         return BM_OK;
-    if (capturing(s))
-        return BM_OK;
     DevBuf<float> ws;
     DevBuf<uint32_t> own;
     if (ws.alloc(p.ws_floats) != hipSuccess || (list && ids.alloc(k) != hipSuccess))
@@ -2024,7 +2031,7 @@ bm_status txn_pairs(bm_index *idx, double other_us, uint32_t *out, bool &taken)
             if (idx->txn_saved_us <= make_us)
                 return BM_OK;
         }
-        if (2 * ((uint64_t)idx->m + idx->nnz) * 4 > ctx->mem_bytes / 16 || capturing(s))
+        if (2 * ((uint64_t)idx->m + idx->nnz) * 4 > ctx->mem_bytes / 16)
             return BM_OK;
         Span sp(ctx, PH_ENCODE);
         DevBuf<uint32_t> count, start, items;
@@ -2502,6 +2509,7 @@ bm_status bm_index_build_sets(bm_context *ctx, uint32_t m, uint32_t n_sets, cons
     if (!out || !offsets || m == 0 || n_sets == 0)
         return fail(ctx, BM_EINVAL, "bm_index_build_sets: null pointer or zero size");
     *out = nullptr;
+    BMC(not_captured(ctx));
     bm_build_opts o;
     bm_build_opts_init(&o);
     if (opts)
@@ -2580,6 +2588,7 @@ bm_status bm_index_build_transactions(bm_context *ctx, uint32_t n_items, uint32_
     if (!out || !offsets || m_txn == 0 || n_items == 0)
         return fail(ctx, BM_EINVAL, "bm_index_build_transactions: null pointer or zero size");
     *out = nullptr;
+    BMC(not_captured(ctx));
     bm_build_opts o;
     bm_build_opts_init(&o);
     if (opts)
@@ -2770,8 +2779,8 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
         return fail(ctx, BM_EINVAL, "index built with min_support > 0 has no BatMap for some items");
     HIPC(ctx, hipSetDevice(ctx->device));
     bool host = ptr_kind(out) == PTR_HOST;
-    if (!host && capturing(ctx->stream))
-        return captured_pairs(idx, out);
+    if (capturing(ctx->stream))
+        return host ? not_captured(ctx) : captured_pairs(idx, out);
     uint32_t *dst = out;
     if (host) {
         HIPC(ctx, idx->pairbuf.ensure(np));
@@ -2823,6 +2832,7 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
     const uint32_t live = idx->n - first;
     if (live < 2)
         return BM_OK;
+    BMC(not_captured(ctx));
     std::vector<uint32_t> ids;
     if (first > 0) {
         ids.assign(idx->h_sorted_items.begin() + first, idx->h_sorted_items.end());
@@ -2959,6 +2969,7 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
                     (unsigned long long)end, (unsigned long long)kNoAllocScratchBytes);
     if (none)
         return BM_OK;
+    BMC(not_captured(ctx));
     uint8_t *sc = ctx->scratch;
     uint32_t *counts = reinterpret_cast<uint32_t *>(sc);
     uint32_t *thr_counts = reinterpret_cast<uint32_t *>(sc + o_cnt);
@@ -3012,6 +3023,7 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
     if (!triples || !out)
         return fail(ctx, BM_EINVAL, "null pointer");
     HIPC(ctx, hipSetDevice(ctx->device));
+    BMC(not_captured(ctx));
     hipStream_t s = ctx->stream;
     DevBuf<uint32_t> tri, flag, res;
     const uint32_t *d_tri = triples;
@@ -3043,8 +3055,8 @@ bm_status bm_triple_supports(bm_index *idx, const uint32_t *triples, uint64_t co
     // slots: 1.3 * 10^7 slot triples a microsecond, a triple's walk 10 ns a slot; bits: the
     // rows at 12 TB/s, mostly one row a triple.  Measured (us, slots and bits): 41,664
     // triples of 64 items, 10^6 transactions, 500 items at 2 %: 94,000 and 250; 100 triples
-    // of maps of 512 slots (300 x 2000): 34.3 and 37.7; one of 8192 slots: 117 and 37.  Rows not yet made are paid by the call or,
-    // item by item named, by the calls before it.
+    // of maps of 512 slots (300 x 2000): 34.3 and 37.7; one of 8192 slots: 117 and 37.
+    // Rows not yet made are paid by the call or, item by item named, by the calls before it.
     const uint64_t ld = bit_row_words(idx->m);
     const double slots_us = 22 + 0.01 * slot_triples / (double)count + slot_triples / 1.3e7;
     const double bits_us = 28 + (double)count * ld * 4 * 1.3 / 12e6;
@@ -3099,6 +3111,7 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
     if (!items || (np && !out))
         return fail(ctx, BM_EINVAL, "null pointer");
     HIPC(ctx, hipSetDevice(ctx->device));
+    BMC(not_captured(ctx));
     hipStream_t s = ctx->stream;
     // host copy of the query (to plan) and device copy (to validate)
     std::vector<uint32_t> q(k);
@@ -3324,6 +3337,7 @@ bm_status batch_create(bm_context *ctx, bm_index *const *idxs, uint32_t count, u
         return fail(ctx, BM_EINVAL, "at most 65535 instances per batch");
     *out = nullptr;
     HIPC(ctx, hipSetDevice(ctx->device));
+    BMC(not_captured(ctx));
     hipStream_t s = ctx->stream;
     std::unique_ptr<bm_batch> b(new (std::nothrow) bm_batch());
     if (!b)
@@ -3573,8 +3587,8 @@ bm_status bm_all_pair_supports_dense(bm_index *idx, uint32_t *out, uint64_t out_
     HIPC(ctx, hipSetDevice(ctx->device));
     BMC(ensure_bits(idx));
     bool host = ptr_kind(out) == PTR_HOST;
-    if (!host && capturing(ctx->stream))
-        return gram_no_scratch(idx, out);
+    if (capturing(ctx->stream))
+        return host ? not_captured(ctx) : gram_no_scratch(idx, out);
     uint32_t *dst = out;
     if (host) {
         HIPC(ctx, idx->pairbuf.ensure(np));
@@ -3677,7 +3691,7 @@ bm_status cross_gram(bm_index *a, bm_index *b, uint32_t *out, bool &taken)
     CompareLoad load;
     load.work_us = slot_pairs_us(slots, a->planes);
     load.wait_us = std::max(index_load(a, 0).wait_us, index_load(b, 0).wait_us);
-    if ((us >= compare_us(load, a->n_failed + b->n_failed, 130) && bitmap_route_env() != 1) || capturing(ctx->stream))
+    if (us >= compare_us(load, a->n_failed + b->n_failed, 130) && bitmap_route_env() != 1)
         return BM_OK;
     DevBuf<float> ws;
     if (ws.alloc(p.ws_floats) != hipSuccess)
@@ -3761,6 +3775,7 @@ bm_status bm_cross_pair_supports(bm_index *a, bm_index *b, uint32_t *out, uint64
     ctx->err.clear();
     AllocScope scope(ctx->as);
     begin_query(ctx);
+    BMC(not_captured(ctx));
     BMC(check_cross(a, b));
     const uint64_t cells = (uint64_t)a->n * b->n;
     if (!out)
@@ -3796,6 +3811,7 @@ bm_status bm_cross_pairs(bm_index *a, bm_index *b, uint32_t min_support, bm_pair
     if (!n_out)
         return fail(ctx, BM_EINVAL, "n_out is null");
     *n_out = 0;
+    BMC(not_captured(ctx));
     BMC(check_cross(a, b));
     const uint64_t cells = (uint64_t)a->n * b->n;
     HIPC(ctx, hipSetDevice(ctx->device));
@@ -4400,6 +4416,7 @@ bm_status bm_server_create(bm_index *idx, const bm_server_opts *opts, bm_server 
         return fail(ctx, BM_EINVAL, "the server's launches compare the paper's 8-bit 2-of-3 maps; this index has "
                     "%u-bit slots or order-3 maps", idx->planes);
     HIPC(ctx, hipSetDevice(idx->device));
+    BMC(not_captured(ctx));
     // bit rows for the queries that will be counted from them, when the whole
     // index would be (each query then goes by its own expected time)
     bool by_bits = false;

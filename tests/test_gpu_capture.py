@@ -130,3 +130,44 @@ def test_product_without_scratch(stream_ctx, monkeypatch, tile, m, n, p):
     assert np.array_equal(idx.all_pair_supports_dense(), want)
     replays(stream, c, idx.all_pair_supports_dense, out, want,
             lambda: np.testing.assert_array_equal(idx.all_pair_supports_dense(), want))
+
+
+def test_waiting_calls_are_refused_whole(stream_ctx):
+    """Calls that wait for the device: refused under capture before they grow a buffer or queue anything, so
+    the capture stays valid and later eager calls work on memory of their own."""
+    stream, c = stream_ctx
+    m, n = 20_000, 260
+    off, tids = datagen.bernoulli_sets(m, n, 0.03, seed=11)
+    rows, items = datagen.sets_to_transactions(m, off, tids)
+    want = oracle.all_pairs(off, tids)
+    idx, other = (bm.Index.from_sets(c, m, off, tids) for _ in range(2))
+    triples = bm.Index.from_sets(c, m, off, tids, order=3)
+    out = torch.full((want.size,), -1, dtype=torch.int32, device="cuda:0")
+    pairs = torch.zeros(3 * want.size, dtype=torch.int32, device="cuda:0")
+    rect = torch.zeros(n * n, dtype=torch.int32, device="cuda:0")
+    q = np.arange(40, dtype=np.uint32)
+    calls = [
+        lambda: idx.frequent_pairs_into(5, pairs), lambda: idx.frequent_pairs_noalloc(5, pairs),
+        lambda: idx.all_pair_supports(np.zeros(want.size, np.uint32)), lambda: idx.subset_pair_supports(q, out),
+        lambda: bm.cross_pair_supports(idx, other, rect), lambda: bm.cross_pairs(idx, other, 3, pairs),
+        lambda: triples.triple_supports([(0, 1, 2)]), lambda: bm.Index.from_sets(c, m, off, tids),
+        lambda: bm.Index.from_transactions(c, n, rows, items), lambda: bm.Batch(c, [idx], [out]),
+        lambda: bm.Server(idx, streams=1, memory_budget=1 << 20),
+    ]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        for call in calls:
+            with pytest.raises(bm.BatmapError) as e:
+                call()
+            assert e.value.status == bm.BM_EINVAL
+        idx.all_pair_supports(out)                       # the capture is still good
+    assert len(idx.frequent_pairs(5)) == int((want >= 5).sum())
+    assert np.array_equal(idx.subset_pair_supports(q)[:bm.n_pairs(40)], oracle.subset_pairs(off, tids, q))
+    assert np.array_equal(bm.cross_pair_supports(idx, other), oracle.cross(off, tids, off, tids).reshape(n, n))
+    assert np.array_equal(triples.triple_supports([(0, 1, 2)]), oracle.triples(off, tids, np.array([[0, 1, 2]], np.uint32)))
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+    del g
