@@ -431,7 +431,7 @@ struct bm_index {
     uint64_t bit_rows_made = 0;  // by calls that made the rows of their list alone
     // what calls would have saved (us) with all bit rows, or with the incidences
     // grouped by transaction, in place: once that pays for making them, they are made
-    double bits_saved_us = 0, txn_saved_us = 0;
+    double bits_saved_us = 0, txn_saved_us = 0, plan_saved_us = 0;
     DevBuf<float> gram_ws;       // bm_all_pair_supports_dense
     // counting by transactions: items grouped by transaction, made at first use
     DevBuf<uint32_t> txn_start, txn_items;
@@ -662,14 +662,28 @@ bool bitmap_route_on(const bm_context *ctx)
            !getenv("BM_PACKED_ROWS");
 }
 
-// Expected time of a slot compare (us): fixed_us for launches, zero fill and planning,
-// 5 more where there are corrections, and its load.  Slots and bits measured (MI355X,
-// us, rows kept): 100,000 x 64 of 16,384 slots: 187 and 20; 5 * 10^6 x 32 of 65,536: 25
-// and 35; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x 2000 Zipf at 2 %: 4700 and 670; 10^6
-// x 1500 at 0.05 % (16-bit): 332 and 390.
+// Expected time of counting all of an index's pairs by slots (us): fixed_us for launches,
+// zero fill and planning, 5 more where there are corrections, and its load.  Slots and
+// bits measured (MI355X, us, rows kept): 100,000 x 64 of 16,384 slots: 187 and 20; 5 *
+// 10^6 x 32 of 65,536: 25 and 35; 50,000 x 4000 at 5 %: 1818 and 153; 10^6 x 2000 Zipf at
+// 2 %: 4700 and 670; 10^6 x 1500 at 0.05 % (16-bit): 332 and 390.
 double compare_us(const CompareLoad &l, uint64_t n_corr, double fixed_us)
 {
     return fixed_us + (n_corr ? 5 : 0) + l.wait_us + l.work_us;
+}
+
+// That of a compare of listed maps, of two families', of a batch that runs once, of one
+// beside which every pair is filled and thresholded, or instead of which rows would be
+// made that other calls use too: an item's walk over up to 256 groups of the widest map
+// at 1 us a group (2 with wider slots), above what it takes alone.  By the load above,
+// which is of the compare's kernels only, these went by slots where rows are the faster
+// way (us, slots and rows): 33 of 300 sets over 2 * 10^7 transactions 155 and 67, frequent
+// pairs of few of 9000 items 152 and 80, two families of 64 over 5 * 10^7 220 and 125,
+// three of 300 over 10^6 once 1684 and 185.
+double walk_us(double slot_pairs, uint32_t planes, double r_max, double fixed_us)
+{
+    return fixed_us + std::min(256.0, 3 * r_max / kSlotsPerGroup) * (planes == 8 ? 1 : 2) +
+           slot_pairs_us(slot_pairs, planes);
 }
 
 // The load of the index's maps from sorted index `first` on.
@@ -685,6 +699,35 @@ const CompareLoad &index_load(bm_index *idx, uint32_t first)
 // Expected time of counting its pairs by slots in a call that only launches.
 double slots_us(bm_index *idx, uint32_t first) { return compare_us(index_load(idx, first), idx->n_corr, 10); }
 
+// The same beside what else a call does over every pair (see walk_us).
+double slots_walk_us(const bm_index *idx, uint32_t first)
+{
+    return walk_us(class_work(first ? classes_from(idx->classes, first) : idx->classes), idx->planes,
+                   idx->h_r_sorted.back(), 20);
+}
+
+// What a call that counts the pairs of the maps from sorted index `first` on expects of
+// slots, where bit rows take bits_us.  Rows that are not made yet serve other calls too,
+// so the walk decides whether they are.  An index that holds them may hold no plan; one
+// takes about 100 us, and is made once the calls before have lost that much to the rows.
+double call_slots_us(bm_index *idx, uint32_t first, double bits_us)
+{
+    const double walk = slots_walk_us(idx, first);
+    if (!idx->bits.p || bits_us >= walk)
+        return walk;
+    if (first && !(classes_from(idx->classes, first).size() == 1 && index_load(idx, first).few))
+        return walk;
+    // the whole triangle is filled, and thresholded, all the same
+    const double us = slots_us(idx, first) + 3e-6 * (double)(n_pairs(idx->n) - n_pairs(idx->n - first));
+    if (idx->planned_first == first || bits_us <= us)
+        return us;
+    idx->plan_saved_us += bits_us - us;
+    if (idx->plan_saved_us <= 100)
+        return walk;
+    idx->plan_saved_us = 0;
+    return us;
+}
+
 // Expected time of writing bit rows (us): the rows out and the tids in at 2.5 TB/s.
 double bit_rows_us(double rows, uint64_t row_words, double tids) { return 12 + (rows * row_words + tids) * 4 / 2.5e6; }
 
@@ -698,7 +741,7 @@ bool bit_rows_fit(const bm_context *ctx, uint64_t rows, uint64_t row_words)
 
 // Whether all pairs of an index that holds its bit rows will be counted from
 // them, now and at every later call.
-bool pairs_by_kept_bits(bm_index *idx)
+bool pairs_by_kept_bits(const bm_index *idx)
 {
     const bm_context *ctx = idx->ctx;
     if (!idx->bits.p || !bitmap_route_on(ctx) || bitmap_route_env() == 2 || idx->classes.empty() ||
@@ -706,7 +749,7 @@ bool pairs_by_kept_bits(bm_index *idx)
         return false;
     return bitmap_route_env() == 1 ||
            plan_gram(idx->n, idx->n, true, bit_row_words(idx->m), (uint32_t)ctx->n_cu, pinned_gram_tile()).us <
-               slots_us(idx, idx->first_built);
+               slots_walk_us(idx, idx->first_built);
 }
 
 // Persistent plans run as one single-launch list: range (-1, all items),
@@ -2788,9 +2831,9 @@ bm_status bm_all_pair_supports(bm_index *idx, uint32_t *out, uint64_t out_len)
     }
     bool taken = false;
     DevBuf<uint32_t> ids;
-    const double by_slots = slots_us(idx, 0);
     const GramChoice c = choose_gram(idx, false, idx->n);
-    BMC(txn_pairs(idx, std::min(by_slots, c.us), dst, taken));
+    const double by_slots = call_slots_us(idx, 0, c.us);
+    BMC(txn_pairs(idx, std::min(slots_walk_us(idx, 0), c.us), dst, taken));
     if (!taken)
         BMC(gram_pairs(idx, nullptr, idx->n, c, by_slots, dst, ids, taken));
     if (!taken)
@@ -2838,12 +2881,12 @@ bm_status bm_frequent_pairs(bm_index *idx, uint32_t min_support, bm_pair *out, u
         ids.assign(idx->h_sorted_items.begin() + first, idx->h_sorted_items.end());
         std::sort(ids.begin(), ids.end());
     }
-    const double by_slots = slots_us(idx, first);
     DevBuf<uint32_t> d_ids;
     bool by_txn = false, by_bits = false;
     HIPC(ctx, idx->pairbuf.ensure(np));
     const GramChoice c = choose_gram(idx, first > 0, live);
-    BMC(txn_pairs(idx, std::min(by_slots, c.us), idx->pairbuf.p, by_txn));
+    const double by_slots = call_slots_us(idx, first, c.us);
+    BMC(txn_pairs(idx, std::min(slots_walk_us(idx, first), c.us), idx->pairbuf.p, by_txn));
     if (!by_txn)
         BMC(gram_pairs(idx, first ? ids.data() : nullptr, live, c, by_slots, idx->pairbuf.p, d_ids, by_bits));
     uint32_t n_eff = idx->n;
@@ -2933,7 +2976,7 @@ bm_status bm_frequent_pairs_noalloc(bm_index *idx, uint32_t min_support, bm_pair
     const uint64_t room = o_work < kNoAllocScratchBytes ? (kNoAllocScratchBytes - o_work) / 4 : 0;
     GramPlan gram;
     const bool own = idx->planned_first != UINT32_MAX && idx->planned_first <= first;
-    double us = slots_us(idx, own ? idx->planned_first : first) + (own ? 0 : 50);  // planned and uploaded
+    double us = compare_us(index_load(idx, own ? idx->planned_first : first), idx->n_corr, own ? 20 : 70);
     bool by_bits = false, by_txn = false;
     if (o_work <= kNoAllocScratchBytes && bitmap_route_on(ctx)) {
         if (idx->bits.p && bitmap_route_env() != 2) {
@@ -3151,11 +3194,9 @@ bm_status bm_subset_pair_supports(bm_index *idx, const uint32_t *items, uint32_t
                 return (uint32_t)r;
             });
             // the slot compare plans its tiles on the host and uploads five lists: about 60
-            // us; how it would run is only looked at where the work alone leaves it open
-            double by_slots = 60 + slot_pairs_us(class_work(cls), idx->planes);
+            // us
             const GramChoice c = choose_gram(idx, true, k);
-            if (c.us >= by_slots)
-                by_slots = compare_us(compare_load(cls, idx->planes), idx->n_corr, 60);
+            const double by_slots = walk_us(class_work(cls), idx->planes, cls.back().r, 60);
             BMC(gram_pairs(idx, q.data(), k, c, by_slots, dst, ids, taken));
         }
         if (taken) {
@@ -3287,11 +3328,13 @@ bm_status batch_by_bits(bm_batch *b, const std::vector<double> &inst_work, bool 
             double us = plan_gram(ix->n, ix->n, true, ld, (uint32_t)ctx->n_cu, pinned_gram_tile()).us;
             if (once && !ix->bits.p)  // a batch to be replayed keeps its rows
                 us += bit_rows_us(ix->n, ld, (double)ix->nnz);
-            // several instances' items wait for one another's
-            CompareLoad load = index_load(ix, 0);
-            if (b->idx.size() > 1)
-                load.wait_us = std::max(0.0, load.wait_us / b->idx.size() - load.work_us);
-            if ((us >= compare_us(load, ix->n_corr, 10) && bitmap_route_env() != 1) ||
+            // replayed, one instance's items fill the chip while another's walk (three of
+            // 200,000 x 3000 at 0.2 %: 819 us by slots, 918 from rows)
+            const CompareLoad &l = index_load(ix, 0);
+            const double by_slots = once || b->idx.size() == 1
+                                        ? walk_us(inst_work[q], ix->planes, ix->h_r_sorted.back(), 10)
+                                        : 10 + std::max(l.work_us, l.wait_us);
+            if ((us >= by_slots && bitmap_route_env() != 1) ||
                 (!ix->bits.p && !bit_rows_fit(ctx, ix->n, ld)))
                 continue;
             const uint64_t bytes = ix->bits.p ? 0 : ((uint64_t)ix->n + 1) * ld * 4;
@@ -3686,12 +3729,9 @@ bm_status cross_gram(bm_index *a, bm_index *b, uint32_t *out, bool &taken)
     for (const Cls &x : a->classes)
         for (const Cls &y : b->classes)
             slots += 3.0 * std::max(x.r, y.r) * x.count * y.count;
-    // planning, the uploads and the launches of the slot compare: about 130 us; the
-    // load's wait as among all of a family's maps, the one that waits longer
-    CompareLoad load;
-    load.work_us = slot_pairs_us(slots, a->planes);
-    load.wait_us = std::max(index_load(a, 0).wait_us, index_load(b, 0).wait_us);
-    if (us >= compare_us(load, a->n_failed + b->n_failed, 130) && bitmap_route_env() != 1)
+    // planning, the uploads and the launches of the slot compare: about 130 us
+    const double r_max = std::max(a->h_r_sorted.back(), b->h_r_sorted.back());
+    if (us >= walk_us(slots, a->planes, r_max, 130) && bitmap_route_env() != 1)
         return BM_OK;
     DevBuf<float> ws;
     if (ws.alloc(p.ws_floats) != hipSuccess)

@@ -879,6 +879,7 @@ CompareLoad compare_load(const std::vector<Cls> &cls, uint32_t planes)
         return l;
     }
     l.work_us *= 3;
+    l.few = cls.size() == 1;
     if (!near)
         l.wait_us = 0.2 * std::min(256.0, G);
     else if (cls.size() > 1)

@@ -185,9 +185,10 @@ constexpr uint64_t kGramMaxStages = (1u << 24) / kGramStage;
 
 // What a slot compare of all pairs among maps of these classes takes beyond its
 // launches (us): its slot pairs at the rate of their width, and the wait for its
-// longest work item.
+// longest work item.  few: few maps of one width (group-parallel tiles).
 struct CompareLoad {
     double work_us = 0, wait_us = 0;
+    bool few = false;
 };
 double slot_pairs_us(double slot_pairs, uint32_t planes);
 CompareLoad compare_load(const std::vector<Cls> &cls, uint32_t planes);

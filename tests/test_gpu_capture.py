@@ -171,3 +171,27 @@ def test_waiting_calls_are_refused_whole(stream_ctx):
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
     del g
+
+
+@pytest.mark.parametrize("m,n,p", [(10_000_000, 3, 0.005), (10_000_000, 12, 0.004), (100_000, 64, 0.05)])
+def test_few_sets_go_over_to_slots(stream_ctx, m, n, p):
+    """The rows that a build leaves count first and stay for other calls; a plan is made once calls have paid for it."""
+    stream, c = stream_ctx
+    off, tids = datagen.sets_from_probs(m, np.full(n, p), seed=7)
+    want = oracle.all_pairs(off, tids, threads=0)
+    idx = bm.Index.from_sets(c, m, off, tids)
+    out = torch.zeros(want.size, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    slots = []
+    for call in range(40):
+        out.fill_(-1)
+        torch.cuda.synchronize()
+        c.set_profiling(True)
+        idx.all_pair_supports(out)
+        slots.append(c.timings()["compare_slot_pairs"] > 0)
+        c.set_profiling(False)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want)
+    assert not slots[0] and slots == sorted(slots)
+    assert slots[-1] == (m == 10_000_000)
+    replays(stream, c, idx.all_pair_supports, out, want, lambda: idx.frequent_pairs(1))
+    idx.close()
