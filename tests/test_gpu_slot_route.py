@@ -3,6 +3,8 @@ once more with every call kept on slots: by expected time most of their instance
 which no map and no correction can reach."""
 import pytest
 
+import datagen
+
 torch = pytest.importorskip("torch")
 bm = pytest.importorskip("paper_1102_1003_amd")
 
@@ -46,4 +48,13 @@ def slots(monkeypatch):
         assert self.n < 2 or t["compare_slot_pairs"] > 0
         return got
     monkeypatch.setattr(bm.Index, "all_pair_supports", all_pair_supports)
+    # a context's own stream does not wait for the stream that the data is drawn on, and in a second run of the
+    # same test no allocation does either
+    drawn = datagen.bernoulli_sets_device
+
+    def bernoulli_sets_device(*args, **kw):
+        got = drawn(*args, **kw)
+        torch.cuda.synchronize()
+        return got
+    monkeypatch.setattr(datagen, "bernoulli_sets_device", bernoulli_sets_device)
     yield
